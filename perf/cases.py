@@ -78,7 +78,11 @@ def draw(rng):
     hidden = rng.choice([128, 256, 320, 512, 768, 768, 1024, 1024])
     seq = _log_int(rng, 8, 512)
     batch = _log_int(rng, 1, max(1, min(64, MAX_TOKENS // seq)))
-    c = _module("", kind, rng.randint(1, 6), hidden, batch, seq, w_bits=rng.choice([2, 4, 4, 4, 8]), a_bits=rng.choice([4, 8, 8, 8]),
+    layers = rng.randint(1, 6)
+    # 4-bit activations on single layers only: their coarse codes flip so widely from layer to layer that two correct
+    # implementations differ by 10% after five layers
+    a_bits = rng.choice([4, 8]) if layers == 1 else 8
+    c = _module("", kind, layers, hidden, batch, seq, w_bits=rng.choice([2, 4, 4, 4, 8]), a_bits=a_bits,
                 per_channel=rng.choice([0, 1, 1]), min_len=rng.choice([0, 0, 1]) * max(1, seq // 3))
     if kind == "step":
         c["lam"] = rng.choice([0.0, 0.0, round(rng.uniform(0.05, 0.95), 2)])
@@ -253,7 +257,7 @@ def tolerance(case):
     if case["kind"] == "quantize":
         return "exact"
     if case["kind"] == "rem":
-        return {"rel": 5e-3, "max": 5e-2}  # one product deep: single bf16 roundings
+        return {"rel": 5e-3, "max": 0.25}  # one product deep: single bf16 roundings (0.06% seen, 6% in the worst element)
     if case["kind"] == "calibrate":
         return {"rel": 1.2e-2, "max": 2e-2}  # maxima of bf16 activations: 0.3% seen
     if case["dtype"] == "f32":
