@@ -129,7 +129,7 @@ __global__ void gemm_nt_simt_k(const TA* __restrict__ A, int lda, const TA* __re
 // bf16 and their products and partial sums are exact in fp32 while they stay below 2^24 (always for
 // 4-bit weights: K * 255 * 7 < 2^24 up to K = 9398; with 8-bit weights only up to K = 518, beyond
 // that a product on bf16 codes rounds like any fp32 sum); the int8 mode is exact for every supported K.
-// Requires M and N multiples of 128, K a multiple of 64 (128 int8 codes) and 16-byte aligned rows.
+// Which sizes it takes: see mfma_ok (bf16) and gemm_i8_ok.
 // ------------------------------------------------------------------------------
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -144,10 +144,14 @@ constexpr int kBK = 64;  // k-granularity of the MFMA kernels, in 2-byte element
 #include "mrem_gemm_dl.h"
 namespace mrem {
 
-static bool mfma_ok(const void* A, int lda, const void* B, int ldb, int M, int N, int K) {
-  return M % 128 == 0 && N % 128 == 0 && K % kBK == 0 && lda % 8 == 0 && ldb % 8 == 0 &&
-         (reinterpret_cast<uintptr_t>(A) & 15) == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0;
+// Whole 16-byte chunks are fetched: rows start 16-byte aligned, and the index that is contiguous in memory (the
+// contraction index, or the row index of a transposed operand) is a multiple of 8.  Everything else may be ragged.
+static bool mfma_ok(int a_t, int b_t, const void* A, int lda, const void* B, int ldb, int M, int N, int K) {
+  return lda % 8 == 0 && ldb % 8 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0 &&
+         (a_t ? M % 8 == 0 : K % 8 == 0) && (b_t ? N % 8 == 0 : K % 8 == 0);
 }
+// no tile of 128 x 128 and no stage of the contraction is partly filled
+static bool whole_tiles(int M, int N, int K) { return M % 128 == 0 && N % 128 == 0 && K % kBK == 0; }
 
 static void gemm_launch(int dt, int a_t, int b_t, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K,
                         const Epilogue& e, hipStream_t st);
@@ -175,25 +179,44 @@ bool gemm_i8_ok(const void* A, int lda, const void* B, int ldb, int M, int N, in
 }
 // int8 mode: two int8 codes travel as one 16-bit element, so leading dimensions and the contraction
 // length are halved.
-// Which tile serves a product (measured on the module step, two streams sharing the device):
-//   256 x 256 (8 wavefronts of 64 x 128, two stages of 128-byte rows, one block per compute unit) when the
-//     output has at least 192 such tiles -- the query/key/value and first feed-forward projections and
-//     the input gradient of the second one at 4096 tokens: half the operand bytes per flop of the small tile;
+// Which tile serves a product, by how many compute units (256) the output's tiles can occupy.  Times of single
+// products on rotating operands (bf16, us), each against the next candidate:
+//   64 x 64, 8 wavefronts in two groups, up to 256 such tiles: a k-step is a chain of latencies, shorter the smaller
+//     the tile (1000 x 768 x 3072: 15.6 against 18.5 for 128 x 64; weight gradient 768 x 768 x 4096: 20.2 against 24.2,
+//     and 34.9 for 128 x 128);
+//   128 x 64, 8 wavefronts in two groups, three stages, up to 256 such tiles (2304 x 768 x 3072: 20.0 against 22.6 for
+//     64 x 64 and 26.0 for 128 x 128);
+//   256 x 256 (8 wavefronts of 64 x 128, two stages, one block per compute unit) from 144 such tiles on: half the
+//     operand bytes per flop of the small tile (4096 x 2304 x 768: 25.7 against 28.1; 4096 x 4096 x 1024: 40 against 57);
 //   128 x 128 with 8 wavefronts (two groups of 4; each group multiplies every other 16-deep k-substep of a
 //     stage and the groups' partial sums meet in LDS before the epilogue), four stages of 128-byte rows, one
-//     block per compute unit, when the output has at most 256 such tiles -- one tile per compute unit, so the
-//     second wavefront on each SIMD is what overlaps fragment reads, barriers and MFMA issue;
+//     block per compute unit, up to 256 such tiles -- one tile per compute unit, so the second wavefront on each
+//     SIMD is what overlaps fragment reads, barriers and MFMA issue (4096 x 1024 x 4096: 41.4 against 52.9 for 128 x 64);
 //   128 x 128 with 4 wavefronts of 64 x 64, four stages of 64-byte rows, two blocks per compute unit, otherwise:
-//     the second block fills the barrier and epilogue gaps of the first.
-//   Four stages hide the latency of operands that the previous kernel has just written or that come from HBM.
+//     the second block fills the barrier and epilogue gaps of the first (6144 x 768 x 3072: 51.6 against 57.3 for
+//     128 x 64).  Sizes with partly filled tiles take 128 x 64 here (2310 x 3072 x 768: 22.2 against 23.1).
 template <bool AT, bool BT, class TO, bool I8>
 static void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                             hipStream_t st, int splits) {
-  if (splits == 1 && M % 256 == 0 && N % 256 == 0 && (M / 256) * (N / 256) >= 192)
-    return launch_dl<256, 256, 4, 2, AT, BT, 2, 128, TO, I8, 1>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-  if ((M / 128) * (N / 128) <= 256)
+  auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const bool whole = whole_tiles(M, N, K);
+  if (splits > 1)
     return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st, splits);
-  return launch_dl<128, 128, 2, 2, AT, BT, 4, 64, TO, I8, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st, splits);
+  if (tiles(64, 64) <= 256)
+    return launch_dl<64, 64, 2, 2, AT, BT, 4, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  if (tiles(128, 64) <= 256)
+    return launch_dl<128, 64, 2, 2, AT, BT, 3, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  if (tiles(256, 256) >= 144) {
+    if (whole && M % 256 == 0 && N % 256 == 0)
+      return launch_dl<256, 256, 4, 2, AT, BT, 2, 128, TO, I8, 1>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+    return launch_dl<256, 256, 4, 2, AT, BT, 2, 128, TO, I8, 1, 1, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  }
+  if (tiles(128, 128) <= 256) {
+    if (whole) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+    return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  }
+  if (whole) return launch_dl<128, 128, 2, 2, AT, BT, 4, 64, TO, I8, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  return launch_dl<128, 64, 2, 2, AT, BT, 3, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
 }
 static void gemm_i8_launch(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                            hipStream_t st) {
@@ -222,16 +245,17 @@ void gemm_nt(int dt, const void* A, int lda, const void* B, int ldb, void* C, in
   gemm(dt, 0, 0, A, lda, B, ldb, C, ldc, M, N, K, e, st, prof);
 }
 
-// Tiles for at most half of the compute units and a long contraction (weight gradients of the
-// square projections): two k-slices.  (Larger weight gradients run beside the rest of the backward
+// Tiles for a quarter to half of the compute units and a long contraction (weight gradients of 1024 x 1024 and
+// 2304 x 768): two k-slices; with fewer tiles the 64 x 64 ones take over (768 x 768 over 4096 tokens; three layers'
+// step 1774 -> 1733 us).  64 x 64 tiles for 1024 x 1024 too cost the six-layer step 0.6%: twice the operand traffic
+// beside the other stream's kernels.  (Larger weight gradients run beside the rest of the backward
 // pass, where a second slice only adds atomic traffic.)  Two atomic adds onto a zeroed fp32 value
 // commute exactly, so the result does not depend on which slice arrives first.
 static int f32_k_slices(int M, int N, int K) {
-  const int tiles = (M / 128) * (N / 128);
-  return (tiles <= 128 && K >= 2048 && (K / kBK) % 2 == 0) ? 2 : 1;
+  return (whole_tiles(M, N, K) && (M / 128) * (N / 128) <= 128 && (M / 64) * (N / 64) > 192 && K >= 2048 && (K / kBK) % 2 == 0) ? 2 : 1;
 }
 int gemm_f32_k_slices(int dt, int M, int N, int K) {
-  return (dt == DT_BF16 && M % 128 == 0 && N % 128 == 0 && K % kBK == 0) ? f32_k_slices(M, N, K) : 1;
+  return dt == DT_BF16 ? f32_k_slices(M, N, K) : 1;
 }
 
 template <bool AT, bool BT>
@@ -248,7 +272,7 @@ static void launch_mfma_modes(const void* A, int lda, const void* B, int ldb, vo
 
 static void gemm_launch(int dt, int a_t, int b_t, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K,
                         const Epilogue& e, hipStream_t st) {
-  if (dt == DT_BF16 && mfma_ok(A, lda, B, ldb, M, N, K)) {
+  if (dt == DT_BF16 && mfma_ok(a_t, b_t, A, lda, B, ldb, M, N, K)) {
     if (!a_t && !b_t) {
       launch_mfma_modes<false, false>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
     } else if (!a_t && b_t) {

@@ -946,3 +946,54 @@ def test_rem_step_matches_oracle(B, dt, T, N, K, w_bits, per_channel, n_steps):
         if not per_channel:
             assert np.all(cur[N * K:N * K + N] == cur[N * K])           # the one step stays one step
     B.mrem_destroy(ctx)
+
+
+# --------------------------------------------------------------------------------
+# matrix products at the edges of their tiles
+# --------------------------------------------------------------------------------
+
+# (T, N, K) of a product and its two gradients, by the tile that serves the forward product (256 compute units):
+# 64 x 64 with less than one tile, one 16-byte chunk, and remainders in all three sizes; 128 x 64; 128 x 128 and
+# 128 x 64 above one tile per compute unit; 256 x 256.  Contractions: 8 (one partly filled stage) up to several stages
+# with a remainder, and exactly one stage.
+@pytest.mark.parametrize("T,N,K", [(8, 8, 8), (24, 72, 40), (64, 64, 64), (72, 136, 200), (1032, 1544, 72), (1544, 2056, 136), (2312, 2056, 72),
+                                   (2824, 3080, 136), (3072, 3072, 64)])
+def test_products_at_tile_edges(B, T, N, K):
+    """y = a W^T, dW = dy^T a^ and d a^ = dy W^ of one mrem_rem_step against float64 on the operands the kernels read.
+    Activations are integers + 1/4 and s_a = 1, so codes are the integers and code - v = -1/4 for every element:
+    d s_a = -1/4 sum(d a^).  Bounds: bf16 rounding of a stored value (2^-8 relative, twice the unit roundoff), and the
+    fp32 summation bound n * 2^-23 * sum of magnitudes with n terms."""
+    torch = _torch()
+    g = torch.Generator("cuda").manual_seed(T * 7 + N * 3 + K)
+    ctx = B.mrem_create(n_layers=1, hidden=64, n_heads=1, ffn=64, max_batch=1, max_seq=8, w_bits=4, a_bits=8, act_dtype=B.MREM_BF16, loss_mean=0)
+    a = (torch.randint(-20, 21, (T, K), generator=g, device="cuda").float() + 0.25).bfloat16()
+    w = torch.randn(N, K, generator=g, device="cuda", dtype=torch.float32) * 0.02
+    vec = torch.zeros(B.mrem_rem_vector_count(N, K), dtype=torch.float32, device="cuda")
+    vec[:N * K] = w.reshape(-1)
+    s_w = w.abs().amax(dim=1) / 6.5                      # nothing is clipped: the straight-through mask is 1 everywhere
+    vec[N * K:N * K + N] = s_w
+    vec[N * K + N] = 1.0
+    m, v, grads = torch.zeros_like(vec), torch.zeros_like(vec), torch.full_like(vec, float("nan"))
+    y_fp, y_q = (torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+    ws = torch.full((B.mrem_rem_workspace_bytes(ctx, T, N, K),), 255, dtype=torch.uint8, device="cuda")   # NaN in every type
+    B.mrem_rem_step(ctx, T, N, K, vec, m, v, 1, 0.0, w, a, a, loss, y_fp, y_q, grads, ws)
+    torch.cuda.synchronize()
+    a64, w64 = a.double(), w.bfloat16().double()
+    codes_a, codes_w = torch.round(a.double()), torch.round((w / s_w[:, None]).double())
+
+    def check(got, ref, terms, mags, stored):
+        tol = terms * 2.0 ** -23 * mags + (2.0 ** -8 * ref.abs() if stored else 0.0) + 1e-30
+        bad = ~((got.double() - ref).abs() <= tol)
+        assert not bad.any(), (int(bad.sum()), (got.double() - ref).abs().max().item())
+
+    check(y_fp, a64 @ w64.T, K, a64.abs() @ w64.abs().T, True)
+    # the epilogue multiplies by the step in fp32: three roundings more
+    check(y_q, (codes_a @ codes_w.T) * s_w.double(), K + 3, (codes_a.abs() @ codes_w.abs().T) * s_w.double(), True)
+    dy = (2.0 * (y_q.float() - y_fp.float())).bfloat16().double()
+    check(grads[:N * K].reshape(N, K), dy.T @ codes_a, T, dy.abs().T @ codes_a.abs(), False)
+    what = (s_w[:, None] * codes_w.float()).bfloat16().double()
+    dxh, mag = dy @ what, (dy.abs() @ what.abs())
+    ds, tol = -0.25 * dxh.sum().item(), 0.25 * ((2.0 ** -8 * dxh.abs()).sum() + (N + 64) * 2.0 ** -23 * mag.sum()).item()
+    assert abs(grads[N * K + N].item() - ds) <= tol, (grads[N * K + N].item(), ds, tol)
+    B.mrem_destroy(ctx)
