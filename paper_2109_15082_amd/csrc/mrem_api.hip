@@ -353,8 +353,8 @@ void student_forward(const Run& r, const float* params, const void* x_q, void* p
     student_linear(r, params, l, 0, r.at(w.xcodes), r.at8(w.xcodes8), r.at(w.qkv));
     const AttnQ aq = make_attn_q(c, params, l, true);
     timed(r, "qkv_quantize_k", (double)T * 3 * H * 2 * es, [&] { qkv_quantize(c->dt, r.at(w.qkv), r.at(w.qkvcodes), T, H, aq.q, aq.k, aq.v, r.st); });
-    if (attn_mfma_ok(c->dt, r.S, c->d)) {
-      attn_fwd_mfma(r.at(w.qkvcodes), r.at(w.ctx), r.at(w.ctxcodes), aq, r.seqlens, r.B, r.S, c->nh, nullptr, r.at<float>(w.stat_m),
+    if (attn_mfma_ok(c->dt, c->d)) {
+      attn_fwd_mfma(r.at(w.qkvcodes), r.at(w.ctx), r.at(w.ctxcodes), aq, r.seqlens, r.B, r.S, c->nh, c->d, nullptr, r.at<float>(w.stat_m),
                     r.at<float>(w.stat_l), r.st, r.at8(w.ctxcodes8));
     } else {
       attn_fwd(c->dt, r.at(w.qkvcodes), r.at(w.ctx), r.at(w.ctxcodes), aq, r.seqlens, r.B, r.S, c->nh, c->d, nullptr, r.st);
@@ -423,8 +423,8 @@ void teacher_forward(const Run& r, const float* teacher, const void* cache, cons
       calib(l, 2, q + (size_t)H * es, c->dt, T, H, 3 * H, 0, 0);
       calib(l, 4, q + (size_t)2 * H * es, c->dt, T, H, 3 * H, 0, 0);
     }
-    if (attn_mfma_ok(c->dt, r.S, c->d))
-      attn_fwd_mfma(r.at(r.p.t_qkv), r.at(r.p.t_ctx), nullptr, AttnQ(), r.seqlens, r.B, r.S, c->nh,
+    if (attn_mfma_ok(c->dt, c->d))
+      attn_fwd_mfma(r.at(r.p.t_qkv), r.at(r.p.t_ctx), nullptr, AttnQ(), r.seqlens, r.B, r.S, c->nh, c->d,
                     calib_params ? r.at<float>(r.p.pmax) : nullptr, nullptr, nullptr, r.st);
     else
       attn_fwd(c->dt, r.at(r.p.t_qkv), r.at(r.p.t_ctx), nullptr, AttnQ(), r.seqlens, r.B, r.S, c->nh, c->d,
@@ -616,9 +616,9 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
     {
       int n = r.B * c->nh * r.S;
       float* parts = red.take((size_t)n);
-      if (attn_mfma_ok(c->dt, r.S, c->d))
-        n = attn_bwd_mfma(r.at(w.qkvcodes), r.at(r.p.dc), r.at(r.p.dqkvh), aq, r.seqlens, r.B, r.S, c->nh, r.at<float>(w.stat_m),
-                          r.at<float>(w.stat_l), r.at(r.p.s_ph), r.at(r.p.s_da), parts, r.st);
+      if (attn_mfma_ok(c->dt, c->d))
+        n = attn_bwd_mfma(r.at(w.qkvcodes), r.at(r.p.dc), r.at(r.p.dqkvh), aq, r.seqlens, r.B, r.S, c->nh, c->d,
+                          r.at<float>(w.stat_m), r.at<float>(w.stat_l), r.at(r.p.s_ph), r.at(r.p.s_da), parts, r.st);
       else
         attn_bwd(c->dt, r.at(w.qkvcodes), r.at(r.p.dc), r.at(r.p.dqkvh), aq, r.seqlens, r.B, r.S, c->nh, c->d, r.at<float>(r.p.s_da),
                  r.at<float>(r.p.s_ph), parts, r.st);

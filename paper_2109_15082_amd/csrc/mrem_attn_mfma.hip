@@ -1,21 +1,33 @@
-// Softmax attention on the matrix cores (v_mfma_f32_32x32x16_bf16) for head
-// dimension 64, bf16 storage and 64 <= seq <= 384: forward, and the backward pass
-// split into a query-major and a key-major kernel.  Operands are quantizer codes
-// (Section 3.1: Q, K, V and the softmax probabilities are quantized before their
-// products), so Q*K^T and P*V are exact integer products in fp32.
+// Softmax attention on the matrix cores (v_mfma_f32_32x32x16_bf16) for head dimensions 32 and 64 and
+// bf16 storage: forward, and the backward pass split into a query-major and a key-major kernel.
+// Operands are quantizer codes (Section 3.1: Q, K, V and the softmax probabilities are quantized
+// before their products), so Q*K^T and P*V are exact integer products in fp32.
 //
 // Layout trick used throughout: the score tile is computed transposed,
 // D[key][query] = K_tile * Q_tile^T, so that in the 32x32 accumulator layout a lane
 // owns ONE query (lane % 32) and 16 of the 32 keys of the tile; the other 16 keys sit
 // in lane ^ 32.  Row-wise softmax statistics then need a single cross-lane exchange,
 // and the accumulator registers already have the layout of the B operand of the next
-// product (contraction over keys), with the key order fixed by `key_of`.
+// product (contraction over keys), with the key order fixed by `key_of`.  The key-major
+// kernel mirrors it: D[query][key] = Q_tile * K_tile^T, a lane owns one key.
 //
 // All tiles (K, V, Q, dC) sit row-major in LDS as they do in memory; where a product
 // needs an operand with the contraction index along the rows, the fragment is gathered
 // with the transposing LDS read (ds_read_tr16_b64), see `ld_frag_tr`.
+//
+// A block is up to 128 rows (32 per wavefront) of one (batch, head).  The other side of the
+// product passes through LDS in chunks of 128 rows, so a block takes 37 KB and under 170
+// registers at every length and several share a compute unit.  Up to 128 keys (one chunk) the
+// probabilities stay in registers between the pass that forms the row statistics and the pass
+// that uses them; longer rows form their tiles twice, since a probability is normalised before
+// it is quantized.  The scores, the exponentials and the quantizer are vector-ALU work (about
+// 25 instructions per query-key pair and pass), which is what bounds these kernels: keeping a
+// row of 384 keys in registers instead (and all its keys in LDS) left one wavefront per SIMD.
+// Chunks beyond the valid keys of a sequence are skipped.
 #include "mrem_common.h"
 #include "mrem_kernels.h"
+
+#include <type_traits>
 
 namespace mrem {
 
@@ -25,8 +37,10 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
-constexpr int kD = 64;            // head dimension handled here
-constexpr int kRowStride = 72;    // elements per row of a row-major LDS tile (144 bytes)
+constexpr int kChunk = 128;  // rows of the other operand in LDS at a time
+// elements per row of a row-major LDS tile (144 or 80 bytes: 16-byte stores and reads without bank conflicts)
+template <int D>
+struct Tile { static constexpr int kStride = D + 8; };
 
 // key (row of the transposed score tile) held in accumulator register i of a lane in half h
 __device__ __forceinline__ int key_of(int t, int i, int h) { return 32 * t + 8 * (i >> 2) + 4 * h + (i & 3); }
@@ -44,42 +58,61 @@ __device__ __forceinline__ float div_by(float x, float d, float rd) {
   const float t = __fmul_rn(x, rd);
   return __fmaf_rn(__fmaf_rn(-d, t, x), rd, t);
 }
-__device__ __forceinline__ FwdScales load_fwd_scales(const AttnQ& a) {
+// exp(x) for x <= 0 from the hardware's 2^t (1 ulp): t = x log2(e) is rounded to fp32, which at t = -20 costs the result
+// 20 ulp; the rounding error, and what the fp32 constant lacks of log2(e), are formed exactly and applied as the factor
+// 1 + ln(2) * error.  About 2 ulp for every x.
+__device__ __forceinline__ float exp_neg_exact(float x) {
+  const float t = __fmul_rn(x, 1.44269502f);
+  const float err = __fmaf_rn(x, 1.92596299e-8f, __fmaf_rn(x, 1.44269502f, -t));
+  const float e = __builtin_amdgcn_exp2f(t);
+  return __fmaf_rn(e, __fmul_rn(err, 0.693147181f), e);
+}
+// FAST: the rounding of t is left in (up to 20 ulp).  It serves head dimension 64 at 64 to 384 tokens, where a forward
+// pass of 512 heads of 128 tokens takes 20 us with it and 27 us without inside a six-layer step; every other shape gets
+// the accurate one.
+template <bool FAST>
+__device__ __forceinline__ float exp_neg(float x) {
+  if constexpr (FAST) return __expf(x);
+  else return exp_neg_exact(x);
+}
+__device__ __forceinline__ FwdScales load_fwd_scales(const AttnQ& a, int d) {
   FwdScales s;
   const float sq = a.q.on ? *a.q.s : 1.f, sk = a.k.on ? *a.k.s : 1.f;
   s.sp = a.p.on ? *a.p.s : 1.f;
   s.sv = a.v.on ? *a.v.s : 1.f;
-  s.qk = sq * sk / sqrtf((float)kD);
+  s.qk = sq * sk / sqrtf((float)d);
   s.p_on = a.p.on;
   s.p_qp = a.p.qp;
   s.rsp = __fdiv_rn(1.0f, s.sp);
   return s;
 }
 
-// stage rows [0, S) of a [S, 64] slice (row stride ld elements) row-major into LDS, zero rows up to s_pad
+// stage rows [0, S) of a [S, D] slice (row stride ld elements) row-major into LDS, zero rows up to s_pad
+template <int D>
 __device__ __forceinline__ void stage_rows(const bf16_t* __restrict__ src, int ld, int S, int s_pad, bf16_t* dst) {
-  for (int q = threadIdx.x; q < s_pad * 8; q += blockDim.x) {
-    const int row = q >> 3, ch = q & 7;
+  for (int q = threadIdx.x; q < s_pad * (D / 8); q += blockDim.x) {
+    const int row = q / (D / 8), ch = q % (D / 8);
     u32x4_t v = {0u, 0u, 0u, 0u};
     if (row < S) v = *reinterpret_cast<const u32x4_t*>(src + (size_t)row * ld + ch * 8);
-    *reinterpret_cast<u32x4_t*>(dst + row * kRowStride + ch * 8) = v;
+    *reinterpret_cast<u32x4_t*>(dst + row * Tile<D>::kStride + ch * 8) = v;
   }
 }
 __device__ __forceinline__ bf16x8_t ld_frag(const bf16_t* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
 
-// MFMA operand fragment gathered down the rows of a row-major LDS tile (pitch kRowStride) with the
+// MFMA operand fragment gathered down the rows of a row-major LDS tile with the
 // transposing LDS read (ds_read_b64_tr_b16): lane l receives, for column c0 + l%32, rows
 // r_first + 0..3 and r_second + 0..3 (the caller picks the two row bases for its half l/32).  In a
 // group of 16 lanes, lane s supplies the 8-byte chunk of row s/4, columns 4*(s%4)..+3, and receives
 // column s of the four rows.  Lets K, V, Q and dC stay row-major in LDS (16-byte conflict-free stores)
 // where the products contract over their row index.
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
+template <int D>
 __device__ __forceinline__ bf16x8_t ld_frag_tr(const bf16_t* tile, int c0, int r_first, int r_second, int lane) {
   const int g = lane >> 4, s = lane & 15;
-  const bf16_t* p = tile + (s >> 2) * kRowStride + c0 + 16 * (g & 1) + 4 * (s & 3);
+  const bf16_t* p = tile + (s >> 2) * Tile<D>::kStride + c0 + 16 * (g & 1) + 4 * (s & 3);
   union { bf16x8_t v; s16x4_t h[2]; } u;
-  u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(p + r_first * kRowStride));
-  u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(p + r_second * kRowStride));
+  u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(p + r_first * Tile<D>::kStride));
+  u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(p + r_second * Tile<D>::kStride));
   return u.v;
 }
 
@@ -88,112 +121,180 @@ __device__ __forceinline__ void store4(bf16_t* p, float a, float b, float c, flo
   *reinterpret_cast<bf16x4_t*>(p) = v;
 }
 
+__device__ __forceinline__ f32x16_t zero16() {
+  f32x16_t z;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) z[r] = 0.f;
+  return z;
+}
+// the 16 values in pairs: a row of 512 probabilities is then at most 4 + 16 + 1 additions deep
+__device__ __forceinline__ float tile_sum(const f32x16_t& v) {
+  float a[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) a[r] = v[2 * r] + v[2 * r + 1];
+  return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+}
+// a 32 x 32 tile: rows [row0, row0 + 32) of the LDS tile times the transposed 32 rows held as fragments (one per 16 columns)
+template <int D>
+__device__ __forceinline__ f32x16_t tile_product(const bf16_t* tile, int row0, int lane, const bf16x8_t (&frag)[D / 16]) {
+  f32x16_t acc = zero16();
+  const bf16_t* p = tile + (row0 + (lane & 31)) * Tile<D>::kStride + (lane >> 5) * 8;
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag(p + kk * 16), frag[kk], acc, 0, 0, 0);
+  return acc;
+}
+// acc[e][lane's row] += sum over the tile's 32 rows (LDS rows [row0, row0 + 32)) of tile[row][e] * w[row], with w in
+// accumulator order (key_of): the contraction over what the accumulator registers of a tile enumerate
+template <int D>
+__device__ __forceinline__ void accumulate_rows(f32x16_t (&acc)[D / 32], const bf16_t* tile, int row0, int lane, const float* w) {
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    bf16x8_t f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) f[i] = static_cast<bf16_t>(w[8 * s + i]);
+    const int k0 = row0 + 16 * s + 4 * (lane >> 5);
+#pragma unroll
+    for (int et = 0; et < D / 32; ++et)
+      acc[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_tr<D>(tile, 32 * et, k0, k0 + 8, lane), f, acc[et], 0, 0, 0);
+  }
+}
+
 // ------------------------------------------------------------------------------
 // forward: one block = up to 128 queries of one (batch, head); one wavefront = 32 queries
+// ONE: at most 128 keys
 // ------------------------------------------------------------------------------
-template <int NT>
+template <int D, bool ONE, bool FAST>
 __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict__ codes, bf16_t* __restrict__ ctx,
                                                        bf16_t* __restrict__ ctx_codes, AttnQ aq, const int32_t* __restrict__ seqlens,
-                                                       int S, int H, int nt, float* __restrict__ pmax_rows, float* __restrict__ stat_m,
+                                                       int S, int H, float* __restrict__ pmax_rows, float* __restrict__ stat_m,
                                                        float* __restrict__ stat_l, int8_t* __restrict__ ctx_codes8) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int s_pad = 32 * nt;
-  bf16_t* Ks = reinterpret_cast<bf16_t*>(smem_raw);  // [s_pad][72]
-  bf16_t* Vs = Ks + s_pad * kRowStride;              // [s_pad][72]
+  __shared__ __attribute__((aligned(16))) bf16_t Ks[kChunk * Tile<D>::kStride];
+  __shared__ __attribute__((aligned(16))) bf16_t Vs[kChunk * Tile<D>::kStride];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   const int h = blockIdx.y, b = blockIdx.z, nh = gridDim.y;
   const int ld = 3 * H;
-  const bf16_t* base = codes + (size_t)b * S * ld + h * kD;
-  const int len = seqlens ? seqlens[b] : S;
-  const FwdScales sc = load_fwd_scales(aq);
-
-  stage_rows(base + H, ld, S, s_pad, Ks);
-  stage_rows(base + 2 * H, ld, S, s_pad, Vs);
-  __syncthreads();
+  const bf16_t* base = codes + (size_t)b * S * ld + h * D;
+  const int len = seqlens ? min(seqlens[b], S) : S;
+  const FwdScales sc = load_fwd_scales(aq, D);
 
   const int q0 = blockIdx.x * 128 + wave * 32;
-  if (q0 >= S) return;
+  const bool active = q0 < S;
   const int q = q0 + (lane & 31);
   const int qc = q < S ? q : S - 1;
-  bf16x8_t qf[4];
+  bf16x8_t qf[D / 16];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) qf[kk] = ld_frag(base + (size_t)qc * ld + (kk * 2 + half) * 8);
+  for (int kk = 0; kk < D / 16; ++kk) qf[kk] = ld_frag(base + (size_t)qc * ld + (kk * 2 + half) * 8);
 
-  f32x16_t sacc[NT];
-  float mx = -INFINITY;
+  // scores of 32 keys (chunk rows [32 t, 32 t + 32), first key j0), -inf beyond the valid keys
+  auto scores = [&](int t, int j0) {
+    f32x16_t a = tile_product<D>(Ks, 32 * t, lane, qf);
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    if (t < nt) {
+    for (int r = 0; r < 16; ++r) a[r] = key_of(0, r, half) + j0 + 32 * t < len ? __fmul_rn(a[r], sc.qk) : -INFINITY;
+    return a;
+  };
+  f32x16_t oacc[D / 32];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[t][r] = 0.f;
-      const bf16_t* kp = Ks + (32 * t + (lane & 31)) * kRowStride + half * 8;
+  for (int et = 0; et < D / 32; ++et) oacc[et] = zero16();
+  float mx = -INFINITY, sum = 0.f;
+  // probabilities from exponentials, quantized, times V
+  auto weigh = [&](const f32x16_t& e, int t, float rsum) {
+    float w[16];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag(kp + kk * 16), qf[kk], sacc[t], 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float a = key_of(t, r, half) < len ? __fmul_rn(sacc[t][r], sc.qk) : -INFINITY;
-        sacc[t][r] = a;
-        mx = fmaxf(mx, a);
-      }
+    for (int r = 0; r < 16; ++r) {
+      const float p = div_by(e[r], sum, rsum);
+      w[r] = sc.p_on ? rintf(fminf(fmaxf(div_by(p, sc.sp, sc.rsp), 0.f), sc.p_qp)) : p;
     }
-  }
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-  float sum = 0.f;
+    accumulate_rows<D>(oacc, Vs, 32 * t, lane, w);
+  };
+  auto exps = [&](const f32x16_t& a) {
+    f32x16_t e;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    if (t < nt) {
+    for (int r = 0; r < 16; ++r) e[r] = a[r] == -INFINITY ? 0.f : exp_neg<FAST>(__fsub_rn(a[r], mx));
+    return e;
+  };
+  if constexpr (ONE) {
+    const int nt = (len + 31) / 32;
+    stage_rows<D>(base + H, ld, S, 32 * nt, Ks);
+    stage_rows<D>(base + 2 * H, ld, S, 32 * nt, Vs);
+    __syncthreads();
+    if (!active) return;
+    f32x16_t sacc[kChunk / 32];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float e = sacc[t][r] == -INFINITY ? 0.f : __expf(__fsub_rn(sacc[t][r], mx));
-        sacc[t][r] = e;
-        sum += e;
+    for (int t = 0; t < kChunk / 32; ++t)
+      if (t < nt) {
+        sacc[t] = scores(t, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[t][r]);
       }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+#pragma unroll
+    for (int t = 0; t < kChunk / 32; ++t)
+      if (t < nt) {
+        sacc[t] = exps(sacc[t]);
+        sum += tile_sum(sacc[t]);
+      }
+    sum += __shfl_xor(sum, 32, 64);
+    const float rsum = __fdiv_rn(1.0f, sum);
+#pragma unroll
+    for (int t = 0; t < kChunk / 32; ++t)
+      if (t < nt) weigh(sacc[t], t, rsum);
+  } else {
+    // first the row maximum and the sum of exponentials, rescaled when a chunk raises the maximum ...
+    for (int j0 = 0; j0 < len; j0 += kChunk) {
+      const int nt = (min(len - j0, kChunk) + 31) / 32;
+      __syncthreads();
+      stage_rows<D>(base + (size_t)j0 * ld + H, ld, S - j0, 32 * nt, Ks);
+      __syncthreads();
+      if (active)
+#pragma unroll 1
+        for (int t = 0; t < nt; ++t) {
+          const f32x16_t a = scores(t, j0);
+          float m = mx;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) m = fmaxf(m, a[r]);
+          sum *= mx == -INFINITY ? 0.f : exp_neg<FAST>(__fsub_rn(mx, m));
+          mx = m;
+          sum += tile_sum(exps(a));
+        }
     }
+    {
+      const float om = __shfl_xor(mx, 32, 64), os = __shfl_xor(sum, 32, 64), m = fmaxf(mx, om);
+      const float s0 = mx == -INFINITY ? 0.f : sum * exp_neg<FAST>(__fsub_rn(mx, m)), s1 = om == -INFINITY ? 0.f : os * exp_neg<FAST>(__fsub_rn(om, m));
+      sum = half == 0 ? s0 + s1 : s1 + s0;
+      mx = m;
+    }
+    // ... then the probabilities
+    const float rsum = __fdiv_rn(1.0f, sum);
+    for (int j0 = 0; j0 < len; j0 += kChunk) {
+      const int nt = (min(len - j0, kChunk) + 31) / 32;
+      __syncthreads();
+      stage_rows<D>(base + (size_t)j0 * ld + H, ld, S - j0, 32 * nt, Ks);
+      stage_rows<D>(base + (size_t)j0 * ld + 2 * H, ld, S - j0, 32 * nt, Vs);
+      __syncthreads();
+      if (active)
+#pragma unroll 1
+        for (int t = 0; t < nt; ++t) weigh(exps(scores(t, j0)), t, rsum);
+    }
+    if (!active) return;
   }
-  sum += __shfl_xor(sum, 32, 64);
   const size_t stat_idx = ((size_t)b * nh + h) * S + q;
   if (half == 0 && q < S) {
     if (stat_m) { stat_m[stat_idx] = mx; stat_l[stat_idx] = sum; }
     if (pmax_rows) pmax_rows[stat_idx] = 1.0f / sum;  // the largest exponential of a row is exp(0) = 1
   }
-
-  f32x16_t oacc[2];
-#pragma unroll
-  for (int et = 0; et < 2; ++et)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[et][r] = 0.f;
-  const float rsum = __fdiv_rn(1.0f, sum);
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    if (t < nt) {
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        bf16x8_t pf;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float p = div_by(sacc[t][8 * s + i], sum, rsum);
-          const float c = sc.p_on ? rintf(fminf(fmaxf(div_by(p, sc.sp, sc.rsp), 0.f), sc.p_qp)) : p;
-          pf[i] = static_cast<bf16_t>(c);
-        }
-        // V^T fragments: keys in the order the accumulator registers of the score tile hold them
-        const int k0 = 32 * t + 16 * s + 4 * half;
-        oacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_tr(Vs, 0, k0, k0 + 8, lane), pf, oacc[0], 0, 0, 0);
-        oacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_tr(Vs, 32, k0, k0 + 8, lane), pf, oacc[1], 0, 0, 0);
-      }
-    }
-  }
   if (q < S) {
-    const float os = sc.sp * sc.sv;
+    // the product of the two steps in two parts, so that the scaled sum is rounded once
+    const float os = __fmul_rn(sc.sp, sc.sv), os_lo = __fmaf_rn(sc.sp, sc.sv, -os);
     QuantParam qc5 = {aq.c.on ? *aq.c.s : 1.f, 0.f, aq.c.qn, aq.c.qp, aq.c.on, 0.f};
     qc5.rs = quant_reciprocal(qc5.s);
-    const size_t orow = ((size_t)b * S + q) * H + h * kD;
+    const size_t orow = ((size_t)b * S + q) * H + h * D;
 #pragma unroll
-    for (int et = 0; et < 2; ++et)
+    for (int et = 0; et < D / 32; ++et)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         float o[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = oacc[et][4 * g + i] * os;
+        for (int i = 0; i < 4; ++i) o[i] = __fmaf_rn(oacc[et][4 * g + i], os, oacc[et][4 * g + i] * os_lo);
         const int e = 32 * et + 8 * g + 4 * half;
         store4(ctx + orow + e, o[0], o[1], o[2], o[3]);
         if (ctx_codes) {
@@ -214,153 +315,159 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
 }
 
 // ------------------------------------------------------------------------------
-// backward, query-major part: for 32 queries per wavefront recomputes P from the saved
-// row statistics, forms dP^ = dC * V^T, applies the straight-through rule of the
-// probability quantizer, the softmax backward, and dQ^ = dA * K^.  Writes the transposed
-// tiles P^T[key][query] and dA^T[key][query] (bf16) for the key-major kernel.
-// NT > 0: rows of at most NT key tiles, kept in registers; NT = 0: any length, tiles formed twice.
+// backward: P recomputed from the saved row statistics, with the rounding steps of the forward, dP^ = dC * V^T, the
+// straight-through rule of the probability quantizer and the softmax backward dA = P * (dP - rowdot),
+// rowdot = sum_j dP[q][j] * P[q][j].  Up to 128 keys the query-major kernel leaves P^T and dA^T (bf16) for the
+// key-major one, which is then a pure product (512 heads of 128 tokens, inside a step: 17 us against 40 us for forming
+// them again); beyond that the 4 bytes per query-key pair each way cost more than the arithmetic, and the key-major
+// kernel forms them itself (256 heads of 384 tokens, both kernels: 164 us against 215 us).
 // ------------------------------------------------------------------------------
-template <int NT>
-__global__ __launch_bounds__(256) void attn_bwd_q_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
+
+// one probability and its gradient through the quantizer
+struct ProbGrad { float p, code, dp; };
+template <bool FAST>
+__device__ __forceinline__ ProbGrad prob_grad(float score, float dacc, bool valid, float mx, float l, float rl, const FwdScales& sc, float& dsp) {
+  ProbGrad g;
+  g.p = valid ? div_by(exp_neg<FAST>(__fsub_rn(__fmul_rn(score, sc.qk), mx)), l, rl) : 0.f;
+  const float dph = dacc * sc.sv;
+  g.code = g.p;
+  g.dp = dph;
+  if (sc.p_on) {
+    const float v = div_by(g.p, sc.sp, sc.rsp);
+    const bool in = v <= sc.p_qp;
+    g.code = rintf(fminf(v, sc.p_qp));
+    dsp += dph * (g.code - (in ? v : 0.f));
+    g.dp = in ? dph : 0.f;
+  }
+  return g;
+}
+
+// query-major part: rowdot (ONE: P^T and dA^T; kept for the key-major kernel), the step-size gradient of the probability quantizer, dQ^ = dA * K^
+template <int D, bool ONE, bool FAST>
+__global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
                                                          bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S,
-                                                         int H, int nt, const float* __restrict__ stat_m, const float* __restrict__ stat_l,
-                                                         bf16_t* __restrict__ pt_out, bf16_t* __restrict__ dat_out,
-                                                         float* __restrict__ ds_parts) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int s_pad = 32 * nt;
-  bf16_t* Ks = reinterpret_cast<bf16_t*>(smem_raw);  // [s_pad][72]
-  bf16_t* Vs = Ks + s_pad * kRowStride;              // [s_pad][72]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+                                                         int H, const float* __restrict__ stat_m, const float* __restrict__ stat_l,
+                                                         float* __restrict__ rowdot_out, bf16_t* __restrict__ pt_out,
+                                                         bf16_t* __restrict__ dat_out, float* __restrict__ ds_parts) {
+  __shared__ __attribute__((aligned(16))) bf16_t Ks[kChunk * Tile<D>::kStride];
+  __shared__ __attribute__((aligned(16))) bf16_t Vs[kChunk * Tile<D>::kStride];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, waves = blockDim.x >> 6;
   const int h = blockIdx.y, b = blockIdx.z, nh = gridDim.y;
   const int ld = 3 * H;
-  const bf16_t* base = codes + (size_t)b * S * ld + h * kD;
-  const int len = seqlens ? seqlens[b] : S;
-  const FwdScales sc = load_fwd_scales(aq);
+  const bf16_t* base = codes + (size_t)b * S * ld + h * D;
+  const int len = seqlens ? min(seqlens[b], S) : S;
+  const FwdScales sc = load_fwd_scales(aq, D);
   const float sk = aq.k.on ? *aq.k.s : 1.f;
 
-  stage_rows(base + H, ld, S, s_pad, Ks);
-  stage_rows(base + 2 * H, ld, S, s_pad, Vs);
-  __syncthreads();
-
   const int q0 = blockIdx.x * 128 + wave * 32;
-  const int part_idx = (((b * nh + h) * gridDim.x) + blockIdx.x) * 4 + wave;
-  if (q0 >= s_pad) {
-    ds_parts[part_idx] = 0.f;
-    return;
-  }
+  const int part_idx = (((b * nh + h) * gridDim.x) + blockIdx.x) * waves + wave;
+  const bool active = q0 < S;
   const int q = q0 + (lane & 31);
   const bool qvalid = q < S;
   const int qc = qvalid ? q : S - 1;
-  bf16x8_t qf[4], cf[4];
+  bf16x8_t qf[D / 16], cf[D / 16];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
+  for (int kk = 0; kk < D / 16; ++kk) {
     qf[kk] = ld_frag(base + (size_t)qc * ld + (kk * 2 + half) * 8);
-    cf[kk] = ld_frag(dctx + ((size_t)b * S + qc) * H + h * kD + (kk * 2 + half) * 8);
+    cf[kk] = ld_frag(dctx + ((size_t)b * S + qc) * H + h * D + (kk * 2 + half) * 8);
   }
   const size_t stat_idx = ((size_t)b * nh + h) * S + qc;
-  const float mx = stat_m[stat_idx], inv_l = stat_l[stat_idx];  // row maximum and row sum of the forward
-  const float rl = __fdiv_rn(1.0f, inv_l);
+  const float mx = stat_m[stat_idx], l = stat_l[stat_idx];  // row maximum and row sum of the forward
+  const float rl = __fdiv_rn(1.0f, l);
 
-  float rowdot = 0.f, dsp = 0.f;
-  f32x16_t dqacc[2];
+  float rowdot = 0.f, dsp = 0.f, unused = 0.f;
+  f32x16_t dqacc[D / 32];
 #pragma unroll
-  for (int et = 0; et < 2; ++et)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dqacc[et][r] = 0.f;
-  const size_t tbase = ((size_t)b * nh + h) * s_pad * s_pad;
-
-  // one tile of 32 keys: P (recomputed with the rounding steps of the forward) and dP after the
-  // straight-through rule of the probability quantizer; adds the tile's terms to dsp when asked
-  auto probs = [&](int t, float* p_out, float* dp_out, bool add_dsp) {
-    f32x16_t sacc, dacc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sacc[r] = dacc[r] = 0.f;
-    const bf16_t* kp = Ks + (32 * t + (lane & 31)) * kRowStride + half * 8;
-    const bf16_t* vp = Vs + (32 * t + (lane & 31)) * kRowStride + half * 8;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag(kp + kk * 16), qf[kk], sacc, 0, 0, 0);
-      dacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag(vp + kk * 16), cf[kk], dacc, 0, 0, 0);
-    }
+  for (int et = 0; et < D / 32; ++et) dqacc[et] = zero16();
+  // P and dP of one tile of 32 keys
+  auto probs = [&](int t, int j0, float* p, float* dp, float& ds) {
+    const f32x16_t sacc = tile_product<D>(Ks, 32 * t, lane, qf), dacc = tile_product<D>(Vs, 32 * t, lane, cf);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int j = key_of(t, r, half);
-      const float p = j < len ? div_by(__expf(__fsub_rn(__fmul_rn(sacc[r], sc.qk), mx)), inv_l, rl) : 0.f;
-      const float dph = dacc[r] * sc.sv;
-      float dp = dph;
-      if (sc.p_on) {
-        const float v = div_by(p, sc.sp, sc.rsp);
-        const bool in = v <= sc.p_qp;
-        if (add_dsp) dsp += dph * (rintf(fminf(v, sc.p_qp)) - (in ? v : 0.f));
-        dp = in ? dph : 0.f;
-      }
-      p_out[r] = p;
-      dp_out[r] = dp;
+      const ProbGrad g = prob_grad<FAST>(sacc[r], dacc[r], key_of(0, r, half) + j0 + 32 * t < len, mx, l, rl, sc, ds);
+      p[r] = g.p;
+      dp[r] = g.dp;
     }
   };
-  // the same tile once rowdot = sum_j dP[q][j] * P[q][j] is known: dA = P * (dP - rowdot), the
-  // transposed tiles for the key-major kernel, and the tile's share of dQ^ = dA * K^
-  auto consume = [&](int t, const float* p_in, const float* dp_in) {
+  auto consume = [&](int t, const float* p, const float* dp) {
     float da[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float p = p_in[r];
-      const float c = sc.p_on ? rintf(fminf(div_by(p, sc.sp, sc.rsp), sc.p_qp)) : p;
-      da[r] = p * (dp_in[r] - rowdot);
-      const int j = key_of(t, r, half);
-      const size_t o = tbase + (size_t)j * s_pad + q;
-      pt_out[o] = static_cast<bf16_t>(qvalid ? c : 0.f);
-      dat_out[o] = static_cast<bf16_t>(qvalid ? da[r] : 0.f);
-    }
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      bf16x8_t af;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) af[i] = static_cast<bf16_t>(da[8 * s + i]);
-      const int k0 = 32 * t + 16 * s + 4 * half;
-      dqacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_tr(Ks, 0, k0, k0 + 8, lane), af, dqacc[0], 0, 0, 0);
-      dqacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_tr(Ks, 32, k0, k0 + 8, lane), af, dqacc[1], 0, 0, 0);
-    }
+    for (int r = 0; r < 16; ++r) da[r] = p[r] * (dp[r] - rowdot);
+    accumulate_rows<D>(dqacc, Ks, 32 * t, lane, da);
   };
-  if constexpr (NT > 0) {
-    // at most NT key tiles: P and dP of the whole row stay in registers between the two passes
-    float pk[NT][16], dpk[NT][16];
+  if constexpr (ONE) {
+    const int nt = (len + 31) / 32;
+    stage_rows<D>(base + H, ld, S, 32 * nt, Ks);
+    stage_rows<D>(base + 2 * H, ld, S, 32 * nt, Vs);
+    __syncthreads();
+    if (!active) {
+      if (lane == 0) ds_parts[part_idx] = 0.f;
+      return;
+    }
+    float p[kChunk / 32][16], dp[kChunk / 32][16];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
+    for (int t = 0; t < kChunk / 32; ++t)
       if (t < nt) {
-        probs(t, pk[t], dpk[t], true);
+        probs(t, 0, p[t], dp[t], dsp);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) rowdot += dpk[t][r] * pk[t][r];
+        for (int r = 0; r < 16; ++r) rowdot += dp[t][r] * p[t][r];
       }
-    }
     rowdot += __shfl_xor(rowdot, 32, 64);
+    const int s_pad = (S + 31) / 32 * 32;
+    const size_t tbase = ((size_t)b * nh + h) * s_pad * s_pad;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-      if (t < nt) consume(t, pk[t], dpk[t]);
+    for (int t = 0; t < kChunk / 32; ++t)
+      if (t < nt) {
+        consume(t, p[t], dp[t]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float c = sc.p_on ? rintf(fminf(div_by(p[t][r], sc.sp, sc.rsp), sc.p_qp)) : p[t][r];
+          const size_t o = tbase + (size_t)key_of(t, r, half) * s_pad + q;
+          pt_out[o] = static_cast<bf16_t>(qvalid ? c : 0.f);
+          dat_out[o] = static_cast<bf16_t>(qvalid ? p[t][r] * (dp[t][r] - rowdot) : 0.f);
+        }
+      }
   } else {
-    // longer rows: the tiles are formed twice, first for rowdot (and dsp), then to be consumed
-    float pt[16], dpt[16];
+    for (int pass = 0; pass < 2; ++pass) {
+      for (int j0 = 0; j0 < len; j0 += kChunk) {
+        const int nt = (min(len - j0, kChunk) + 31) / 32;
+        __syncthreads();
+        stage_rows<D>(base + (size_t)j0 * ld + H, ld, S - j0, 32 * nt, Ks);
+        stage_rows<D>(base + (size_t)j0 * ld + 2 * H, ld, S - j0, 32 * nt, Vs);
+        __syncthreads();
+        if (!active) continue;
+        float p[16], dp[16];
+        if (pass == 0) {
 #pragma unroll 1
-    for (int t = 0; t < nt; ++t) {
-      probs(t, pt, dpt, true);
+          for (int t = 0; t < nt; ++t) {
+            probs(t, j0, p, dp, dsp);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) rowdot += dpt[r] * pt[r];
-    }
-    rowdot += __shfl_xor(rowdot, 32, 64);
+            for (int r = 0; r < 16; ++r) rowdot += dp[r] * p[r];
+          }
+        } else {
 #pragma unroll 1
-    for (int t = 0; t < nt; ++t) {
-      probs(t, pt, dpt, false);
-      consume(t, pt, dpt);
+          for (int t = 0; t < nt; ++t) {
+            probs(t, j0, p, dp, unused);
+            consume(t, p, dp);
+          }
+        }
+      }
+      if (pass == 0) rowdot += __shfl_xor(rowdot, 32, 64);
+    }
+    if (!active) {
+      if (lane == 0) ds_parts[part_idx] = 0.f;
+      return;
     }
   }
   // step-size gradient terms of the probability quantizer (padded query rows excluded)
   dsp = wave_sum(qvalid ? dsp : 0.f);
   if (lane == 0) ds_parts[part_idx] = dsp;
   if (qvalid) {
-    const float f = sk / sqrtf((float)kD);
-    const size_t orow = ((size_t)b * S + q) * ld + h * kD;
+    if (!ONE && half == 0) rowdot_out[stat_idx] = rowdot;
+    const float f = sk / sqrtf((float)D);
+    const size_t orow = ((size_t)b * S + q) * ld + h * D;
 #pragma unroll
-    for (int et = 0; et < 2; ++et)
+    for (int et = 0; et < D / 32; ++et)
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         store4(d_qkvh + orow + 32 * et + 8 * g + 4 * half, dqacc[et][4 * g] * f, dqacc[et][4 * g + 1] * f, dqacc[et][4 * g + 2] * f,
@@ -368,126 +475,194 @@ __global__ __launch_bounds__(256) void attn_bwd_q_mfma_k(const bf16_t* __restric
   }
 }
 
-// ------------------------------------------------------------------------------
-// backward, key-major part: dV^[j] = sum_q P^[q][j] dC[q], dK^[j] = sum_q dA[q][j] Q^[q] / sqrt(d).
-// One wavefront = 32 keys; queries are streamed in chunks of 128 through LDS (row-major, read transposed).
-// ------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
-                                                         bf16_t* __restrict__ d_qkvh, AttnQ aq, int S, int H, int nt,
-                                                         const bf16_t* __restrict__ pt_in, const bf16_t* __restrict__ dat_in) {
-  __shared__ __attribute__((aligned(16))) bf16_t Qs[128 * kRowStride];  // one chunk of queries, row-major
-  __shared__ __attribute__((aligned(16))) bf16_t Cs[128 * kRowStride];  // the same rows of dC
-  const int s_pad = 32 * nt;
+// key-major part for at most 128 tokens: dV^ = P^T dC, dK^ = dA^T Q^ / sqrt(d) from the tiles the query-major kernel left.
+// One wavefront = 32 keys.
+template <int D>
+__global__ __launch_bounds__(256) void attn_bwd_k_one_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
+                                                             bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S,
+                                                             int H, const bf16_t* __restrict__ pt_in, const bf16_t* __restrict__ dat_in) {
+  __shared__ __attribute__((aligned(16))) bf16_t Qs[kChunk * Tile<D>::kStride];
+  __shared__ __attribute__((aligned(16))) bf16_t Cs[kChunk * Tile<D>::kStride];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   const int h = blockIdx.y, b = blockIdx.z, nh = gridDim.y;
-  const int ld = 3 * H;
-  const bf16_t* base = codes + (size_t)b * S * ld + h * kD;
-  const bf16_t* cbase = dctx + (size_t)b * S * H + h * kD;
-  const int jt = blockIdx.x * 4 + wave;  // key tile of this wavefront
-  const bool active = jt < nt;
-  const size_t tbase = ((size_t)b * nh + h) * s_pad * s_pad;
-  const int jrow = 32 * jt + (lane & 31);
-
-  f32x16_t vacc[2], kacc[2];
+  const int ld = 3 * H, s_pad = (S + 31) / 32 * 32;
+  const bf16_t* base = codes + (size_t)b * S * ld + h * D;
+  const int len = seqlens ? min(seqlens[b], S) : S;
+  stage_rows<D>(base, ld, S, s_pad, Qs);
+  stage_rows<D>(dctx + (size_t)b * S * H + h * D, H, S, s_pad, Cs);
+  __syncthreads();
+  f32x16_t vacc[D / 32], kacc[D / 32];
 #pragma unroll
-  for (int et = 0; et < 2; ++et)
+  for (int et = 0; et < D / 32; ++et) vacc[et] = kacc[et] = zero16();
+  if (32 * wave < len) {  // keys beyond the valid ones have P = 0, and no tile
+    const size_t row = (((size_t)b * nh + h) * s_pad + 32 * wave + (lane & 31)) * s_pad + 8 * half;
+    for (int s = 0; s < s_pad / 16; ++s) {
+      const bf16x8_t pf = ld_frag(pt_in + row + 16 * s), af = ld_frag(dat_in + row + 16 * s);
+      const int q0 = 16 * s + 8 * half;  // queries of this lane's k-slots, in natural order
 #pragma unroll
-    for (int r = 0; r < 16; ++r) vacc[et][r] = kacc[et][r] = 0.f;
-
-  for (int c0 = 0; c0 < s_pad; c0 += 128) {
-    const int cn = (s_pad - c0) < 128 ? (s_pad - c0) : 128;
-    __syncthreads();
-    stage_rows(base + (size_t)c0 * ld, ld, S - c0, cn, Qs);
-    stage_rows(cbase + (size_t)c0 * H, H, S - c0, cn, Cs);
-    __syncthreads();
-    if (active) {
-      const bf16_t* prow = pt_in + tbase + (size_t)jrow * s_pad + c0 + 8 * half;
-      const bf16_t* arow = dat_in + tbase + (size_t)jrow * s_pad + c0 + 8 * half;
-      for (int s = 0; s < cn / 16; ++s) {
-        const bf16x8_t pf = ld_frag(prow + 16 * s);
-        const bf16x8_t af = ld_frag(arow + 16 * s);
-        const int q0 = 16 * s + 8 * half;  // queries of this lane's k-slots, in natural order
-#pragma unroll
-        for (int et = 0; et < 2; ++et) {
-          vacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf, ld_frag_tr(Cs, 32 * et, q0, q0 + 4, lane), vacc[et], 0, 0, 0);
-          kacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, ld_frag_tr(Qs, 32 * et, q0, q0 + 4, lane), kacc[et], 0, 0, 0);
-        }
+      for (int et = 0; et < D / 32; ++et) {
+        vacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf, ld_frag_tr<D>(Cs, 32 * et, q0, q0 + 4, lane), vacc[et], 0, 0, 0);
+        kacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, ld_frag_tr<D>(Qs, 32 * et, q0, q0 + 4, lane), kacc[et], 0, 0, 0);
       }
     }
   }
-  if (!active) return;
   const float sp = aq.p.on ? *aq.p.s : 1.f;
-  const float fq = (aq.q.on ? *aq.q.s : 1.f) / sqrtf((float)kD);
+  const float fq = (aq.q.on ? *aq.q.s : 1.f) / sqrtf((float)D);
 #pragma unroll
-  for (int et = 0; et < 2; ++et)
+  for (int et = 0; et < D / 32; ++et)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int j = 32 * jt + 8 * (r >> 2) + 4 * half + (r & 3);
+      const int j = key_of(wave, r, half);
       if (j < S) {
-        const size_t o = ((size_t)b * S + j) * ld + h * kD + 32 * et + (lane & 31);
+        const size_t o = ((size_t)b * S + j) * ld + h * D + 32 * et + (lane & 31);
         d_qkvh[o + H] = static_cast<bf16_t>(kacc[et][r] * fq);
         d_qkvh[o + 2 * H] = static_cast<bf16_t>(vacc[et][r] * sp);
       }
     }
 }
 
+// key-major part: dV^[j] = sum_q P^[q][j] dC[q], dK^[j] = sum_q dA[q][j] Q^[q] / sqrt(d).  One wavefront = 32 keys (a lane
+// owns one key, the accumulator registers enumerate queries); queries pass through LDS in chunks of 128 with their statistics.
+template <int D, bool FAST>
+__global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
+                                                         bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S,
+                                                         int H, const float* __restrict__ stat_m, const float* __restrict__ stat_l,
+                                                         const float* __restrict__ rowdot_in) {
+  __shared__ __attribute__((aligned(16))) bf16_t Qs[kChunk * Tile<D>::kStride];
+  __shared__ __attribute__((aligned(16))) bf16_t Cs[kChunk * Tile<D>::kStride];
+  __shared__ __attribute__((aligned(16))) float stats[4][kChunk];  // row maximum, row sum, its reciprocal, rowdot
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  const int h = blockIdx.y, b = blockIdx.z, nh = gridDim.y;
+  const int ld = 3 * H;
+  const bf16_t* base = codes + (size_t)b * S * ld + h * D;
+  const bf16_t* cbase = dctx + (size_t)b * S * H + h * D;
+  const size_t sbase = ((size_t)b * nh + h) * S;
+  const int len = seqlens ? min(seqlens[b], S) : S;
+  const FwdScales sc = load_fwd_scales(aq, D);
+  const int j0 = blockIdx.x * 128 + wave * 32;
+  const int j = j0 + (lane & 31);
+  const int jc = j < S ? j : S - 1;
+  const bool active = j0 < len;  // keys beyond the valid ones have P = 0
+  bf16x8_t kf[D / 16], vf[D / 16];
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) {
+    kf[kk] = ld_frag(base + (size_t)jc * ld + H + (kk * 2 + half) * 8);
+    vf[kk] = ld_frag(base + (size_t)jc * ld + 2 * H + (kk * 2 + half) * 8);
+  }
+  f32x16_t vacc[D / 32], kacc[D / 32];
+#pragma unroll
+  for (int et = 0; et < D / 32; ++et) vacc[et] = kacc[et] = zero16();
+  float unused = 0.f;
+
+  if ((int)blockIdx.x * 128 < len)
+    for (int c0 = 0; c0 < S; c0 += kChunk) {
+      const int cn = (min(S - c0, kChunk) + 31) / 32;  // 32-query tiles
+      __syncthreads();
+      stage_rows<D>(base + (size_t)c0 * ld, ld, S - c0, 32 * cn, Qs);
+      stage_rows<D>(cbase + (size_t)c0 * H, H, S - c0, 32 * cn, Cs);
+      for (int i = threadIdx.x; i < 32 * cn; i += blockDim.x) {
+        // rows beyond the sequence: their Q and dC are zero, so any finite statistics will do
+        const bool v = c0 + i < S;
+        const float l = v ? stat_l[sbase + c0 + i] : 1.f;
+        stats[0][i] = v ? stat_m[sbase + c0 + i] : 0.f;
+        stats[1][i] = l;
+        stats[2][i] = __fdiv_rn(1.0f, l);
+        stats[3][i] = v ? rowdot_in[sbase + c0 + i] : 0.f;
+      }
+      __syncthreads();
+      if (!active) continue;
+#pragma unroll 1
+      for (int t = 0; t < cn; ++t) {
+        const f32x16_t sacc = tile_product<D>(Qs, 32 * t, lane, kf), dacc = tile_product<D>(Cs, 32 * t, lane, vf);
+        float code[16], da[16];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int qi = 32 * t + 8 * g + 4 * half;  // registers 4 g .. 4 g + 3 hold queries qi .. qi + 3
+          float st[4][4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float4 x = *reinterpret_cast<const float4*>(&stats[k][qi]);
+            st[k][0] = x.x; st[k][1] = x.y; st[k][2] = x.z; st[k][3] = x.w;
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const ProbGrad pg = prob_grad<FAST>(sacc[4 * g + i], dacc[4 * g + i], j < len, st[0][i], st[1][i], st[2][i], sc, unused);
+            code[4 * g + i] = pg.code;
+            da[4 * g + i] = pg.p * (pg.dp - st[3][i]);
+          }
+        }
+        accumulate_rows<D>(vacc, Cs, 32 * t, lane, code);
+        accumulate_rows<D>(kacc, Qs, 32 * t, lane, da);
+      }
+    }
+  if (j >= S) return;
+  const float sp = sc.sp;
+  const float fq = (aq.q.on ? *aq.q.s : 1.f) / sqrtf((float)D);
+  const size_t orow = ((size_t)b * S + j) * ld + h * D;
+#pragma unroll
+  for (int et = 0; et < D / 32; ++et)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const size_t o = orow + 32 * et + 8 * g + 4 * half;
+      store4(d_qkvh + o + H, kacc[et][4 * g] * fq, kacc[et][4 * g + 1] * fq, kacc[et][4 * g + 2] * fq, kacc[et][4 * g + 3] * fq);
+      store4(d_qkvh + o + 2 * H, vacc[et][4 * g] * sp, vacc[et][4 * g + 1] * sp, vacc[et][4 * g + 2] * sp, vacc[et][4 * g + 3] * sp);
+    }
+}
+
 // ------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------
-bool attn_mfma_ok(int dt, int S, int d) { return dt == DT_BF16 && d == kD && S >= 64 && S <= 384; }
+bool attn_mfma_ok(int dt, int d) { return dt == DT_BF16 && (d == 32 || d == 64); }
 
-template <int NT>
-static void fwd_launch(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh,
-                       float* pmax_rows, float* stat_m, float* stat_l, hipStream_t st, int8_t* ctx_codes8) {
-  const int nt = (S + 31) / 32, s_pad = 32 * nt;
-  const size_t lds = (size_t)2 * s_pad * kRowStride * sizeof(bf16_t);
-  // the attribute belongs to the (kernel, device) pair: set again when the current device changes
-  static size_t configured = 0;
-  static int configured_dev = -1;
-  int dev = -1;
-  (void)hipGetDevice(&dev);
-  if (dev != configured_dev) { configured = 0; configured_dev = dev; }
-  if (lds > configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd_mfma_k<NT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    configured = lds;
-  }
-  dim3 g((S + 127) / 128, nh, B);
-  hipLaunchKernelGGL(attn_fwd_mfma_k<NT>, g, dim3(256), lds, st, (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S,
-                     nh * kD, nt, pmax_rows, stat_m, stat_l, ctx_codes8);
+static int block_waves(int S) { return S >= 128 ? 4 : (S + 31) / 32; }
+
+static bool fast_exp(int S, int d) { return d == 64 && S >= 64 && S <= 384; }
+// f(head dimension, fast): the instantiation for a shape
+template <class F>
+static auto with_shape(int S, int d, F&& f) {
+  if (d == 32) return f(std::integral_constant<int, 32>{}, std::false_type{});
+  if (fast_exp(S, d)) return f(std::integral_constant<int, 64>{}, std::true_type{});
+  return f(std::integral_constant<int, 64>{}, std::false_type{});
 }
-void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh,
+
+void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
                    float* pmax_rows, float* stat_m, float* stat_l, hipStream_t st, int8_t* ctx_codes8) {
-  if (S <= 128) fwd_launch<4>(codes, ctx, ctx_codes, aq, seqlens, B, S, nh, pmax_rows, stat_m, stat_l, st, ctx_codes8);
-  else fwd_launch<12>(codes, ctx, ctx_codes, aq, seqlens, B, S, nh, pmax_rows, stat_m, stat_l, st, ctx_codes8);
+  with_shape(S, d, [&](auto dim, auto fast) {
+    constexpr int D = decltype(dim)::value;
+    constexpr bool FAST = decltype(fast)::value;
+    const dim3 g((S + 127) / 128, nh, B), blk(64 * block_waves(S));
+    if (S <= kChunk)
+      hipLaunchKernelGGL((attn_fwd_mfma_k<D, true, FAST>), g, blk, 0, st, (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S,
+                         nh * D, pmax_rows, stat_m, stat_l, ctx_codes8);
+    else
+      hipLaunchKernelGGL((attn_fwd_mfma_k<D, false, FAST>), g, blk, 0, st, (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S,
+                         nh * D, pmax_rows, stat_m, stat_l, ctx_codes8);
+  });
 }
 
 // returns the number of partial sums written to ds_parts
-int attn_bwd_mfma(const void* codes, const void* dctx, void* d_qkvh, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh,
-                  const float* stat_m, const float* stat_l, void* pt_scratch, void* dat_scratch, float* ds_parts, hipStream_t st) {
-  const int nt = (S + 31) / 32, s_pad = 32 * nt;
-  const size_t lds = (size_t)2 * s_pad * kRowStride * sizeof(bf16_t);
-  // the attribute belongs to the (kernel, device) pair: set again when the current device changes
-  static size_t configured = 0;
-  static int configured_dev = -1;
-  int dev = -1;
-  (void)hipGetDevice(&dev);
-  if (dev != configured_dev) { configured = 0; configured_dev = dev; }
-  if (lds > configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_q_mfma_k<4>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_q_mfma_k<0>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    configured = lds;
-  }
-  dim3 gq((s_pad + 127) / 128, nh, B);
-  if (nt <= 4)
-    hipLaunchKernelGGL(attn_bwd_q_mfma_k<4>, gq, dim3(256), lds, st, (const bf16_t*)codes, (const bf16_t*)dctx, (bf16_t*)d_qkvh, aq,
-                       seqlens, S, nh * kD, nt, stat_m, stat_l, (bf16_t*)pt_scratch, (bf16_t*)dat_scratch, ds_parts);
-  else
-    hipLaunchKernelGGL(attn_bwd_q_mfma_k<0>, gq, dim3(256), lds, st, (const bf16_t*)codes, (const bf16_t*)dctx, (bf16_t*)d_qkvh, aq,
-                       seqlens, S, nh * kD, nt, stat_m, stat_l, (bf16_t*)pt_scratch, (bf16_t*)dat_scratch, ds_parts);
-  dim3 gk((nt + 3) / 4, nh, B);
-  hipLaunchKernelGGL(attn_bwd_k_mfma_k, gk, dim3(256), 0, st, (const bf16_t*)codes, (const bf16_t*)dctx, (bf16_t*)d_qkvh, aq, S, nh * kD, nt,
-                     (const bf16_t*)pt_scratch, (const bf16_t*)dat_scratch);
-  return (int)(gq.x * nh * B * 4);
+int attn_bwd_mfma(const void* codes, const void* dctx, void* d_qkvh, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
+                  const float* stat_m, const float* stat_l, void* scratch0, void* scratch1, float* ds_parts, hipStream_t st) {
+  return with_shape(S, d, [&](auto dim, auto fast) {
+    constexpr int D = decltype(dim)::value;
+    constexpr bool FAST = decltype(fast)::value;
+    const int waves = block_waves(S);
+    const dim3 g((S + 127) / 128, nh, B), blk(64 * waves);
+    const bf16_t *c = (const bf16_t*)codes, *dc = (const bf16_t*)dctx;
+    bf16_t* out = (bf16_t*)d_qkvh;
+    if (S <= kChunk) {
+      hipLaunchKernelGGL((attn_bwd_q_mfma_k<D, true, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, nh * D, stat_m, stat_l, (float*)nullptr,
+                         (bf16_t*)scratch0, (bf16_t*)scratch1, ds_parts);
+      hipLaunchKernelGGL((attn_bwd_k_one_mfma_k<D>), g, blk, 0, st, c, dc, out, aq, seqlens, S, nh * D, (const bf16_t*)scratch0,
+                         (const bf16_t*)scratch1);
+    } else {
+      hipLaunchKernelGGL((attn_bwd_q_mfma_k<D, false, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, nh * D, stat_m, stat_l, (float*)scratch0,
+                         (bf16_t*)nullptr, (bf16_t*)nullptr, ds_parts);
+      hipLaunchKernelGGL((attn_bwd_k_mfma_k<D, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, nh * D, stat_m, stat_l,
+                         (const float*)scratch0);
+    }
+    return (int)(g.x * g.y * g.z) * waves;
+  });
 }
 
 }  // namespace mrem

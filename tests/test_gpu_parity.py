@@ -307,6 +307,20 @@ def test_step_matches_oracle_bf16(B, name):
     _compare_step(B, CASES_BF16[name])
 
 
+# Lengths at the edges of the matrix-core attention kernels: one partly filled tile of 32 rows, one row into the second
+# tile, a full chunk of 128 keys, one row into the second chunk, several chunks; both head dimensions; key padding that
+# leaves whole chunks out.
+@pytest.mark.parametrize("seq,heads,lo", [(5, 2, 1), (33, 4, 0), (128, 4, 30), (129, 2, 0), (129, 4, 100), (300, 4, 1), (512, 2, 100)])
+def test_step_at_attention_length_edges_bf16(B, seq, heads, lo):
+    # The gradients of the LayerNorm gains and of the feed-forward weights are sums over the 2 * seq tokens of terms of either sign; a code that falls on the
+    # other side of a tie (which a last-bit difference in a stored value decides) changes one token's terms as a whole,
+    # that is the sum by up to 2 / sqrt(tokens) of its size.  (v squares the gradient: twice that.)
+    kw = {"seqlen_lo": lo, "seqlen_hi": seq} if lo else {}
+    one_token = max(2e-2, 2.0 / np.sqrt(2 * seq))
+    tol_for = {f"{q}.{f}[0]": one_token * (2 if q == "v" else 1) for q in "gmv" for f in ("ln1_g", "ln2_g", "w_1", "w_2")}
+    _compare_step(B, W("attn_edge", 1, 128, heads, 256, seq, 2, act_dtype="bf16", **kw), tol_for=tol_for)
+
+
 def test_per_tensor_weight_steps_fp32(B):
     """One step per weight matrix (Section 3.1's default granularity): whole step against the oracle;
     the step fields stay tied and carry the summed gradient."""
