@@ -78,6 +78,26 @@ def test_quantize_codes_bit_exact(B, N, K, bits):
     assert np.array_equal(codes.cpu().numpy().astype(np.int64), c_ref)
 
 
+# rows around the lengths where a wavefront, a block, or two passes serve a row (1024, 4096), whole 16-byte chunks and not;
+# tensors of less than one, exactly one and several parts, with the last weights outside the 16-byte chunks
+@pytest.mark.parametrize("N,K,per_channel", [(5, 1024, 1), (3, 1023, 1), (3, 1028, 1), (3, 1025, 1), (2, 4096, 1), (2, 4095, 1), (2, 4100, 1),
+                                             (1, 1, 0), (1, 3, 0), (1, 4, 0), (1, 4096, 0), (3, 2731, 0), (700, 3001, 0)])
+@pytest.mark.parametrize("init", [0, 1])
+def test_quantize_edges_bit_exact(B, N, K, per_channel, init):
+    torch = _torch()
+    rng = np.random.default_rng(N * 5000 + K)
+    w = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    w[N - 1, K - 1] = -0.2                                  # the largest weight is the last one
+    amax = np.abs(w).max(axis=1) if per_channel else np.abs(w).max().reshape(1)
+    s = amax / np.float32(7) if init else (amax / np.float32(9)).astype(np.float32)
+    scale = torch.full((s.size,), float("nan"), dtype=torch.float32, device="cuda") if init else torch.from_numpy(s).cuda()
+    codes = torch.full((N, K), 99, dtype=torch.int8, device="cuda")
+    B.mrem_quantize(torch.from_numpy(w).cuda(), N, K, 4, per_channel, init, scale, codes)
+    assert np.array_equal(scale.cpu().numpy(), s.astype(np.float32))
+    ref = np.rint(np.clip(w / s.astype(np.float32)[:, None], np.float32(-7), np.float32(7))).astype(np.int8)
+    assert np.array_equal(codes.cpu().numpy(), ref)
+
+
 def test_quantize_rejects_bad_arguments(B):
     torch = _torch()
     w = torch.zeros((4, 8), dtype=torch.float32, device="cuda")
