@@ -206,6 +206,7 @@ Plan make_plan(const mrem_ctx* c, int B, int S) {
   // second-stage launch at the end of the backward pass): two LayerNorms, two bias column sums,
   // the elementwise kernels (at most 2048 blocks, up to 3 values each) and the attention rows
   size_t np = 2 * (size_t)ln_bwd_parts((int)T) * (3 * H + 2) + (size_t)kColMaxParts * (F + 3 * H) + 8 * 2048 + (size_t)B * c->nh * S;
+  static_assert(8 * 3 * kCalibParts <= 8 * 2048, "the partial ranges of a layer's eight quantizers fit too");
   np = (np + 63) & ~size_t(63);
   p.partials_per_layer = np;
   p.partials = b.take(np * 4 * c->L);
@@ -389,23 +390,23 @@ void student_forward(const Run& r, const float* params, const void* x_q, void* p
   }
 }
 
-// Full-precision module.  With calib_params != null the clipping ranges of the
-// eight activation quantizers of every layer are derived on the way.
+// Full-precision module.  With calib_params != null the ranges of the inputs of the eight activation quantizers of
+// every layer are taken on the way, into `parts`; calib_jobs collects what turns them into steps and offsets.
 // Layers [l0, l1) (l1 < 0: to the last layer).
 void teacher_forward(const Run& r, const float* teacher, const void* cache, const void* x_fp, void* per_layer_fp, float* calib_params,
-                     int l0 = 0, int l1 = -1) {
+                     int l0 = 0, int l1 = -1, float* parts = nullptr, std::vector<CalibJob>* calib_jobs = nullptr) {
   const mrem_ctx* c = r.c;
   const size_t es = dt_size(c->dt);
   const int H = c->H, F = c->F, T = r.T;
   const size_t slice = (size_t)T * H * es;
   const float qp_s = (float)((1 << (c->cfg.a_bits > 0 ? c->cfg.a_bits - 1 : 1)) - 1);
   const float qp_u = (float)((1 << (c->cfg.a_bits > 0 ? c->cfg.a_bits : 1)) - 1);
-  float* parts = r.at<float>(r.p.partials);
-  auto calib = [&](int l, int idx, const void* a, int dt, int rows, int cols, int ld, int gelu, int mode) {
+  auto job = [&](int l, int idx, int nparts, int mode) {
     float* base = calib_params + c->layer_stride * l;
-    const int n = absminmax(dt, a, rows, cols, ld, gelu, parts, r.st);
-    calib_finalize(parts, n, mode, mode == 0 ? qp_s : qp_u, base + c->foff[MREM_F_S_A] + idx, base + c->foff[MREM_F_Z_A] + idx, r.st);
+    calib_jobs->push_back(CalibJob{parts, base + c->foff[MREM_F_S_A] + idx, base + c->foff[MREM_F_Z_A] + idx, nparts, mode, mode == 0 ? qp_s : qp_u});
+    parts += 3 * nparts;
   };
+  auto calib = [&](int l, int idx, const void* a, int dt, int rows, int cols, int mode) { job(l, idx, absminmax(dt, a, rows, cols, 1, cols, parts, r.st), mode); };
   if (l1 < 0) l1 = c->L;
   for (int l = l0; l < l1; ++l) {
     const float* base = teacher + c->layer_stride * l;
@@ -414,14 +415,14 @@ void teacher_forward(const Run& r, const float* teacher, const void* cache, cons
     const void* x = l == 0 ? x_fp : (const char*)per_layer_fp + slice * (l - 1);
     void* f = (char*)per_layer_fp + slice * l;
     Epilogue e;
-    if (calib_params) calib(l, 0, x, c->dt, T, H, H, 0, 0);
+    if (calib_params) calib(l, 0, x, c->dt, T, H, 0);
     e.bias = base + c->foff[MREM_F_B_QKV];
     gemm_nt(c->dt, x, H, W(0), H, r.at(r.p.t_qkv), 3 * H, T, 3 * H, H, e, r.st, r.prof);
     if (calib_params) {
-      const char* q = r.at<char>(r.p.t_qkv);
-      calib(l, 1, q, c->dt, T, H, 3 * H, 0, 0);
-      calib(l, 2, q + (size_t)H * es, c->dt, T, H, 3 * H, 0, 0);
-      calib(l, 4, q + (size_t)2 * H * es, c->dt, T, H, 3 * H, 0, 0);
+      const int n = absminmax(c->dt, r.at(r.p.t_qkv), T, H, 3, 3 * H, parts, r.st);
+      job(l, 1, n, 0);
+      job(l, 2, n, 0);
+      job(l, 4, n, 0);
     }
     if (attn_mfma_ok(c->dt, c->d))
       attn_fwd_mfma(r.at(r.p.t_qkv), r.at(r.p.t_ctx), nullptr, AttnQ(), r.seqlens, r.B, r.S, c->nh, c->d,
@@ -430,8 +431,8 @@ void teacher_forward(const Run& r, const float* teacher, const void* cache, cons
       attn_fwd(c->dt, r.at(r.p.t_qkv), r.at(r.p.t_ctx), nullptr, AttnQ(), r.seqlens, r.B, r.S, c->nh, c->d,
                calib_params ? r.at<float>(r.p.pmax) : nullptr, r.st);
     if (calib_params) {
-      calib(l, 3, r.at(r.p.pmax), DT_F32, 1, r.B * c->nh * r.S, r.B * c->nh * r.S, 0, 1);
-      calib(l, 5, r.at(r.p.t_ctx), c->dt, T, H, H, 0, 0);
+      calib(l, 3, r.at(r.p.pmax), DT_F32, 1, r.B * c->nh * r.S, 1);
+      calib(l, 5, r.at(r.p.t_ctx), c->dt, T, H, 0);
     }
     e.bias = base + c->foff[MREM_F_B_O];
     gemm_nt(c->dt, r.at(r.p.t_ctx), H, W(1), H, r.at(r.p.t_o), H, T, H, H, e, r.st, r.prof);
@@ -439,13 +440,12 @@ void teacher_forward(const Run& r, const float* teacher, const void* cache, cons
       ln_fwd(c->dt, x, r.at(r.p.t_o), base + c->foff[MREM_F_LN1_G], base + c->foff[MREM_F_LN1_B], r.at(r.p.t_x1), nullptr, QArg(),
              r.at<float>(r.p.t_mu), r.at<float>(r.p.t_rstd), T, H, c->cfg.ln_eps, r.st);
     });
-    if (calib_params) calib(l, 6, r.at(r.p.t_x1), c->dt, T, H, H, 0, 0);
+    if (calib_params) calib(l, 6, r.at(r.p.t_x1), c->dt, T, H, 0);
     e.bias = base + c->foff[MREM_F_B_1];
     if (calib_params) {
       // pre-activation first, so that the range of gelu(u) can be measured on unrounded values
       gemm_nt(c->dt, r.at(r.p.t_x1), H, W(2), H, r.at(r.p.t_g), F, T, F, H, e, r.st, r.prof);
-      calib(l, 7, r.at(r.p.t_g), c->dt, T, F, F, 1, 2);
-      gelu_quantize(c->dt, r.at(r.p.t_g), r.at(r.p.t_g), (int64_t)T * F, QArg(), r.st);
+      job(l, 7, gelu_minmax(c->dt, r.at(r.p.t_g), (int64_t)T * F, parts, r.st), 2);
     } else {
       e.gelu = 1;
       gemm_nt(c->dt, r.at(r.p.t_x1), H, W(2), H, r.at(r.p.t_g), F, T, F, H, e, r.st, r.prof);
@@ -808,8 +808,11 @@ extern "C" mrem_status mrem_module_calibrate(mrem_ctx* ctx, float* params, const
   REQUIRE_PTR(x_fp, "mrem_module_calibrate");
   if (ctx->cfg.a_bits == 0) return fail(ctx, MREM_EINVAL, "mrem_module_calibrate: activation quantizers are off (a_bits = 0)");
   Run r{ctx, plan, (char*)workspace, (hipStream_t)hip_stream, batch, seq, batch * seq, seqlens, &ctx->prof};
-  // Layer by layer with two alternating output buffers: only the ranges are wanted, not the per-layer outputs.
+  // Layer by layer with two alternating output buffers: only the ranges are wanted, not the per-layer outputs.  Nothing
+  // of the pass depends on the steps, so all of them are formed at the end.
   {
+    std::vector<CalibJob> jobs;
+    jobs.reserve((size_t)ctx->L * 8);
     mrem_ctx one = *ctx;
     one.L = 1;
     const size_t es = dt_size(ctx->dt);
@@ -819,9 +822,10 @@ extern "C" mrem_status mrem_module_calibrate(mrem_ctx* ctx, float* params, const
       Run rl = r;
       rl.c = &one;
       teacher_forward(rl, teacher + ctx->layer_stride * l, (const char*)teacher_cache + (size_t)ctx->tc_layer_stride * l * es, x,
-                      bufs[l & 1], params + ctx->layer_stride * l);
+                      bufs[l & 1], params + ctx->layer_stride * l, 0, -1, r.at<float>(r.p.partials) + r.p.partials_per_layer * l, &jobs);
       x = bufs[l & 1];
     }
+    calib_finalize(jobs.data(), (int)jobs.size(), r.st);
   }
   return finish(ctx, "mrem_module_calibrate");
 }

@@ -205,10 +205,23 @@ int attn_bwd_mfma(const void* codes, const void* dctx, void* d_qkvh, const AttnQ
                   const float* stat_m, const float* stat_l, void* scratch0, void* scratch1, float* ds_parts, hipStream_t st);
 
 // ---- calibration reductions -------------------------------------------------------
-// partials[grid][3]: max|a|, min(f(a)), max(f(a)) over a strided [rows, cols] view; f = gelu if gelu != 0
-int absminmax(int dt, const void* a, int rows, int cols, int ld, int gelu, float* partials, hipStream_t st);
-// mode 0: s = max|a| / qp ; mode 1: s = max / qp (z = 0) ; mode 2: z = min, s = (max - z) / qp
-void calib_finalize(const float* partials, int nparts, int mode, float qp, float* s_out, float* z_out, hipStream_t st);
+// Each leaves partials[count][3] (max|a|, min(a), max(a)) of at most kCalibParts blocks and returns the count.
+// `sections` column sections of `cols` values in rows of pitch ld, each with its own partials, one set behind the other;
+// cols is a multiple of 8, or rows = sections = 1.
+constexpr int kCalibParts = 512;
+int absminmax(int dt, const void* a, int rows, int cols, int sections, int ld, float* partials, hipStream_t st);
+// u := round(gelu(u)) in place; the partials are those of the unrounded gelu(u)
+int gelu_minmax(int dt, void* u, int64_t n, float* partials, hipStream_t st);
+// mode 0: s = max|a| / qp ; mode 1: s = max / qp (z = 0) ; mode 2: z = min, s = (max - z) / qp.  One launch per
+// kMaxCalibJobs quantizers.
+constexpr int kMaxCalibJobs = 64;
+struct CalibJob {
+  const float* partials;
+  float *s_out, *z_out;
+  int nparts, mode;
+  float qp;
+};
+void calib_finalize(const CalibJob* jobs, int njobs, hipStream_t st);
 
 // ---- update ----------------------------------------------------------------------
 struct AdamArg {
