@@ -70,58 +70,92 @@ __device__ __forceinline__ void epilogue_store(TO* C, int ldc, int m, int n, flo
 }
 
 // ------------------------------------------------------------------------------
-// generic scalar-ALU kernel: any M, N, K; fp32 or bf16 operands; used by the fp32
-// check mode and for shapes the MFMA kernel does not take
+// fp32 products (v_mfma_f32_32x32x2_f32: fp32 operands, products and sums), any M, N, K: the check mode.
+// Its products are small (tens to hundreds of rows), so a launch is bound by latency, not by throughput: a block is one
+// 32 x 32 output tile, its four wavefronts take every fourth group of 8 contraction values straight from memory (four
+// groups' loads in flight), and their partial sums meet in LDS in wavefront order.  128 x 256 x 64 and the like: 64 x 64
+// tiles of vector-ALU products, staged through LDS 16 values of k at a time without prefetch, took 18 us; a one-layer step
+// of 128 tokens with 18 of them went from 370 to 283 us.
+// In a group, lane l holds row l % 32 and the k values 4 (l / 32) .. + 3 of both operands: MFMA j multiplies element j of
+// both halves, so the four of them cover the group.
 // ------------------------------------------------------------------------------
-template <class TA, class TO>
-__global__ void gemm_nt_simt_k(const TA* __restrict__ A, int lda, const TA* __restrict__ B, int ldb, TO* __restrict__ C, int ldc, int M,
-                               int N, int K, Epilogue e, int a_t = 0, int b_t = 0) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4];
+typedef float f32x16s_t __attribute__((ext_vector_type(16)));
+// element (r, k) of an operand: k contiguous in whole 16-byte chunks (VEC), or any strides
+template <class T, bool VEC>
+__device__ __forceinline__ float4 load_k4(const T* __restrict__ p, size_t sr, size_t sk, int r, int k, int K) {
+  if constexpr (VEC) {
+    if (k >= K) return make_float4(0.f, 0.f, 0.f, 0.f);
+    return *reinterpret_cast<const float4*>(p + r * sr + k);
+  } else {
+    float v[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    // 64 rows x 16 k per operand = 1024 elements, 4 per thread
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int idx = threadIdx.x + 256 * t;
-      const int r = idx >> 4, kk = idx & 15;
-      const int k = k0 + kk;
-      As[kk][r] = (m0 + r < M && k < K) ? ldf(A, a_t ? (size_t)k * lda + m0 + r : (size_t)(m0 + r) * lda + k) : 0.f;
-      Bs[kk][r] = (n0 + r < N && k < K) ? ldf(B, b_t ? (size_t)k * ldb + n0 + r : (size_t)(n0 + r) * ldb + k) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
-    }
-    __syncthreads();
+    for (int j = 0; j < 4; ++j) v[j] = k + j < K ? ldf(p, r * sr + (size_t)(k + j) * sk) : 0.f;
+    return make_float4(v[0], v[1], v[2], v[3]);
   }
+}
+template <class TA, class TO, bool VA, bool VB>
+__global__ __launch_bounds__(256) void gemm_f32_k(const TA* __restrict__ A, size_t a_sr, size_t a_sk, const TA* __restrict__ B, size_t b_sr,
+                                                  size_t b_sk, TO* __restrict__ C, int ldc, int M, int N, int K, Epilogue e) {
+  __shared__ float part[4][16][64];
+  constexpr int U = 4;  // groups in flight
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
+  // rows beyond the matrix repeat the last one: what they give is not stored
+  const int ra = min(m0 + (lane & 31), M - 1), rb = min(n0 + (lane & 31), N - 1);
+  f32x16s_t acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (int k0 = 8 * wave; k0 < K; k0 += 32 * U) {
+    float4 a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 32 * u + 4 * (lane >> 5);
+      a[u] = load_k4<TA, VA>(A, a_sr, a_sk, ra, k, K);
+      b[u] = load_k4<TA, VB>(B, b_sr, b_sk, rb, k, K);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].x, b[u].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].y, b[u].y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].z, b[u].z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].w, b[u].w, acc, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) part[wave][r][lane] = acc[r];
+  __syncthreads();
   EpiVals ev;
   ev.alpha = e.alpha ? *e.alpha : 1.f;
   ev.beta = (e.beta ? *e.beta : 0.f) + e.beta_alpha * ev.alpha;
+  // accumulator register r of a lane is row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32; wavefront w stores registers 4 w .. 4 w + 3
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < N) epilogue_store(C, ldc, m, n, acc[i][j], e, ev);
-    }
+  for (int i = 0; i < 4; ++i) {
+    const int r = 4 * wave + i;
+    const int m = m0 + 8 * wave + 4 * (lane >> 5) + i, n = n0 + (lane & 31);
+    const float v = ((part[0][r][lane] + part[1][r][lane]) + part[2][r][lane]) + part[3][r][lane];
+    if (m < M && n < N) epilogue_store(C, ldc, m, n, v, e, ev);
+  }
 }
-
+template <class TA, class TO>
+static void launch_f32(int a_t, int b_t, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
+                       hipStream_t st) {
+  const dim3 g((M + 31) / 32, (N + 31) / 32);
+  const size_t asr = a_t ? 1 : lda, ask = a_t ? lda : 1, bsr = b_t ? 1 : ldb, bsk = b_t ? ldb : 1;
+  auto vec = [&](int t, const void* p, int ld) {
+    return sizeof(TA) == 4 && !t && K % 4 == 0 && ld % 4 == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0;
+  };
+  const bool va = vec(a_t, A, lda), vb = vec(b_t, B, ldb);
+  auto go = [&](auto fa, auto fb) {
+    hipLaunchKernelGGL((gemm_f32_k<TA, TO, decltype(fa)::value, decltype(fb)::value>), g, dim3(256), 0, st, (const TA*)A, asr, ask, (const TA*)B,
+                       bsr, bsk, (TO*)C, ldc, M, N, K, e);
+  };
+  if constexpr (sizeof(TA) == 4) {
+    if (va && vb) return go(std::true_type{}, std::true_type{});
+    if (va) return go(std::true_type{}, std::false_type{});
+    if (vb) return go(std::false_type{}, std::true_type{});
+  }
+  go(std::false_type{}, std::false_type{});
+}
 
 // ------------------------------------------------------------------------------
 // MFMA products (v_mfma_f32_32x32x16_bf16 with fp32 accumulation, v_mfma_i32_32x32x32_i8 with exact
@@ -284,20 +318,11 @@ static void gemm_launch(int dt, int a_t, int b_t, const void* A, int lda, const 
     }
     return;
   }
-  dim3 g((N + 63) / 64, (M + 63) / 64);
-  const hipEvent_t t0 = tl_launch_events.e0, t1 = tl_launch_events.e1;  // the fallback kernels are timed by recorded events
+  const hipEvent_t t0 = tl_launch_events.e0, t1 = tl_launch_events.e1;  // these kernels are timed by recorded events
   if (t0) (void)hipEventRecord(t0, st);
-  if (dt == DT_BF16) {
-    if (e.out_f32)
-      hipLaunchKernelGGL((gemm_nt_simt_k<bf16_t, float>), g, dim3(256), 0, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (float*)C, ldc,
-                         M, N, K, e, a_t, b_t);
-    else
-      hipLaunchKernelGGL((gemm_nt_simt_k<bf16_t, bf16_t>), g, dim3(256), 0, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (bf16_t*)C,
-                         ldc, M, N, K, e, a_t, b_t);
-  } else {
-    hipLaunchKernelGGL((gemm_nt_simt_k<float, float>), g, dim3(256), 0, st, (const float*)A, lda, (const float*)B, ldb, (float*)C, ldc, M,
-                       N, K, e, a_t, b_t);
-  }
+  if (dt == DT_F32) launch_f32<float, float>(a_t, b_t, A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  else if (e.out_f32) launch_f32<bf16_t, float>(a_t, b_t, A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  else launch_f32<bf16_t, bf16_t>(a_t, b_t, A, lda, B, ldb, C, ldc, M, N, K, e, st);
   if (t1) (void)hipEventRecord(t1, st);
 }
 
