@@ -302,8 +302,8 @@ void student_linear(const Run& r, const float* params, int l, int i, const void*
   gemm_nt(c->dt, in_codes, c->wK[i], r.at(r.p.lw[l].wcodes[i]), c->wK[i], out, c->wN[i], r.T, c->wN[i], c->wK[i], e, r.st, r.prof);
 }
 
-// (layers [l0, l1); l1 < 0: to the last layer)
-void prepare_weights(const Run& r, const float* params, int l0 = 0, int l1 = -1) {
+// (layers [l0, l1); l1 < 0: to the last layer; backward: also the dequantized copy that the input gradients read)
+void prepare_weights(const Run& r, const float* params, bool backward, int l0 = 0, int l1 = -1) {
   const mrem_ctx* c = r.c;
   if (l1 < 0) l1 = c->L;
   if (l0 >= l1) return;
@@ -316,7 +316,7 @@ void prepare_weights(const Run& r, const float* params, int l0 = 0, int l1 = -1)
       j.w = base + c->foff[kWField[i]]; j.sw = base + c->foff[kSField[i]];
       j.codes8 = r.at8(r.p.lw[l].wcodes8[i]);
       j.codes = j.codes8 ? nullptr : r.at(r.p.lw[l].wcodes[i]);  // the forward reads one or the other
-      j.what = r.at(r.p.lw[l].what[i]); j.zcorr = r.at<float>(r.p.lw[l].zcorr[i]);
+      j.what = backward ? r.at(r.p.lw[l].what[i]) : nullptr; j.zcorr = r.at<float>(r.p.lw[l].zcorr[i]);
       j.N = c->wN[i]; j.K = c->wK[i];
       jobs.push_back(j);
     }
@@ -324,7 +324,7 @@ void prepare_weights(const Run& r, const float* params, int l0 = 0, int l1 = -1)
   double nw = 0;
   for (const WeightJob& j : jobs) nw += (double)j.N * j.K;
   // fp32 master in; codes (int8, or the storage type) and the dequantized copy out
-  timed(r, "weight_codes_k", nw * (4 + (r.i8() ? 1 : dt_size(c->dt)) + dt_size(c->dt)),
+  timed(r, "weight_codes_k", nw * (4 + (r.i8() ? 1 : dt_size(c->dt)) + (backward ? dt_size(c->dt) : 0)),
         [&] { weight_prepare(c->dt, jobs.data(), (int)jobs.size(), c->cfg.w_bits, r.st); });
 }
 
@@ -852,7 +852,7 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
   }
   if (per_layer_fp) teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp, nullptr);
   if (per_layer_q) {
-    prepare_weights(r, params);
+    prepare_weights(r, params, false);
     student_forward(r, params, x_q, per_layer_q);
   }
   return finish(ctx, who);
@@ -951,9 +951,9 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
     // Only the first layer's weights are prepared on this stream; those of the layers above are prepared on the side
     // stream ahead of the teacher's pass (which has slack before the loss needs it), so the quantized pass starts after
     // one layer's worth of that work instead of the whole module's.
-    prepare_weights(r, params, 0, 1);
+    prepare_weights(r, params, true, 0, 1);
     if (ctx->L > 1) {
-      prepare_weights(rt, params, 1, ctx->L);
+      prepare_weights(rt, params, true, 1, ctx->L);
       (void)hipEventRecord(ctx->ev_codes, ctx->side);
     }
     // the two passes are enqueued layer by layer in turn, so that both streams have work from the
@@ -967,7 +967,7 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
   } else {
     teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp, nullptr);
     zero_gradient_slots(r, grads);
-    prepare_weights(r, params);
+    prepare_weights(r, params, true);
     student_forward(r, params, x_in, per_layer_q, 0, -1, mix_fp, x_q, lambda);
   }
   if (fork) (void)hipStreamWaitEvent(r.st, ctx->ev_join, 0);
