@@ -1030,14 +1030,16 @@ extern "C" mrem_status mrem_rem_step(mrem_ctx* ctx, int64_t T, int64_t N, int64_
   float* grads = grads_out ? grads_out : reinterpret_cast<float*>(ws + p.grads);
   float* parts = reinterpret_cast<float*>(ws + p.partials);
   GemmProfile* prof = &ctx->prof;
+  // one launch for both weight sets: the frozen ones rounded to the storage type; codes and the dequantized copy of the trained ones
+  WeightJob wj[2];
+  wj[0].w = w; wj[0].sw = sw; wj[0].codes = ws + p.wcodes; wj[0].what = ws + p.what; wj[0].zcorr = nullptr; wj[0].codes8 = nullptr;
+  wj[0].N = (int)N; wj[0].K = (int)K;
+  wj[1] = wj[0];
+  wj[1].w = w_fp; wj[1].sw = nullptr; wj[1].codes = ws + p.wt; wj[1].what = nullptr;
+  weight_prepare(dt, wj, 2, ctx->cfg.w_bits, st);
   // full-precision product  y = a W^T  on the original weights
-  convert_f32(dt, w_fp, ws + p.wt, N * K, st);
   gemm_nt(dt, a_fp, (int)K, ws + p.wt, (int)K, y_fp, (int)N, (int)T, (int)N, (int)K, Epilogue(), st, prof);
   // quantized product  y^ = Q(a) Q(w)^T: codes of both operands, the two steps in the epilogue
-  WeightJob wj;
-  wj.w = w; wj.sw = sw; wj.codes = ws + p.wcodes; wj.what = ws + p.what; wj.zcorr = reinterpret_cast<float*>(ws + p.zcorr); wj.codes8 = nullptr;
-  wj.N = (int)N; wj.K = (int)K;
-  weight_prepare(dt, &wj, 1, ctx->cfg.w_bits, st);
   QArg qa;
   qa.on = 1; qa.s = sa; qa.qp = (float)((1 << (ctx->cfg.a_bits - 1)) - 1); qa.qn = -qa.qp;
   act_quantize(dt, a_q, ws + p.xcodes, T * K, qa, st);

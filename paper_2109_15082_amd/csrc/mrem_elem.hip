@@ -1054,7 +1054,7 @@ struct WeightJobTable {
   int njobs;
 };
 template <class T>
-__global__ __launch_bounds__(128) void weight_codes_k(WeightJobTable tab, float qp, int on) {
+__global__ __launch_bounds__(128) void weight_codes_k(WeightJobTable tab, float qp, int quantize) {
   __shared__ float red[17];
   int ji = 0;
   while (ji + 1 < tab.njobs && (int)blockIdx.x >= tab.first_row[ji + 1]) ++ji;
@@ -1063,6 +1063,7 @@ __global__ __launch_bounds__(128) void weight_codes_k(WeightJobTable tab, float 
   const float* __restrict__ w = jb.w;
   T* __restrict__ codes = reinterpret_cast<T*>(jb.codes);
   T* __restrict__ what = reinterpret_cast<T*>(jb.what);
+  const bool on = quantize && jb.sw;
   const float s = on ? jb.sw[n] : 1.f;
   float acc = 0.f;
   const size_t row = (size_t)n * K;
@@ -1079,6 +1080,7 @@ __global__ __launch_bounds__(128) void weight_codes_k(WeightJobTable tab, float 
     if (jb.codes8) store8_i8(jb.codes8 + row + k, c, 0.f);
     if (what) store8(what + row + k, x);
   }
+  if (!jb.zcorr) return;
   acc = block_sum(acc, red);
   // s * sum_k code (s = 1 with the weight quantizers off): what the offset z of an asymmetric input
   // quantizer multiplies in the product's epilogue, x^ = s_a q + z (Section 3.1)

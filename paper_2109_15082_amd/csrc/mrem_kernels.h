@@ -102,10 +102,10 @@ void tie_steps_max(float* scale, int64_t N, hipStream_t st);
 constexpr int kMaxMatrixJobs = 24;
 struct WeightJob {
   const float* w;
-  const float* sw;
+  const float* sw;  // null: this matrix is only rounded to the storage type (as with bits = 0)
   void* codes;     // may be null when only the int8 codes are wanted
   void* what;
-  float* zcorr;
+  float* zcorr;    // may be null
   int8_t* codes8;  // may be null
   int N, K;
 };
