@@ -154,8 +154,7 @@ CASES_BF16 = {
     # attention): ternary weights, and ternary weights with 4-bit activations
     "w2a8_bf16": W("w2a8_bf16", 2, 128, 2, 512, 128, 2, act_dtype="bf16", w_bits=2),
     "w2a4_bf16": W("w2a4_bf16", 2, 128, 2, 512, 128, 2, act_dtype="bf16", w_bits=2, a_bits=4),
-    # a sequence longer than the matrix-core attention kernels take (they stop at 384 keys): the scalar attention
-    # path beside the matrix-core products, T = 512
+    # the longest sequence (four chunks of keys in the attention kernels), T = 512
     "s512_bf16": W("s512_bf16", 1, 128, 2, 256, 512, 1, act_dtype="bf16"),
 }
 # fp32 mode at several tiles without the margin guarantee (about 7e5 quantized values:
@@ -920,7 +919,7 @@ def test_non_finite_loss_sets_the_flag(B):
 # --------------------------------------------------------------------------------
 
 # the last two: a contraction of one 64-deep stage only (fewer stages than the product kernel keeps in flight), and a
-# weight gradient over 2048 tokens with a single output tile (two k-slices, each shared by two groups of wavefronts)
+# weight gradient over 2048 tokens with a single output tile of 128 x 128
 # (these two run one step: with 2048 tokens one channel's step gradient is within its tolerance of zero, AdamW then moves
 # that step by the full rate in either direction, and the second step's codes of that channel differ between the sides)
 @pytest.mark.parametrize("dt,T,N,K,w_bits,per_channel,n_steps", [("f32", 40, 24, 72, 4, 1, 2), ("f32", 64, 32, 64, 2, 0, 2), ("bf16", 256, 384, 128, 4, 1, 2),
