@@ -293,6 +293,7 @@ void student_linear(const Run& r, const float* params, int l, int i, const void*
   if (c->cfg.w_bits > 0) e.col_scale = base + c->foff[kSField[i]];
   if (q.on && q.z) { e.beta = q.z; e.col_vec = r.at<float>(r.p.lw[l].zcorr[i]); }
   e.bias = base + c->foff[kBField[i]];
+  e.chain = !(q.on && c->cfg.w_bits > 0);  // sums of integer codes are exact in any order
   if (r.i8() && in_codes8) {
     // unsigned codes (GELU output) are stored recentred by half their range; the epilogue adds that back
     if (q.z) e.beta_alpha = 0.5f * (q.qp + 1.f);
@@ -415,6 +416,7 @@ void teacher_forward(const Run& r, const float* teacher, const void* cache, cons
     const void* x = l == 0 ? x_fp : (const char*)per_layer_fp + slice * (l - 1);
     void* f = (char*)per_layer_fp + slice * l;
     Epilogue e;
+    e.chain = 1;
     if (calib_params) calib(l, 0, x, c->dt, T, H, 0);
     e.bias = base + c->foff[MREM_F_B_QKV];
     gemm_nt(c->dt, x, H, W(0), H, r.at(r.p.t_qkv), 3 * H, T, 3 * H, H, e, r.st, r.prof);

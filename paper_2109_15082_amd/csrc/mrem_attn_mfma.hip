@@ -16,14 +16,16 @@
 // with the transposing LDS read (ds_read_tr16_b64), see `ld_frag_tr`.
 //
 // A block is up to 128 rows (32 per wavefront) of one (batch, head).  The other side of the
-// product passes through LDS in chunks of 128 rows, so a block takes 37 KB and under 170
-// registers at every length and several share a compute unit.  Up to 128 keys (one chunk) the
-// probabilities stay in registers between the pass that forms the row statistics and the pass
-// that uses them; longer rows form their tiles twice, since a probability is normalised before
-// it is quantized.  The scores, the exponentials and the quantizer are vector-ALU work (about
-// 25 instructions per query-key pair and pass), which is what bounds these kernels: keeping a
-// row of 384 keys in registers instead (and all its keys in LDS) left one wavefront per SIMD.
-// Chunks beyond the valid keys of a sequence are skipped.
+// product passes through LDS in chunks of 128 rows, so a block takes 37 KB (20 KB for head
+// dimension 32) and registers, not LDS, say how many share a compute unit.  Up to 128 keys (one
+// chunk) the scores and probabilities stay in registers between the pass that forms the row
+// statistics and the pass that uses them.  Longer rows of codes form their tiles again for each
+// pass, since a probability is normalised before it is quantized: the scores, the exponentials
+// and the quantizer are vector-ALU work, which is what bounds these kernels, and a whole row in
+// registers leaves one wavefront per SIMD (16 x 384 tokens, step of 6 layers of 1024: 7126 us
+// against 7015).  Wavefronts per SIMD: forward 3 to 4 up to 128 keys, 2 to 3 beyond; backward 2
+// to 4 (160 to 254 registers for head dimension 64).  Chunks beyond the valid keys of a sequence
+// are skipped.
 #include "mrem_common.h"
 #include "mrem_kernels.h"
 
@@ -58,22 +60,17 @@ __device__ __forceinline__ float div_by(float x, float d, float rd) {
   const float t = __fmul_rn(x, rd);
   return __fmaf_rn(__fmaf_rn(-d, t, x), rd, t);
 }
-// exp(x) for x <= 0 from the hardware's 2^t (1 ulp): t = x log2(e) is rounded to fp32, which at t = -20 costs the result
-// 20 ulp; the rounding error, and what the fp32 constant lacks of log2(e), are formed exactly and applied as the factor
-// 1 + ln(2) * error.  About 2 ulp for every x.
-__device__ __forceinline__ float exp_neg_exact(float x) {
-  const float t = __fmul_rn(x, 1.44269502f);
-  const float err = __fmaf_rn(x, 1.92596299e-8f, __fmaf_rn(x, 1.44269502f, -t));
-  const float e = __builtin_amdgcn_exp2f(t);
-  return __fmaf_rn(e, __fmul_rn(err, 0.693147181f), e);
-}
-// FAST: the rounding of t is left in (up to 20 ulp).  It serves head dimension 64 at 64 to 384 tokens, where a forward
-// pass of 512 heads of 128 tokens takes 20 us with it and 27 us without inside a six-layer step; every other shape gets
-// the accurate one.
+// Two arithmetics.  Which one serves a shape is part of its results: a probability that rounds the other way flips a code,
+// and flips multiply from layer to layer, so the bits of a forward pass are kept.
+//   FAST (head dimension 64, 64 to 384 tokens): the hardware's 2^t with t rounded to fp32 (up to 20 ulp for the smallest
+//     probabilities), a row's exponentials added one after the other by each half wavefront.
+//   otherwise: expf, and the order of a row that is spread over 64 lanes, lane l adding keys l, l + 64, ... and the lanes
+//     meeting in a binary tree; products of operands that are not integer codes are fp32 fused multiply-adds with the
+//     contraction index ascending.  These are the results of the scalar kernels (mrem_attn.hip), bit for bit.
 template <bool FAST>
 __device__ __forceinline__ float exp_neg(float x) {
   if constexpr (FAST) return __expf(x);
-  else return exp_neg_exact(x);
+  else return expf(x);
 }
 __device__ __forceinline__ FwdScales load_fwd_scales(const AttnQ& a, int d) {
   FwdScales s;
@@ -127,13 +124,6 @@ __device__ __forceinline__ f32x16_t zero16() {
   for (int r = 0; r < 16; ++r) z[r] = 0.f;
   return z;
 }
-// the 16 values in pairs: a row of 512 probabilities is then at most 4 + 16 + 1 additions deep
-__device__ __forceinline__ float tile_sum(const f32x16_t& v) {
-  float a[8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) a[r] = v[2 * r] + v[2 * r + 1];
-  return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-}
 // a 32 x 32 tile: rows [row0, row0 + 32) of the LDS tile times the transposed 32 rows held as fragments (one per 16 columns)
 template <int D>
 __device__ __forceinline__ f32x16_t tile_product(const bf16_t* tile, int row0, int lane, const bf16x8_t (&frag)[D / 16]) {
@@ -159,11 +149,49 @@ __device__ __forceinline__ void accumulate_rows(f32x16_t (&acc)[D / 32], const b
   }
 }
 
+// The same two products for operands that are not integer codes, as chains of fp32 fused multiply-adds:
+// v_mfma_f32_32x32x2_f32 adds its two products with k ascending and rounds after each (16 times the cycles of the bf16 form).
+// Values 2 j (lower half of the wavefront) and 2 j + 1 (upper half) of 8 consecutive ones:
+__device__ __forceinline__ float pick(unsigned pair, int half) { return __uint_as_float(half ? pair & 0xffff0000u : pair << 16); }
+template <int D>
+__device__ __forceinline__ f32x16_t tile_product_chain(const bf16_t* tile, int row0, int lane, const float (&frag)[D / 2]) {
+  f32x16_t acc = zero16();
+  const bf16_t* p = tile + (row0 + (lane & 31)) * Tile<D>::kStride;
+#pragma unroll
+  for (int c = 0; c < D / 8; ++c) {
+    const u32x4_t v = *reinterpret_cast<const u32x4_t*>(p + 8 * c);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pick(v[j], lane >> 5), frag[4 * c + j], acc, 0, 0, 0);
+  }
+  return acc;
+}
+template <int D>
+__device__ __forceinline__ void accumulate_rows_chain(f32x16_t (&acc)[D / 32], const bf16_t* tile, int row0, int lane, const float* w) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    // registers 4 g .. 4 g + 3 hold rows 8 g + 0..3 in the lower half of the wavefront and 8 g + 4..7 in the upper one;
+    // exchanging halves gives pairs (row, row + 1) of the two halves: 0 1, 4 5 from the first two registers, 2 3, 6 7
+    float b[4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(w[4 * g + 2 * i]), __float_as_uint(w[4 * g + 2 * i + 1]), false, false);
+      b[i] = __uint_as_float(x[0]);
+      b[2 + i] = __uint_as_float(x[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bf16_t* row = tile + (row0 + 8 * g + 2 * i + (lane >> 5)) * Tile<D>::kStride + (lane & 31);
+#pragma unroll
+      for (int et = 0; et < D / 32; ++et)
+        acc[et] = __builtin_amdgcn_mfma_f32_32x32x2f32(static_cast<float>(row[32 * et]), b[i], acc[et], 0, 0, 0);
+    }
+  }
+}
 // ------------------------------------------------------------------------------
 // forward: one block = up to 128 queries of one (batch, head); one wavefront = 32 queries
-// ONE: at most 128 keys
+// ONE: at most 128 keys.  REAL: the operands are not integer codes (and not FAST).
 // ------------------------------------------------------------------------------
-template <int D, bool ONE, bool FAST>
+template <int D, bool ONE, bool FAST, bool REAL>
 __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict__ codes, bf16_t* __restrict__ ctx,
                                                        bf16_t* __restrict__ ctx_codes, AttnQ aq, const int32_t* __restrict__ seqlens,
                                                        int S, int H, float* __restrict__ pmax_rows, float* __restrict__ stat_m,
@@ -175,6 +203,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
   const int ld = 3 * H;
   const bf16_t* base = codes + (size_t)b * S * ld + h * D;
   const int len = seqlens ? min(seqlens[b], S) : S;
+  const int rows = FAST ? S : len;  // keys that are staged: those beyond are zero rows
   const FwdScales sc = load_fwd_scales(aq, D);
 
   const int q0 = blockIdx.x * 128 + wave * 32;
@@ -182,12 +211,24 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
   const int q = q0 + (lane & 31);
   const int qc = q < S ? q : S - 1;
   bf16x8_t qf[D / 16];
+  float qr[D / 2];
+  if constexpr (REAL) {
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) qf[kk] = ld_frag(base + (size_t)qc * ld + (kk * 2 + half) * 8);
+    for (int c = 0; c < D / 8; ++c) {
+      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(base + (size_t)qc * ld + 8 * c);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) qr[4 * c + j] = pick(v[j], half);
+    }
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) qf[kk] = ld_frag(base + (size_t)qc * ld + (kk * 2 + half) * 8);
+  }
 
   // scores of 32 keys (chunk rows [32 t, 32 t + 32), first key j0), -inf beyond the valid keys
   auto scores = [&](int t, int j0) {
-    f32x16_t a = tile_product<D>(Ks, 32 * t, lane, qf);
+    f32x16_t a;
+    if constexpr (REAL) a = tile_product_chain<D>(Ks, 32 * t, lane, qr);
+    else a = tile_product<D>(Ks, 32 * t, lane, qf);
 #pragma unroll
     for (int r = 0; r < 16; ++r) a[r] = key_of(0, r, half) + j0 + 32 * t < len ? __fmul_rn(a[r], sc.qk) : -INFINITY;
     return a;
@@ -202,9 +243,10 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float p = div_by(e[r], sum, rsum);
-      w[r] = sc.p_on ? rintf(fminf(fmaxf(div_by(p, sc.sp, sc.rsp), 0.f), sc.p_qp)) : p;
+      w[r] = REAL ? round_to<bf16_t>(p) : sc.p_on ? rintf(fminf(fmaxf(div_by(p, sc.sp, sc.rsp), 0.f), sc.p_qp)) : p;
     }
-    accumulate_rows<D>(oacc, Vs, 32 * t, lane, w);
+    if constexpr (REAL) accumulate_rows_chain<D>(oacc, Vs, 32 * t, lane, w);
+    else accumulate_rows<D>(oacc, Vs, 32 * t, lane, w);
   };
   auto exps = [&](const f32x16_t& a) {
     f32x16_t e;
@@ -212,10 +254,47 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
     for (int r = 0; r < 16; ++r) e[r] = a[r] == -INFINITY ? 0.f : exp_neg<FAST>(__fsub_rn(a[r], mx));
     return e;
   };
+  auto raise_max = [&](const f32x16_t& a) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, a[r]);
+  };
+  // the row sum in the order of the arithmetic; `odd`: parity of the tile (keys l and l + 64 are two tiles apart)
+  float part[2][16];
+  if constexpr (!FAST) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[0][r] = part[1][r] = 0.f;
+  }
+  auto add_exps = [&](const f32x16_t& e, auto odd) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if constexpr (FAST) sum += e[r];
+      else part[decltype(odd)::value][r] += e[r];
+    }
+  };
+  auto finish_sum = [&]() {
+    if constexpr (FAST) {
+      sum += __shfl_xor(sum, 32, 64);
+    } else {
+      float y[2];
+#pragma unroll
+      for (int o = 0; o < 2; ++o) {
+        float x[4];  // keys 8 g .. 8 g + 7: bits 0 and 1 of the key, then bit 2, which is the half of the wavefront
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          x[g] = (part[o][4 * g] + part[o][4 * g + 1]) + (part[o][4 * g + 2] + part[o][4 * g + 3]);
+          x[g] += __shfl_xor(x[g], 32, 64);
+        }
+        y[o] = (x[0] + x[1]) + (x[2] + x[3]);
+      }
+      sum = y[0] + y[1];
+    }
+  };
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
   if constexpr (ONE) {
     const int nt = (len + 31) / 32;
-    stage_rows<D>(base + H, ld, S, 32 * nt, Ks);
-    stage_rows<D>(base + 2 * H, ld, S, 32 * nt, Vs);
+    stage_rows<D>(base + H, ld, rows, 32 * nt, Ks);
+    stage_rows<D>(base + 2 * H, ld, rows, 32 * nt, Vs);
     __syncthreads();
     if (!active) return;
     f32x16_t sacc[kChunk / 32];
@@ -223,57 +302,94 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
     for (int t = 0; t < kChunk / 32; ++t)
       if (t < nt) {
         sacc[t] = scores(t, 0);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[t][r]);
+        raise_max(sacc[t]);
       }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
 #pragma unroll
     for (int t = 0; t < kChunk / 32; ++t)
       if (t < nt) {
         sacc[t] = exps(sacc[t]);
-        sum += tile_sum(sacc[t]);
+        if (t & 1) add_exps(sacc[t], odd);
+        else add_exps(sacc[t], even);
       }
-    sum += __shfl_xor(sum, 32, 64);
+    finish_sum();
     const float rsum = __fdiv_rn(1.0f, sum);
 #pragma unroll
     for (int t = 0; t < kChunk / 32; ++t)
       if (t < nt) weigh(sacc[t], t, rsum);
-  } else {
-    // first the row maximum and the sum of exponentials, rescaled when a chunk raises the maximum ...
-    for (int j0 = 0; j0 < len; j0 += kChunk) {
-      const int nt = (min(len - j0, kChunk) + 31) / 32;
-      __syncthreads();
-      stage_rows<D>(base + (size_t)j0 * ld + H, ld, S - j0, 32 * nt, Ks);
-      __syncthreads();
-      if (active)
-#pragma unroll 1
-        for (int t = 0; t < nt; ++t) {
-          const f32x16_t a = scores(t, j0);
-          float m = mx;
+  } else if constexpr (REAL) {
+    // a chain of products is formed once: the whole row (up to 512 keys) stays in registers
+    constexpr int C = 512 / kChunk, N = kChunk / 32;
+    f32x16_t sacc[C * N];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) m = fmaxf(m, a[r]);
-          sum *= mx == -INFINITY ? 0.f : exp_neg<FAST>(__fsub_rn(mx, m));
-          mx = m;
-          sum += tile_sum(exps(a));
-        }
-    }
-    {
-      const float om = __shfl_xor(mx, 32, 64), os = __shfl_xor(sum, 32, 64), m = fmaxf(mx, om);
-      const float s0 = mx == -INFINITY ? 0.f : sum * exp_neg<FAST>(__fsub_rn(mx, m)), s1 = om == -INFINITY ? 0.f : os * exp_neg<FAST>(__fsub_rn(om, m));
-      sum = half == 0 ? s0 + s1 : s1 + s0;
-      mx = m;
-    }
-    // ... then the probabilities
-    const float rsum = __fdiv_rn(1.0f, sum);
-    for (int j0 = 0; j0 < len; j0 += kChunk) {
-      const int nt = (min(len - j0, kChunk) + 31) / 32;
+    for (int c = 0; c < C; ++c) {
+      const int left = len - c * kChunk;
+      if (left <= 0) break;
       __syncthreads();
-      stage_rows<D>(base + (size_t)j0 * ld + H, ld, S - j0, 32 * nt, Ks);
-      stage_rows<D>(base + (size_t)j0 * ld + 2 * H, ld, S - j0, 32 * nt, Vs);
+      stage_rows<D>(base + (size_t)c * kChunk * ld + H, ld, left, min((left + 31) / 32 * 32, kChunk), Ks);
       __syncthreads();
       if (active)
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+          if (32 * t < left) {
+            sacc[N * c + t] = scores(t, c * kChunk);
+            raise_max(sacc[N * c + t]);
+          }
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+#pragma unroll
+    for (int t = 0; t < C * N; ++t)
+      if (32 * t < len) {
+        sacc[t] = exps(sacc[t]);
+        if (t & 1) add_exps(sacc[t], odd);
+        else add_exps(sacc[t], even);
+      }
+    finish_sum();
+    const float rsum = __fdiv_rn(1.0f, sum);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int left = len - c * kChunk;
+      if (left <= 0) break;
+      __syncthreads();
+      stage_rows<D>(base + (size_t)c * kChunk * ld + 2 * H, ld, left, min((left + 31) / 32 * 32, kChunk), Vs);
+      __syncthreads();
+      if (active)
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+          if (32 * t < left) weigh(sacc[N * c + t], t, rsum);
+    }
+    if (!active) return;
+  } else {
+    // The row maximum, then the sum of exponentials, then the probabilities: the scores are formed three times, as a sum
+    // rescaled whenever a chunk raises the maximum would be another sum.
+    float rsum = 0.f;
+    for (int pass = 0; pass < 3; ++pass) {
+      for (int j0 = 0; j0 < len; j0 += kChunk) {
+        const int nt = (min(len - j0, kChunk) + 31) / 32;
+        __syncthreads();
+        stage_rows<D>(base + (size_t)j0 * ld + H, ld, rows - j0, 32 * nt, Ks);
+        if (pass == 2) stage_rows<D>(base + (size_t)j0 * ld + 2 * H, ld, rows - j0, 32 * nt, Vs);
+        __syncthreads();
+        if (!active) continue;
+        if (pass == 0) {
 #pragma unroll 1
-        for (int t = 0; t < nt; ++t) weigh(exps(scores(t, j0)), t, rsum);
+          for (int t = 0; t < nt; ++t) raise_max(scores(t, j0));
+        } else if (pass == 1) {
+#pragma unroll 1
+          for (int t = 0; t < nt; t += 2) {
+            add_exps(exps(scores(t, j0)), even);
+            if (t + 1 < nt) add_exps(exps(scores(t + 1, j0)), odd);
+          }
+        } else {
+#pragma unroll 1
+          for (int t = 0; t < nt; ++t) weigh(exps(scores(t, j0)), t, rsum);
+        }
+      }
+      if (pass == 0) mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      if (pass == 1) {
+        finish_sum();
+        rsum = __fdiv_rn(1.0f, sum);
+      }
     }
     if (!active) return;
   }
@@ -283,8 +399,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
     if (pmax_rows) pmax_rows[stat_idx] = 1.0f / sum;  // the largest exponential of a row is exp(0) = 1
   }
   if (q < S) {
-    // the product of the two steps in two parts, so that the scaled sum is rounded once
-    const float os = __fmul_rn(sc.sp, sc.sv), os_lo = __fmaf_rn(sc.sp, sc.sv, -os);
+    const float os = sc.sp * sc.sv;
     QuantParam qc5 = {aq.c.on ? *aq.c.s : 1.f, 0.f, aq.c.qn, aq.c.qp, aq.c.on, 0.f};
     qc5.rs = quant_reciprocal(qc5.s);
     const size_t orow = ((size_t)b * S + q) * H + h * D;
@@ -294,7 +409,10 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
       for (int g = 0; g < 4; ++g) {
         float o[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = __fmaf_rn(oacc[et][4 * g + i], os, oacc[et][4 * g + i] * os_lo);
+        for (int i = 0; i < 4; ++i) {
+          const float a = oacc[et][4 * g + i];
+          o[i] = FAST ? __fmul_rn(a, os) : __fmul_rn(__fmul_rn(a, sc.sp), sc.sv);
+        }
         const int e = 32 * et + 8 * g + 4 * half;
         store4(ctx + orow + e, o[0], o[1], o[2], o[3]);
         if (ctx_codes) {
@@ -616,53 +734,57 @@ bool attn_mfma_ok(int dt, int d) { return dt == DT_BF16 && (d == 32 || d == 64);
 
 static int block_waves(int S) { return S >= 128 ? 4 : (S + 31) / 32; }
 
-static bool fast_exp(int S, int d) { return d == 64 && S >= 64 && S <= 384; }
-// f(head dimension, fast): the instantiation for a shape
-template <class F>
-static auto with_shape(int S, int d, F&& f) {
-  if (d == 32) return f(std::integral_constant<int, 32>{}, std::false_type{});
-  if (fast_exp(S, d)) return f(std::integral_constant<int, 64>{}, std::true_type{});
-  return f(std::integral_constant<int, 64>{}, std::false_type{});
-}
+static bool fast(int S, int d) { return d == 64 && S >= 64 && S <= 384; }
 
 void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
                    float* pmax_rows, float* stat_m, float* stat_l, hipStream_t st, int8_t* ctx_codes8) {
-  with_shape(S, d, [&](auto dim, auto fast) {
+  auto launch = [&](auto dim, auto one, auto is_fast, auto real) {
     constexpr int D = decltype(dim)::value;
-    constexpr bool FAST = decltype(fast)::value;
-    const dim3 g((S + 127) / 128, nh, B), blk(64 * block_waves(S));
-    if (S <= kChunk)
-      hipLaunchKernelGGL((attn_fwd_mfma_k<D, true, FAST>), g, blk, 0, st, (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S,
-                         nh * D, pmax_rows, stat_m, stat_l, ctx_codes8);
-    else
-      hipLaunchKernelGGL((attn_fwd_mfma_k<D, false, FAST>), g, blk, 0, st, (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S,
-                         nh * D, pmax_rows, stat_m, stat_l, ctx_codes8);
-  });
+    hipLaunchKernelGGL((attn_fwd_mfma_k<D, decltype(one)::value, decltype(is_fast)::value, decltype(real)::value>), dim3((S + 127) / 128, nh, B),
+                       dim3(64 * block_waves(S)), 0, st, (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S, nh * D, pmax_rows,
+                       stat_m, stat_l, ctx_codes8);
+  };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  constexpr std::integral_constant<int, 32> d32{};
+  constexpr std::integral_constant<int, 64> d64{};
+  const bool one = S <= kChunk, real = !aq.p.on;
+  if (fast(S, d)) return one ? launch(d64, yes, yes, no) : launch(d64, no, yes, no);
+  if (d == 64) {
+    if (real) return one ? launch(d64, yes, no, yes) : launch(d64, no, no, yes);
+    return one ? launch(d64, yes, no, no) : launch(d64, no, no, no);
+  }
+  if (real) return one ? launch(d32, yes, no, yes) : launch(d32, no, no, yes);
+  return one ? launch(d32, yes, no, no) : launch(d32, no, no, no);
 }
 
 // returns the number of partial sums written to ds_parts
 int attn_bwd_mfma(const void* codes, const void* dctx, void* d_qkvh, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
                   const float* stat_m, const float* stat_l, void* scratch0, void* scratch1, float* ds_parts, hipStream_t st) {
-  return with_shape(S, d, [&](auto dim, auto fast) {
+  const int waves = block_waves(S);
+  const dim3 g((S + 127) / 128, nh, B), blk(64 * waves);
+  const bf16_t *c = (const bf16_t*)codes, *dc = (const bf16_t*)dctx;
+  bf16_t* out = (bf16_t*)d_qkvh;
+  const int H = nh * d;
+  auto launch = [&](auto dim, auto is_fast) {
     constexpr int D = decltype(dim)::value;
-    constexpr bool FAST = decltype(fast)::value;
-    const int waves = block_waves(S);
-    const dim3 g((S + 127) / 128, nh, B), blk(64 * waves);
-    const bf16_t *c = (const bf16_t*)codes, *dc = (const bf16_t*)dctx;
-    bf16_t* out = (bf16_t*)d_qkvh;
-    if (S <= kChunk) {
-      hipLaunchKernelGGL((attn_bwd_q_mfma_k<D, true, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, nh * D, stat_m, stat_l, (float*)nullptr,
-                         (bf16_t*)scratch0, (bf16_t*)scratch1, ds_parts);
-      hipLaunchKernelGGL((attn_bwd_k_one_mfma_k<D>), g, blk, 0, st, c, dc, out, aq, seqlens, S, nh * D, (const bf16_t*)scratch0,
-                         (const bf16_t*)scratch1);
-    } else {
-      hipLaunchKernelGGL((attn_bwd_q_mfma_k<D, false, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, nh * D, stat_m, stat_l, (float*)scratch0,
-                         (bf16_t*)nullptr, (bf16_t*)nullptr, ds_parts);
-      hipLaunchKernelGGL((attn_bwd_k_mfma_k<D, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, nh * D, stat_m, stat_l,
-                         (const float*)scratch0);
-    }
-    return (int)(g.x * g.y * g.z) * waves;
-  });
+    constexpr bool FAST = decltype(is_fast)::value;
+    hipLaunchKernelGGL((attn_bwd_q_mfma_k<D, false, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)scratch0,
+                       (bf16_t*)nullptr, (bf16_t*)nullptr, ds_parts);
+    hipLaunchKernelGGL((attn_bwd_k_mfma_k<D, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (const float*)scratch0);
+  };
+  if (fast(S, d) && S <= kChunk) {
+    hipLaunchKernelGGL((attn_bwd_q_mfma_k<64, true, true>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)nullptr,
+                       (bf16_t*)scratch0, (bf16_t*)scratch1, ds_parts);
+    hipLaunchKernelGGL((attn_bwd_k_one_mfma_k<64>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, (const bf16_t*)scratch0, (const bf16_t*)scratch1);
+  } else if (fast(S, d)) {
+    launch(std::integral_constant<int, 64>{}, std::true_type{});
+  } else if (d == 64) {
+    launch(std::integral_constant<int, 64>{}, std::false_type{});
+  } else {
+    launch(std::integral_constant<int, 32>{}, std::false_type{});
+  }
+  return (int)(g.x * g.y * g.z) * waves;
 }
 
 }  // namespace mrem

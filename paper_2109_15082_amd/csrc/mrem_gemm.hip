@@ -60,6 +60,17 @@ struct EpiVals {
   float alpha, beta;
 };
 
+// the epilogue's value with every operation rounded (see Epilogue::apart); cs = alpha * col_scale[n]
+__device__ __forceinline__ float epilogue_apart(float acc, float cs, const Epilogue& e, float beta, int m, int n) {
+#pragma clang fp contract(off)
+  float v = acc * cs;
+  if (e.beta) {
+    const float t = (e.col_vec ? e.col_vec[n] : 0.f) + (e.row_vec ? e.row_vec[m] : 0.f);
+    v = __builtin_fmaf(beta, t, v);
+  }
+  if (e.bias) v = v + e.bias[n];
+  return v;
+}
 template <class TO>
 __device__ __forceinline__ void epilogue_store(TO* C, int ldc, int m, int n, float acc, const Epilogue& e, const EpiVals& ev) {
   float v = acc * (ev.alpha * (e.col_scale ? e.col_scale[n] : 1.f));
@@ -176,6 +187,7 @@ constexpr int kBK = 64;  // k-granularity of the MFMA kernels, in 2-byte element
 
 }  // namespace mrem
 #include "mrem_gemm_dl.h"
+#include "mrem_gemm_chain.h"
 namespace mrem {
 
 // Whole 16-byte chunks are fetched: rows start 16-byte aligned, and the index that is contiguous in memory (the
@@ -308,7 +320,11 @@ static void gemm_launch(int dt, int a_t, int b_t, const void* A, int lda, const 
                         const Epilogue& e, hipStream_t st) {
   if (dt == DT_BF16 && mfma_ok(a_t, b_t, A, lda, B, ldb, M, N, K)) {
     if (!a_t && !b_t) {
-      launch_mfma_modes<false, false>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+      const bool whole = whole_tiles(M, N, K);
+      if (e.chain && !e.out_f32 && !whole) return launch_chain(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+      Epilogue ee = e;
+      ee.apart = !whole;
+      launch_mfma_modes<false, false>(A, lda, B, ldb, C, ldc, M, N, K, ee, st);
     } else if (!a_t && b_t) {
       launch_mfma_modes<false, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
     } else if (a_t && b_t) {

@@ -185,6 +185,21 @@ __device__ __forceinline__ void wait_frags(typename OpA::frag_t (&a)[TA], typena
   OpB::tie(b);
 }
 
+// Tile order: consecutive block ids land on different XCDs (8 of them, each with its own L2), so each XCD
+// gets a contiguous range of tiles, walked in groups of 8 tile rows so that concurrently running blocks
+// share operand panels in that L2.
+__device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm, int& tn) {
+  const int nblocks = tiles_m * tiles_n;
+  int pid = blockIdx.x;
+  if ((nblocks & 7) == 0) pid = (pid & 7) * (nblocks >> 3) + (pid >> 3);
+  constexpr int GROUP = 8;
+  const int group_sz = GROUP * tiles_n;
+  const int first_m = pid / group_sz * GROUP;
+  const int gm = (tiles_m - first_m) < GROUP ? (tiles_m - first_m) : GROUP;
+  tm = first_m + (pid % group_sz) % gm;
+  tn = (pid % group_sz) / gm;
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool AT, bool BT, int STAGES, int RB, class TO, bool I8, int MINB, int KG, bool EDGE>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B,
                                                                          int ldb, TO* __restrict__ C, int ldc, int M, int N, int K, Epilogue e,
@@ -207,19 +222,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
   static_assert(!I8 || (!AT && !BT), "int8 operands are read along k only");
   static_assert(STAGES >= 2, "double buffering at least");
 
-  // Tile order: consecutive block ids land on different XCDs (8 of them, each with its own L2), so each XCD
-  // gets a contiguous range of tiles, walked in groups of 8 tile rows so that concurrently running blocks
-  // share operand panels in that L2.
-  const int nblocks = tiles_m * tiles_n;
-  int pid = blockIdx.x;
-  if ((nblocks & 7) == 0) pid = (pid & 7) * (nblocks >> 3) + (pid >> 3);
-  constexpr int GROUP = 8;
-  const int group_sz = GROUP * tiles_n;
-  const int g = pid / group_sz;
-  const int first_m = g * GROUP;
-  const int gm = (tiles_m - first_m) < GROUP ? (tiles_m - first_m) : GROUP;
-  const int tm = first_m + (pid % group_sz) % gm;
-  const int tn = (pid % group_sz) / gm;
+  int tm, tn;
+  tile_of_block(tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -394,7 +398,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
   const float alpha = e.alpha ? *e.alpha : 1.f;
   const float beta = (e.beta ? *e.beta : 0.f) + e.beta_alpha * alpha;
   const bool split = !EDGE && gridDim.y > 1, lead = EDGE || blockIdx.y == 0;
-  auto write_out = [&](auto with_row, auto with_gelu, auto with_split) {
+  auto write_out = [&](auto with_row, auto with_gelu, auto with_split, auto apart) {
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
       const int n = n0 + wn * WN + j * 32 + (lane & 31);
@@ -412,8 +416,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
           if (KG > 1 && !BY_ROWS && (r >> 3) != kg) continue;
           const int dm = 8 * (r >> 2) + (r & 3);
           if (EDGE && mb + dm >= M) continue;
-          float v = (float)acc[i][j][r] * cs + cb;
-          if constexpr (decltype(with_row)::value) v += beta * e.row_vec[mb + dm];
+          float v;
+          if constexpr (decltype(apart)::value) {
+            v = epilogue_apart((float)acc[i][j][r], cs, e, beta, mb + dm, n);
+          } else {
+            v = (float)acc[i][j][r] * cs + cb;
+            if constexpr (decltype(with_row)::value) v += beta * e.row_vec[mb + dm];
+          }
           if constexpr (decltype(with_split)::value) {
             atomicAdd(reinterpret_cast<float*>(out) + (size_t)dm * ldc, v);
           } else {
@@ -425,20 +434,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
     }
   };
   const bool row_term = e.beta && e.row_vec && lead;
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  if constexpr (EDGE && !AT && !BT && !I8) {
+    if (e.apart) return write_out(no, no, no, yes);
+  }
   if constexpr (sizeof(TO) == 4 && !EDGE) {
-    if (split) {
-      if (row_term) write_out(std::true_type{}, std::false_type{}, std::true_type{});
-      else write_out(std::false_type{}, std::false_type{}, std::true_type{});
-      return;
-    }
+    if (split) return row_term ? write_out(yes, no, yes, no) : write_out(no, no, yes, no);
   }
-  if (e.gelu) {
-    if (row_term) write_out(std::true_type{}, std::true_type{}, std::false_type{});
-    else write_out(std::false_type{}, std::true_type{}, std::false_type{});
-  } else {
-    if (row_term) write_out(std::true_type{}, std::false_type{}, std::false_type{});
-    else write_out(std::false_type{}, std::false_type{}, std::false_type{});
-  }
+  if (e.gelu) return row_term ? write_out(yes, yes, no, no) : write_out(no, yes, no, no);
+  return row_term ? write_out(yes, no, no, no) : write_out(no, no, no, no);
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool AT, bool BT, int STAGES, int RB, class TO, bool I8 = false, int MINB = 1, int KG = 1, bool EDGE = false>

@@ -28,6 +28,10 @@ struct QArg {
 // alpha/beta are device scalars (null: alpha = 1, beta = 0); vectors may be null.  beta_alpha
 // undoes a constant subtracted from the codes of A (unsigned codes stored as int8).
 // gelu: out = round(gelu(round(out))) in the storage type.  out_f32: C is fp32.
+// chain: the result must not depend on which tiles serve the product.  Sizes that are not whole tiles then form every sum
+// as one fp32 fused multiply-add after the other with k ascending (bf16 operands, no transposes; ignored otherwise).
+// apart: the operations of the formula above are rounded one by one, in its order (set by gemm for sizes that are not
+// whole tiles; without it multiplication and addition are fused).
 struct Epilogue {
   const float* alpha = nullptr;
   const float* col_scale = nullptr;
@@ -39,6 +43,8 @@ struct Epilogue {
   int out_f32 = 0;
   int c_zeroed = 0;  // the caller has already zeroed an fp32 C (a split contraction adds into it)
   float beta_alpha = 0.f;
+  int chain = 0;
+  int apart = 0;
 };
 
 // Timing of product launches with the pair of HIP events that a launch itself carries (measurement aid).
@@ -195,8 +201,9 @@ void attn_bwd(int dt, const void* codes, const void* dctx, void* d_qkvh, const A
               int d, float* scratch_da, float* scratch_ph, float* ds_rows, hipStream_t st);
 
 // Matrix-core versions (bf16, head dimension 32 or 64).  The forward saves the row maximum and row sum of the
-// softmax (stat_m, stat_l: [B*nh*S], may be null); the backward needs them and two scratch areas (up to 128 tokens
-// each holds B*nh*s_pad^2 bf16 values, s_pad = S rounded up to 32; beyond that the first holds B*nh*S fp32 values)
+// softmax (stat_m, stat_l: [B*nh*S], may be null); the backward needs them and two scratch areas (head dimension 64 and
+// 64 to 128 tokens: each holds B*nh*s_pad^2 bf16 values, s_pad = S rounded up to 32; otherwise the first holds B*nh*S
+// fp32 values)
 // and returns the number of partial sums written to ds_parts (at most B*nh*S).
 bool attn_mfma_ok(int dt, int d);
 void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
