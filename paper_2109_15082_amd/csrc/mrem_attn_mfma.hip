@@ -187,6 +187,24 @@ __device__ __forceinline__ void accumulate_rows_chain(f32x16_t (&acc)[D / 32], c
     }
   }
 }
+// accumulate_rows with weights of 24 bits, in three bf16 parts that add up to them (the gradient of a score where it is
+// held in 32 bits: the sum over a row is zero, and 16 bits leave 2^-9 of its terms)
+template <int D>
+__device__ __forceinline__ void accumulate_rows_wide(f32x16_t (&acc)[D / 32], const bf16_t* tile, int row0, int lane, const float* w) {
+  float rest[16], part[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) rest[r] = w[r];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      part[r] = round_to<bf16_t>(rest[r]);
+      rest[r] = __fsub_rn(rest[r], part[r]);
+    }
+    accumulate_rows<D>(acc, tile, row0, lane, part);
+  }
+}
+
 // ------------------------------------------------------------------------------
 // forward: one block = up to 128 queries of one (batch, head); one wavefront = 32 queries
 // ONE: at most 128 keys.  REAL: the operands are not integer codes (and not FAST).
@@ -511,7 +529,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
     float da[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) da[r] = p[r] * (dp[r] - rowdot);
-    accumulate_rows<D>(dqacc, Ks, 32 * t, lane, da);
+    if constexpr (FAST) accumulate_rows<D>(dqacc, Ks, 32 * t, lane, da);
+    else accumulate_rows_wide<D>(dqacc, Ks, 32 * t, lane, da);
   };
   if constexpr (ONE) {
     const int nt = (len + 31) / 32;
@@ -710,7 +729,8 @@ __global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restric
           }
         }
         accumulate_rows<D>(vacc, Cs, 32 * t, lane, code);
-        accumulate_rows<D>(kacc, Qs, 32 * t, lane, da);
+        if constexpr (FAST) accumulate_rows<D>(kacc, Qs, 32 * t, lane, da);
+        else accumulate_rows_wide<D>(kacc, Qs, 32 * t, lane, da);
       }
     }
   if (j >= S) return;

@@ -340,6 +340,40 @@ def test_step_at_attention_length_edges_bf16(B, seq, heads, lo):
     _compare_step(B, W("attn_edge", 1, 128, heads, 256, seq, 2, act_dtype="bf16", **kw), tol_for=tol_for)
 
 
+@pytest.mark.parametrize("seq,heads", [(9, 2), (40, 2), (40, 4), (150, 4), (400, 2)])
+def test_score_gradient_is_held_in_fp32(B, seq, heads):
+    """The gradient of a row of scores sums to zero (softmax), so keys that are all alike give queries no gradient.  What
+    is left of it is rounding, `seq` errors that add like their square root: 2^-24 / sqrt(seq) of the sum of the terms'
+    magnitudes in fp32 (twice that for the row's own sum of probabilities, twice again for the spread), 2^-9 / sqrt(seq)
+    with terms of 16 bits.  Measured against the same gradient with keys that differ, whose terms cancel to about
+    1 / sqrt(seq) of their magnitudes; the sums of fp32 partial sums may lose sqrt(seq) more."""
+    torch = _torch()
+    H = 128
+    mod = B.MremModule(1, H, heads, 256, 2, seq)
+    rng = np.random.default_rng(seq + heads)
+    t = (rng.standard_normal(mod.teacher.numel()) * 0.1).astype(np.float32)
+    off = lambda f: B.mrem_param_offset(mod.ctx, 0, f)  # noqa: E731
+    for f in ("ln1_g", "ln2_g"):
+        t[off(f):off(f) + H] += 1.0
+    mod.teacher.copy_(torch.from_numpy(t))
+    B.mrem_teacher_prepare(mod.ctx, mod.teacher, mod.teacher_cache)
+    x = torch.from_numpy(rng.standard_normal((2, seq, H)).astype(np.float32)).cuda().bfloat16()
+    norms = []
+    for alike in (False, True):
+        p = t.copy()
+        if alike:
+            p[off("w_qkv") + H * H:off("w_qkv") + 2 * H * H] = 0.0
+            p[off("b_qkv") + H:off("b_qkv") + 2 * H] = 0.5
+        mod.params.copy_(torch.from_numpy(p))
+        mod.init_steps()
+        mod.calibrate(x)
+        grads = torch.zeros_like(mod.params)
+        mod.step(x, x, 0.0, grads_out=grads)
+        norms.append(grads[off("b_qkv"):off("b_qkv") + H].double().norm().item())
+    assert norms[1] <= 4 * 2.0 ** -24 * np.sqrt(seq) * norms[0], (norms[1] / norms[0], 4 * 2.0 ** -24 * np.sqrt(seq))
+    mod.close()
+
+
 def test_per_tensor_weight_steps_fp32(B):
     """One step per weight matrix (Section 3.1's default granularity): whole step against the oracle;
     the step fields stay tied and carry the summed gradient."""
