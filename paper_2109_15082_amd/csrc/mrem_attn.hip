@@ -127,7 +127,7 @@ __global__ void attn_fwd_k(const T* __restrict__ codes, T* __restrict__ ctx, T* 
       const T* vcol = base + 2 * H + h * d + e;
       float acc = 0.f;
       for (int j = 0; j < len; ++j) acc += prow[wave][j] * ldf(vcol, (size_t)j * ld);
-      const float out = acc * sc.sp * sc.sv;
+      const float out = len > 0 ? acc * sc.sp * sc.sv : NAN;  // a sequence without a valid key has no softmax
       const size_t o = ((size_t)b * S + i) * H + h * d + e;
       stf(ctx, o, out);
       if (ctx_codes) {

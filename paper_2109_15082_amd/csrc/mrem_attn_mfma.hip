@@ -429,7 +429,8 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float a = oacc[et][4 * g + i];
-          o[i] = FAST ? __fmul_rn(a, os) : __fmul_rn(__fmul_rn(a, sc.sp), sc.sv);
+          // a sequence without a valid key has no softmax
+          o[i] = len <= 0 ? NAN : FAST ? __fmul_rn(a, os) : __fmul_rn(__fmul_rn(a, sc.sp), sc.sv);
         }
         const int e = 32 * et + 8 * g + 4 * half;
         store4(ctx + orow + e, o[0], o[1], o[2], o[3]);

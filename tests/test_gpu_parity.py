@@ -340,6 +340,29 @@ def test_step_at_attention_length_edges_bf16(B, seq, heads, lo):
     _compare_step(B, W("attn_edge", 1, 128, heads, 256, seq, 2, act_dtype="bf16", **kw), tol_for=tol_for)
 
 
+@pytest.mark.parametrize("dtype,seq,heads", [("bf16", 64, 2), ("bf16", 200, 2), ("bf16", 20, 2), ("bf16", 40, 4), ("bf16", 400, 4), ("bf16", 40, 1), ("f32", 20, 2)])
+def test_sequence_without_a_key_yields_nan(B, dtype, seq, heads):
+    """A sequence without a valid key has no softmax: the full-precision module yields NaN in its rows (the quantized one
+    codes a NaN as the end of its range); the other sequences stay finite."""
+    torch = _torch()
+    H = 128
+    mod = B.MremModule(1, H, heads, 256, 3, seq, act_dtype=dtype)
+    rng = np.random.default_rng(seq + heads)
+    mod.teacher.copy_(torch.from_numpy((rng.standard_normal(mod.teacher.numel()) * 0.1).astype(np.float32)))
+    B.mrem_teacher_prepare(mod.ctx, mod.teacher, mod.teacher_cache)
+    mod.params.copy_(mod.teacher)
+    mod.init_steps()
+    x = torch.from_numpy(rng.standard_normal((3, seq, H)).astype(np.float32)).cuda().to(mod.tdtype)
+    mod.calibrate(x)
+    lens = torch.tensor([seq, 0, 1], dtype=torch.int32, device="cuda")
+    f_fp, f_q = mod.forward(x, x, lens)
+    nan = int(torch.isnan(f_fp[0, 1]).sum())
+    assert nan == f_fp[0, 1].numel()
+    for f in (f_fp, f_q):
+        assert int(torch.isfinite(f[0, ::2]).sum()) == f[0, ::2].numel()
+    mod.close()
+
+
 @pytest.mark.parametrize("seq,heads", [(9, 2), (40, 2), (40, 4), (150, 4), (400, 2)])
 def test_score_gradient_is_held_in_fp32(B, seq, heads):
     """The gradient of a row of scores sums to zero (softmax), so keys that are all alike give queries no gradient.  What
