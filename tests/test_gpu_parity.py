@@ -79,9 +79,9 @@ def test_quantize_codes_bit_exact(B, N, K, bits):
 
 
 # rows around the lengths where a wavefront, a block, or two passes serve a row (1024, 4096), whole 16-byte chunks and not;
-# tensors of less than one, exactly one and several parts, with the last weights outside the 16-byte chunks
+# tensors that one block searches (up to 131072 weights) and that several do, with the last weights outside the 16-byte chunks
 @pytest.mark.parametrize("N,K,per_channel", [(5, 1024, 1), (3, 1023, 1), (3, 1028, 1), (3, 1025, 1), (2, 4096, 1), (2, 4095, 1), (2, 4100, 1),
-                                             (1, 1, 0), (1, 3, 0), (1, 4, 0), (1, 4096, 0), (3, 2731, 0), (700, 3001, 0)])
+                                             (1, 1, 0), (1, 3, 0), (1, 4, 0), (1, 4096, 0), (3, 2731, 0), (32, 4096, 0), (11, 11917, 0), (700, 3001, 0)])
 @pytest.mark.parametrize("init", [0, 1])
 def test_quantize_edges_bit_exact(B, N, K, per_channel, init):
     torch = _torch()
