@@ -8,12 +8,13 @@
 //
 // v_mfma_f32_16x16x4_f32 is such a chain: its result equals four fused multiply-adds with k ascending bit for bit, also
 // where terms are subnormal.  It gives 64 flops a cycle and SIMD, a sixteenth of the bf16 product, which bounds the kernel
-// (4000 x 4096 x 1024: 282 us, 214 at that rate and 2.4 GHz), and vector instructions do not run beside it: a form with
+// (4000 x 4096 x 1024: 280 us, 214 at that rate and 2.4 GHz), and vector instructions do not run beside it: a form with
 // direct loads that converts and rearranges operands per wavefront took 316 us.
 //
-// A block is BM x BN outputs, four wavefronts of (BM / 2) x (BN / 2).  LDS holds the stage's BK values of k as fp32 rows
-// of BM + 16: the four quarters of a wavefront read four consecutive k, 16 banks apart.  A 16-byte chunk of 8 k of one row
-// is stored to 8 such rows; the row index is turned by the chunk (see `slot`), so that the chunks of a wavefront fall on
+// A block is BM x BN outputs, four wavefronts of (BM / 2) x (BN / 2).  LDS holds the stage's BK values of k as fp32, those
+// with k % 4 = q together for the quarter q of a wavefront that multiplies them, so that a lane reads four products'
+// operands (16 bytes) at once; with rows of one k each and 4-byte accesses that product took 305 us on 64 x 64 tiles
+// (291 now) and 23 x 768 x 3072 30 us (28 now).  Groups of 16 bytes change places by row, so that 16 rows fall on
 // different banks.  The next stage waits in registers while one is multiplied; two stages in LDS, one barrier each.
 #pragma once
 
@@ -23,10 +24,12 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 template <int ROWS, int BK>
 struct ChainOperand {
-  static constexpr int CPR = BK / 8, PER = ROWS * CPR / 256, PITCH = ROWS + 16;
+  static constexpr int CPR = BK / 8, PER = ROWS * CPR / 256, G = BK / 16, FLOATS = ROWS * BK;
   static_assert(PER >= 1 && ROWS * CPR % 256 == 0, "the chunks of a stage divide evenly over 256 threads");
-  // column of row r in the rows of chunk c
-  static __device__ __forceinline__ int slot(int r, int c) { return r ^ ((c * (64 / CPR)) & (ROWS - 1)); }
+  // [quarter][row][BK / 4] in groups of 4 values; group g of a row
+  static __device__ __forceinline__ int at(int quarter, int row, int g) {
+    return (quarter * ROWS + row) * (BK / 4) + 4 * (g ^ ((row / (16 / G)) & (G - 1)));
+  }
   static __device__ __forceinline__ void load(u32x4_t (&v)[PER], const bf16_t* __restrict__ p, int ld, int row0, int rows, int k0, int K) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -35,15 +38,17 @@ struct ChainOperand {
       if (k < K) v[i] = *reinterpret_cast<const u32x4_t*>(p + (size_t)r * ld + k);
     }
   }
+  // k = 8 c + 4 h + q of chunk c: value 2 c + h of quarter q
   static __device__ __forceinline__ void store(const u32x4_t (&v)[PER], float* dst) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int id = threadIdx.x + 256 * i, c = id % CPR;
-      float* d = dst + 8 * c * PITCH + slot(id / CPR, c);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        d[(2 * j) * PITCH] = __uint_as_float(v[i][j] << 16);
-        d[(2 * j + 1) * PITCH] = __uint_as_float(v[i][j] & 0xffff0000u);
+      for (int q = 0; q < 4; ++q) {
+        const unsigned lo = v[i][q / 2], hi = v[i][2 + q / 2];
+        const float2 f = q % 2 ? make_float2(__uint_as_float(lo & 0xffff0000u), __uint_as_float(hi & 0xffff0000u))
+                               : make_float2(__uint_as_float(lo << 16), __uint_as_float(hi << 16));
+        *reinterpret_cast<float2*>(dst + at(q, id / CPR, c / 2) + 2 * (c % 2)) = f;
       }
     }
   }
@@ -55,8 +60,8 @@ __global__ __launch_bounds__(256) void gemm_chain_k(const bf16_t* __restrict__ A
   typedef ChainOperand<BM, BK> OpA;
   typedef ChainOperand<BN, BK> OpB;
   constexpr int MT = BM / 32, NT = BN / 32;
-  __shared__ float As[2][BK * OpA::PITCH];
-  __shared__ float Bs[2][BK * OpB::PITCH];
+  __shared__ __attribute__((aligned(16))) float As[2][OpA::FLOATS];
+  __shared__ __attribute__((aligned(16))) float Bs[2][OpB::FLOATS];
   int tm, tn;
   tile_of_block(tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
@@ -82,16 +87,15 @@ __global__ __launch_bounds__(256) void gemm_chain_k(const bf16_t* __restrict__ A
   for (int k0 = 0, buf = 0; k0 < K; k0 += BK, buf ^= 1) {
     const bool more = k0 + BK < K;
     if (more) load(k0 + BK);
-    float a[BK / 4][MT], b[BK / 4][NT];
+    f32x4_t a[BK / 16][MT], b[BK / 16][NT];  // k = 16 g + 4 e + quarter: element e of group g
 #pragma unroll
-    for (int s = 0; s < BK / 4; ++s) {
-      const int k = 4 * s + quarter;
+    for (int g = 0; g < BK / 16; ++g) {
 #pragma unroll
-      for (int i = 0; i < MT; ++i) a[s][i] = As[buf][k * OpA::PITCH + OpA::slot(wm + 16 * i + l16, s / 2)];
+      for (int i = 0; i < MT; ++i) a[g][i] = *reinterpret_cast<const f32x4_t*>(&As[buf][OpA::at(quarter, wm + 16 * i + l16, g)]);
 #pragma unroll
-      for (int j = 0; j < NT; ++j) b[s][j] = Bs[buf][k * OpB::PITCH + OpB::slot(wn + 16 * j + l16, s / 2)];
+      for (int j = 0; j < NT; ++j) b[g][j] = *reinterpret_cast<const f32x4_t*>(&Bs[buf][OpB::at(quarter, wn + 16 * j + l16, g)]);
     }
-    // a single chain per wavefront: all fragments of the stage are read first (23 x 768 x 3072: 30.0 against 32.0 us)
+    // a single chain per wavefront: all fragments of the stage are read first
     if constexpr (MT * NT == 1) __builtin_amdgcn_sched_barrier(0);
     // rows of the accumulator tile are columns of C, so that a lane holds four neighbours of one row
 #pragma unroll
@@ -99,7 +103,7 @@ __global__ __launch_bounds__(256) void gemm_chain_k(const bf16_t* __restrict__ A
 #pragma unroll
       for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[s][j], a[s][i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[s / 4][j][s % 4], a[s / 4][i][s % 4], acc[i][j], 0, 0, 0);
     if (more) store(buf ^ 1);
     __syncthreads();
   }
@@ -133,8 +137,8 @@ static void launch_chain_tile(const void* A, int lda, const void* B, int ldb, vo
               N, K, e, tiles_m, tiles_n);
 }
 // By how many tiles there are for the 256 compute units (us, against the next smaller tile): 128 x 128 from two a compute
-// unit on (4000 x 3072 x 1024, 768 tiles: 209 against 231; 2310 x 3072 x 768, 456: 112 against 106), 64 x 64 from one and a
-// half on (924 x 3072 x 768, 720 tiles: 52 against 59; 924 x 768 x 3072, 180: 89 against 60).
+// unit on (4000 x 4096 x 1024, 1024 tiles: 280 against 291; 2310 x 3072 x 768, 456: 110 against 100), 64 x 64 from one and
+// a half on (924 x 3072 x 768, 720 tiles: 48 against 54; 924 x 768 x 3072, 180: 73 against 57).
 static void launch_chain(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e, hipStream_t st) {
   auto tiles = [&](int b) { return (int64_t)((M + b - 1) / b) * ((N + b - 1) / b); };
   if (tiles(128) >= 512) return launch_chain_tile<128, 128, 16>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
