@@ -66,7 +66,8 @@ __device__ __forceinline__ float div_by(float x, float d, float rd) {
 //     probabilities), a row's exponentials added one after the other by each half wavefront.
 //   otherwise: expf, and the order of a row that is spread over 64 lanes, lane l adding keys l, l + 64, ... and the lanes
 //     meeting in a binary tree; products of operands that are not integer codes are fp32 fused multiply-adds with the
-//     contraction index ascending.  These are the results of the scalar kernels (mrem_attn.hip), bit for bit.
+//     contraction index ascending where the caller asks for it (see Epilogue::chain).  These are the results of the
+//     scalar kernels (mrem_attn.hip), bit for bit.
 template <bool FAST>
 __device__ __forceinline__ float exp_neg(float x) {
   if constexpr (FAST) return __expf(x);
@@ -207,7 +208,7 @@ __device__ __forceinline__ void accumulate_rows_wide(f32x16_t (&acc)[D / 32], co
 
 // ------------------------------------------------------------------------------
 // forward: one block = up to 128 queries of one (batch, head); one wavefront = 32 queries
-// ONE: at most 128 keys.  REAL: the operands are not integer codes (and not FAST).
+// ONE: at most 128 keys.  REAL: the operands are not integer codes and their products are chains (not FAST).
 // ------------------------------------------------------------------------------
 template <int D, bool ONE, bool FAST, bool REAL>
 __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict__ codes, bf16_t* __restrict__ ctx,
@@ -758,7 +759,7 @@ static int block_waves(int S) { return S >= 128 ? 4 : (S + 31) / 32; }
 static bool fast(int S, int d) { return d == 64 && S >= 64 && S <= 384; }
 
 void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
-                   float* pmax_rows, float* stat_m, float* stat_l, hipStream_t st, int8_t* ctx_codes8) {
+                   float* pmax_rows, float* stat_m, float* stat_l, hipStream_t st, bool chain, int8_t* ctx_codes8) {
   auto launch = [&](auto dim, auto one, auto is_fast, auto real) {
     constexpr int D = decltype(dim)::value;
     hipLaunchKernelGGL((attn_fwd_mfma_k<D, decltype(one)::value, decltype(is_fast)::value, decltype(real)::value>), dim3((S + 127) / 128, nh, B),
@@ -769,7 +770,7 @@ void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& a
   constexpr std::false_type no{};
   constexpr std::integral_constant<int, 32> d32{};
   constexpr std::integral_constant<int, 64> d64{};
-  const bool one = S <= kChunk, real = !aq.p.on;
+  const bool one = S <= kChunk, real = !aq.p.on && chain;
   if (fast(S, d)) return one ? launch(d64, yes, yes, no) : launch(d64, no, yes, no);
   if (d == 64) {
     if (real) return one ? launch(d64, yes, no, yes) : launch(d64, no, no, yes);

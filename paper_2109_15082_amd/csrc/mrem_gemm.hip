@@ -60,15 +60,13 @@ struct EpiVals {
   float alpha, beta;
 };
 
-// the epilogue's value with every operation rounded (see Epilogue::apart); cs = alpha * col_scale[n]
-__device__ __forceinline__ float epilogue_apart(float acc, float cs, const Epilogue& e, float beta, int m, int n) {
+// the epilogue's value with every operation rounded (see Epilogue::apart): cs = alpha * col_scale[n], t = col_vec[n] +
+// row_vec[m]
+__device__ __forceinline__ float epilogue_apart(float acc, float cs, bool has_beta, float beta, float t, bool has_bias, float bias) {
 #pragma clang fp contract(off)
   float v = acc * cs;
-  if (e.beta) {
-    const float t = (e.col_vec ? e.col_vec[n] : 0.f) + (e.row_vec ? e.row_vec[m] : 0.f);
-    v = __builtin_fmaf(beta, t, v);
-  }
-  if (e.bias) v = v + e.bias[n];
+  if (has_beta) v = __builtin_fmaf(beta, t, v);
+  if (has_bias) v = v + bias;
   return v;
 }
 template <class TO>

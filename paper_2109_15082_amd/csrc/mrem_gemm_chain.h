@@ -110,17 +110,26 @@ __global__ __launch_bounds__(256) void gemm_chain_k(const bf16_t* __restrict__ A
   const float alpha = e.alpha ? *e.alpha : 1.f;
   const float beta = (e.beta ? *e.beta : 0.f) + e.beta_alpha * alpha;
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int m = m0 + wm + 16 * i + l16;
+  for (int j = 0; j < NT; ++j) {
+    const int n = n0 + wn + 16 * j + 4 * quarter;
+    if (n >= N) continue;  // N is a multiple of 8
+    float cs[4], cv[4], cb[4];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const int n = n0 + wn + 16 * j + 4 * quarter;
-      if (m >= M || n >= N) continue;  // N is a multiple of 8
+    for (int r = 0; r < 4; ++r) {
+      cs[r] = alpha * (e.col_scale ? e.col_scale[n + r] : 1.f);
+      cv[r] = e.beta && e.col_vec ? e.col_vec[n + r] : 0.f;
+      cb[r] = e.bias ? e.bias[n + r] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int m = m0 + wm + 16 * i + l16;
+      if (m >= M) continue;
       typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
       bf16x4_t out;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        float v = epilogue_apart(acc[i][j][r], alpha * (e.col_scale ? e.col_scale[n + r] : 1.f), e, beta, m, n + r);
+        const float t = e.beta && e.row_vec ? cv[r] + e.row_vec[m] : cv[r];
+        float v = epilogue_apart(acc[i][j][r], cs[r], e.beta != nullptr, beta, t, e.bias != nullptr, cb[r]);
         if (e.gelu) v = gelu_t<bf16_t>(round_to<bf16_t>(v));
         out[r] = static_cast<bf16_t>(v);
       }

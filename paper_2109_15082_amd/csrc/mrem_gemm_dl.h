@@ -405,7 +405,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
       if (EDGE && n >= N) continue;
       const float cs = alpha * (e.col_scale ? e.col_scale[n] : 1.f);
       float cb = (e.bias && lead) ? e.bias[n] : 0.f;
-      if (e.beta && e.col_vec && lead) cb += beta * e.col_vec[n];
+      const float cv = (e.beta && e.col_vec && lead) ? e.col_vec[n] : 0.f;
+      if (!decltype(apart)::value && e.beta && e.col_vec && lead) cb += beta * cv;
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         if (KG > 1 && BY_ROWS && i % KG != kg) continue;  // a partner wavefront writes this tile row
@@ -418,7 +419,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
           if (EDGE && mb + dm >= M) continue;
           float v;
           if constexpr (decltype(apart)::value) {
-            v = epilogue_apart((float)acc[i][j][r], cs, e, beta, mb + dm, n);
+            const float t = decltype(with_row)::value ? cv + e.row_vec[mb + dm] : cv;
+            v = epilogue_apart((float)acc[i][j][r], cs, e.beta != nullptr, beta, t, e.bias != nullptr, cb);
           } else {
             v = (float)acc[i][j][r] * cs + cb;
             if constexpr (decltype(with_row)::value) v += beta * e.row_vec[mb + dm];
@@ -437,7 +439,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
   if constexpr (EDGE && !AT && !BT && !I8) {
-    if (e.apart) return write_out(no, no, no, yes);
+    if (e.apart && e.gelu) return row_term ? write_out(yes, yes, no, yes) : write_out(no, yes, no, yes);
+    if (e.apart) return row_term ? write_out(yes, no, no, yes) : write_out(no, no, no, yes);
   }
   if constexpr (sizeof(TO) == 4 && !EDGE) {
     if (split) return row_term ? write_out(yes, no, yes, no) : write_out(no, no, yes, no);

@@ -204,10 +204,10 @@ void attn_bwd(int dt, const void* codes, const void* dctx, void* d_qkvh, const A
 // softmax (stat_m, stat_l: [B*nh*S], may be null); the backward needs them and two scratch areas (head dimension 64 and
 // 64 to 128 tokens: each holds B*nh*s_pad^2 bf16 values, s_pad = S rounded up to 32; otherwise the first holds B*nh*S
 // fp32 values)
-// and returns the number of partial sums written to ds_parts (at most B*nh*S).
+// and returns the number of partial sums written to ds_parts (at most B*nh*S).  chain: as in Epilogue.
 bool attn_mfma_ok(int dt, int d);
 void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
-                   float* pmax_rows, float* stat_m, float* stat_l, hipStream_t st, int8_t* ctx_codes8 = nullptr);
+                   float* pmax_rows, float* stat_m, float* stat_l, hipStream_t st, bool chain, int8_t* ctx_codes8 = nullptr);
 int attn_bwd_mfma(const void* codes, const void* dctx, void* d_qkvh, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
                   const float* stat_m, const float* stat_l, void* scratch0, void* scratch1, float* ds_parts, hipStream_t st);
 
