@@ -200,6 +200,7 @@ Plan make_plan(const mrem_ctx* c, int B, int S) {
   p.dgh = b.take(T * F * es); p.du = b.take(T * F * es); p.dqkvh = b.take(T * 3 * H * es); p.dqkv = b.take(T * 3 * H * es);
   const size_t s_pad = ((size_t)S + 31) / 32 * 32;
   const size_t pp = (size_t)B * c->nh * s_pad * s_pad;
+  // scalar attention keeps two fp32 matrices a head; the matrix-core kernels use less of it (see attn_bwd_mfma)
   p.s_da = b.take(pp * 4); p.s_ph = b.take(pp * 4);
   p.pmax = b.take((size_t)B * c->nh * S * 4);
   // first-stage partial sums of one layer's backward pass (all of them stay until the single
@@ -1002,7 +1003,7 @@ RemPlan rem_plan(int dt, int64_t T, int64_t N, int64_t K) {
   const size_t es = dt_size(dt);
   p.n_vec = ((N * K + N + 1 + 3) / 4) * 4;
   p.wt = b.take((size_t)N * K * es); p.wcodes = b.take((size_t)N * K * es); p.what = b.take((size_t)N * K * es);
-  p.zcorr = b.take((size_t)N * 4);
+  p.zcorr = b.take((size_t)N * 4);  // (nothing is kept here: the size of the workspace stays what callers have stored)
   p.xcodes = b.take((size_t)T * K * es); p.dy = b.take((size_t)T * N * es); p.dxh = b.take((size_t)T * K * es);
   p.partials = b.take(2 * 2048 * 4);
   p.grads = b.take((size_t)p.n_vec * 4);

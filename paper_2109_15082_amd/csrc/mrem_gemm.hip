@@ -84,27 +84,28 @@ __device__ __forceinline__ void epilogue_store(TO* C, int ldc, int m, int n, flo
 // 32 x 32 output tile, its four wavefronts take every fourth group of 8 contraction values straight from memory (four
 // groups' loads in flight), and their partial sums meet in LDS in wavefront order.  128 x 256 x 64 and the like: 64 x 64
 // tiles of vector-ALU products, staged through LDS 16 values of k at a time without prefetch, took 18 us; a one-layer step
-// of 128 tokens with 18 of them went from 370 to 283 us.
+// of 128 tokens with 18 of them went from 370 to 283 us.  Wide modules, one layer: 768 over 512 tokens 2323 -> 922 us, 1024
+// over 4096 tokens 10449 -> 9310 us (its forward passes alone 4477 and 4550).
 // In a group, lane l holds row l % 32 and the k values 4 (l / 32) .. + 3 of both operands: MFMA j multiplies element j of
 // both halves, so the four of them cover the group.
 // ------------------------------------------------------------------------------
 typedef float f32x16s_t __attribute__((ext_vector_type(16)));
 // element (r, k) of an operand: k contiguous in whole 16-byte chunks (VEC), or any strides
-template <class T, bool VEC>
-__device__ __forceinline__ float4 load_k4(const T* __restrict__ p, size_t sr, size_t sk, int r, int k, int K) {
+template <bool VEC>
+__device__ __forceinline__ float4 load_k4(const float* __restrict__ p, size_t sr, size_t sk, int r, int k, int K) {
   if constexpr (VEC) {
     if (k >= K) return make_float4(0.f, 0.f, 0.f, 0.f);
     return *reinterpret_cast<const float4*>(p + r * sr + k);
   } else {
     float v[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = k + j < K ? ldf(p, r * sr + (size_t)(k + j) * sk) : 0.f;
+    for (int j = 0; j < 4; ++j) v[j] = k + j < K ? p[r * sr + (size_t)(k + j) * sk] : 0.f;
     return make_float4(v[0], v[1], v[2], v[3]);
   }
 }
-template <class TA, class TO, bool VA, bool VB>
-__global__ __launch_bounds__(256) void gemm_f32_k(const TA* __restrict__ A, size_t a_sr, size_t a_sk, const TA* __restrict__ B, size_t b_sr,
-                                                  size_t b_sk, TO* __restrict__ C, int ldc, int M, int N, int K, Epilogue e) {
+template <bool VA, bool VB>
+__global__ __launch_bounds__(256) void gemm_f32_k(const float* __restrict__ A, size_t a_sr, size_t a_sk, const float* __restrict__ B, size_t b_sr,
+                                                  size_t b_sk, float* __restrict__ C, int ldc, int M, int N, int K, Epilogue e) {
   __shared__ float part[4][16][64];
   constexpr int U = 4;  // groups in flight
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -119,8 +120,8 @@ __global__ __launch_bounds__(256) void gemm_f32_k(const TA* __restrict__ A, size
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int k = k0 + 32 * u + 4 * (lane >> 5);
-      a[u] = load_k4<TA, VA>(A, a_sr, a_sk, ra, k, K);
-      b[u] = load_k4<TA, VB>(B, b_sr, b_sk, rb, k, K);
+      a[u] = load_k4<VA>(A, a_sr, a_sk, ra, k, K);
+      b[u] = load_k4<VB>(B, b_sr, b_sk, rb, k, K);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -145,24 +146,19 @@ __global__ __launch_bounds__(256) void gemm_f32_k(const TA* __restrict__ A, size
     if (m < M && n < N) epilogue_store(C, ldc, m, n, v, e, ev);
   }
 }
-template <class TA, class TO>
 static void launch_f32(int a_t, int b_t, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                        hipStream_t st) {
   const dim3 g((M + 31) / 32, (N + 31) / 32);
   const size_t asr = a_t ? 1 : lda, ask = a_t ? lda : 1, bsr = b_t ? 1 : ldb, bsk = b_t ? ldb : 1;
-  auto vec = [&](int t, const void* p, int ld) {
-    return sizeof(TA) == 4 && !t && K % 4 == 0 && ld % 4 == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0;
-  };
+  auto vec = [&](int t, const void* p, int ld) { return !t && K % 4 == 0 && ld % 4 == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   const bool va = vec(a_t, A, lda), vb = vec(b_t, B, ldb);
   auto go = [&](auto fa, auto fb) {
-    hipLaunchKernelGGL((gemm_f32_k<TA, TO, decltype(fa)::value, decltype(fb)::value>), g, dim3(256), 0, st, (const TA*)A, asr, ask, (const TA*)B,
-                       bsr, bsk, (TO*)C, ldc, M, N, K, e);
+    hipLaunchKernelGGL((gemm_f32_k<decltype(fa)::value, decltype(fb)::value>), g, dim3(256), 0, st, (const float*)A, asr, ask, (const float*)B, bsr,
+                       bsk, (float*)C, ldc, M, N, K, e);
   };
-  if constexpr (sizeof(TA) == 4) {
-    if (va && vb) return go(std::true_type{}, std::true_type{});
-    if (va) return go(std::true_type{}, std::false_type{});
-    if (vb) return go(std::false_type{}, std::true_type{});
-  }
+  if (va && vb) return go(std::true_type{}, std::true_type{});
+  if (va) return go(std::true_type{}, std::false_type{});
+  if (vb) return go(std::false_type{}, std::true_type{});
   go(std::false_type{}, std::false_type{});
 }
 
@@ -172,7 +168,7 @@ static void launch_f32(int a_t, int b_t, const void* A, int lda, const void* B, 
 // bf16 and their products and partial sums are exact in fp32 while they stay below 2^24 (always for
 // 4-bit weights: K * 255 * 7 < 2^24 up to K = 9398; with 8-bit weights only up to K = 518, beyond
 // that a product on bf16 codes rounds like any fp32 sum); the int8 mode is exact for every supported K.
-// Which sizes it takes: see mfma_ok (bf16) and gemm_i8_ok.
+// Which sizes it takes: see gemm_launch (bf16) and gemm_i8_ok.
 // ------------------------------------------------------------------------------
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -188,12 +184,6 @@ constexpr int kBK = 64;  // k-granularity of the MFMA kernels, in 2-byte element
 #include "mrem_gemm_chain.h"
 namespace mrem {
 
-// Whole 16-byte chunks are fetched: rows start 16-byte aligned, and the index that is contiguous in memory (the
-// contraction index, or the row index of a transposed operand) is a multiple of 8.  Everything else may be ragged.
-static bool mfma_ok(int a_t, int b_t, const void* A, int lda, const void* B, int ldb, int M, int N, int K) {
-  return lda % 8 == 0 && ldb % 8 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0 &&
-         (a_t ? M % 8 == 0 : K % 8 == 0) && (b_t ? N % 8 == 0 : K % 8 == 0);
-}
 // no tile of 128 x 128 and no stage of the contraction is partly filled
 static bool whole_tiles(int M, int N, int K) { return M % 128 == 0 && N % 128 == 0 && K % kBK == 0; }
 
@@ -231,7 +221,9 @@ bool gemm_i8_ok(const void* A, int lda, const void* B, int ldb, int M, int N, in
 //   128 x 64, 8 wavefronts in two groups, three stages, up to 256 such tiles (2304 x 768 x 3072: 20.0 against 22.6 for
 //     64 x 64 and 26.0 for 128 x 128);
 //   256 x 256 (8 wavefronts of 64 x 128, two stages, one block per compute unit) from 144 such tiles on: half the
-//     operand bytes per flop of the small tile (4096 x 2304 x 768: 25.7 against 28.1; 4096 x 4096 x 1024: 40 against 57);
+//     operand bytes per flop of the small tile, which is faster only while its tiles fit two a compute unit (against
+//     128 x 128, bf16 and int8: 128 tiles, 4096 x 2048 x 1024: 29.0 and 24.0, int8 18.4 and 15.3; 144 tiles, 4608 x 2048 x
+//     768: 23.4 and 26.6, int8 16.0 and 17.7; 160 tiles, 2560 x 4096 x 1024: 29.0 and 32.3, int8 19.1 and 20.4);
 //   128 x 128 with 8 wavefronts (two groups of 4; each group multiplies every other 16-deep k-substep of a
 //     stage and the groups' partial sums meet in LDS before the epilogue), four stages of 128-byte rows, one
 //     block per compute unit, up to 256 such tiles -- one tile per compute unit, so the second wavefront on each
@@ -244,8 +236,9 @@ static void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void
                             hipStream_t st, int splits) {
   auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const bool whole = whole_tiles(M, N, K);
-  if (splits > 1)
-    return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st, splits);
+  if constexpr (AT && BT) {
+    if (splits > 1) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st, splits);
+  }
   if (tiles(64, 64) <= 256)
     return launch_dl<64, 64, 2, 2, AT, BT, 4, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   if (tiles(128, 64) <= 256)
@@ -255,12 +248,13 @@ static void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void
       return launch_dl<256, 256, 4, 2, AT, BT, 2, 128, TO, I8, 1>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
     return launch_dl<256, 256, 4, 2, AT, BT, 2, 128, TO, I8, 1, 1, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   }
-  if (tiles(128, 128) <= 256) {
-    if (whole) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-    return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  const bool one_each = tiles(128, 128) <= 256;
+  if constexpr (!I8) {  // (int8 products have whole tiles of 128, see gemm_i8_ok)
+    if (!whole && one_each) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+    if (!whole) return launch_dl<128, 64, 2, 2, AT, BT, 3, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   }
-  if (whole) return launch_dl<128, 128, 2, 2, AT, BT, 4, 64, TO, I8, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-  return launch_dl<128, 64, 2, 2, AT, BT, 3, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  if (one_each) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  return launch_dl<128, 128, 2, 2, AT, BT, 4, 64, TO, I8, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
 }
 static void gemm_i8_launch(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                            hipStream_t st) {
@@ -290,9 +284,10 @@ void gemm_nt(int dt, const void* A, int lda, const void* B, int ldb, void* C, in
 }
 
 // Tiles for a quarter to half of the compute units and a long contraction (weight gradients of 1024 x 1024 and
-// 2304 x 768): two k-slices; with fewer tiles the 64 x 64 ones take over (768 x 768 over 4096 tokens; three layers'
-// step 1774 -> 1733 us).  64 x 64 tiles for 1024 x 1024 too cost the six-layer step 0.6%: twice the operand traffic
-// beside the other stream's kernels.  (Larger weight gradients run beside the rest of the backward
+// 2304 x 768): two k-slices; with fewer tiles the 64 x 64 ones take over (alone, over 4096 tokens, us: 512 x 512 18.5
+// against 20.0, 768 x 768 18.4 and 21.3, 1536 x 512 19.2 and 23.0, 1024 x 1024 19.4 and 24.7; three layers' step of 768
+// 1774 -> 1733).  64 x 64 tiles for 1024 x 1024 too cost the six-layer step 0.6%: twice the operand traffic beside the
+// other stream's kernels.  (Larger weight gradients run beside the rest of the backward
 // pass, where a second slice only adds atomic traffic.)  Two atomic adds onto a zeroed fp32 value
 // commute exactly, so the result does not depend on which slice arrives first.
 static int f32_k_slices(int M, int N, int K) {
@@ -302,42 +297,30 @@ int gemm_f32_k_slices(int dt, int M, int N, int K) {
   return dt == DT_BF16 ? f32_k_slices(M, N, K) : 1;
 }
 
-template <bool AT, bool BT>
-static void launch_mfma_modes(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
-                              hipStream_t st) {
-  if (e.out_f32) {
-    const int splits = e.gelu ? 1 : f32_k_slices(M, N, K);
-    if (splits > 1 && !e.c_zeroed) fill_f32((float*)C, 0.f, (int64_t)M * ldc, st);
-    launch_dl_tiles<AT, BT, float, false>(A, lda, B, ldb, C, ldc, M, N, K, e, st, splits);
-  } else {
-    launch_dl_tiles<AT, BT, bf16_t, false>(A, lda, B, ldb, C, ldc, M, N, K, e, st, 1);
-  }
-}
-
+// bf16 products fetch whole 16-byte chunks: the index that is contiguous in memory (the contraction index, or the row
+// index of a transposed operand) and the leading dimensions are multiples of 8 and operands 16-byte aligned, which the
+// entry points require of widths and pointers; everything else may be ragged.  The callers need three forms: codes or
+// activations times weights, an input gradient (B transposed), and a weight gradient (both transposed, fp32 result).
 static void gemm_launch(int dt, int a_t, int b_t, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K,
                         const Epilogue& e, hipStream_t st) {
-  if (dt == DT_BF16 && mfma_ok(a_t, b_t, A, lda, B, ldb, M, N, K)) {
-    if (!a_t && !b_t) {
-      const bool whole = whole_tiles(M, N, K);
-      if (e.chain && !e.out_f32 && !whole) return launch_chain(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-      Epilogue ee = e;
-      ee.apart = !whole;
-      launch_mfma_modes<false, false>(A, lda, B, ldb, C, ldc, M, N, K, ee, st);
-    } else if (!a_t && b_t) {
-      launch_mfma_modes<false, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-    } else if (a_t && b_t) {
-      launch_mfma_modes<true, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-    } else {
-      launch_mfma_modes<true, false>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-    }
-    return;
+  if (dt == DT_F32) {
+    const hipEvent_t t0 = tl_launch_events.e0, t1 = tl_launch_events.e1;  // these kernels are timed by recorded events
+    if (t0) (void)hipEventRecord(t0, st);
+    launch_f32(a_t, b_t, A, lda, B, ldb, C, ldc, M, N, K, e, st);
+    if (t1) (void)hipEventRecord(t1, st);
+  } else if (a_t) {
+    const int splits = f32_k_slices(M, N, K);
+    if (splits > 1 && !e.c_zeroed) fill_f32((float*)C, 0.f, (int64_t)M * ldc, st);
+    launch_dl_tiles<true, true, float, false>(A, lda, B, ldb, C, ldc, M, N, K, e, st, splits);
+  } else if (b_t) {
+    launch_dl_tiles<false, true, bf16_t, false>(A, lda, B, ldb, C, ldc, M, N, K, e, st, 1);
+  } else if (const bool whole = whole_tiles(M, N, K); e.chain && !whole) {
+    launch_chain(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  } else {
+    Epilogue ee = e;
+    ee.apart = !whole;
+    launch_dl_tiles<false, false, bf16_t, false>(A, lda, B, ldb, C, ldc, M, N, K, ee, st, 1);
   }
-  const hipEvent_t t0 = tl_launch_events.e0, t1 = tl_launch_events.e1;  // these kernels are timed by recorded events
-  if (t0) (void)hipEventRecord(t0, st);
-  if (dt == DT_F32) launch_f32<float, float>(a_t, b_t, A, lda, B, ldb, C, ldc, M, N, K, e, st);
-  else if (e.out_f32) launch_f32<bf16_t, float>(a_t, b_t, A, lda, B, ldb, C, ldc, M, N, K, e, st);
-  else launch_f32<bf16_t, bf16_t>(a_t, b_t, A, lda, B, ldb, C, ldc, M, N, K, e, st);
-  if (t1) (void)hipEventRecord(t1, st);
 }
 
 }  // namespace mrem

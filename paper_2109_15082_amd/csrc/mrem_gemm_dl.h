@@ -30,7 +30,7 @@
 //     With 64 rows a k-row is 128 bytes, half of the banks: bit 0 of k already picks the half, and the
 //     slot is c ^ (((k >> 1) & 1) << 2) ^ (((k >> 3) & 1) << 1).
 //
-// EDGE: any M, N and K whose 16-byte chunks are whole (see mfma_ok).  A lane whose chunk lies beyond the
+// EDGE: any M, N and K whose 16-byte chunks are whole (see gemm_launch).  A lane whose chunk lies beyond the
 // last row fetches the last row's instead (what it multiplies into is never stored).  The stage that the
 // contraction does not fill is taken first, before the loop: its chunks beyond the contraction come from a
 // block of zeros, so they add nothing, and the loop itself is that of whole tiles (with the test in the
