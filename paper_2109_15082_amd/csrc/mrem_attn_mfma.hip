@@ -150,6 +150,27 @@ __device__ __forceinline__ void accumulate_rows(f32x16_t (&acc)[D / 32], const b
   }
 }
 
+// accumulate_rows with the rows in natural order along the contraction (8 consecutive ones a half wavefront), which is the
+// order of sums that the key gradients of FAST shapes keep: the halves exchange every other four rows
+template <int D>
+__device__ __forceinline__ void accumulate_rows_natural(f32x16_t (&acc)[D / 32], const bf16_t* tile, int row0, int lane, const float* w) {
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    union { bf16x8_t v; unsigned u[4]; } f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) f.v[i] = static_cast<bf16_t>(w[8 * s + i]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const auto x = __builtin_amdgcn_permlane32_swap(f.u[i], f.u[i + 2], false, false);
+      f.u[i] = x[0];
+      f.u[i + 2] = x[1];
+    }
+    const int k0 = row0 + 16 * s + 8 * (lane >> 5);
+#pragma unroll
+    for (int et = 0; et < D / 32; ++et)
+      acc[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_tr<D>(tile, 32 * et, k0, k0 + 4, lane), f.v, acc[et], 0, 0, 0);
+  }
+}
 // The same two products for operands that are not integer codes, as chains of fp32 fused multiply-adds:
 // v_mfma_f32_32x32x2_f32 adds its two products with k ascending and rounds after each (16 times the cycles of the bf16 form).
 // Values 2 j (lower half of the wavefront) and 2 j + 1 (upper half) of 8 consecutive ones:
@@ -730,9 +751,13 @@ __global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restric
             da[4 * g + i] = pg.p * (pg.dp - st[3][i]);
           }
         }
-        accumulate_rows<D>(vacc, Cs, 32 * t, lane, code);
-        if constexpr (FAST) accumulate_rows<D>(kacc, Qs, 32 * t, lane, da);
-        else accumulate_rows_wide<D>(kacc, Qs, 32 * t, lane, da);
+        if constexpr (FAST) {
+          accumulate_rows_natural<D>(vacc, Cs, 32 * t, lane, code);
+          accumulate_rows_natural<D>(kacc, Qs, 32 * t, lane, da);
+        } else {
+          accumulate_rows<D>(vacc, Cs, 32 * t, lane, code);
+          accumulate_rows_wide<D>(kacc, Qs, 32 * t, lane, da);
+        }
       }
     }
   if (j >= S) return;

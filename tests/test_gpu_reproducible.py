@@ -77,7 +77,11 @@ def _module(shape, w_bits, a_bits, per_channel, seed):
     return mod, x_fp, x_q, rng
 
 
-def checksums(name):
+#: cases whose whole step repeats: whole tiles and the hardware's exponential
+STEPS = ("d64_s128_whole", "d64_s384_whole")
+
+
+def checksums(name, step=False):
     import torch
     from paper_2109_15082_amd import binding as B
     *shape, w_bits, a_bits, lo, per_channel = CASES[name]
@@ -91,6 +95,11 @@ def checksums(name):
             for f in ("s_a", "z_a"):
                 o = B.mrem_param_offset(mod.ctx, l, f)
                 steps += mod.params[o:o + 8].cpu().numpy().tobytes()
+    if step:
+        grads = torch.zeros_like(mod.params)
+        mod.step(x_fp, x_q, 0.0, lens, grads_out=grads)
+        torch.cuda.synchronize()
+        return [f"{zlib.crc32(grads.cpu().numpy().tobytes()):08x}"]
     f_fp, f_q = mod.forward(x_fp, x_q, lens)
     torch.cuda.synchronize()
     return [f"{zlib.crc32(b):08x}" for b in (steps, *(f.cpu().view(torch.int16).numpy().tobytes() for f in (f_fp, f_q)))]
@@ -124,6 +133,11 @@ def test_calibration_and_forward_bits(name):
     assert got == ref, "clip ranges, full-precision outputs, quantized outputs"
 
 
+@pytest.mark.parametrize("name", STEPS)
+def test_step_gradient_bits(name):
+    assert checksums(name, step=True) == _golden()["step_" + name]
+
+
 def test_step_gradients_of_a_deep_step_over_few_tokens():
     """The forward passes repeat bit by bit, so what is left is the rounding of the backward pass to bf16 (2^-9 an element,
     in other places than before: its fp32 sums are not pinned), averaged by sums over at least 100 x 512 elements; forward
@@ -138,5 +152,7 @@ if __name__ == "__main__":
     sys.path.insert(0, os.getcwd())
     for n in CASES:
         print(n, *checksums(n), flush=True)
+    for n in STEPS:
+        print("step_" + n, *checksums(n, step=True), flush=True)
     for l, row in enumerate(deep_step_gradients()):
         print(f"deep_step_s_a_{l}", *(float(v).hex() for v in row))
