@@ -4,7 +4,7 @@
 // Why: the quantizers amplify rounding.  A sum taken in another order moves the clip ranges that a calibration finds and
 // with them codes of every layer above; of a step of six layers of 1024 over 100 tokens that moved the second moments by
 // up to 44 percent (a step size's gradient is a sum that cancels).  Whole tiles have one order each; for all other sizes
-// this kernel keeps the sums the same whatever tile serves them.
+// this kernel keeps the sums the same whatever tile serves them, where the caller asks for it (Epilogue::chain).
 //
 // v_mfma_f32_16x16x4_f32 is such a chain: its result equals four fused multiply-adds with k ascending bit for bit, also
 // where terms are subnormal.  It gives 64 flops a cycle and SIMD, a sixteenth of the bf16 product, which bounds the kernel
