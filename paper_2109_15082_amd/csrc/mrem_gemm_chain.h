@@ -7,106 +7,173 @@
 // this kernel keeps the sums the same whatever tile serves them, where the caller asks for it (Epilogue::chain).
 //
 // v_mfma_f32_16x16x4_f32 is such a chain: its result equals four fused multiply-adds with k ascending bit for bit, also
-// where terms are subnormal.  It gives 64 flops a cycle and SIMD, a sixteenth of the bf16 product, which bounds the kernel
-// (4000 x 4096 x 1024: 280 us, 214 at that rate and 2.4 GHz), and vector instructions do not run beside it: a form with
-// direct loads that converts and rearranges operands per wavefront took 316 us.
+// where terms are subnormal.  It gives 64 flops a cycle and SIMD, a sixteenth of the bf16 product, which bounds large
+// products; small ones are bound by the chain itself, K / 4 instructions of 33.6 cycles each, whatever the tile.  One
+// ordinary vector instruction between two of them costs 16 cycles, every further one 4 (they share the multipliers), an LDS
+// read next to nothing up to two an instruction.  So the loop holds nothing else: operands go global -> LDS as they are
+// (direct loads, three stages of 64 values of k ahead, swizzled as in mrem_gemm_dl.h), and a lane reads its value straight
+// into the upper half of a register whose lower half is zero (ds_read_u16_d16_hi), which is the conversion.  Reads run AHEAD
+// steps in front of the instruction that needs them and are waited for one step at a time; stage addresses advance in scalar
+// registers.  23 x 768 x 3072: 17.1 us (43 cycles an instruction); with fp32 in LDS, converted by the threads that stored
+// it, and a wait for all of a stage's reads 27.8 us.  500 x 1024 x 4096: 38 and 56 us.  4000 x 4096 x 1024: 268 and 283 us
+// (214 at the instruction's rate and 2.4 GHz).
 //
-// A block is BM x BN outputs, four wavefronts of (BM / 2) x (BN / 2).  LDS holds the stage's BK values of k as fp32, those
-// with k % 4 = q together for the quarter q of a wavefront that multiplies them, so that a lane reads four products'
-// operands (16 bytes) at once; with rows of one k each and 4-byte accesses that product took 305 us on 64 x 64 tiles
-// (291 now) and 23 x 768 x 3072 30 us (28 now).  Groups of 16 bytes change places by row, so that 16 rows fall on
-// different banks.  The next stage waits in registers while one is multiplied; two stages in LDS, one barrier each.
+// A block is WM x WN wavefronts of MT x NT tiles of 16 x 16.
 #pragma once
 
 namespace mrem {
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <int ROWS, int BK>
-struct ChainOperand {
-  static constexpr int CPR = BK / 8, PER = ROWS * CPR / 256, G = BK / 16, FLOATS = ROWS * BK;
-  static_assert(PER >= 1 && ROWS * CPR % 256 == 0, "the chunks of a stage divide evenly over 256 threads");
-  // [quarter][row][BK / 4] in groups of 4 values; group g of a row
-  static __device__ __forceinline__ int at(int quarter, int row, int g) {
-    return (quarter * ROWS + row) * (BK / 4) + 4 * (g ^ ((row / (16 / G)) & (G - 1)));
-  }
-  static __device__ __forceinline__ void load(u32x4_t (&v)[PER], const bf16_t* __restrict__ p, int ld, int row0, int rows, int k0, int K) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int id = threadIdx.x + 256 * i, r = min(row0 + id / CPR, rows - 1), k = k0 + id % CPR * 8;  // rows beyond the matrix repeat the last one
-      v[i] = u32x4_t{0u, 0u, 0u, 0u};
-      if (k < K) v[i] = *reinterpret_cast<const u32x4_t*>(p + (size_t)r * ld + k);
-    }
-  }
-  // k = 8 c + 4 h + q of chunk c: value 2 c + h of quarter q
-  static __device__ __forceinline__ void store(const u32x4_t (&v)[PER], float* dst) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int id = threadIdx.x + 256 * i, c = id % CPR;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const unsigned lo = v[i][q / 2], hi = v[i][2 + q / 2];
-        const float2 f = q % 2 ? make_float2(__uint_as_float(lo & 0xffff0000u), __uint_as_float(hi & 0xffff0000u))
-                               : make_float2(__uint_as_float(lo << 16), __uint_as_float(hi << 16));
-        *reinterpret_cast<float2*>(dst + at(q, id / CPR, c / 2) + 2 * (c % 2)) = f;
-      }
-    }
-  }
-};
+template <int OFF>
+__device__ __forceinline__ void lds_read_u16_hi(float& v, int addr) {
+  asm volatile("ds_read_u16_d16_hi %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFF));
+}
 
-template <int BM, int BN, int BK>
-__global__ __launch_bounds__(256) void gemm_chain_k(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
-                                                    bf16_t* __restrict__ C, int ldc, int M, int N, int K, Epilogue e, int tiles_m, int tiles_n) {
-  typedef ChainOperand<BM, BK> OpA;
-  typedef ChainOperand<BN, BK> OpB;
-  constexpr int MT = BM / 32, NT = BN / 32;
-  __shared__ __attribute__((aligned(16))) float As[2][OpA::FLOATS];
-  __shared__ __attribute__((aligned(16))) float Bs[2][OpB::FLOATS];
+// values of T tiles for one step (k = 4 STEP + quarter) of the stage OFF bytes on
+template <int OFF, int STEP, int T>
+__device__ __forceinline__ void chain_read(float (&f)[T], const int (&addr)[8]) {
+  static_for<T>([&](auto i) { lds_read_u16_hi<OFF + 8 * (STEP & 1) + 2048 * i.value>(f[i.value], addr[STEP / 2]); });
+}
+template <int T>
+__device__ __forceinline__ void chain_tie(float (&f)[T]) {
+#pragma unroll
+  for (int i = 0; i < T; ++i) asm volatile("" : "+v"(f[i]));
+}
+// at most N LDS reads may still be in flight (they return in order)
+template <int N>
+__device__ __forceinline__ void wait_lgkmcnt() {
+  static_assert(N >= 0 && N < 16, "4-bit counter");
+  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
+}
+
+template <int MT, int NT, int WM, int WN, int AHEAD>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_chain_k(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
+                                                             bf16_t* __restrict__ C, int ldc, int M, int N, int K, Epilogue e, int tiles_m, int tiles_n) {
+  constexpr int BM = 16 * MT * WM, BN = 16 * NT * WN, BK = 64, RB = 2 * BK, NW = WM * WN, STAGES = 4, STEPS = BK / 4;
+  constexpr int RING = AHEAD < 2 ? 2 : AHEAD < 4 ? 4 : 8;  // steps whose operands are in registers or on the way
+  typedef DlOperand<false, BM, RB, 1> OpA;
+  typedef DlOperand<false, BN, RB, 1> OpB;
+  constexpr int STAGE_BYTES = OpA::BYTES + OpB::BYTES, LPW = (OpA::LOADS + OpB::LOADS) / NW;
+  static_assert((OpA::LOADS + OpB::LOADS) % NW == 0, "the loads of a stage divide evenly over the wavefronts");
+  static_assert((STAGES - 1) * STAGE_BYTES + 2048 * (MT > NT ? MT : NT) <= 65536, "an LDS read reaches every stage with its 16-bit offset");
+  static_assert(AHEAD >= 1 && AHEAD < RING && STEPS % RING == 0 && AHEAD * (MT + NT) < 16, "LDS reads in flight fit the 4-bit counter");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE_BYTES];
   int tm, tn;
   tile_of_block(tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, quarter = lane >> 4;
-  const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
-  u32x4_t va[OpA::PER], vb[OpB::PER];
+  const int lane = threadIdx.x & 63, l16 = lane & 15, quarter = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN * (16 * MT), wn = wave % WN * (16 * NT);
+  const int KT = (K + BK - 1) / BK, tail = K % BK;
+
+  // sources of this wavefront's loads: its operand's first row, and a lane's offset (rows beyond the matrix repeat the last one)
+  const unsigned char* base[LPW];
+  unsigned src[LPW];
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) {
+    const int gi = wave * LPW + i, p = gi * 1024 + lane * 16;
+    base[i] = reinterpret_cast<const unsigned char*>(gi < OpA::LOADS ? A + (size_t)m0 * lda : B + (size_t)n0 * ldb);
+    src[i] = (unsigned)(gi < OpA::LOADS ? OpA::src_offset_edge(p, lda, M - m0) : OpB::src_offset_edge(p - OpA::BYTES, ldb, N - n0));
+  }
+  // Fetch a stage into its slot.  Stages beyond the last are the last one again (nobody reads them): the loop has no case for
+  // them.  Chunks beyond the contraction come from a block of zeros.
+  auto issue = [&](int stage, int slot) {
+    unsigned char* dst = smem + slot * STAGE_BYTES + wave * (LPW * 1024);
+    const int kt = stage < KT ? stage : KT - 1;
+    auto load = [&](int i, const unsigned char* s) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)s, (__attribute__((address_space(3))) void*)(dst + i * 1024), 16, 0, 0);
+    };
+    if (tail && kt == KT - 1) {
+#pragma unroll
+      for (int i = 0; i < LPW; ++i) {
+        const int gi = wave * LPW + i, p = gi * 1024 + lane * 16;
+        const int k = gi < OpA::LOADS ? OpA::k_of(p) : OpB::k_of(p - OpA::BYTES);
+        load(i, k < tail ? base[i] + (size_t)kt * RB + src[i] : reinterpret_cast<const unsigned char*>(&kZeroChunk));
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < LPW; ++i) load(i, base[i] + (size_t)kt * RB + src[i]);
+    }
+  };
+
+  // LDS addresses of k values quarter and 4 + quarter (8 bytes on) of the eight chunks of a stage
+  int a_addr[8], b_addr[8];
+  const int lds0 = (int)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const int at = l16 * RB + ((c ^ OpA::swizzle_k(l16)) << 4) + 2 * quarter;  // 16 rows on: the swizzle is the same
+    a_addr[c] = lds0 + wm * RB + at;
+    b_addr[c] = lds0 + OpA::BYTES + wn * RB + at;
+  }
   f32x4_t acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  auto load = [&](int k0) {
-    OpA::load(va, A, lda, m0, M, k0, K);
-    OpB::load(vb, B, ldb, n0, N, k0, K);
-  };
-  auto store = [&](int buf) {
-    OpA::store(va, As[buf]);
-    OpB::store(vb, Bs[buf]);
-  };
-  load(0);
-  store(0);
-  __syncthreads();
-  for (int k0 = 0, buf = 0; k0 < K; k0 += BK, buf ^= 1) {
-    const bool more = k0 + BK < K;
-    if (more) load(k0 + BK);
-    f32x4_t a[BK / 16][MT], b[BK / 16][NT];  // k = 16 g + 4 e + quarter: element e of group g
+  float fa[RING][MT], fb[RING][NT];  // the lower halves stay zero
 #pragma unroll
-    for (int g = 0; g < BK / 16; ++g) {
+  for (int s = 0; s < RING; ++s) {
 #pragma unroll
-      for (int i = 0; i < MT; ++i) a[g][i] = *reinterpret_cast<const f32x4_t*>(&As[buf][OpA::at(quarter, wm + 16 * i + l16, g)]);
+    for (int i = 0; i < MT; ++i) fa[s][i] = 0.f;
 #pragma unroll
-      for (int j = 0; j < NT; ++j) b[g][j] = *reinterpret_cast<const f32x4_t*>(&Bs[buf][OpB::at(quarter, wn + 16 * j + l16, g)]);
-    }
-    // a single chain per wavefront: all fragments of the stage are read first
-    if constexpr (MT * NT == 1) __builtin_amdgcn_sched_barrier(0);
-    // rows of the accumulator tile are columns of C, so that a lane holds four neighbours of one row
-#pragma unroll
-    for (int s = 0; s < BK / 4; ++s)
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[s / 4][j][s % 4], a[s / 4][i][s % 4], acc[i][j], 0, 0, 0);
-    if (more) store(buf ^ 1);
-    __syncthreads();
+    for (int j = 0; j < NT; ++j) fb[s][j] = 0.f;
   }
+  auto read = [&](auto slot, auto step) {
+    constexpr int off = decltype(slot)::value * STAGE_BYTES, s = decltype(step)::value;
+    chain_read<off, s>(fa[s % RING], a_addr);
+    chain_read<off, s>(fb[s % RING], b_addr);
+  };
+  // rows of the accumulator tile are columns of C, so that a lane holds four neighbours of one row
+  auto multiply = [&](auto step) {
+    constexpr int s = decltype(step)::value % RING;
+    wait_lgkmcnt<AHEAD * (MT + NT)>();  // the steps read after this one
+    chain_tie(fa[s]);
+    chain_tie(fb[s]);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[s][j], fa[s][i], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Stage kt.  Its operands are read AHEAD steps before they are multiplied, those of the next stage's first steps behind
+  // the barrier that hands it over.  No branch may join while reads are in flight: a register that is copied there is copied
+  // before it has arrived.  So the last stage reads on into the next slot, and what it reads is dropped.
+  auto run_stage = [&](int kt, auto slot) {
+    static_for<STEPS - AHEAD>([&](auto s) {
+      read(slot, std::integral_constant<int, s.value + AHEAD>{});
+      multiply(s);
+    });
+    wait_vmcnt<LPW*(STAGES - 3)>();  // own loads of the next stage have landed
+    __builtin_amdgcn_s_barrier();    // everybody's have, and everybody holds the operands of the stage before this one
+    issue(kt + STAGES - 1, (slot.value + STAGES - 1) % STAGES);
+    static_for<AHEAD>([&](auto s) {
+      read(std::integral_constant<int, (slot.value + 1) % STAGES>{}, s);
+      multiply(std::integral_constant<int, STEPS - AHEAD + s.value>{});
+    });
+  };
+  for (int s = 0; s < STAGES - 1; ++s) issue(s, s);
+  wait_vmcnt<LPW*(STAGES - 2)>();
+  __builtin_amdgcn_s_barrier();  // stage 0 has landed for everybody
+  static_for<AHEAD>([&](auto s) { read(std::integral_constant<int, 0>{}, s); });
+  for (int kt = 0;;) {
+    run_stage(kt, std::integral_constant<int, 0>{});
+    if (++kt >= KT) break;
+    run_stage(kt, std::integral_constant<int, 1>{});
+    if (++kt >= KT) break;
+    run_stage(kt, std::integral_constant<int, 2>{});
+    if (++kt >= KT) break;
+    run_stage(kt, std::integral_constant<int, 3>{});
+    if (++kt >= KT) break;
+  }
+  // nothing is on its way into a register or into LDS when the block ends
+  wait_lgkmcnt<0>();
+#pragma unroll
+  for (int s = 0; s < RING; ++s) {
+    chain_tie(fa[s]);
+    chain_tie(fb[s]);
+  }
+  wait_vmcnt<0>();
   const float alpha = e.alpha ? *e.alpha : 1.f;
   const float beta = (e.beta ? *e.beta : 0.f) + e.beta_alpha * alpha;
 #pragma unroll
@@ -138,21 +205,21 @@ __global__ __launch_bounds__(256) void gemm_chain_k(const bf16_t* __restrict__ A
   }
 }
 
-template <int BM, int BN, int BK>
+template <int MT, int NT, int WM, int WN, int AHEAD>
 static void launch_chain_tile(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                               hipStream_t st) {
+  constexpr int BM = 16 * MT * WM, BN = 16 * NT * WN;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  MREM_LAUNCH((gemm_chain_k<BM, BN, BK>), dim3(tiles_m * tiles_n), dim3(256), 0, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (bf16_t*)C, ldc, M,
-              N, K, e, tiles_m, tiles_n);
+  MREM_LAUNCH((gemm_chain_k<MT, NT, WM, WN, AHEAD>), dim3(tiles_m * tiles_n), dim3(64 * WM * WN), 0, st, (const bf16_t*)A, lda, (const bf16_t*)B,
+              ldb, (bf16_t*)C, ldc, M, N, K, e, tiles_m, tiles_n);
 }
-// By how many tiles there are for the 256 compute units (us, against the next smaller tile): 128 x 128 from two a compute
-// unit on (4000 x 4096 x 1024, 1024 tiles: 280 against 291; 2310 x 3072 x 768, 456: 110 against 100), 64 x 64 from one and
-// a half on (924 x 3072 x 768, 720 tiles: 48 against 54; 924 x 768 x 3072, 180: 73 against 57).
+// 64 x 64 from 480 such tiles on, almost two a compute unit (us, against 32 x 32: 500 x 4096 x 1024, 512 tiles: 38.9 and 41.5;
+// 2048 x 960 x 320, 480: 15.5 and 16.7; 4000 x 1024 x 4096, 1008: 254 and 266; 2310 x 768 x 768, 444: 29.7 and 28.7).
+// 128 x 128 tiles take as long as 64 x 64 ones (4000 x 4096 x 1024: 261 and 268; 4000 x 1024 x 4096: 255 and 254).
 static void launch_chain(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e, hipStream_t st) {
   auto tiles = [&](int b) { return (int64_t)((M + b - 1) / b) * ((N + b - 1) / b); };
-  if (tiles(128) >= 512) return launch_chain_tile<128, 128, 16>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-  if (tiles(64) >= 384) return launch_chain_tile<64, 64, 32>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-  launch_chain_tile<32, 32, 64>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  if (tiles(64) >= 480) return launch_chain_tile<2, 2, 2, 2, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  launch_chain_tile<1, 1, 2, 2, 3>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
 }
 
 }  // namespace mrem
