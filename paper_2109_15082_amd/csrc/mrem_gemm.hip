@@ -181,6 +181,7 @@ constexpr int kBK = 64;  // k-granularity of the MFMA kernels, in 2-byte element
 
 }  // namespace mrem
 #include "mrem_gemm_dl.h"
+#include "mrem_gemm_quad.h"
 #include "mrem_gemm_chain.h"
 namespace mrem {
 
@@ -220,14 +221,20 @@ bool gemm_i8_ok(const void* A, int lda, const void* B, int ldb, int M, int N, in
 //     and 34.9 for 128 x 128);
 //   128 x 64, 8 wavefronts in two groups, three stages, up to 256 such tiles (2304 x 768 x 3072: 20.0 against 22.6 for
 //     64 x 64 and 26.0 for 128 x 128);
-//   256 x 256 (8 wavefronts of 64 x 128, two stages, one block per compute unit) from 144 such tiles on: half the
-//     operand bytes per flop of the small tile, which is faster only while its tiles fit two a compute unit (against
-//     128 x 128, bf16 and int8: 128 tiles, 4096 x 2048 x 1024: 29.0 and 24.0, int8 18.4 and 15.3; 144 tiles, 4608 x 2048 x
-//     768: 23.4 and 26.6, int8 16.0 and 17.7; 160 tiles, 2560 x 4096 x 1024: 29.0 and 32.3, int8 19.1 and 20.4);
 //   128 x 128 with 8 wavefronts (two groups of 4; each group multiplies every other 16-deep k-substep of a
 //     stage and the groups' partial sums meet in LDS before the epilogue), four stages of 128-byte rows, one
 //     block per compute unit, up to 256 such tiles -- one tile per compute unit, so the second wavefront on each
 //     SIMD is what overlaps fragment reads, barriers and MFMA issue (4096 x 1024 x 4096: 41.4 against 52.9 for 128 x 64);
+//   128 x 256 (mrem_gemm_quad.h) up to 256 such tiles: one round of blocks with 3/4 of the operand bytes per flop of two
+//     128 x 128 tiles a compute unit (6144 x 1024 x 4096: 57.3 against 73.6, int8 30.1 and 37.6; 2310 x 3072 x 768: 17.1
+//     and 21.2; 2000 x 4096 x 1024: 21.4 and 26.3; 1500 x 3072 x 768, 144 tiles: 14.8 and 16.6);
+//   256 x 256 (mrem_gemm_quad.h) beyond that: half the operand bytes per flop of 128 x 128 (4096 x 4096 x 1024: 32.0; 3000 x
+//     3072 x 768, 144 tiles: 24.4 against 28.2 for 288 tiles of 128 x 256).
+// The two large tiles need an even number of whole stages (K a multiple of 128, 256 for int8).  Other contractions take
+//   256 x 256 (8 wavefronts of 64 x 128, two stages) from 144 such tiles on: half the
+//     operand bytes per flop of the small tile, which is faster only while its tiles fit two a compute unit (against
+//     128 x 128, bf16 and int8: 128 tiles, 4096 x 2048 x 1024: 29.0 and 24.0, int8 18.4 and 15.3; 144 tiles, 4608 x 2048 x
+//     768: 23.4 and 26.6, int8 16.0 and 17.7; 160 tiles, 2560 x 4096 x 1024: 29.0 and 32.3, int8 19.1 and 20.4);
 //   128 x 128 with 4 wavefronts of 64 x 64, four stages of 64-byte rows, two blocks per compute unit, otherwise:
 //     the second block fills the barrier and epilogue gaps of the first (6144 x 768 x 3072: 51.6 against 57.3 for
 //     128 x 64).  Sizes with partly filled tiles take 128 x 64 here (2310 x 3072 x 768: 22.2 against 23.1).
@@ -243,17 +250,28 @@ static void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void
     return launch_dl<64, 64, 2, 2, AT, BT, 4, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   if (tiles(128, 64) <= 256)
     return launch_dl<128, 64, 2, 2, AT, BT, 3, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  if (tiles(128, 128) <= 256) {
+    if constexpr (!I8) {  // (int8 products have whole tiles of 128, see gemm_i8_ok)
+      if (!whole) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+    }
+    return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  }
+  if (quad_ok(K)) {
+    if (tiles(128, 256) <= 256) {
+      if (M % 128 == 0 && N % 256 == 0) return launch_quad<128, AT, BT, TO, I8, false>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+      return launch_quad<128, AT, BT, TO, I8, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+    }
+    if (M % 256 == 0 && N % 256 == 0) return launch_quad<256, AT, BT, TO, I8, false>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+    return launch_quad<256, AT, BT, TO, I8, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  }
   if (tiles(256, 256) >= 144) {
     if (whole && M % 256 == 0 && N % 256 == 0)
       return launch_dl<256, 256, 4, 2, AT, BT, 2, 128, TO, I8, 1>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
     return launch_dl<256, 256, 4, 2, AT, BT, 2, 128, TO, I8, 1, 1, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   }
-  const bool one_each = tiles(128, 128) <= 256;
-  if constexpr (!I8) {  // (int8 products have whole tiles of 128, see gemm_i8_ok)
-    if (!whole && one_each) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+  if constexpr (!I8) {
     if (!whole) return launch_dl<128, 64, 2, 2, AT, BT, 3, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   }
-  if (one_each) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   return launch_dl<128, 128, 2, 2, AT, BT, 4, 64, TO, I8, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
 }
 static void gemm_i8_launch(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
