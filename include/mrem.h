@@ -16,13 +16,14 @@
  *  - Boundary notes: quantizer placement (all six products of a layer) and the plain chain-rule step gradient
  *    are fixed, not options; lr and lambda are arguments of the step, their schedules are mrem_schedule_*.
  *  - All work is enqueued on the caller's hipStream_t (passed as void*, NULL = the
- *    default stream) or ordered with it: mrem_module_step runs the full-precision
- *    forward pass, the weight-gradient products and the update of each layer's
- *    weight matrices on a side stream that the context owns (default priority,
- *    created on the first step), forked from the caller's stream by events and
- *    joined to it before the loss and before the call's last kernels; to the caller
- *    the call behaves like work on its own stream.  Calls return without
- *    synchronising.
+ *    default stream) or ordered with it: mrem_module_step (above a few tokens) runs
+ *    the full-precision forward pass, the weight-gradient products and the update of
+ *    each layer's weight matrices on a side stream that the context owns (default
+ *    priority, created on the first call that uses it), forked from the caller's
+ *    stream by events and joined to it before the loss and before the call's last
+ *    kernels; mrem_module_forward does the same with the full-precision pass, unless
+ *    the caller's stream is being captured.  To the caller a call behaves like work
+ *    on its own stream.  Calls return without synchronising.
  *  - Arguments are validated on the host before anything is enqueued; a call that
  *    returns an error has had no effect on device memory.
  *  - Return value: MREM_OK or a negative mrem_status.  mrem_last_error() gives a

@@ -8,6 +8,8 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -32,6 +34,11 @@ struct mrem_ctx {
   std::vector<hipEvent_t> ev_ready;  // [4 * l + i]: the output gradient of linear layer i of layer l is written
   std::vector<hipEvent_t> ev_done;   // [4 * l + i]: its weight-gradient product has read it
   int side_device = -1;
+  int step_device = -1;  // the device of the first step
+  // Forward passes on one context may come from several threads (each with its own workspace and stream) and share the side
+  // stream: its creation, and each recording of the two events below with the wait for it, happen under the lock.
+  std::shared_ptr<std::mutex> side_lock = std::make_shared<std::mutex>();
+  hipEvent_t ev_pass_fork = nullptr, ev_pass_join = nullptr;
   GemmProfile prof;                // per-launch timing of the matrix products (measurement aid)
   int32_t* nonfinite_flag = nullptr;  // device, caller-owned, optional
 };
@@ -82,7 +89,7 @@ extern "C" mrem_status mrem_create(const mrem_config* cfg, mrem_ctx** out) {
 // a creation that failed half way).
 static void release_side(mrem_ctx* ctx) {
   if (ctx->side) (void)hipStreamSynchronize(ctx->side);
-  for (hipEvent_t* e : {&ctx->ev_fork, &ctx->ev_join, &ctx->ev_codes}) {
+  for (hipEvent_t* e : {&ctx->ev_fork, &ctx->ev_join, &ctx->ev_codes, &ctx->ev_pass_fork, &ctx->ev_pass_join}) {
     if (*e) (void)hipEventDestroy(*e);
     *e = nullptr;
   }
@@ -100,7 +107,9 @@ static bool create_side(mrem_ctx* ctx, int dev) {
   bool ok = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) == hipSuccess &&
             hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming) == hipSuccess &&
             hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&ctx->ev_codes, hipEventDisableTiming) == hipSuccess;
+            hipEventCreateWithFlags(&ctx->ev_codes, hipEventDisableTiming) == hipSuccess &&
+            hipEventCreateWithFlags(&ctx->ev_pass_fork, hipEventDisableTiming) == hipSuccess &&
+            hipEventCreateWithFlags(&ctx->ev_pass_join, hipEventDisableTiming) == hipSuccess;
   ctx->ev_layer.assign((size_t)ctx->L, nullptr);
   ctx->ev_ready.assign((size_t)ctx->L * 4, nullptr);
   ctx->ev_done.assign((size_t)ctx->L * 4, nullptr);
@@ -518,6 +527,7 @@ struct Update {
   const hipEvent_t* ev_ready;  // four per layer
   const hipEvent_t* ev_done;   // four per layer
   hipEvent_t ev_join;
+  bool by_layer;               // one handover to `side` a layer instead of one a product
 };
 void update_matrices(const Run& r, const Update& u, float* grads, int l, hipStream_t st);
 
@@ -541,19 +551,37 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
     red.next = r.at<float>(r.p.partials) + r.p.partials_per_layer * l;
     // The weight-gradient products feed nothing but the update, so with a side stream they run
     // there, beside the input-gradient products and the bandwidth-bound kernels of this stream.
-    // The output-gradient buffers are shared by all layers: before this stream overwrites one, it
-    // waits until the product of the layer above has read it.
+    // Handed over one by one, each output gradient has one buffer, which this stream overwrites in the layer below only
+    // when the product has read it.  Handed over by the layer, two layers alternate between two sets of buffers (the
+    // second is the full-precision pass's scratch, which nobody needs any more).
+    const bool by_layer = up.side && up.by_layer, second = by_layer && (l & 1);
+    const size_t dr2 = second ? r.p.t_y : r.p.dr2, dr1 = second ? r.p.t_o : r.p.dr1, du = second ? r.p.t_g : r.p.du, dqkv = second ? r.p.t_qkv : r.p.dqkv;
+    const size_t dr1_above = by_layer && !second ? r.p.t_o : r.p.dr1;
+    if (by_layer && l + 2 < L) (void)hipStreamWaitEvent(r.st, up.ev_done[4 * (l + 2)], 0);
+    Run rs = r;
+    if (up.side) rs.st = up.side;
     auto issue_wgrad = [&](int i, const void* dy, const void* codes) {
-      if (!up.side) { wgrad(r, params, grads, l, i, dy, codes); return; }
-      (void)hipEventRecord(up.ev_ready[4 * l + i], r.st);
-      (void)hipStreamWaitEvent(up.side, up.ev_ready[4 * l + i], 0);
-      Run rs = r;
-      rs.st = up.side;
+      if (by_layer) return;
+      if (up.side) {
+        (void)hipEventRecord(up.ev_ready[4 * l + i], r.st);
+        (void)hipStreamWaitEvent(up.side, up.ev_ready[4 * l + i], 0);
+      }
       wgrad(rs, params, grads, l, i, dy, codes);
-      (void)hipEventRecord(up.ev_done[4 * l + i], up.side);
+      if (up.side) (void)hipEventRecord(up.ev_done[4 * l + i], up.side);
     };
     auto before_overwrite = [&](int i) {
-      if (up.side && l < L - 1) (void)hipStreamWaitEvent(r.st, up.ev_done[4 * (l + 1) + i], 0);
+      if (up.side && !by_layer && l < L - 1) (void)hipStreamWaitEvent(r.st, up.ev_done[4 * (l + 1) + i], 0);
+    };
+    // all that the side stream does for this layer, once everything it reads is enqueued on this one
+    auto hand_over = [&]() {
+      (void)hipEventRecord(up.ev_layer[l], r.st);
+      (void)hipStreamWaitEvent(up.side, up.ev_layer[l], 0);
+      if (!by_layer) return;
+      wgrad(rs, params, grads, l, 3, r.at(dr2), r.at(w.gcodes));
+      wgrad(rs, params, grads, l, 2, r.at(du), r.at(w.x1codes));
+      wgrad(rs, params, grads, l, 1, r.at(dr1), r.at(w.ctxcodes));
+      wgrad(rs, params, grads, l, 0, r.at(dqkv), r.at(w.xcodes));
+      if (l >= 2) (void)hipEventRecord(up.ev_done[4 * l], up.side);
     };
     // second LayerNorm: dy = [dr1 + dxh*mask of the layer above] + gradient of this layer's Eq. 3 term,
     // which the same kernel forms from the two layer outputs (it also returns the squared-error sum)
@@ -568,8 +596,8 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
       // in: layer output, the two LayerNorm inputs, the full-precision output (loss), above the top layer also the two
       // gradients from above; out: the gradient of the LayerNorm input
       timed(r, "ln_bwd_k", (double)T * H * es * ((top ? 4 : 6) + (in_loss ? 1 : 0)), [&] {
-        n = ln_bwd(c->dt, top ? nullptr : r.at(r.p.dr1), top ? nullptr : r.at(r.p.dxh), fq, q_above, r.at(w.x1), r.at(w.y),
-                   r.at<float>(w.mu2), r.at<float>(w.rstd2), base + c->foff[MREM_F_LN2_G], r.at(r.p.dr2), parts, T, H, r.st,
+        n = ln_bwd(c->dt, top ? nullptr : r.at(dr1_above), top ? nullptr : r.at(r.p.dxh), fq, q_above, r.at(w.x1), r.at(w.y),
+                   r.at<float>(w.mu2), r.at<float>(w.rstd2), base + c->foff[MREM_F_LN2_G], r.at(dr2), parts, T, H, r.st,
                    in_loss ? ffp : nullptr, scale);
       });
       red.add(parts, n, wd, 0, H, g + c->foff[MREM_F_LN2_G]);
@@ -580,8 +608,8 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
       red.add(parts, n, wd, 3 * H + 1, 1, loss_out + 1 + l, in_loss ? scale : 0.f);
     }
     // second feed-forward projection
-    issue_wgrad(3, r.at(r.p.dr2), r.at(w.gcodes));
-    dgrad(r, l, 3, r.at(r.p.dr2), r.at(r.p.dgh));
+    issue_wgrad(3, r.at(dr2), r.at(w.gcodes));
+    dgrad(r, l, 3, r.at(dr2), r.at(r.p.dgh));
     // GELU and its output quantizer
     {
       // the kernel also leaves the column sums of du per row slab: the bias gradient of the first projection
@@ -590,21 +618,21 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
       before_overwrite(2);
       ColGrid cg{};
       timed(r, "gelu_quant_bwd_k", (double)T * F * 3 * es,
-            [&] { cg = gelu_quant_bwd(c->dt, r.at(r.p.dgh), r.at(w.u), r.at(r.p.du), T, F, make_q(c, params, l, 7), parts, cols, r.st); });
+            [&] { cg = gelu_quant_bwd(c->dt, r.at(r.p.dgh), r.at(w.u), r.at(du), T, F, make_q(c, params, l, 7), parts, cols, r.st); });
       red.add(parts, cg.gx * cg.gy, 1, 0, 1, g + c->foff[MREM_F_S_A] + 7);
       red.add(cols, cg.gy, F, 0, F, g + c->foff[MREM_F_B_1]);
     }
     // first feed-forward projection
-    issue_wgrad(2, r.at(r.p.du), r.at(w.x1codes));
-    dgrad(r, l, 2, r.at(r.p.du), r.at(r.p.dx1h));
+    issue_wgrad(2, r.at(du), r.at(w.x1codes));
+    dgrad(r, l, 2, r.at(du), r.at(r.p.dx1h));
     // first LayerNorm: dy = dr2 (residual) + dx1h through the FFN-input quantizer
     {
       float* parts = red.take((size_t)ln_bwd_parts(T) * (3 * H + 2));
       before_overwrite(1);
       int n = 0;
       timed(r, "ln_bwd_k", (double)T * H * es * 6, [&] {
-        n = ln_bwd(c->dt, r.at(r.p.dr2), r.at(r.p.dx1h), r.at(w.x1), make_q(c, params, l, 6), x, r.at(w.o),
-                   r.at<float>(w.mu1), r.at<float>(w.rstd1), base + c->foff[MREM_F_LN1_G], r.at(r.p.dr1), parts, T, H, r.st);
+        n = ln_bwd(c->dt, r.at(dr2), r.at(r.p.dx1h), r.at(w.x1), make_q(c, params, l, 6), x, r.at(w.o),
+                   r.at<float>(w.mu1), r.at<float>(w.rstd1), base + c->foff[MREM_F_LN1_G], r.at(dr1), parts, T, H, r.st);
       });
       const int wd = 3 * H + 2;
       red.add(parts, n, wd, 0, H, g + c->foff[MREM_F_LN1_G]);
@@ -613,8 +641,8 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
       red.add(parts, n, wd, 3 * H, 1, g + c->foff[MREM_F_S_A] + 6);
     }
     // attention output projection
-    issue_wgrad(1, r.at(r.p.dr1), r.at(w.ctxcodes));
-    dgrad(r, l, 1, r.at(r.p.dr1), r.at(r.p.dch));
+    issue_wgrad(1, r.at(dr1), r.at(w.ctxcodes));
+    dgrad(r, l, 1, r.at(dr1), r.at(r.p.dch));
     {
       float* parts = red.take(2048);
       int n = 0;
@@ -642,7 +670,7 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
       before_overwrite(0);
       ColGrid cg{};
       timed(r, "qkv_quant_bwd_k", (double)T * 3 * H * 3 * es,
-            [&] { cg = qkv_quant_bwd(c->dt, r.at(r.p.dqkvh), r.at(w.qkv), r.at(r.p.dqkv), T, H, aq.q, aq.k, aq.v, parts, cols, r.st); });
+            [&] { cg = qkv_quant_bwd(c->dt, r.at(r.p.dqkvh), r.at(w.qkv), r.at(dqkv), T, H, aq.q, aq.k, aq.v, parts, cols, r.st); });
       const int n = cg.gx * cg.gy;
       red.add(parts, n, 3, 0, 1, g + c->foff[MREM_F_S_A] + 1);
       red.add(parts, n, 3, 1, 1, g + c->foff[MREM_F_S_A] + 2);
@@ -650,8 +678,9 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
       red.add(cols, cg.gy, 3 * H, 0, 3 * H, g + c->foff[MREM_F_B_QKV]);
     }
     // query/key/value projection
-    issue_wgrad(0, r.at(r.p.dqkv), r.at(w.xcodes));
-    dgrad(r, l, 0, r.at(r.p.dqkv), r.at(r.p.dxh));
+    issue_wgrad(0, r.at(dqkv), r.at(w.xcodes));
+    if (by_layer && l > 0) hand_over();
+    dgrad(r, l, 0, r.at(dqkv), r.at(r.p.dxh));
     if (l == 0) {
       // nothing flows out of the module (Section 4.2); only the input quantizer's step needs dxh
       float* parts = red.take(2048);
@@ -662,14 +691,9 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
     // again (the input gradients used the dequantized copies): its second-stage reductions and
     // the update of its four matrices, which is bound by memory traffic, run beside the
     // matrix products of the layers below.
-    hipStream_t us = r.st;
-    if (up.side) {
-      us = up.side;
-      (void)hipEventRecord(up.ev_layer[l], r.st);
-      (void)hipStreamWaitEvent(us, up.ev_layer[l], 0);
-    }
-    reduce_jobs(red.jobs.data() + first_job, (int)(red.jobs.size() - first_job), us);
-    update_matrices(r, up, grads, l, us);
+    if (up.side && (!by_layer || l == 0)) hand_over();
+    reduce_jobs(red.jobs.data() + first_job, (int)(red.jobs.size() - first_job), rs.st);
+    update_matrices(r, up, grads, l, rs.st);
   }
   if (up.side) {
     (void)hipEventRecord(up.ev_join, up.side);
@@ -844,7 +868,7 @@ extern "C" mrem_status mrem_module_calibrate(mrem_ctx* ctx, float* params, const
 namespace {
 mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teacher, const void* teacher_cache, const void* x_fp,
                          const void* x_q, const int32_t* seqlens, int32_t batch, int32_t seq, void* per_layer_fp, void* per_layer_q,
-                         void* workspace, size_t workspace_bytes, void* hip_stream, const char* who) {
+                         void* workspace, size_t workspace_bytes, void* hip_stream, bool two_streams, const char* who) {
   Plan plan;
   mrem_status s = check_common(ctx, batch, seq, workspace, workspace_bytes, who, &plan);
   if (s != MREM_OK) return s;
@@ -861,6 +885,39 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
     REQUIRE_PTR(x_q, who);
     if (!aligned16(per_layer_q)) return fail(ctx, MREM_EINVAL, std::string(who) + ": per_layer_q misaligned");
   }
+  // The passes share nothing but their inputs: the full-precision one runs on the side stream, forked from the caller's and
+  // joined to it (both passes of a 23-token sentence through three layers of 768: 373 us one after the other, 264 now; six
+  // layers of 1024 over 4096 tokens: 1840 and 1660).  Not while the caller's stream is being captured: the side stream may
+  // serve another thread meanwhile.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+  bool fork = two_streams && per_layer_fp && per_layer_q && !ctx->prof.on;
+  if (fork && (hipStreamIsCapturing(r.st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
+    (void)hipGetLastError();
+    fork = false;
+  }
+  if (fork) {
+    const std::lock_guard<std::mutex> lock(*ctx->side_lock);
+    int dev = -1;
+    fork = hipGetDevice(&dev) == hipSuccess && (ctx->side || create_side(ctx, dev)) && dev == ctx->side_device;
+    if (fork) {
+      (void)hipEventRecord(ctx->ev_pass_fork, r.st);
+      (void)hipStreamWaitEvent(ctx->side, ctx->ev_pass_fork, 0);
+    }
+  }
+  if (fork) {
+    Run rt = r;
+    rt.st = ctx->side;
+    prepare_weights(r, params, false);
+    // layer by layer in turn, so that both streams have work from the start
+    for (int l = 0; l < ctx->L; ++l) {
+      teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, nullptr, l, l + 1);
+      student_forward(r, params, x_q, per_layer_q, l, l + 1);
+    }
+    const std::lock_guard<std::mutex> lock(*ctx->side_lock);
+    (void)hipEventRecord(ctx->ev_pass_join, ctx->side);
+    (void)hipStreamWaitEvent(r.st, ctx->ev_pass_join, 0);
+    return finish(ctx, who);
+  }
   if (per_layer_fp) teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp, nullptr);
   if (per_layer_q) {
     prepare_weights(r, params, false);
@@ -874,7 +931,7 @@ extern "C" mrem_status mrem_module_forward(mrem_ctx* ctx, const float* params, c
                                            const void* x_fp, const void* x_q, const int32_t* seqlens, int32_t batch, int32_t seq,
                                            void* per_layer_fp, void* per_layer_q, void* workspace, size_t workspace_bytes, void* hip_stream) {
   return forward_impl(ctx, params, teacher, teacher_cache, x_fp, x_q, seqlens, batch, seq, per_layer_fp, per_layer_q, workspace,
-                      workspace_bytes, hip_stream, "mrem_module_forward");
+                      workspace_bytes, hip_stream, true, "mrem_module_forward");
 }
 
 // ------------------------------------------------------------------------------
@@ -914,7 +971,7 @@ extern "C" mrem_status mrem_module_forward_static(mrem_ctx* ctx, const float* pa
   // Nothing in the forward passes reads scratch memory that the same call has not written, so the
   // contents a previous call left behind need no clearing.
   return forward_impl(ctx, params, teacher, teacher_cache, x_fp, x_q, seqlens, batch, seq, per_layer_fp, per_layer_q,
-                      g_scratch_ptr[dev], MREM_STATIC_SCRATCH_BYTES, hip_stream, who);
+                      g_scratch_ptr[dev], MREM_STATIC_SCRATCH_BYTES, hip_stream, false, who);
 }
 
 extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* adam_m, float* adam_v, int64_t step_index, float lr,
@@ -944,10 +1001,25 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
   // the loss: kernels of the two passes fill each other's tails.
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return fail(ctx, MREM_EHIP, "mrem_module_step: no current device");
-  if (!ctx->side && !create_side(ctx, dev))
-    return fail(ctx, MREM_EHIP, "mrem_module_step: cannot create the side stream and its events");
-  if (dev != ctx->side_device) return fail(ctx, MREM_EINVAL, "mrem_module_step: the context was first used on another device");
-  const bool fork = !ctx->prof.on;  // per-launch timing wants every product alone on the device
+  {
+    const std::lock_guard<std::mutex> lock(*ctx->side_lock);
+    if (!ctx->side && !create_side(ctx, dev))
+      return fail(ctx, MREM_EHIP, "mrem_module_step: cannot create the side stream and its events");
+  }
+  if (ctx->step_device < 0) ctx->step_device = dev;
+  if (dev != ctx->step_device) return fail(ctx, MREM_EINVAL, "mrem_module_step: the context was first used on another device");
+  // What the second stream is worth depends on the size.  A wait for an event takes the host 11 us, five launches' time, and
+  // with a handover for every product a layer needs nine of them, so a step of few tokens is bound by the host: 3 layers of
+  // 256 over 66 tokens 718 us, 532 with one handover a layer, 551 on one stream; 3 of 512 over 427: 735, 664, 786; 6 of 1024
+  // over 495: 2512, 2396, 2949.  From about 2^19 activations a layer on the device is the limit, and products that start
+  // later cost up to 1.5% (2 of 768 over 992 tokens: 670, 681, 762; 6 of 1024 over 4096: 4305, 4350).  With one layer there is
+  // nothing to overlap the update with (1 of 1024 over 400: 435, 450, 469), and the shortest steps are quickest on one stream
+  // (1 of 64 over 128, fp32: 290, 235, 198; 1 of 512 over 200: 282, 262, 255; 2 of 128 over 80: 494, 405, 332).
+  const int64_t acts = (int64_t)r.T * ctx->H;
+  const bool fork = !ctx->prof.on &&  // per-launch timing wants every product alone on the device
+                    acts * ctx->L * ctx->L > (1 << 17) &&
+                    dev == ctx->side_device;  // (a forward pass may have created the stream on another device)
+  const bool by_layer = ctx->L > 1 && acts <= (1 << 19);
   // Eq. 4: with lambda > 0 the quantized module reads lambda * x_fp + (1 - lambda) * x_q, formed by its first kernel
   const bool mix = lambda > 0.f && x_fp != x_q;
   const void* x_in = mix ? r.at(r.p.xmix) : x_q;
@@ -962,8 +1034,8 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
     // Only the first layer's weights are prepared on this stream; those of the layers above are prepared on the side
     // stream ahead of the teacher's pass (which has slack before the loss needs it), so the quantized pass starts after
     // one layer's worth of that work instead of the whole module's.
-    prepare_weights(r, params, true, 0, 1);
-    if (ctx->L > 1) {
+    prepare_weights(r, params, true, 0, by_layer ? -1 : 1);
+    if (ctx->L > 1 && !by_layer) {
       prepare_weights(rt, params, true, 1, ctx->L);
       (void)hipEventRecord(ctx->ev_codes, ctx->side);
     }
@@ -971,7 +1043,7 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
     // start also when the caller's queue was empty
     for (int l = 0; l < ctx->L; ++l) {
       teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, nullptr, l, l + 1);
-      if (l == 1) (void)hipStreamWaitEvent(r.st, ctx->ev_codes, 0);
+      if (l == 1 && !by_layer) (void)hipStreamWaitEvent(r.st, ctx->ev_codes, 0);
       student_forward(r, params, x_in, per_layer_q, l, l + 1, mix_fp, x_q, lambda);
     }
     (void)hipEventRecord(ctx->ev_join, ctx->side);
@@ -983,7 +1055,7 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
   }
   if (fork) (void)hipStreamWaitEvent(r.st, ctx->ev_join, 0);
   const Update up{params, adam_m, adam_v, adam_arg(ctx, step_index, lr), grads_out != nullptr, fork ? ctx->side : nullptr,
-                  ctx->ev_layer.data(), ctx->ev_ready.data(), ctx->ev_done.data(), ctx->ev_join};
+                  ctx->ev_layer.data(), ctx->ev_ready.data(), ctx->ev_done.data(), ctx->ev_join, by_layer};
   student_backward(r, params, x_in, per_layer_fp, per_layer_q, grads, loss_out, up);
   update_vectors(r, up, grads);
   return finish(ctx, "mrem_module_step");
