@@ -19,13 +19,11 @@
 // product passes through LDS in chunks of 128 rows, so a block takes 37 KB (20 KB for head
 // dimension 32) and registers, not LDS, say how many share a compute unit.  Up to 128 keys (one
 // chunk) the scores and probabilities stay in registers between the pass that forms the row
-// statistics and the pass that uses them.  Longer rows of codes form their tiles again for each
-// pass, since a probability is normalised before it is quantized: the scores, the exponentials
-// and the quantizer are vector-ALU work, which is what bounds these kernels, and a whole row in
-// registers leaves one wavefront per SIMD (16 x 384 tokens, step of 6 layers of 1024: 7126 us
-// against 7015).  Wavefronts per SIMD: forward 3 to 4 up to 128 keys, 2 to 3 beyond; backward 2
-// to 4 (160 to 254 registers for head dimension 64).  Chunks beyond the valid keys of a sequence
-// are skipped.
+// statistics and the pass that uses them.  Longer rows are shared out among the wavefronts of a block of 32
+// queries (attn_fwd_row_k); the backward pass forms their tiles again for each pass.  The scores, the
+// exponentials and the quantizer are vector-ALU work, which is what bounds these kernels, and a whole row in
+// one wavefront's registers leaves one wavefront per SIMD.  Wavefronts per SIMD: forward 3 to 4; backward 2
+// to 4 (160 to 254 registers for head dimension 64).  Chunks beyond the valid keys of a sequence are skipped.
 #include "mrem_common.h"
 #include "mrem_kernels.h"
 
@@ -83,6 +81,23 @@ __device__ __forceinline__ FwdScales load_fwd_scales(const AttnQ& a, int d) {
   s.p_qp = a.p.qp;
   s.rsp = __fdiv_rn(1.0f, s.sp);
   return s;
+}
+
+// scores of 32 keys from accumulators, first key `key0`; -inf beyond the valid keys (a tile without such keys skips the tests,
+// two of the six instructions a score costs a forward pass ahead of its exponential)
+__device__ __forceinline__ void scale_scores(f32x16_t& a, const FwdScales& sc, int key0, int half, int len) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) a[r] = __fmul_rn(a[r], sc.qk);
+  if (key0 + 32 <= len) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if (key_of(0, r, half) + key0 >= len) a[r] = -INFINITY;
+}
+// what the exponentials of a row are taken against: with a row of -inf only, 0, so that each of them is 0 and not NaN
+__device__ __forceinline__ float finite_max(float mx) { return mx == -INFINITY ? 0.f : mx; }
+// code of a probability, or the probability itself (NaN gives code 0)
+__device__ __forceinline__ float prob_code(float p, const FwdScales& sc) {
+  return sc.p_on ? rintf(__builtin_amdgcn_fmed3f(div_by(p, sc.sp, sc.rsp), 0.f, sc.p_qp)) : p;
 }
 
 // stage rows [0, S) of a [S, D] slice (row stride ld elements) row-major into LDS, zero rows up to s_pad
@@ -227,6 +242,49 @@ __device__ __forceinline__ void accumulate_rows_wide(f32x16_t (&acc)[D / 32], co
   }
 }
 
+// sum of a lane's 16 partial sums and those of the other half of the wavefront, in the order of the binary tree
+__device__ __forceinline__ float sum_of_parts(const float (&part)[16]) {
+  float x[4];  // keys 8 g .. 8 g + 7: bits 0 and 1 of the key, then bit 2, which is the half of the wavefront
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    x[g] = (part[4 * g] + part[4 * g + 1]) + (part[4 * g + 2] + part[4 * g + 3]);
+    x[g] += __shfl_xor(x[g], 32, 64);
+  }
+  return (x[0] + x[1]) + (x[2] + x[3]);
+}
+// 32 columns of the context of a lane's query (16 of them here, from element `o` on) and their codes
+template <bool FAST>
+__device__ __forceinline__ void store_context(const f32x16_t& acc, const AttnQ& aq, const FwdScales& sc, int len, size_t o, bf16_t* __restrict__ ctx,
+                                              bf16_t* __restrict__ ctx_codes, int8_t* __restrict__ ctx_codes8) {
+  const float os = sc.sp * sc.sv;
+  QuantParam qc5 = {aq.c.on ? *aq.c.s : 1.f, 0.f, aq.c.qn, aq.c.qp, aq.c.on, 0.f};
+  qc5.rs = quant_reciprocal(qc5.s);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float a = acc[4 * g + i];
+      // a sequence without a valid key has no softmax
+      v[i] = len <= 0 ? NAN : FAST ? __fmul_rn(a, os) : __fmul_rn(__fmul_rn(a, sc.sp), sc.sv);
+    }
+    store4(ctx + o + 8 * g, v[0], v[1], v[2], v[3]);
+    if (ctx_codes) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float r = round_to<bf16_t>(v[i]);
+        v[i] = qc5.on ? q_code(q_ratio_fma(r, qc5), qc5) : r;
+      }
+      store4(ctx_codes + o + 8 * g, v[0], v[1], v[2], v[3]);
+      if (ctx_codes8) {
+        const unsigned pk = ((unsigned)(int)v[0] & 0xffu) | (((unsigned)(int)v[1] & 0xffu) << 8) | (((unsigned)(int)v[2] & 0xffu) << 16) |
+                            (((unsigned)(int)v[3] & 0xffu) << 24);
+        *reinterpret_cast<unsigned*>(ctx_codes8 + o + 8 * g) = pk;
+      }
+    }
+  }
+}
+
 // ------------------------------------------------------------------------------
 // forward: one block = up to 128 queries of one (batch, head); one wavefront = 32 queries
 // ONE: at most 128 keys.  REAL: the operands are not integer codes and their products are chains (not FAST).
@@ -269,8 +327,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
     f32x16_t a;
     if constexpr (REAL) a = tile_product_chain<D>(Ks, 32 * t, lane, qr);
     else a = tile_product<D>(Ks, 32 * t, lane, qf);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) a[r] = key_of(0, r, half) + j0 + 32 * t < len ? __fmul_rn(a[r], sc.qk) : -INFINITY;
+    scale_scores(a, sc, j0 + 32 * t, half, len);
     return a;
   };
   f32x16_t oacc[D / 32];
@@ -283,15 +340,16 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float p = div_by(e[r], sum, rsum);
-      w[r] = REAL ? round_to<bf16_t>(p) : sc.p_on ? rintf(fminf(fmaxf(div_by(p, sc.sp, sc.rsp), 0.f), sc.p_qp)) : p;
+      w[r] = REAL ? round_to<bf16_t>(p) : prob_code(p, sc);
     }
     if constexpr (REAL) accumulate_rows_chain<D>(oacc, Vs, 32 * t, lane, w);
     else accumulate_rows<D>(oacc, Vs, 32 * t, lane, w);
   };
   auto exps = [&](const f32x16_t& a) {
     f32x16_t e;
+    const float top = finite_max(mx);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) e[r] = a[r] == -INFINITY ? 0.f : exp_neg<FAST>(__fsub_rn(a[r], mx));
+    for (int r = 0; r < 16; ++r) e[r] = exp_neg<FAST>(__fsub_rn(a[r], top));
     return e;
   };
   auto raise_max = [&](const f32x16_t& a) {
@@ -315,18 +373,8 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
     if constexpr (FAST) {
       sum += __shfl_xor(sum, 32, 64);
     } else {
-      float y[2];
-#pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        float x[4];  // keys 8 g .. 8 g + 7: bits 0 and 1 of the key, then bit 2, which is the half of the wavefront
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          x[g] = (part[o][4 * g] + part[o][4 * g + 1]) + (part[o][4 * g + 2] + part[o][4 * g + 3]);
-          x[g] += __shfl_xor(x[g], 32, 64);
-        }
-        y[o] = (x[0] + x[1]) + (x[2] + x[3]);
-      }
-      sum = y[0] + y[1];
+      const float y = sum_of_parts(part[0]);
+      sum = y + sum_of_parts(part[1]);
     }
   };
   constexpr std::integral_constant<int, 0> even{};
@@ -357,7 +405,8 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
 #pragma unroll
     for (int t = 0; t < kChunk / 32; ++t)
       if (t < nt) weigh(sacc[t], t, rsum);
-  } else if constexpr (REAL) {
+  } else {
+    static_assert(REAL, "rows of more than one chunk: attn_fwd_row_k");
     // a chain of products is formed once: the whole row (up to 512 keys) stays in registers
     constexpr int C = 512 / kChunk, N = kChunk / 32;
     f32x16_t sacc[C * N];
@@ -399,39 +448,6 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
           if (32 * t < left) weigh(sacc[N * c + t], t, rsum);
     }
     if (!active) return;
-  } else {
-    // The row maximum, then the sum of exponentials, then the probabilities: the scores are formed three times, as a sum
-    // rescaled whenever a chunk raises the maximum would be another sum.
-    float rsum = 0.f;
-    for (int pass = 0; pass < 3; ++pass) {
-      for (int j0 = 0; j0 < len; j0 += kChunk) {
-        const int nt = (min(len - j0, kChunk) + 31) / 32;
-        __syncthreads();
-        stage_rows<D>(base + (size_t)j0 * ld + H, ld, rows - j0, 32 * nt, Ks);
-        if (pass == 2) stage_rows<D>(base + (size_t)j0 * ld + 2 * H, ld, rows - j0, 32 * nt, Vs);
-        __syncthreads();
-        if (!active) continue;
-        if (pass == 0) {
-#pragma unroll 1
-          for (int t = 0; t < nt; ++t) raise_max(scores(t, j0));
-        } else if (pass == 1) {
-#pragma unroll 1
-          for (int t = 0; t < nt; t += 2) {
-            add_exps(exps(scores(t, j0)), even);
-            if (t + 1 < nt) add_exps(exps(scores(t + 1, j0)), odd);
-          }
-        } else {
-#pragma unroll 1
-          for (int t = 0; t < nt; ++t) weigh(exps(scores(t, j0)), t, rsum);
-        }
-      }
-      if (pass == 0) mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      if (pass == 1) {
-        finish_sum();
-        rsum = __fdiv_rn(1.0f, sum);
-      }
-    }
-    if (!active) return;
   }
   const size_t stat_idx = ((size_t)b * nh + h) * S + q;
   if (half == 0 && q < S) {
@@ -439,38 +455,191 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
     if (pmax_rows) pmax_rows[stat_idx] = 1.0f / sum;  // the largest exponential of a row is exp(0) = 1
   }
   if (q < S) {
-    const float os = sc.sp * sc.sv;
-    QuantParam qc5 = {aq.c.on ? *aq.c.s : 1.f, 0.f, aq.c.qn, aq.c.qp, aq.c.on, 0.f};
-    qc5.rs = quant_reciprocal(qc5.s);
     const size_t orow = ((size_t)b * S + q) * H + h * D;
 #pragma unroll
-    for (int et = 0; et < D / 32; ++et)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float o[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float a = oacc[et][4 * g + i];
-          // a sequence without a valid key has no softmax
-          o[i] = len <= 0 ? NAN : FAST ? __fmul_rn(a, os) : __fmul_rn(__fmul_rn(a, sc.sp), sc.sv);
-        }
-        const int e = 32 * et + 8 * g + 4 * half;
-        store4(ctx + orow + e, o[0], o[1], o[2], o[3]);
-        if (ctx_codes) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float r = round_to<bf16_t>(o[i]);
-            o[i] = qc5.on ? q_code(q_ratio_fma(r, qc5), qc5) : r;
-          }
-          store4(ctx_codes + orow + e, o[0], o[1], o[2], o[3]);
-          if (ctx_codes8) {
-            const unsigned pk = ((unsigned)(int)o[0] & 0xffu) | (((unsigned)(int)o[1] & 0xffu) << 8) | (((unsigned)(int)o[2] & 0xffu) << 16) |
-                                (((unsigned)(int)o[3] & 0xffu) << 24);
-            *reinterpret_cast<unsigned*>(ctx_codes8 + orow + e) = pk;
-          }
-        }
-      }
+    for (int et = 0; et < D / 32; ++et) store_context<FAST>(oacc[et], aq, sc, len, orow + 32 * et + 4 * half, ctx, ctx_codes, ctx_codes8);
   }
+}
+
+// ------------------------------------------------------------------------------
+// Rows of more than 128 keys: a block is 32 queries, its four wavefronts share out the keys, so that a wavefront's scores (up
+// to four tiles) stay in registers from the product to the probabilities.  A sum rescaled whenever the maximum rises would be
+// another sum; this way every exponential is still formed once and not twice, every score once and not three times.  Maximum
+// and row sum pass through LDS, the sum from wavefront to wavefront, since its order is part of the result.  The probabilities
+// go to LDS as the fragments of their product with V, which one wavefront per 32 columns forms, in the order of the keys.
+// K comes straight from memory (no two wavefronts read the same rows), V through LDS in chunks of 128 rows.
+// Vector-ALU instructions bound it; 3 or 4 blocks a compute unit.  Inside a step, against 128 queries a block, every tile
+// formed three times: 8 x 512 tokens, 12 heads: 99 -> 53 us; 16 x 384 tokens, 16 heads: 87 -> 69 us.
+// ------------------------------------------------------------------------------
+
+// Which head and which of the nq blocks of its rows a block takes: the blocks of a head run on one XCD, whose L2 then holds the
+// other side of its products.  Blocks are dealt out to the eight XCDs in turn; heads beyond a multiple of eight go in order.
+__device__ __forceinline__ void row_of_block(int nq, int heads, int& head, int& blk) {
+  const int id = blockIdx.x, dealt = heads / 8 * 8 * nq;
+  if (id < dealt) {
+    head = id / 8 / nq * 8 + id % 8;
+    blk = id / 8 % nq;
+  } else {
+    head = heads / 8 * 8 + (id - dealt) / nq;
+    blk = (id - dealt) % nq;
+  }
+}
+
+template <int D, bool FAST>
+__global__ __launch_bounds__(256, FAST ? 4 : 3) void attn_fwd_row_k(const bf16_t* __restrict__ codes, bf16_t* __restrict__ ctx, bf16_t* __restrict__ ctx_codes,
+                                                         AttnQ aq, const int32_t* __restrict__ seqlens, int S, int B, int nh,
+                                                         float* __restrict__ pmax_rows, float* __restrict__ stat_m, float* __restrict__ stat_l,
+                                                         int8_t* __restrict__ ctx_codes8) {
+  // tiles of a wavefront (up to 384 or 512 keys); rows of V in LDS at a time (FAST: four blocks a compute unit); 16-byte pieces of those per thread
+  constexpr int TW = FAST ? 3 : 4, RC = 32 * TW, CH = RC * (D / 8) / 256;
+  static_assert(RC * (D / 8) % 256 == 0, "whole pieces");
+  __shared__ __attribute__((aligned(16))) bf16_t Vs[RC * Tile<D>::kStride];
+  // the sums on their way from wavefront to wavefront, then the fragments of the probabilities
+  __shared__ __attribute__((aligned(16))) union { float sums[32][64]; u32x4_t p[4 * TW][2][64]; } x;
+  __shared__ float row_max[4][32], row_sum[32];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
+  int head, blk;
+  row_of_block((S + 31) / 32, B * nh, head, blk);
+  const int b = head / nh, h = head % nh, H = nh * D, ld = 3 * H;
+  const bf16_t* base = codes + (size_t)b * S * ld + h * D;
+  const int len = seqlens ? min(seqlens[b], S) : S;
+  const int rows = FAST ? S : len;  // rows of V that are staged: those beyond are zero rows
+  const FwdScales sc = load_fwd_scales(aq, D);
+  const int nt = max(len + 31, 0) / 32, tw = (nt + 3) / 4;  // tiles of the row, of a wavefront
+  const int t0 = wave * tw, n = max(min(nt - t0, tw), 0);
+  const int q = blk * 32 + (lane & 31), qc = min(q, S - 1);
+
+  u32x4_t vreg[CH];
+  auto load_v = [&](int j0) {
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      const int c = threadIdx.x + 256 * i, row = j0 + c / (D / 8);
+      vreg[i] = u32x4_t{0u, 0u, 0u, 0u};
+      if (row < rows) vreg[i] = *reinterpret_cast<const u32x4_t*>(base + 2 * H + (size_t)row * ld + c % (D / 8) * 8);
+    }
+  };
+  auto store_v = [&]() {
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      const int c = threadIdx.x + 256 * i;
+      *reinterpret_cast<u32x4_t*>(Vs + c / (D / 8) * Tile<D>::kStride + c % (D / 8) * 8) = vreg[i];
+    }
+  };
+  bf16x8_t qf[D / 16], kf[TW][D / 16];
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) qf[kk] = ld_frag(base + (size_t)qc * ld + (kk * 2 + half) * 8);
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+    if (t < n) {
+      const bf16_t* p = base + H + (size_t)min(32 * (t0 + t) + (lane & 31), S - 1) * ld + half * 8;
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk) kf[t][kk] = ld_frag(p + kk * 16);
+    }
+  load_v(0);
+  f32x16_t e[TW];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+    if (t < n) {
+      e[t] = zero16();
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk) e[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t][kk], qf[kk], e[t], 0, 0, 0);
+      scale_scores(e[t], sc, 32 * (t0 + t), half, len);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, e[t][r]);
+    }
+  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  if (half == 0) row_max[wave][lane] = mx;
+  store_v();
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 4; ++w) mx = fmaxf(mx, row_max[w][lane & 31]);
+  const float top = finite_max(mx);
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+    if (t < n)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) e[t][r] = exp_neg<FAST>(__fsub_rn(e[t][r], top));
+  // the row sum in the order of the arithmetic (see exp_neg)
+#pragma unroll 1
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
+      if constexpr (FAST) {
+        float sum = w ? x.sums[0][lane] : 0.f;
+#pragma unroll
+        for (int t = 0; t < TW; ++t)
+          if (t < n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum += e[t][r];
+        if (w < 3) {
+          x.sums[0][lane] = sum;
+        } else {
+          sum += __shfl_xor(sum, 32, 64);
+          if (half == 0) row_sum[lane] = sum;
+        }
+      } else {
+        float y[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {  // tiles of either parity (keys l and l + 64 are two tiles apart)
+          float part[16];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) part[r] = w ? x.sums[16 * o + r][lane] : 0.f;
+#pragma unroll
+          for (int t = 0; t < TW; ++t)
+            if (t < n && ((t0 + t) & 1) == o)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) part[r] += e[t][r];
+          if (w < 3) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x.sums[16 * o + r][lane] = part[r];
+          } else {
+            y[o] = sum_of_parts(part);
+          }
+        }
+        if (w == 3 && half == 0) row_sum[lane] = y[0] + y[1];
+      }
+    }
+    __syncthreads();
+  }
+  const float sum = row_sum[lane & 31], rsum = __fdiv_rn(1.0f, sum);
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+    if (t < n)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        bf16x8_t f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) f[i] = static_cast<bf16_t>(prob_code(div_by(e[t][8 * s + i], sum, rsum), sc));
+        x.p[t0 + t][s][lane] = __builtin_bit_cast(u32x4_t, f);
+      }
+  f32x16_t oacc = zero16();
+  for (int j0 = 0; j0 < len; j0 += RC) {
+    const bool more = j0 + RC < len;
+    if (more) load_v(j0 + RC);
+    __syncthreads();
+    if (wave < D / 32)
+#pragma unroll
+      for (int t = 0; t < TW; ++t)
+        if (j0 + 32 * t < len)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const int k0 = 32 * t + 16 * s + 4 * half;
+            const bf16x8_t f = __builtin_bit_cast(bf16x8_t, x.p[j0 / 32 + t][s][lane]);
+            oacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_tr<D>(Vs, 32 * wave, k0, k0 + 8, lane), f, oacc, 0, 0, 0);
+          }
+    if (more) {
+      __syncthreads();
+      store_v();
+    }
+  }
+  if (q >= S) return;
+  const size_t stat_idx = (size_t)head * S + q;
+  if (wave == 0 && half == 0) {
+    if (stat_m) { stat_m[stat_idx] = mx; stat_l[stat_idx] = sum; }
+    if (pmax_rows) pmax_rows[stat_idx] = 1.0f / sum;  // the largest exponential of a row is exp(0) = 1
+  }
+  if (wave < D / 32)
+    store_context<FAST>(oacc, aq, sc, len, ((size_t)b * S + q) * H + h * D + 32 * wave + 4 * half, ctx, ctx_codes, ctx_codes8);
 }
 
 // ------------------------------------------------------------------------------
@@ -795,14 +964,19 @@ void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& a
   constexpr std::false_type no{};
   constexpr std::integral_constant<int, 32> d32{};
   constexpr std::integral_constant<int, 64> d64{};
+  auto launch_row = [&](auto dim, auto is_fast) {
+    constexpr int D = decltype(dim)::value;
+    hipLaunchKernelGGL((attn_fwd_row_k<D, decltype(is_fast)::value>), dim3((S + 31) / 32 * nh * B), dim3(256), 0, st, (const bf16_t*)codes,
+                       (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S, B, nh, pmax_rows, stat_m, stat_l, ctx_codes8);
+  };
   const bool one = S <= kChunk, real = !aq.p.on && chain;
-  if (fast(S, d)) return one ? launch(d64, yes, yes, no) : launch(d64, no, yes, no);
+  if (fast(S, d)) return one ? launch(d64, yes, yes, no) : launch_row(d64, yes);
   if (d == 64) {
     if (real) return one ? launch(d64, yes, no, yes) : launch(d64, no, no, yes);
-    return one ? launch(d64, yes, no, no) : launch(d64, no, no, no);
+    return one ? launch(d64, yes, no, no) : launch_row(d64, no);
   }
   if (real) return one ? launch(d32, yes, no, yes) : launch(d32, no, no, yes);
-  return one ? launch(d32, yes, no, no) : launch(d32, no, no, no);
+  return one ? launch(d32, yes, no, no) : launch_row(d32, no);
 }
 
 // returns the number of partial sums written to ds_parts
