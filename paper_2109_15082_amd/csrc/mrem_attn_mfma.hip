@@ -20,10 +20,11 @@
 // dimension 32) and registers, not LDS, say how many share a compute unit.  Up to 128 keys (one
 // chunk) the scores and probabilities stay in registers between the pass that forms the row
 // statistics and the pass that uses them.  Longer rows are shared out among the wavefronts of a block of 32
-// queries (attn_fwd_row_k); the backward pass forms their tiles again for each pass.  The scores, the
-// exponentials and the quantizer are vector-ALU work, which is what bounds these kernels, and a whole row in
-// one wavefront's registers leaves one wavefront per SIMD.  Wavefronts per SIMD: forward 3 to 4; backward 2
-// to 4 (160 to 254 registers for head dimension 64).  Chunks beyond the valid keys of a sequence are skipped.
+// queries (attn_fwd_row_k, attn_bwd_q_row_k), except in the backward pass of the FAST arithmetic, whose sums
+// over a row keep their order: it forms the tiles again for each pass.  The scores, the exponentials and the
+// quantizer are vector-ALU work, which is what bounds these kernels, and a whole row in one wavefront's
+// registers leaves one wavefront per SIMD.  Wavefronts per SIMD: forward 3 to 4; backward 2 to 3 (160 to 256
+// registers for head dimension 64).  Chunks beyond the valid keys of a sequence are skipped.
 #include "mrem_common.h"
 #include "mrem_kernels.h"
 
@@ -654,9 +655,9 @@ __global__ __launch_bounds__(256, FAST ? 4 : 3) void attn_fwd_row_k(const bf16_t
 // one probability and its gradient through the quantizer
 struct ProbGrad { float p, code, dp; };
 template <bool FAST>
-__device__ __forceinline__ ProbGrad prob_grad(float score, float dacc, bool valid, float mx, float l, float rl, const FwdScales& sc, float& dsp) {
+__device__ __forceinline__ ProbGrad prob_grad(float scaled, float dacc, bool valid, float mx, float l, float rl, const FwdScales& sc, float& dsp) {
   ProbGrad g;
-  g.p = valid ? div_by(exp_neg<FAST>(__fsub_rn(__fmul_rn(score, sc.qk), mx)), l, rl) : 0.f;
+  g.p = valid ? div_by(exp_neg<FAST>(__fsub_rn(scaled, mx)), l, rl) : 0.f;
   const float dph = dacc * sc.sv;
   g.code = g.p;
   g.dp = dph;
@@ -671,7 +672,7 @@ __device__ __forceinline__ ProbGrad prob_grad(float score, float dacc, bool vali
 }
 
 // query-major part: rowdot (ONE: P^T and dA^T; kept for the key-major kernel), the step-size gradient of the probability quantizer, dQ^ = dA * K^
-template <int D, bool ONE, bool FAST>
+template <int D, bool ONE>
 __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
                                                          bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S,
                                                          int H, const float* __restrict__ stat_m, const float* __restrict__ stat_l,
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
     const f32x16_t sacc = tile_product<D>(Ks, 32 * t, lane, qf), dacc = tile_product<D>(Vs, 32 * t, lane, cf);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const ProbGrad g = prob_grad<FAST>(sacc[r], dacc[r], key_of(0, r, half) + j0 + 32 * t < len, mx, l, rl, sc, ds);
+      const ProbGrad g = prob_grad<true>(__fmul_rn(sacc[r], sc.qk), dacc[r], key_of(0, r, half) + j0 + 32 * t < len, mx, l, rl, sc, ds);
       p[r] = g.p;
       dp[r] = g.dp;
     }
@@ -721,8 +722,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
     float da[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) da[r] = p[r] * (dp[r] - rowdot);
-    if constexpr (FAST) accumulate_rows<D>(dqacc, Ks, 32 * t, lane, da);
-    else accumulate_rows_wide<D>(dqacc, Ks, 32 * t, lane, da);
+    accumulate_rows<D>(dqacc, Ks, 32 * t, lane, da);
   };
   if constexpr (ONE) {
     const int nt = (len + 31) / 32;
@@ -801,6 +801,125 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
       for (int g = 0; g < 4; ++g)
         store4(d_qkvh + orow + 32 * et + 8 * g + 4 * half, dqacc[et][4 * g] * f, dqacc[et][4 * g + 1] * f, dqacc[et][4 * g + 2] * f,
                dqacc[et][4 * g + 3] * f);
+  }
+}
+
+// The query-major part where the order of its sums is free (not FAST): 32 queries a block, the keys shared out among its
+// wavefronts as in attn_fwd_row_k, so that probabilities and their gradients are formed once and stay in registers until the
+// row's sum over them is known, instead of being formed again.  A wavefront's part of dQ^ meets the others' in LDS.
+// Inside a step, 8 x 512 tokens, 12 heads: 106 -> 64 us against 128 queries a block and two passes over the keys.
+template <int D>
+__global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
+                                                           bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S, int B,
+                                                           int nh, const float* __restrict__ stat_m, const float* __restrict__ stat_l,
+                                                           float* __restrict__ rowdot_out, float* __restrict__ ds_parts) {
+  constexpr int TW = 4;  // tiles of a wavefront (up to 512 keys)
+  // one tile of K per wavefront, then the wavefronts' parts of dQ^
+  __shared__ __attribute__((aligned(16))) union { bf16_t k[4][32 * Tile<D>::kStride]; float dq[4][D / 32][16][64]; } x;
+  __shared__ float dots[4][32], ds[4];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, waves = blockDim.x >> 6;
+  int head, blk;
+  row_of_block((S + 31) / 32, B * nh, head, blk);
+  const int b = head / nh, h = head % nh, H = nh * D, ld = 3 * H;
+  const bf16_t* base = codes + (size_t)b * S * ld + h * D;
+  const int len = seqlens ? min(seqlens[b], S) : S;
+  const FwdScales sc = load_fwd_scales(aq, D);
+  const float sk = aq.k.on ? *aq.k.s : 1.f;
+  const int nt = max(len + 31, 0) / 32, tw = (nt + waves - 1) / waves;  // tiles of the row, of a wavefront
+  const int t0 = wave * tw, n = max(min(nt - t0, tw), 0);
+  const int q = blk * 32 + (lane & 31), qc = min(q, S - 1);
+  const bool qvalid = q < S;
+  // a lane's part of rows 32 (t0 + t) .. + 31 of K or V as an operand; rows beyond the sequence repeat its last one (their
+  // probabilities are 0)
+  auto load_rows = [&](bf16x8_t (&f)[D / 16], int column, int t) {
+    const bf16_t* p = base + column + (size_t)min(32 * (t0 + t) + (lane & 31), S - 1) * ld + half * 8;
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) f[kk] = ld_frag(p + kk * 16);
+  };
+  bf16x8_t qf[D / 16], cf[D / 16], kf[D / 16], vf[D / 16];
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) {
+    qf[kk] = ld_frag(base + (size_t)qc * ld + (kk * 2 + half) * 8);
+    cf[kk] = ld_frag(dctx + ((size_t)b * S + qc) * H + h * D + (kk * 2 + half) * 8);
+  }
+  if (n > 0) {
+    load_rows(kf, H, 0);
+    load_rows(vf, 2 * H, 0);
+  }
+  const size_t stat_idx = (size_t)head * S + qc;
+  const float mx = stat_m[stat_idx], l = stat_l[stat_idx];  // row maximum and row sum of the forward
+  const float rl = __fdiv_rn(1.0f, l);
+
+  float p[TW][16], dp[TW][16], rowdot = 0.f, dsp = 0.f;
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+    if (t < n) {
+      f32x16_t sacc = zero16(), dacc = zero16();
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk) {
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], sacc, 0, 0, 0);
+        dacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kk], cf[kk], dacc, 0, 0, 0);
+      }
+      if (t + 1 < TW && t + 1 < n) {
+        load_rows(kf, H, t + 1);
+        load_rows(vf, 2 * H, t + 1);
+      }
+      scale_scores(sacc, sc, 32 * (t0 + t), half, len);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const ProbGrad g = prob_grad<false>(sacc[r], dacc[r], true, mx, l, rl, sc, dsp);
+        p[t][r] = g.p;
+        dp[t][r] = g.dp;
+        rowdot += g.dp * g.p;
+      }
+    }
+  rowdot += __shfl_xor(rowdot, 32, 64);
+  if (half == 0) dots[wave][lane] = rowdot;
+  dsp = wave_sum(qvalid ? dsp : 0.f);  // step-size gradient terms of the probability quantizer (padded query rows excluded)
+  if (lane == 0) ds[wave] = dsp;
+  if (n > 0) load_rows(kf, H, 0);
+  __syncthreads();
+  rowdot = 0.f;
+  for (int w = 0; w < waves; ++w) rowdot += dots[w][lane & 31];
+
+  f32x16_t dq[D / 32];
+#pragma unroll
+  for (int et = 0; et < D / 32; ++et) dq[et] = zero16();
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+    if (t < n) {
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk)
+        *reinterpret_cast<bf16x8_t*>(&x.k[wave][(lane & 31) * Tile<D>::kStride + (kk * 2 + half) * 8]) = kf[kk];
+      if (t + 1 < TW && t + 1 < n) load_rows(kf, H, t + 1);
+      float da[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) da[r] = p[t][r] * (dp[t][r] - rowdot);
+      accumulate_rows_wide<D>(dq, x.k[wave], 0, lane, da);
+    }
+  __syncthreads();
+#pragma unroll
+  for (int et = 0; et < D / 32; ++et)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x.dq[wave][et][r][lane] = dq[et][r];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float sum = 0.f;
+    for (int w = 0; w < waves; ++w) sum += ds[w];
+    ds_parts[(size_t)head * ((S + 31) / 32) + blk] = sum;
+  }
+  if (!qvalid) return;
+  if (wave == 0 && half == 0) rowdot_out[stat_idx] = rowdot;
+  const float f = sk / sqrtf((float)D);
+  const size_t orow = ((size_t)b * S + q) * ld + h * D;
+  for (int i = wave; i < D / 8; i += waves) {  // 8 columns, 4 of them here
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[j] = x.dq[0][i / 4][4 * (i % 4) + j][lane];
+      for (int w = 1; w < waves; ++w) v[j] += x.dq[w][i / 4][4 * (i % 4) + j][lane];
+    }
+    store4(d_qkvh + orow + 8 * i + 4 * half, v[0] * f, v[1] * f, v[2] * f, v[3] * f);
   }
 }
 
@@ -915,7 +1034,7 @@ __global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restric
           }
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const ProbGrad pg = prob_grad<FAST>(sacc[4 * g + i], dacc[4 * g + i], j < len, st[0][i], st[1][i], st[2][i], sc, unused);
+            const ProbGrad pg = prob_grad<FAST>(__fmul_rn(sacc[4 * g + i], sc.qk), dacc[4 * g + i], j < len, st[0][i], st[1][i], st[2][i], sc, unused);
             code[4 * g + i] = pg.code;
             da[4 * g + i] = pg.p * (pg.dp - st[3][i]);
           }
@@ -990,21 +1109,23 @@ int attn_bwd_mfma(const void* codes, const void* dctx, void* d_qkvh, const AttnQ
   auto launch = [&](auto dim, auto is_fast) {
     constexpr int D = decltype(dim)::value;
     constexpr bool FAST = decltype(is_fast)::value;
-    hipLaunchKernelGGL((attn_bwd_q_mfma_k<D, false, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)scratch0,
-                       (bf16_t*)nullptr, (bf16_t*)nullptr, ds_parts);
+    int parts = (int)(g.x * g.y * g.z) * waves;
+    if constexpr (FAST) {
+      hipLaunchKernelGGL((attn_bwd_q_mfma_k<D, false>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)scratch0,
+                         (bf16_t*)nullptr, (bf16_t*)nullptr, ds_parts);
+    } else {
+      parts = (S + 31) / 32 * nh * B;
+      hipLaunchKernelGGL((attn_bwd_q_row_k<D>), dim3(parts), dim3(64 * waves), 0, st, c, dc, out, aq, seqlens, S, B, nh, stat_m, stat_l,
+                         (float*)scratch0, ds_parts);
+    }
     hipLaunchKernelGGL((attn_bwd_k_mfma_k<D, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (const float*)scratch0);
+    return parts;
   };
-  if (fast(S, d) && S <= kChunk) {
-    hipLaunchKernelGGL((attn_bwd_q_mfma_k<64, true, true>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)nullptr,
-                       (bf16_t*)scratch0, (bf16_t*)scratch1, ds_parts);
-    hipLaunchKernelGGL((attn_bwd_k_one_mfma_k<64>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, (const bf16_t*)scratch0, (const bf16_t*)scratch1);
-  } else if (fast(S, d)) {
-    launch(std::integral_constant<int, 64>{}, std::true_type{});
-  } else if (d == 64) {
-    launch(std::integral_constant<int, 64>{}, std::false_type{});
-  } else {
-    launch(std::integral_constant<int, 32>{}, std::false_type{});
-  }
+  if (!fast(S, d)) return d == 64 ? launch(std::integral_constant<int, 64>{}, std::false_type{}) : launch(std::integral_constant<int, 32>{}, std::false_type{});
+  if (S > kChunk) return launch(std::integral_constant<int, 64>{}, std::true_type{});
+  hipLaunchKernelGGL((attn_bwd_q_mfma_k<64, true>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)nullptr, (bf16_t*)scratch0,
+                     (bf16_t*)scratch1, ds_parts);
+  hipLaunchKernelGGL((attn_bwd_k_one_mfma_k<64>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, (const bf16_t*)scratch0, (const bf16_t*)scratch1);
   return (int)(g.x * g.y * g.z) * waves;
 }
 
