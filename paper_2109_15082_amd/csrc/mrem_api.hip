@@ -492,6 +492,18 @@ void wgrad(const Run& r, const float* params, float* grads, int l, int i, const 
   e.c_zeroed = 1;  // the step starts by zeroing the gradients that are formed in k-slices
   gemm(c->dt, 1, 1, dy, c->wN[i], codes_in, c->wK[i], g + c->foff[kWField[i]], c->wK[i], c->wN[i], c->wK[i], r.T, e, r.st, r.prof);
 }
+// ... and all four of layer l as one list; dy and codes_in by linear layer
+std::vector<WgradJob> wgrad_jobs(const Run& r, const float* params, float* grads, int l, const size_t (&dy)[4]) {
+  const mrem_ctx* c = r.c;
+  const LayerWs& w = r.p.lw[l];
+  const size_t codes[4] = {w.xcodes, w.ctxcodes, w.x1codes, w.gcodes};
+  std::vector<WgradJob> jobs;
+  for (int i = 3; i >= 0; --i) {
+    const QArg q = make_q(c, params, l, kInQuant[i]);
+    jobs.push_back(WgradJob{r.at(dy[i]), r.at(codes[i]), grads + c->layer_stride * l + c->foff[kWField[i]], q.on ? q.s : nullptr, c->wN[i], c->wK[i]});
+  }
+  return jobs;
+}
 // input-gradient product: d(in^) = dY * W^ with the dequantized weights [N_out, K_in]
 void dgrad(const Run& r, int l, int i, const void* dy, void* out) {
   const mrem_ctx* c = r.c;
@@ -501,13 +513,14 @@ void dgrad(const Run& r, int l, int i, const void* dy, void* out) {
 
 // Zeroes what the backward pass adds into (weight gradients formed in two k-slices) or never
 // writes (the slots of the fixed quantizer offsets; the vectors of a layer are one region).
-void zero_gradient_slots(const Run& r, float* grads) {
+// `together`: those of the layers above the lowest are written by one launch a layer, whole.
+void zero_gradient_slots(const Run& r, float* grads, bool together) {
   const mrem_ctx* c = r.c;
   std::vector<FillRegion> regions;
   for (int l = 0; l < c->L; ++l) {
     float* g = grads + c->layer_stride * l;
     regions.push_back(FillRegion{g + c->foff[MREM_F_B_QKV], c->layer_stride - c->foff[MREM_F_B_QKV]});
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4 && !(together && l > 0); ++i)
       if (gemm_f32_k_slices(c->dt, c->wN[i], c->wK[i], r.T) > 1)
         regions.push_back(FillRegion{g + c->foff[kWField[i]], (int64_t)c->wN[i] * c->wK[i]});
   }
@@ -528,6 +541,7 @@ struct Update {
   const hipEvent_t* ev_done;   // four per layer
   hipEvent_t ev_join;
   bool by_layer;               // one handover to `side` a layer instead of one a product
+  int wgrad_tile;              // then, above the lowest layer: the tile that serves a layer's weight gradients in one launch (0: none)
 };
 void update_matrices(const Run& r, const Update& u, float* grads, int l, hipStream_t st);
 
@@ -554,10 +568,11 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
     // Handed over one by one, each output gradient has one buffer, which this stream overwrites in the layer below only
     // when the product has read it.  Handed over by the layer, two layers alternate between two sets of buffers (the
     // second is the full-precision pass's scratch, which nobody needs any more).
-    const bool by_layer = up.side && up.by_layer, second = by_layer && (l & 1);
+    // The lowest layer's products, with nothing to run beside them afterwards, are not held back for one launch.
+    const bool sets = up.side && up.by_layer, second = sets && (l & 1), by_layer = sets && (l > 0 || !up.wgrad_tile);
     const size_t dr2 = second ? r.p.t_y : r.p.dr2, dr1 = second ? r.p.t_o : r.p.dr1, du = second ? r.p.t_g : r.p.du, dqkv = second ? r.p.t_qkv : r.p.dqkv;
-    const size_t dr1_above = by_layer && !second ? r.p.t_o : r.p.dr1;
-    if (by_layer && l + 2 < L) (void)hipStreamWaitEvent(r.st, up.ev_done[4 * (l + 2)], 0);
+    const size_t dr1_above = sets && !second ? r.p.t_o : r.p.dr1;
+    if (sets && l + 2 < L) (void)hipStreamWaitEvent(r.st, up.ev_done[4 * (l + 2)], 0);
     Run rs = r;
     if (up.side) rs.st = up.side;
     auto issue_wgrad = [&](int i, const void* dy, const void* codes) {
@@ -570,13 +585,19 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
       if (up.side) (void)hipEventRecord(up.ev_done[4 * l + i], up.side);
     };
     auto before_overwrite = [&](int i) {
-      if (up.side && !by_layer && l < L - 1) (void)hipStreamWaitEvent(r.st, up.ev_done[4 * (l + 1) + i], 0);
+      if (up.side && !sets && l < L - 1) (void)hipStreamWaitEvent(r.st, up.ev_done[4 * (l + 1) + i], 0);
     };
     // all that the side stream does for this layer, once everything it reads is enqueued on this one
     auto hand_over = [&]() {
       (void)hipEventRecord(up.ev_layer[l], r.st);
       (void)hipStreamWaitEvent(up.side, up.ev_layer[l], 0);
       if (!by_layer) return;
+      if (up.wgrad_tile) {
+        const std::vector<WgradJob> jobs = wgrad_jobs(r, params, grads, l, {dqkv, dr1, du, dr2});
+        gemm_wgrads(jobs.data(), (int)jobs.size(), r.T, up.wgrad_tile, rs.st);
+        if (l >= 2) (void)hipEventRecord(up.ev_done[4 * l], up.side);
+        return;
+      }
       wgrad(rs, params, grads, l, 3, r.at(dr2), r.at(w.gcodes));
       wgrad(rs, params, grads, l, 2, r.at(du), r.at(w.x1codes));
       wgrad(rs, params, grads, l, 1, r.at(dr1), r.at(w.ctxcodes));
@@ -1012,14 +1033,20 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
   // with a handover for every product a layer needs nine of them, so a step of few tokens is bound by the host: 3 layers of
   // 256 over 66 tokens 718 us, 532 with one handover a layer, 551 on one stream; 3 of 512 over 427: 735, 664, 786; 6 of 1024
   // over 495: 2512, 2396, 2949.  From about 2^19 activations a layer on the device is the limit, and products that start
-  // later cost up to 1.5% (2 of 768 over 992 tokens: 670, 681, 762; 6 of 1024 over 4096: 4305, 4350).  With one layer there is
-  // nothing to overlap the update with (1 of 1024 over 400: 435, 450, 469), and the shortest steps are quickest on one stream
-  // (1 of 64 over 128, fp32: 290, 235, 198; 1 of 512 over 200: 282, 262, 255; 2 of 128 over 80: 494, 405, 332).
+  // later cost up to 1.5% (2 of 768 over 992 tokens: 670, 681, 762; 6 of 1024 over 4096: 4305, 4350) unless the weight
+  // gradients of a layer are one launch (wgrads_tile: 4261).  With one layer there is nothing to overlap the update with (1
+  // of 1024 over 400: 435, 450, 469), and the shortest steps are quickest on one stream (1 of 64 over 128, fp32: 290, 235,
+  // 198; 1 of 512 over 200: 282, 262, 255; 2 of 128 over 80: 494, 405, 332).
   const int64_t acts = (int64_t)r.T * ctx->H;
   const bool fork = !ctx->prof.on &&  // per-launch timing wants every product alone on the device
                     acts * ctx->L * ctx->L > (1 << 17) &&
                     dev == ctx->side_device;  // (a forward pass may have created the stream on another device)
-  const bool by_layer = ctx->L > 1 && acts <= (1 << 19);
+  const bool few = ctx->L > 1 && acts <= (1 << 19);
+  int wgrad_tile = 0;
+  if (fork && ctx->L > 1 && !few) {
+    const std::vector<WgradJob> jobs = wgrad_jobs(r, params, grads, 0, {r.p.dqkv, r.p.dr1, r.p.du, r.p.dr2});
+    wgrad_tile = wgrads_tile(ctx->dt, jobs.data(), (int)jobs.size(), r.T);
+  }
   // Eq. 4: with lambda > 0 the quantized module reads lambda * x_fp + (1 - lambda) * x_q, formed by its first kernel
   const bool mix = lambda > 0.f && x_fp != x_q;
   const void* x_in = mix ? r.at(r.p.xmix) : x_q;
@@ -1030,12 +1057,12 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
     rt.st = ctx->side;
     (void)hipEventRecord(ctx->ev_fork, r.st);
     (void)hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0);
-    zero_gradient_slots(r, grads);
+    zero_gradient_slots(r, grads, wgrad_tile > 0);
     // Only the first layer's weights are prepared on this stream; those of the layers above are prepared on the side
     // stream ahead of the teacher's pass (which has slack before the loss needs it), so the quantized pass starts after
     // one layer's worth of that work instead of the whole module's.
-    prepare_weights(r, params, true, 0, by_layer ? -1 : 1);
-    if (ctx->L > 1 && !by_layer) {
+    prepare_weights(r, params, true, 0, few ? -1 : 1);
+    if (ctx->L > 1 && !few) {
       prepare_weights(rt, params, true, 1, ctx->L);
       (void)hipEventRecord(ctx->ev_codes, ctx->side);
     }
@@ -1043,19 +1070,19 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
     // start also when the caller's queue was empty
     for (int l = 0; l < ctx->L; ++l) {
       teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, nullptr, l, l + 1);
-      if (l == 1 && !by_layer) (void)hipStreamWaitEvent(r.st, ctx->ev_codes, 0);
+      if (l == 1 && !few) (void)hipStreamWaitEvent(r.st, ctx->ev_codes, 0);
       student_forward(r, params, x_in, per_layer_q, l, l + 1, mix_fp, x_q, lambda);
     }
     (void)hipEventRecord(ctx->ev_join, ctx->side);
   } else {
     teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp, nullptr);
-    zero_gradient_slots(r, grads);
+    zero_gradient_slots(r, grads, false);
     prepare_weights(r, params, true);
     student_forward(r, params, x_in, per_layer_q, 0, -1, mix_fp, x_q, lambda);
   }
   if (fork) (void)hipStreamWaitEvent(r.st, ctx->ev_join, 0);
   const Update up{params, adam_m, adam_v, adam_arg(ctx, step_index, lr), grads_out != nullptr, fork ? ctx->side : nullptr,
-                  ctx->ev_layer.data(), ctx->ev_ready.data(), ctx->ev_done.data(), ctx->ev_join, by_layer};
+                  ctx->ev_layer.data(), ctx->ev_ready.data(), ctx->ev_done.data(), ctx->ev_join, few || wgrad_tile > 0, wgrad_tile};
   student_backward(r, params, x_in, per_layer_fp, per_layer_q, grads, loss_out, up);
   update_vectors(r, up, grads);
   return finish(ctx, "mrem_module_step");

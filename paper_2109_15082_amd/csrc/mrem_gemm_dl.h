@@ -189,16 +189,19 @@ __device__ __forceinline__ void wait_frags(typename OpA::frag_t (&a)[TA], typena
 // Tile order: consecutive block ids land on different XCDs (8 of them, each with its own L2), so each XCD
 // gets a contiguous range of tiles, walked in groups of 8 tile rows so that concurrently running blocks
 // share operand panels in that L2.
-__device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int nblocks = tiles_m * tiles_n;
-  int pid = blockIdx.x;
-  if ((nblocks & 7) == 0) pid = (pid & 7) * (nblocks >> 3) + (pid >> 3);
+__device__ __forceinline__ void tile_of_index(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
   constexpr int GROUP = 8;
   const int group_sz = GROUP * tiles_n;
   const int first_m = pid / group_sz * GROUP;
   const int gm = (tiles_m - first_m) < GROUP ? (tiles_m - first_m) : GROUP;
   tm = first_m + (pid % group_sz) % gm;
   tn = (pid % group_sz) / gm;
+}
+__device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm, int& tn) {
+  const int nblocks = tiles_m * tiles_n;
+  int pid = blockIdx.x;
+  if ((nblocks & 7) == 0) pid = (pid & 7) * (nblocks >> 3) + (pid >> 3);
+  tile_of_index(pid, tiles_m, tiles_n, tm, tn);
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool AT, bool BT, int STAGES, int RB, class TO, bool I8, int MINB, int KG, bool EDGE>

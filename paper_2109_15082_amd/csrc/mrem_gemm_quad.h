@@ -31,9 +31,10 @@ __device__ __forceinline__ void buffer_to_lds(const unsigned char* p, const unsi
 #endif
 }
 
+// tile (tm, tn) of a product
 template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE>
-__global__ __launch_bounds__(512, 1) void gemm_quad_k(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
-                                                      TO* __restrict__ C, int ldc, int M, int N, int K, Epilogue e, int tiles_m, int tiles_n) {
+__device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb, TO* __restrict__ C, int ldc, int M,
+                                          int N, int K, const Epilogue& e, int tm, int tn) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_quad[];
   constexpr int BN = 256, HA = BM / 2, HN = BN / 2, RB = 128, BK = RB / 2, KK = RB / 32;
   constexpr int WAVES_M = HA / 32, WAVES_N = 8 / WAVES_M, WN = HN / WAVES_N, NT = WN / 32;
@@ -43,8 +44,6 @@ __global__ __launch_bounds__(512, 1) void gemm_quad_k(const bf16_t* __restrict__
   constexpr int LA = OpA::LOADS / 8, LB = OpB::LOADS / 8;                            // direct loads of a half per wavefront
   static_assert(LA >= 1 && LB >= 1 && KK == 4, "whole loads of a half per wavefront; four k-substeps a stage");
 
-  int tm, tn;
-  tile_of_block(tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -247,23 +246,77 @@ __global__ __launch_bounds__(512, 1) void gemm_quad_k(const bf16_t* __restrict__
   else choose(no);
 }
 
+template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE>
+__global__ __launch_bounds__(512, 1) void gemm_quad_k(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
+                                                      TO* __restrict__ C, int ldc, int M, int N, int K, Epilogue e, int tiles_m, int tiles_n) {
+  int tm, tn;
+  tile_of_block(tiles_m, tiles_n, tm, tn);
+  quad_tile<BM, AT, BT, TO, I8, EDGE>(A, lda, B, ldb, C, ldc, M, N, K, e, tm, tn);
+}
+
+// The weight gradients of a layer in one launch, at most one tile a compute unit.  Products of
+// their own took 64 x 64 or 128 x 128 tiles or slices of the contraction to fill the chip, with up to four times the operand
+// bytes per flop; the step has another stream's kernels for the units that one round of large tiles leaves over.
+// Steps, us: six layers of 1024 over 32 x 128 tokens
+// 4480 -> 4261, 16 x 384 6490 -> 6133, three of 768 over 32 x 128 1720 -> 1652, six of 320 over 4096 1774 -> 1636.
+struct QuadJob {
+  WgradJob j;
+  int tiles_m, tiles_n, first;  // its tiles, and how many the jobs before it have
+};
+struct QuadJobs { QuadJob job[kMaxWgradJobs]; };
+template <int BM, bool EDGE>
+__global__ __launch_bounds__(512, 1) void gemm_quad_wgrads_k(QuadJobs jobs, int njobs, int K) {
+  // each XCD takes a contiguous range of all tiles (see tile_of_block); what eight do not divide goes in order
+  int pid = blockIdx.x;
+  const int each = (int)gridDim.x >> 3;
+  if (pid < 8 * each) pid = (pid & 7) * each + (pid >> 3);
+  int i = 0;
+  while (i + 1 < njobs && pid >= jobs.job[i + 1].first) ++i;
+  const QuadJob& q = jobs.job[i];
+  int tm, tn;
+  tile_of_index(pid - q.first, q.tiles_m, q.tiles_n, tm, tn);
+  Epilogue e;
+  e.alpha = q.j.alpha;
+  quad_tile<BM, true, true, float, false, EDGE>((const bf16_t*)q.j.dy, q.j.M, (const bf16_t*)q.j.x, q.j.N, q.j.dw, q.j.N, q.j.M, q.j.N, K, e, tm, tn);
+}
+
 // whole stages, an even number of them
 static bool quad_ok(int K) { return K % (2 * kBK) == 0; }
+
+// LDS of a kernel of BM x 256 tiles, beyond what is allowed without asking
+template <int BM>
+static size_t quad_lds(const void* kernel, std::atomic<int>& configured_dev) {
+  constexpr size_t lds = 2 * (BM + 256) * 128;
+  int dev = -1;
+  (void)hipGetDevice(&dev);
+  if (dev != configured_dev.load()) {
+    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    configured_dev.store(dev);
+  }
+  return lds;
+}
 
 template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE>
 static void launch_quad(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e, hipStream_t st) {
   constexpr int BN = 256;
-  constexpr size_t lds = 2 * (BM + BN) * 128;
   static std::atomic<int> configured_dev{-1};
-  int dev = -1;
-  (void)hipGetDevice(&dev);
-  if (dev != configured_dev.load()) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_quad_k<BM, AT, BT, TO, I8, EDGE>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    configured_dev.store(dev);
-  }
+  const size_t lds = quad_lds<BM>(reinterpret_cast<const void*>(&gemm_quad_k<BM, AT, BT, TO, I8, EDGE>), configured_dev);
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   MREM_LAUNCH((gemm_quad_k<BM, AT, BT, TO, I8, EDGE>), dim3(tiles_m * tiles_n), dim3(512), lds, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C,
               ldc, M, N, K, e, tiles_m, tiles_n);
+}
+
+template <int BM, bool EDGE>
+static void launch_quad_wgrads(const WgradJob* jobs, int njobs, int K, hipStream_t st) {
+  static std::atomic<int> configured_dev{-1};
+  const size_t lds = quad_lds<BM>(reinterpret_cast<const void*>(&gemm_quad_wgrads_k<BM, EDGE>), configured_dev);
+  QuadJobs q{};
+  int tiles = 0;
+  for (int i = 0; i < njobs; ++i) {
+    q.job[i] = QuadJob{jobs[i], (jobs[i].M + BM - 1) / BM, (jobs[i].N + 255) / 256, tiles};
+    tiles += q.job[i].tiles_m * q.job[i].tiles_n;
+  }
+  hipLaunchKernelGGL((gemm_quad_wgrads_k<BM, EDGE>), dim3(tiles), dim3(512), lds, st, q, njobs, K);
 }
 
 }  // namespace mrem

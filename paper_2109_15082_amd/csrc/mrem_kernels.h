@@ -91,6 +91,17 @@ void gemm(int dt, int a_t, int b_t, const void* A, int lda, const void* B, int l
 bool gemm_i8_ok(const void* A, int lda, const void* B, int ldb, int M, int N, int K);
 void gemm_i8(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e, hipStream_t st,
              GemmProfile* prof = nullptr);
+// Weight gradients of one layer in one launch: dw[M,N] (fp32) = alpha * dy[K,M]^T * x[K,N], bf16 operands, K tokens.
+constexpr int kMaxWgradJobs = 4;
+struct WgradJob {
+  const void *dy, *x;
+  float* dw;
+  const float* alpha;  // device scalar, or null
+  int M, N;
+};
+// rows of the tile that serves these shapes in one launch, 0: they are products of their own
+int wgrads_tile(int dt, const WgradJob* jobs, int njobs, int K);
+void gemm_wgrads(const WgradJob* jobs, int njobs, int K, int tile, hipStream_t st);
 // C[M,N] = A[M,K] * B[N,K]^T  (both operands contiguous along K)
 void gemm_nt(int dt, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K,
              const Epilogue& e, hipStream_t st, GemmProfile* prof = nullptr);
