@@ -86,13 +86,22 @@ __device__ __forceinline__ FwdScales load_fwd_scales(const AttnQ& a, int d) {
 
 // scores of 32 keys from accumulators, first key `key0`; -inf beyond the valid keys (a tile without such keys skips the tests,
 // two of the six instructions a score costs a forward pass ahead of its exponential)
-__device__ __forceinline__ void scale_scores(f32x16_t& a, const FwdScales& sc, int key0, int half, int len) {
-#pragma unroll
-  for (int r = 0; r < 16; ++r) a[r] = __fmul_rn(a[r], sc.qk);
+__device__ __forceinline__ void mask_scores(f32x16_t& a, int key0, int half, int len) {
   if (key0 + 32 <= len) return;
 #pragma unroll
   for (int r = 0; r < 16; ++r)
     if (key_of(0, r, half) + key0 >= len) a[r] = -INFINITY;
+}
+__device__ __forceinline__ void scale_scores(f32x16_t& a, const FwdScales& sc, int key0, int half, int len) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) a[r] = __fmul_rn(a[r], sc.qk);
+  mask_scores(a, key0, half, len);
+}
+// the same plus `c`, in one rounding (the backward pass of the FAST arithmetic takes a score less the row's maximum so)
+__device__ __forceinline__ void scale_scores(f32x16_t& a, const FwdScales& sc, int key0, int half, int len, float c) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) a[r] = __fmaf_rn(a[r], sc.qk, c);
+  mask_scores(a, key0, half, len);
 }
 // what the exponentials of a row are taken against: with a row of -inf only, 0, so that each of them is 0 and not NaN
 __device__ __forceinline__ float finite_max(float mx) { return mx == -INFINITY ? 0.f : mx; }
@@ -650,14 +659,16 @@ __global__ __launch_bounds__(256, FAST ? 4 : 3) void attn_fwd_row_k(const bf16_t
 // key-major one, which is then a pure product (512 heads of 128 tokens, inside a step: 17 us against 40 us for forming
 // them again); beyond that the 4 bytes per query-key pair each way cost more than the arithmetic, and the key-major
 // kernel forms them itself (256 heads of 384 tokens, both kernels: 164 us against 215 us).
+// Tiles without masked keys skip the mask's tests (256 heads of 384 tokens, query-major: 89 -> 73 us inside a step), and the
+// tiles of P^T and dA^T are transposed in LDS on their way out, 16 bytes a lane instead of 2 (512 heads of 128: 37 -> 34 us).
 // ------------------------------------------------------------------------------
 
-// one probability and its gradient through the quantizer
+// one probability (x: its score less the row's maximum) and its gradient through the quantizer
 struct ProbGrad { float p, code, dp; };
 template <bool FAST>
-__device__ __forceinline__ ProbGrad prob_grad(float scaled, float dacc, bool valid, float mx, float l, float rl, const FwdScales& sc, float& dsp) {
+__device__ __forceinline__ ProbGrad prob_grad(float x, float dacc, bool valid, float l, float rl, const FwdScales& sc, float& dsp) {
   ProbGrad g;
-  g.p = valid ? div_by(exp_neg<FAST>(__fsub_rn(scaled, mx)), l, rl) : 0.f;
+  g.p = valid ? div_by(exp_neg<FAST>(x), l, rl) : 0.f;
   const float dph = dacc * sc.sv;
   g.code = g.p;
   g.dp = dph;
@@ -680,6 +691,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
                                                          bf16_t* __restrict__ dat_out, float* __restrict__ ds_parts) {
   __shared__ __attribute__((aligned(16))) bf16_t Ks[kChunk * Tile<D>::kStride];
   __shared__ __attribute__((aligned(16))) bf16_t Vs[kChunk * Tile<D>::kStride];
+  __shared__ __attribute__((aligned(16))) bf16_t Ts[ONE ? 4 : 1][2][ONE ? 32 * Tile<32>::kStride : 8];  // ONE: a tile of P and dA per wavefront
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, waves = blockDim.x >> 6;
   const int h = blockIdx.y, b = blockIdx.z, nh = gridDim.y;
   const int ld = 3 * H;
@@ -710,10 +722,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
   for (int et = 0; et < D / 32; ++et) dqacc[et] = zero16();
   // P and dP of one tile of 32 keys
   auto probs = [&](int t, int j0, float* p, float* dp, float& ds) {
-    const f32x16_t sacc = tile_product<D>(Ks, 32 * t, lane, qf), dacc = tile_product<D>(Vs, 32 * t, lane, cf);
+    f32x16_t sacc = tile_product<D>(Ks, 32 * t, lane, qf);
+    const f32x16_t dacc = tile_product<D>(Vs, 32 * t, lane, cf);
+    scale_scores(sacc, sc, j0 + 32 * t, half, len, -mx);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const ProbGrad g = prob_grad<true>(__fmul_rn(sacc[r], sc.qk), dacc[r], key_of(0, r, half) + j0 + 32 * t < len, mx, l, rl, sc, ds);
+      const ProbGrad g = prob_grad<true>(sacc[r], dacc[r], true, l, rl, sc, ds);
       p[r] = g.p;
       dp[r] = g.dp;
     }
@@ -747,13 +761,27 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
 #pragma unroll
     for (int t = 0; t < kChunk / 32; ++t)
       if (t < nt) {
-        consume(t, p[t], dp[t]);
+        float da[16], code[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
+          da[r] = qvalid ? p[t][r] * (dp[t][r] - rowdot) : 0.f;
           const float c = sc.p_on ? rintf(fminf(div_by(p[t][r], sc.sp, sc.rsp), sc.p_qp)) : p[t][r];
-          const size_t o = tbase + (size_t)key_of(t, r, half) * s_pad + q;
-          pt_out[o] = static_cast<bf16_t>(qvalid ? c : 0.f);
-          dat_out[o] = static_cast<bf16_t>(qvalid ? p[t][r] * (dp[t][r] - rowdot) : 0.f);
+          code[r] = qvalid ? c : 0.f;
+        }
+        accumulate_rows<D>(dqacc, Ks, 32 * t, lane, da);
+        // transposed on the way: a lane holds a query, a row in memory is a key
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int o = (lane & 31) * Tile<32>::kStride + 8 * g + 4 * half;
+          store4(Ts[wave][0] + o, code[4 * g], code[4 * g + 1], code[4 * g + 2], code[4 * g + 3]);
+          store4(Ts[wave][1] + o, da[4 * g], da[4 * g + 1], da[4 * g + 2], da[4 * g + 3]);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const int k0 = 16 * s + 8 * half;
+          const size_t o = tbase + (size_t)(32 * t + (lane & 31)) * s_pad + q0 + k0;
+          *reinterpret_cast<bf16x8_t*>(pt_out + o) = ld_frag_tr<32>(Ts[wave][0], 0, k0, k0 + 4, lane);
+          *reinterpret_cast<bf16x8_t*>(dat_out + o) = ld_frag_tr<32>(Ts[wave][1], 0, k0, k0 + 4, lane);
         }
       }
   } else {
@@ -867,7 +895,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restr
       scale_scores(sacc, sc, 32 * (t0 + t), half, len);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const ProbGrad g = prob_grad<false>(sacc[r], dacc[r], true, mx, l, rl, sc, dsp);
+        const ProbGrad g = prob_grad<false>(__fsub_rn(sacc[r], mx), dacc[r], true, l, rl, sc, dsp);
         p[t][r] = g.p;
         dp[t][r] = g.dp;
         rowdot += g.dp * g.p;
@@ -1034,7 +1062,7 @@ __global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restric
           }
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const ProbGrad pg = prob_grad<FAST>(__fmul_rn(sacc[4 * g + i], sc.qk), dacc[4 * g + i], j < len, st[0][i], st[1][i], st[2][i], sc, unused);
+            const ProbGrad pg = prob_grad<FAST>(__fsub_rn(__fmul_rn(sacc[4 * g + i], sc.qk), st[0][i]), dacc[4 * g + i], j < len, st[1][i], st[2][i], sc, unused);
             code[4 * g + i] = pg.code;
             da[4 * g + i] = pg.p * (pg.dp - st[3][i]);
           }
