@@ -21,9 +21,10 @@
  *    each layer's weight matrices on a side stream that the context owns (default
  *    priority, created on the first call that uses it), forked from the caller's
  *    stream by events and joined to it before the loss and before the call's last
- *    kernels; mrem_module_forward does the same with the full-precision pass, unless
- *    the caller's stream is being captured.  To the caller a call behaves like work
- *    on its own stream.  Calls return without synchronising.
+ *    kernels; mrem_module_forward does the same with the full-precision pass and a
+ *    stream of its own, except in the smallest calls and while the caller's stream is
+ *    being captured.  To the caller a call behaves like work on its own stream.
+ *    Calls return without synchronising.
  *  - Arguments are validated on the host before anything is enqueued; a call that
  *    returns an error has had no effect on device memory.
  *  - Return value: MREM_OK or a negative mrem_status.  mrem_last_error() gives a

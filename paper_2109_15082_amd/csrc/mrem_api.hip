@@ -34,11 +34,13 @@ struct mrem_ctx {
   std::vector<hipEvent_t> ev_ready;  // [4 * l + i]: the output gradient of linear layer i of layer l is written
   std::vector<hipEvent_t> ev_done;   // [4 * l + i]: its weight-gradient product has read it
   int side_device = -1;
-  int step_device = -1;  // the device of the first step
-  // Forward passes on one context may come from several threads (each with its own workspace and stream) and share the side
-  // stream: its creation, and each recording of the two events below with the wait for it, happen under the lock.
-  std::shared_ptr<std::mutex> side_lock = std::make_shared<std::mutex>();
+  // The same for the full-precision pass of mrem_module_forward, which has a stream of its own: a step's side stream may be
+  // part of a capture.  Forward passes on one context may come from several threads (each with its own workspace and stream)
+  // and share it: its creation, and each recording of an event with the wait for it, happen under the lock.
+  hipStream_t pass_side = nullptr;
   hipEvent_t ev_pass_fork = nullptr, ev_pass_join = nullptr;
+  int pass_device = -1;
+  std::shared_ptr<std::mutex> pass_lock = std::make_shared<std::mutex>();
   GemmProfile prof;                // per-launch timing of the matrix products (measurement aid)
   int32_t* nonfinite_flag = nullptr;  // device, caller-owned, optional
 };
@@ -89,7 +91,7 @@ extern "C" mrem_status mrem_create(const mrem_config* cfg, mrem_ctx** out) {
 // a creation that failed half way).
 static void release_side(mrem_ctx* ctx) {
   if (ctx->side) (void)hipStreamSynchronize(ctx->side);
-  for (hipEvent_t* e : {&ctx->ev_fork, &ctx->ev_join, &ctx->ev_codes, &ctx->ev_pass_fork, &ctx->ev_pass_join}) {
+  for (hipEvent_t* e : {&ctx->ev_fork, &ctx->ev_join, &ctx->ev_codes}) {
     if (*e) (void)hipEventDestroy(*e);
     *e = nullptr;
   }
@@ -107,9 +109,7 @@ static bool create_side(mrem_ctx* ctx, int dev) {
   bool ok = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) == hipSuccess &&
             hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming) == hipSuccess &&
             hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&ctx->ev_codes, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&ctx->ev_pass_fork, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&ctx->ev_pass_join, hipEventDisableTiming) == hipSuccess;
+            hipEventCreateWithFlags(&ctx->ev_codes, hipEventDisableTiming) == hipSuccess;
   ctx->ev_layer.assign((size_t)ctx->L, nullptr);
   ctx->ev_ready.assign((size_t)ctx->L * 4, nullptr);
   ctx->ev_done.assign((size_t)ctx->L * 4, nullptr);
@@ -124,9 +124,32 @@ static bool create_side(mrem_ctx* ctx, int dev) {
   return true;
 }
 
+static void release_pass_side(mrem_ctx* ctx) {
+  if (ctx->pass_side) (void)hipStreamSynchronize(ctx->pass_side);
+  for (hipEvent_t* e : {&ctx->ev_pass_fork, &ctx->ev_pass_join}) {
+    if (*e) (void)hipEventDestroy(*e);
+    *e = nullptr;
+  }
+  if (ctx->pass_side) (void)hipStreamDestroy(ctx->pass_side);
+  ctx->pass_side = nullptr;
+  ctx->pass_device = -1;
+}
+static bool create_pass_side(mrem_ctx* ctx, int dev) {
+  if (hipStreamCreateWithFlags(&ctx->pass_side, hipStreamNonBlocking) != hipSuccess ||
+      hipEventCreateWithFlags(&ctx->ev_pass_fork, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&ctx->ev_pass_join, hipEventDisableTiming) != hipSuccess) {
+    release_pass_side(ctx);
+    (void)hipGetLastError();  // the passes run one after the other
+    return false;
+  }
+  ctx->pass_device = dev;
+  return true;
+}
+
 extern "C" void mrem_destroy(mrem_ctx* ctx) {
   if (!ctx) return;
   release_side(ctx);
+  release_pass_side(ctx);
   delete ctx;
 }
 extern "C" int64_t mrem_param_count(const mrem_ctx* ctx) { return ctx ? ctx->layer_stride * ctx->L : -1; }
@@ -906,36 +929,41 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
     REQUIRE_PTR(x_q, who);
     if (!aligned16(per_layer_q)) return fail(ctx, MREM_EINVAL, std::string(who) + ": per_layer_q misaligned");
   }
-  // The passes share nothing but their inputs: the full-precision one runs on the side stream, forked from the caller's and
+  // The passes share nothing but their inputs: the full-precision one runs on a side stream, forked from the caller's and
   // joined to it (both passes of a 23-token sentence through three layers of 768: 373 us one after the other, 264 now; six
   // layers of 1024 over 4096 tokens: 1840 and 1660).  Not while the caller's stream is being captured: the side stream may
-  // serve another thread meanwhile.
+  // serve another thread meanwhile.  Nor for the smallest calls, where forking and joining cost the host 35 us and the device
+  // has little to do beside it (us, forked and not: one layer of 64 over 8 tokens 109 and 72, of 256 over 400 107 and 91, of
+  // 768 over 23 105 and 118, over 400 133 and 172; two of 128 over 256 150 and 140, of 256 over 400 147 and 178; three of 64
+  // over 8 205 and 195, of 128 over 256 200 and 206; many tokens: one of 64 over 4096 93 and 78, of 256 over 2048 95 and 92,
+  // two of 128 over 1024 141 and 148).
   hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
-  bool fork = two_streams && per_layer_fp && per_layer_q && !ctx->prof.on;
+  bool fork = two_streams && per_layer_fp && per_layer_q && !ctx->prof.on &&
+              (ctx->L * ctx->H >= 384 || (int64_t)ctx->L * ctx->H * r.T >= (ctx->L > 1 ? 1 << 18 : 1 << 20));
   if (fork && (hipStreamIsCapturing(r.st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
     (void)hipGetLastError();
     fork = false;
   }
   if (fork) {
-    const std::lock_guard<std::mutex> lock(*ctx->side_lock);
+    const std::lock_guard<std::mutex> lock(*ctx->pass_lock);
     int dev = -1;
-    fork = hipGetDevice(&dev) == hipSuccess && (ctx->side || create_side(ctx, dev)) && dev == ctx->side_device;
+    fork = hipGetDevice(&dev) == hipSuccess && (ctx->pass_side || create_pass_side(ctx, dev)) && dev == ctx->pass_device;
     if (fork) {
       (void)hipEventRecord(ctx->ev_pass_fork, r.st);
-      (void)hipStreamWaitEvent(ctx->side, ctx->ev_pass_fork, 0);
+      (void)hipStreamWaitEvent(ctx->pass_side, ctx->ev_pass_fork, 0);
     }
   }
   if (fork) {
     Run rt = r;
-    rt.st = ctx->side;
+    rt.st = ctx->pass_side;
     prepare_weights(r, params, false);
     // layer by layer in turn, so that both streams have work from the start
     for (int l = 0; l < ctx->L; ++l) {
       teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, nullptr, l, l + 1);
       student_forward(r, params, x_q, per_layer_q, l, l + 1);
     }
-    const std::lock_guard<std::mutex> lock(*ctx->side_lock);
-    (void)hipEventRecord(ctx->ev_pass_join, ctx->side);
+    const std::lock_guard<std::mutex> lock(*ctx->pass_lock);
+    (void)hipEventRecord(ctx->ev_pass_join, ctx->pass_side);
     (void)hipStreamWaitEvent(r.st, ctx->ev_pass_join, 0);
     return finish(ctx, who);
   }
@@ -1022,13 +1050,9 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
   // the loss: kernels of the two passes fill each other's tails.
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return fail(ctx, MREM_EHIP, "mrem_module_step: no current device");
-  {
-    const std::lock_guard<std::mutex> lock(*ctx->side_lock);
-    if (!ctx->side && !create_side(ctx, dev))
-      return fail(ctx, MREM_EHIP, "mrem_module_step: cannot create the side stream and its events");
-  }
-  if (ctx->step_device < 0) ctx->step_device = dev;
-  if (dev != ctx->step_device) return fail(ctx, MREM_EINVAL, "mrem_module_step: the context was first used on another device");
+  if (!ctx->side && !create_side(ctx, dev))
+    return fail(ctx, MREM_EHIP, "mrem_module_step: cannot create the side stream and its events");
+  if (dev != ctx->side_device) return fail(ctx, MREM_EINVAL, "mrem_module_step: the context was first used on another device");
   // What the second stream is worth depends on the size.  A wait for an event takes the host 11 us, five launches' time, and
   // with a handover for every product a layer needs nine of them, so a step of few tokens is bound by the host: 3 layers of
   // 256 over 66 tokens 718 us, 532 with one handover a layer, 551 on one stream; 3 of 512 over 427: 735, 664, 786; 6 of 1024
@@ -1039,8 +1063,7 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
   // 198; 1 of 512 over 200: 282, 262, 255; 2 of 128 over 80: 494, 405, 332).
   const int64_t acts = (int64_t)r.T * ctx->H;
   const bool fork = !ctx->prof.on &&  // per-launch timing wants every product alone on the device
-                    acts * ctx->L * ctx->L > (1 << 17) &&
-                    dev == ctx->side_device;  // (a forward pass may have created the stream on another device)
+                    acts * ctx->L * ctx->L > (1 << 17);
   const bool few = ctx->L > 1 && acts <= (1 << 19);
   int wgrad_tile = 0;
   if (fork && ctx->L > 1 && !few) {

@@ -1,0 +1,41 @@
+"""Both forward passes of a call, side by side or one after the other: one result, whatever the size and the stream."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+# around the sizes from which on the full-precision pass gets a stream of its own (layers * width 384; layers * width * tokens
+# 2^20 for one layer, 2^18 for more)
+@pytest.mark.parametrize("layers,hidden,batch,seq", [(1, 64, 1, 8), (3, 128, 1, 8), (1, 320, 2, 23), (1, 384, 2, 23), (1, 256, 32, 128), (2, 128, 8, 128)])
+def test_both_passes_equal_single_passes(layers, hidden, batch, seq):
+    import torch
+    from paper_2109_15082_amd import binding as B
+    rng = np.random.default_rng(hidden)
+    mod = B.MremModule(layers, hidden, hidden // 64, 4 * hidden, batch, seq)
+    mod.teacher.copy_(torch.from_numpy(rng.standard_normal(mod.teacher.numel(), dtype=np.float32) * np.float32(0.02)))
+    B.mrem_teacher_prepare(mod.ctx, mod.teacher, mod.teacher_cache)
+    mod.params.copy_(mod.teacher)
+    mod.init_steps()
+    x = torch.from_numpy(rng.standard_normal((batch, seq, hidden), dtype=np.float32)).cuda().bfloat16()
+    mod.calibrate(x)
+    f_fp, f_q = (f.clone() for f in mod.forward(x, x))
+    B.mrem_profile_gemm_begin(mod.ctx)  # times each product, on one stream
+    g_fp, g_q = (g.clone() for g in mod.forward(x, x))
+    B.mrem_profile_gemm_end(mod.ctx)
+    assert torch.equal(f_fp, g_fp) and torch.equal(f_q, g_q)
+    # while the caller's stream is captured: replays repeat the eager results
+    out_fp, out_q = mod.new_outputs(batch, seq)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        mod.forward(x, x, None, out_fp, out_q)
+    for _ in range(3):
+        out_fp.zero_()
+        out_q.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out_fp, f_fp) and torch.equal(out_q, f_q)
+        h_fp, h_q = mod.forward(x, x)
+        assert torch.equal(h_fp, f_fp) and torch.equal(h_q, f_q)
