@@ -315,14 +315,15 @@ int gemm_f32_k_slices(int dt, int M, int N, int K) {
   return dt == DT_BF16 ? f32_k_slices(M, N, K) : 1;
 }
 
-// A layer's weight gradients in one launch: the smaller of the large tiles with which all of them fit into one round of blocks,
-// over contractions of whole stages, an even number.  More tiles than units (wider than about 1200) would leave a second round
-// nearly empty.  A launch takes as long as one tile's contraction, so few tiles serve only short ones: steps, us, single
-// products first, three layers of 256 (24 tiles) over 4096 tokens 757 and 773, over 2560 681 and 635; of 320 (57 tiles) over
-// 4096 923 and 886; of 512 (96 tiles) 1134 and 1099, over 2048 880 and 827; two of 1024 over 4096 1505 and 1463.
-// Below 2048 tokens the single products are short.
+// A layer's weight gradients in one launch: the smaller of the large tiles with which all of them fit into one round of blocks.
+// More tiles than units (wider than about 1200) would leave a second round nearly empty.  A launch takes as long as one tile's
+// contraction, so few tiles serve only short ones: steps, us, single products first, three layers of 256 (24 tiles) over 4096
+// tokens 757 and 773, over 2560 681 and 635; of 320 (57 tiles) over 4096 923 and 886; of 512 (96 tiles) 1134 and 1099, over
+// 2048 880 and 827; two of 1024 over 4096 1505 and 1463.  Token counts that are not whole stages: three of 768 over 2310 1323
+// and 1271, six of 1024 over 3640 4299 and 4135, of 512 over 3589 2256 and 2091.  Fewer tokens: four of 768 over 1500 1527 and
+// 1425, two of 1024 over 1111 939 and 912; below that the single products are short.
 int wgrads_tile(int dt, const WgradJob* jobs, int njobs, int K) {
-  if (dt != DT_BF16 || !quad_ok(K) || K < 2048) return 0;
+  if (dt != DT_BF16 || K < 1024) return 0;
   for (const int bm : {128, 256}) {
     int64_t tiles = 0;
     for (int i = 0; i < njobs; ++i) tiles += (int64_t)((jobs[i].M + bm - 1) / bm) * ((jobs[i].N + 255) / 256);
@@ -332,7 +333,7 @@ int wgrads_tile(int dt, const WgradJob* jobs, int njobs, int K) {
   return 0;
 }
 void gemm_wgrads(const WgradJob* jobs, int njobs, int K, int tile, hipStream_t st) {
-  bool whole = true;
+  bool whole = quad_ok(K);
   for (int i = 0; i < njobs; ++i) whole = whole && jobs[i].M % tile == 0 && jobs[i].N % 256 == 0;
   if (tile == 128) return whole ? launch_quad_wgrads<128, false>(jobs, njobs, K, st) : launch_quad_wgrads<128, true>(jobs, njobs, K, st);
   whole ? launch_quad_wgrads<256, false>(jobs, njobs, K, st) : launch_quad_wgrads<256, true>(jobs, njobs, K, st);

@@ -18,7 +18,7 @@
 
 namespace mrem {
 
-// L direct loads of 1 KiB from p + o (a lane's bytes) on; bytes from `end` (if any) on are not read
+// L direct loads of 1 KiB from p + o (a lane's bytes) on; bytes from `end` (if any) on are not read, LDS gets zeros for them
 template <int L>
 __device__ __forceinline__ void buffer_to_lds(const unsigned char* p, const unsigned char* end, const unsigned (&o)[L], unsigned char* dst) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass does not know the resource type
@@ -48,7 +48,9 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const int KT = K / BK;
+  // EDGE, both operands transposed: rows beyond the contraction are beyond the end of both operands and read as zeros, so any K
+  // is an even number of stages
+  const int KT = EDGE && AT && BT ? (K + 2 * BK - 1) / (2 * BK) * 2 : K / BK;
 
   // sources: the first element of a half's next stage (uniform) and this lane's offsets from it
   const size_t adv_a = AT ? (size_t)BK * lda * 2 : RB, adv_b = BT ? (size_t)BK * ldb * 2 : RB;
@@ -63,7 +65,7 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
   for (int i = 0; i < LA; ++i) oa[i] = (unsigned)OpA::src_offset((wave * LA + i) * 1024 + lane * 16, lda);
 #pragma unroll
   for (int i = 0; i < LB; ++i) ob[i] = (unsigned)OpB::src_offset((wave * LB + i) * 1024 + lane * 16, ldb);
-  // EDGE: nothing is fetched from beyond the end of an operand.  What a partly filled tile holds for rows that the matrix does
+  // EDGE: nothing is fetched from beyond the end of an operand (such bytes are zeros in LDS).  What a partly filled tile holds for rows that the matrix does
   // not have only enters results that are not stored.
   const unsigned char* const end_a = reinterpret_cast<const unsigned char*>(A + (size_t)((AT ? K : M) - 1) * lda + (AT ? M : K));
   const unsigned char* const end_b = reinterpret_cast<const unsigned char*>(B + (size_t)((BT ? K : N) - 1) * ldb + (BT ? N : K));

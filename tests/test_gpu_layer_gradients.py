@@ -6,10 +6,12 @@ pytestmark = pytest.mark.gpu
 
 
 # Tiles of 128 x 256, whole and partly filled (320 and 576 wide), and of 256 x 256, whole (1024) and partly filled (992 wide);
-# contractions of an even number of stages with and without whole rounds; three layers alternate between the two sets of
-# output gradients, four wait for the first one again.  Above 2^19 activations a layer, from 2048 tokens on.
+# contractions of an even number of stages, and of any length (6, 97 and 99 tokens into the last two stages, one less than them); three layers alternate between the two sets of
+# output gradients, four wait for the first one again.  Above 2^19 activations a layer, from 1024 tokens on.
 @pytest.mark.parametrize("layers,hidden,heads,ffn,batch,seq", [(2, 768, 12, 3072, 16, 128), (4, 320, 5, 1280, 32, 128), (3, 576, 9, 2304, 17, 128),
-                                                               (3, 1024, 16, 4096, 17, 128), (2, 992, 31, 3968, 18, 128), (2, 256, 4, 1024, 64, 40)])
+                                                               (3, 1024, 16, 4096, 17, 128), (2, 992, 31, 3968, 18, 128), (2, 256, 4, 1024, 64, 40),
+                                                               (2, 768, 12, 3072, 30, 77), (3, 1024, 16, 4096, 25, 91), (3, 320, 5, 1280, 33, 65),
+                                                               (2, 768, 12, 3072, 25, 87), (3, 768, 12, 3072, 15, 100)])
 def test_one_launch_equals_single_products(layers, hidden, heads, ffn, batch, seq):
     import torch
     from paper_2109_15082_amd import binding as B
