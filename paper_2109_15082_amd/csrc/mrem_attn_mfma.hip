@@ -84,6 +84,11 @@ __device__ __forceinline__ FwdScales load_fwd_scales(const AttnQ& a, int d) {
   return s;
 }
 
+// a - b, an operation of its own: never half of a fused multiply-add, whatever the compiler finds in front of it
+__device__ __forceinline__ float sub_apart(float a, float b) {
+#pragma clang fp contract(off)
+  return a - b;
+}
 // scores of 32 keys from accumulators, first key `key0`; -inf beyond the valid keys (a tile without such keys skips the tests,
 // two of the six instructions a score costs a forward pass ahead of its exponential)
 __device__ __forceinline__ void mask_scores(f32x16_t& a, int key0, int half, int len) {
@@ -97,7 +102,7 @@ __device__ __forceinline__ void scale_scores(f32x16_t& a, const FwdScales& sc, i
   for (int r = 0; r < 16; ++r) a[r] = __fmul_rn(a[r], sc.qk);
   mask_scores(a, key0, half, len);
 }
-// the same plus `c`, in one rounding (the backward pass of the FAST arithmetic takes a score less the row's maximum so)
+// the same plus `c`, in one rounding: how the backward pass takes a score less the row's maximum
 __device__ __forceinline__ void scale_scores(f32x16_t& a, const FwdScales& sc, int key0, int half, int len, float c) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) a[r] = __fmaf_rn(a[r], sc.qk, c);
@@ -359,7 +364,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
     f32x16_t e;
     const float top = finite_max(mx);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) e[r] = exp_neg<FAST>(__fsub_rn(a[r], top));
+    for (int r = 0; r < 16; ++r) e[r] = exp_neg<FAST>(sub_apart(a[r], top));
     return e;
   };
   auto raise_max = [&](const f32x16_t& a) {
@@ -569,7 +574,7 @@ __global__ __launch_bounds__(256, FAST ? 4 : 3) void attn_fwd_row_k(const bf16_t
   for (int t = 0; t < TW; ++t)
     if (t < n)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) e[t][r] = exp_neg<FAST>(__fsub_rn(e[t][r], top));
+      for (int r = 0; r < 16; ++r) e[t][r] = exp_neg<FAST>(sub_apart(e[t][r], top));
   // the row sum in the order of the arithmetic (see exp_neg)
 #pragma unroll 1
   for (int w = 0; w < 4; ++w) {
@@ -653,12 +658,14 @@ __global__ __launch_bounds__(256, FAST ? 4 : 3) void attn_fwd_row_k(const bf16_t
 }
 
 // ------------------------------------------------------------------------------
-// backward: P recomputed from the saved row statistics, with the rounding steps of the forward, dP^ = dC * V^T, the
-// straight-through rule of the probability quantizer and the softmax backward dA = P * (dP - rowdot),
-// rowdot = sum_j dP[q][j] * P[q][j].  Up to 128 keys the query-major kernel leaves P^T and dA^T (bf16) for the
-// key-major one, which is then a pure product (512 heads of 128 tokens, inside a step: 17 us against 40 us for forming
-// them again); beyond that the 4 bytes per query-key pair each way cost more than the arithmetic, and the key-major
-// kernel forms them itself (256 heads of 384 tokens, both kernels: 164 us against 215 us).
+// backward: P recomputed from the saved row statistics, with the rounding steps of the forward but for one: a score less the
+// row's maximum is one fused multiply-add, in every kernel of the pass (the forward rounds the score first, so a probability
+// may differ from the forward's by the rounding of its score).  dP^ = dC * V^T, the straight-through rule of the probability
+// quantizer and the softmax backward dA = P * (dP - rowdot), rowdot = sum_j dP[q][j] * P[q][j].  Up to 128 keys the
+// query-major kernel leaves P^T and dA^T (bf16) for the key-major one, which is then a pure product (512 heads of 128
+// tokens, inside a step: 17 us against 40 us for forming them again); beyond that the 4 bytes per query-key pair each way
+// cost more than the arithmetic, and the key-major kernel forms them itself (256 heads of 384 tokens, both kernels: 164 us
+// against 215 us).
 // Tiles without masked keys skip the mask's tests (256 heads of 384 tokens, query-major: 89 -> 73 us inside a step), and the
 // tiles of P^T and dA^T are transposed in LDS on their way out, 16 bytes a lane instead of 2 (512 heads of 128: 37 -> 34 us).
 // ------------------------------------------------------------------------------
@@ -832,22 +839,29 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
   }
 }
 
-// The query-major part where the order of its sums is free (not FAST): 32 queries a block, the keys shared out among its
-// wavefronts as in attn_fwd_row_k, so that probabilities and their gradients are formed once and stay in registers until the
-// row's sum over them is known, instead of being formed again.  A wavefront's part of dQ^ meets the others' in LDS.
-// Inside a step, 8 x 512 tokens, 12 heads: 106 -> 64 us against 128 queries a block and two passes over the keys.
+// The query-major part of the other arithmetic (not FAST): 32 queries a block, the keys shared out among its wavefronts as in
+// attn_fwd_row_k, so that probabilities and their gradients are formed once and stay in registers until the row's sum over
+// them is known, instead of being formed again.  Every sum over keys is one chain with the keys ascending, as in a wavefront
+// that holds the whole row: rowdot, the step gradient's sum and the accumulators of dQ^ go from wavefront to wavefront
+// through LDS.  Inside a step, 8 x 512 tokens, 12 heads: 106 -> 70 us against 128 queries a block and two passes over the keys
+// (64 us with parts summed apart and the row maximum subtracted on its own, which moved a step's results by up to 0.5%).
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
                                                            bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S, int B,
                                                            int nh, const float* __restrict__ stat_m, const float* __restrict__ stat_l,
                                                            float* __restrict__ rowdot_out, float* __restrict__ ds_parts) {
   constexpr int TW = 4;  // tiles of a wavefront (up to 512 keys)
-  // one tile of K per wavefront, then the wavefronts' parts of dQ^
-  __shared__ __attribute__((aligned(16))) union { bf16_t k[4][32 * Tile<D>::kStride]; float dq[4][D / 32][16][64]; } x;
-  __shared__ float dots[4][32], ds[4];
+  // per wavefront: what a unit of dP^ adds to the step gradient, then 32 columns of a tile of K
+  __shared__ __attribute__((aligned(16))) union { float4 term[TW][4][64]; bf16_t k[32 * Tile<32>::kStride]; } x[4];
+  __shared__ float dq_sums[D / 32][16][64], dots[64], dsps[64];  // from wavefront to wavefront
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, waves = blockDim.x >> 6;
+  const int nq = (S + 127) / 128 * waves;  // one partial sum for each 32 queries of whole groups of 128
   int head, blk;
-  row_of_block((S + 31) / 32, B * nh, head, blk);
+  row_of_block(nq, B * nh, head, blk);
+  if (32 * blk >= S) {
+    if (threadIdx.x == 0) ds_parts[(size_t)head * nq + blk] = 0.f;
+    return;
+  }
   const int b = head / nh, h = head % nh, H = nh * D, ld = 3 * H;
   const bf16_t* base = codes + (size_t)b * S * ld + h * D;
   const int len = seqlens ? min(seqlens[b], S) : S;
@@ -859,8 +873,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restr
   const bool qvalid = q < S;
   // a lane's part of rows 32 (t0 + t) .. + 31 of K or V as an operand; rows beyond the sequence repeat its last one (their
   // probabilities are 0)
+  auto row_at = [&](int column, int t) { return base + column + (size_t)min(32 * (t0 + t) + (lane & 31), S - 1) * ld + half * 8; };
   auto load_rows = [&](bf16x8_t (&f)[D / 16], int column, int t) {
-    const bf16_t* p = base + column + (size_t)min(32 * (t0 + t) + (lane & 31), S - 1) * ld + half * 8;
+    const bf16_t* p = row_at(column, t);
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) f[kk] = ld_frag(p + kk * 16);
   };
@@ -878,7 +893,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restr
   const float mx = stat_m[stat_idx], l = stat_l[stat_idx];  // row maximum and row sum of the forward
   const float rl = __fdiv_rn(1.0f, l);
 
-  float p[TW][16], dp[TW][16], rowdot = 0.f, dsp = 0.f;
+  // the probability, negative where the quantizer clips it, and the gradient of its code
+  float p[TW][16], dph[TW][16];
 #pragma unroll
   for (int t = 0; t < TW; ++t)
     if (t < n) {
@@ -892,62 +908,113 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restr
         load_rows(kf, H, t + 1);
         load_rows(vf, 2 * H, t + 1);
       }
-      scale_scores(sacc, sc, 32 * (t0 + t), half, len);
+      scale_scores(sacc, sc, 32 * (t0 + t), half, len, -mx);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const ProbGrad g = prob_grad<false>(__fsub_rn(sacc[r], mx), dacc[r], true, l, rl, sc, dsp);
-        p[t][r] = g.p;
-        dp[t][r] = g.dp;
-        rowdot += g.dp * g.p;
+      for (int g = 0; g < 4; ++g) {
+        float term[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float pr = div_by(exp_neg<false>(sacc[4 * g + i]), l, rl);
+          const float v = div_by(pr, sc.sp, sc.rsp);
+          const bool in = v <= sc.p_qp;
+          term[i] = rintf(fminf(v, sc.p_qp)) - (in ? v : 0.f);
+          p[t][4 * g + i] = in || !sc.p_on ? pr : -pr;
+          dph[t][4 * g + i] = dacc[4 * g + i] * sc.sv;
+        }
+        x[wave].term[t][g][lane] = make_float4(term[0], term[1], term[2], term[3]);
       }
     }
-  rowdot += __shfl_xor(rowdot, 32, 64);
-  if (half == 0) dots[wave][lane] = rowdot;
-  dsp = wave_sum(qvalid ? dsp : 0.f);  // step-size gradient terms of the probability quantizer (padded query rows excluded)
-  if (lane == 0) ds[wave] = dsp;
-  if (n > 0) load_rows(kf, H, 0);
-  __syncthreads();
-  rowdot = 0.f;
-  for (int w = 0; w < waves; ++w) rowdot += dots[w][lane & 31];
-
-  f32x16_t dq[D / 32];
+  auto dp_of = [&](int t, int r) { return signbit(p[t][r]) ? 0.f : dph[t][r]; };
+#pragma unroll 1
+  for (int w = 0; w < waves; ++w) {
+    if (wave == w) {
+      float rowdot = w ? dots[lane] : 0.f, dsp = w ? dsps[lane] : 0.f;
 #pragma unroll
-  for (int et = 0; et < D / 32; ++et) dq[et] = zero16();
+      for (int t = 0; t < TW; ++t)
+        if (t < n)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const float4 term = x[wave].term[t][g][lane];
+            const float e[4] = {term.x, term.y, term.z, term.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              rowdot = __fmaf_rn(dp_of(t, 4 * g + i), fabsf(p[t][4 * g + i]), rowdot);
+              if (sc.p_on) dsp = __fmaf_rn(dph[t][4 * g + i], e[i], dsp);
+            }
+          }
+      if (w == waves - 1) {
+        rowdot += __shfl_xor(rowdot, 32, 64);
+        dsp = wave_sum(qvalid ? dsp : 0.f);  // step-size gradient terms of the probability quantizer (padded query rows excluded)
+        if (lane == 0) ds_parts[(size_t)head * nq + blk] = dsp;
+        if (half == 0 && qvalid) rowdot_out[stat_idx] = rowdot;
+      }
+      dots[lane] = rowdot;
+      dsps[lane] = dsp;
+    }
+    __syncthreads();
+  }
+  const float rowdot = dots[lane];
+
+  // the gradient of a score in three bf16 parts that add up to it (see accumulate_rows_wide)
+  bf16x8_t da[TW][3][2];
 #pragma unroll
   for (int t = 0; t < TW; ++t)
-    if (t < n) {
+    if (t < n)
 #pragma unroll
-      for (int kk = 0; kk < D / 16; ++kk)
-        *reinterpret_cast<bf16x8_t*>(&x.k[wave][(lane & 31) * Tile<D>::kStride + (kk * 2 + half) * 8]) = kf[kk];
-      if (t + 1 < TW && t + 1 < n) load_rows(kf, H, t + 1);
-      float da[16];
+      for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) da[r] = p[t][r] * (dp[t][r] - rowdot);
-      accumulate_rows_wide<D>(dq, x.k[wave], 0, lane, da);
+        for (int i = 0; i < 8; ++i) {
+          float rest = fabsf(p[t][8 * s + i]) * (dp_of(t, 8 * s + i) - rowdot);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            da[t][k][s][i] = static_cast<bf16_t>(rest);
+            rest = __fsub_rn(rest, static_cast<float>(da[t][k][s][i]));
+          }
+        }
+  // 32 columns at a time: while a wavefront adds to the second ones, the next adds to the first
+  auto load_columns = [&](bf16x8_t (&f)[2], int et, int t) {
+    const bf16_t* r = row_at(H + 32 * et, t);
+    f[0] = ld_frag(r);
+    f[1] = ld_frag(r + 16);
+  };
+  bf16x8_t kc[2];
+  if (n > 0) load_columns(kc, 0, 0);
+#pragma unroll 1
+  for (int s = 0; s < waves + D / 32 - 1; ++s) {
+    const int et = s - wave;
+    if (et >= 0 && et < D / 32 && (n > 0 || wave == 0)) {
+      f32x16_t acc = zero16();
+      if (wave)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = dq_sums[et][r][lane];
+#pragma unroll
+      for (int t = 0; t < TW; ++t)
+        if (t < n) {
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+            *reinterpret_cast<bf16x8_t*>(&x[wave].k[(lane & 31) * Tile<32>::kStride + (c * 2 + half) * 8]) = kc[c];
+          if (t + 1 < TW && t + 1 < n) load_columns(kc, et, t + 1);
+          else if (et + 1 < D / 32) load_columns(kc, et + 1, 0);
+#pragma unroll
+          for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              const int k0 = 16 * j + 4 * half;
+              acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag_tr<32>(x[wave].k, 0, k0, k0 + 8, lane), da[t][k][j], acc, 0, 0, 0);
+            }
+        }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dq_sums[et][r][lane] = acc[r];
     }
-  __syncthreads();
-#pragma unroll
-  for (int et = 0; et < D / 32; ++et)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) x.dq[wave][et][r][lane] = dq[et][r];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float sum = 0.f;
-    for (int w = 0; w < waves; ++w) sum += ds[w];
-    ds_parts[(size_t)head * ((S + 31) / 32) + blk] = sum;
+    __syncthreads();
   }
   if (!qvalid) return;
-  if (wave == 0 && half == 0) rowdot_out[stat_idx] = rowdot;
   const float f = sk / sqrtf((float)D);
   const size_t orow = ((size_t)b * S + q) * ld + h * D;
   for (int i = wave; i < D / 8; i += waves) {  // 8 columns, 4 of them here
-    float v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v[j] = x.dq[0][i / 4][4 * (i % 4) + j][lane];
-      for (int w = 1; w < waves; ++w) v[j] += x.dq[w][i / 4][4 * (i % 4) + j][lane];
-    }
-    store4(d_qkvh + orow + 8 * i + 4 * half, v[0] * f, v[1] * f, v[2] * f, v[3] * f);
+    const float(&v)[16][64] = dq_sums[i / 4];
+    const int r = 4 * (i % 4);
+    store4(d_qkvh + orow + 8 * i + 4 * half, v[r][lane] * f, v[r + 1][lane] * f, v[r + 2][lane] * f, v[r + 3][lane] * f);
   }
 }
 
@@ -1062,7 +1129,7 @@ __global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restric
           }
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const ProbGrad pg = prob_grad<FAST>(__fsub_rn(__fmul_rn(sacc[4 * g + i], sc.qk), st[0][i]), dacc[4 * g + i], j < len, st[1][i], st[2][i], sc, unused);
+            const ProbGrad pg = prob_grad<FAST>(__fmaf_rn(sacc[4 * g + i], sc.qk, -st[0][i]), dacc[4 * g + i], j < len, st[1][i], st[2][i], sc, unused);
             code[4 * g + i] = pg.code;
             da[4 * g + i] = pg.p * (pg.dp - st[3][i]);
           }
@@ -1142,7 +1209,6 @@ int attn_bwd_mfma(const void* codes, const void* dctx, void* d_qkvh, const AttnQ
       hipLaunchKernelGGL((attn_bwd_q_mfma_k<D, false>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)scratch0,
                          (bf16_t*)nullptr, (bf16_t*)nullptr, ds_parts);
     } else {
-      parts = (S + 31) / 32 * nh * B;
       hipLaunchKernelGGL((attn_bwd_q_row_k<D>), dim3(parts), dim3(64 * waves), 0, st, c, dc, out, aq, seqlens, S, B, nh, stat_m, stat_l,
                          (float*)scratch0, ds_parts);
     }
