@@ -230,7 +230,11 @@ bool gemm_i8_ok(const void* A, int lda, const void* B, int ldb, int M, int N, in
 //     and 21.2; 2000 x 4096 x 1024: 21.4 and 26.3; 1500 x 3072 x 768, 144 tiles: 14.8 and 16.6);
 //   256 x 256 (mrem_gemm_quad.h) beyond that: half the operand bytes per flop of 128 x 128 (4096 x 4096 x 1024: 32.0; 3000 x
 //     3072 x 768, 144 tiles: 24.4 against 28.2 for 288 tiles of 128 x 256).
-// The two large tiles need an even number of whole stages (K a multiple of 128, 256 for int8).  Other contractions take
+// The two large tiles need an even number of whole stages (K a multiple of 128, 256 for int8).  Partly filled tiles sum the
+// even and the odd k-substeps apart, as the tiles above do, so that a row's sums do not depend on how many rows there are,
+// until 256 x 256 tiles take over: 128 x 256 does so in a second set of accumulators (2310 x 3072 x 768 inside a step: 20.7,
+// 25.1 on 128 x 64), 256 x 256 has no registers for it, and the few sizes between the two (2800 x 3072 x 1024) stay on 128 x
+// 64, where a second round of 128 x 256 would be nearly empty (41.7 and 47.2).  Other contractions take
 //   256 x 256 (8 wavefronts of 64 x 128, two stages) from 144 such tiles on: half the
 //     operand bytes per flop of the small tile, which is faster only while its tiles fit two a compute unit (against
 //     128 x 128, bf16 and int8: 128 tiles, 4096 x 2048 x 1024: 29.0 and 24.0, int8 18.4 and 15.3; 144 tiles, 4608 x 2048 x
@@ -256,8 +260,12 @@ static void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void
     }
     return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   }
-  if (quad_ok(K)) {
+  const bool pair = !whole && tiles(256, 256) < 144;
+  if (quad_ok(K) && (tiles(128, 256) <= 256 || !pair)) {
     if (tiles(128, 256) <= 256) {
+      if constexpr (!I8) {
+        if (pair) return launch_quad<128, AT, BT, TO, I8, true, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+      }
       if (M % 128 == 0 && N % 256 == 0) return launch_quad<128, AT, BT, TO, I8, false>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
       return launch_quad<128, AT, BT, TO, I8, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
     }

@@ -1,5 +1,7 @@
-// Large tiles of the matrix product: 256 x 256 and 128 x 256.  Same contract, operand modes, LDS layouts and order of sums
-// as gemm_dl_k (mrem_gemm_dl.h); what differs is how long a load may take to land, and what a wavefront issues when.
+// Large tiles of the matrix product: 256 x 256 and 128 x 256.  Same contract, operand modes and LDS layouts as gemm_dl_k
+// (mrem_gemm_dl.h); what differs is how long a load may take to land, and what a wavefront issues when.  Sums are those of
+// the gemm_dl_k tile that serves the same size where a contraction is no even number of stages: one chain over k, or (PAIR)
+// two, of the even and of the odd k-substeps, which meet before the epilogue.
 //
 // Two stages of 64 KB are all that fit into LDS, and a stage that is refilled as a whole leaves its loads one k-step (about
 // 1 us), while a quarter of them come from beyond the L2.  Here a stage is four halves, the first and second half of the
@@ -32,7 +34,7 @@ __device__ __forceinline__ void buffer_to_lds(const unsigned char* p, const unsi
 }
 
 // tile (tm, tn) of a product
-template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE>
+template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE, bool PAIR>
 __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb, TO* __restrict__ C, int ldc, int M,
                                           int N, int K, const Epilogue& e, int tm, int tn) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_quad[];
@@ -88,11 +90,12 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
   for (int i = 0; i < OpB::NADDR; ++i) b_addr[i] += lds0 + B0;
 
   typedef typename std::conditional<I8, i32x16_t, f32x16_t>::type acc_t;
-  acc_t acc[2][2][NT];  // quadrant (rows, columns), tile
+  constexpr int P = PAIR ? 2 : 1;
+  acc_t acc[2][2][P][NT];  // quadrant (rows, columns), chain, tile
 #pragma unroll
-  for (int i = 0; i < 4 * NT; ++i)
+  for (int i = 0; i < 4 * P * NT; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i / (2 * NT)][i / NT % 2][i % NT][r] = 0;
+    for (int r = 0; r < 16; ++r) acc[i / (2 * P * NT)][i / (P * NT) % 2][i / NT % P][i % NT][r] = 0;
   typename OpA::frag_t fa[2][KK][1];
   typename OpB::frag_t fb[2][KK][NT];
   // k-substep `k` of a half that is read
@@ -103,9 +106,10 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
     OpB::template read<decltype(k)::value, decltype(at)::value>(f[decltype(k)::value], b_addr, 0);
   };
   // a quadrant's matrix instructions; `refill` sends out what the phase fetches, `read` (a k-substep) what it reads
-  auto multiply = [&](acc_t (&c)[NT], const typename OpA::frag_t (&a)[KK][1], const typename OpB::frag_t (&b)[KK][NT], auto refill, auto read) {
+  auto multiply = [&](acc_t (&acc_q)[P][NT], const typename OpA::frag_t (&a)[KK][1], const typename OpB::frag_t (&b)[KK][NT], auto refill, auto read) {
     auto substep = [&](auto kk) {
       constexpr int k = decltype(kk)::value;
+      acc_t(&c)[NT] = acc_q[k % P];
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
         if constexpr (I8) c[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(OpA::regs(a[k][0]), OpB::regs(b[k][j]), c[j], 0, 0, 0);
@@ -153,31 +157,31 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
   constexpr std::integral_constant<int, 2> c2{};
   constexpr std::integral_constant<int, 3> c3{};
   constexpr std::integral_constant<int, 4> c4{};
-  // A k-step in slot P.  LAST: 0 not one of the last two, 1 the last but one, 2 the last.  Halves go out in the order A0(kt + 2),
+  // A k-step in slot S.  LAST: 0 not one of the last two, 1 the last but one, 2 the last.  Halves go out in the order A0(kt + 2),
   // A1(kt + 2), B1(kt + 2), B0(kt + 3); `third` says whether there is a k-step kt + 3.
   auto k_step = [&](auto par, auto last_, bool third) {
-    constexpr int P = decltype(par)::value, LAST = decltype(last_)::value, Q = P ^ 1;
-    constexpr std::integral_constant<int, P * SLOT_A + OpA::BYTES> a1{};
-    constexpr std::integral_constant<int, P * SLOT_B + OpB::BYTES> b1{};
+    constexpr int S = decltype(par)::value, LAST = decltype(last_)::value, Q = S ^ 1;
+    constexpr std::integral_constant<int, S * SLOT_A + OpA::BYTES> a1{};
+    constexpr std::integral_constant<int, S * SLOT_B + OpB::BYTES> b1{};
     constexpr std::integral_constant<int, Q * SLOT_B> b0_next{};
     constexpr std::integral_constant<int, Q * SLOT_A> a0_next{};
     if constexpr (LAST == 0) hand_over(c2, c4);
     else if constexpr (LAST == 1) hand_over(c2, c3);
     else hand_over(c0, c1);
-    multiply(acc[0][0], fa[P], fb[0], [&] { if constexpr (LAST == 0) fetch_a(0, P); }, [&](auto k) { read_a(fa[Q], a1, k); });
+    multiply(acc[0][0], fa[S], fb[0], [&] { if constexpr (LAST == 0) fetch_a(0, S); }, [&](auto k) { read_a(fa[Q], a1, k); });
     arrived_a(fa[Q]);
     if constexpr (LAST == 0) hand_over(c3, c3);
     else if constexpr (LAST == 1) hand_over(c2, c2);
     else hand_over(c0, c0);
-    multiply(acc[1][0], fa[Q], fb[0], [&] { if constexpr (LAST == 0) fetch_a(1, P); }, [&](auto k) { read_b(fb[1], b1, k); });
+    multiply(acc[1][0], fa[Q], fb[0], [&] { if constexpr (LAST == 0) fetch_a(1, S); }, [&](auto k) { read_b(fb[1], b1, k); });
     arrived_b(fb[1]);
     if constexpr (LAST == 0) hand_over(c4, c2);
     else if constexpr (LAST == 1) hand_over(c2, c1);
-    multiply(acc[1][1], fa[Q], fb[1], [&] { if constexpr (LAST == 0) fetch_b(1, P); }, [&](auto k) { if constexpr (LAST < 2) read_b(fb[0], b0_next, k); });
+    multiply(acc[1][1], fa[Q], fb[1], [&] { if constexpr (LAST == 0) fetch_b(1, S); }, [&](auto k) { if constexpr (LAST < 2) read_b(fb[0], b0_next, k); });
     if constexpr (LAST < 2) arrived_b(fb[0]);
     if constexpr (LAST == 0) hand_over(c3, c3);
     else if constexpr (LAST == 1) hand_over(c1, c1);
-    multiply(acc[0][1], fa[P], fb[1], [&] { if (LAST == 0 && third) fetch_b(0, Q); }, [&](auto k) { if constexpr (LAST < 2) read_a(fa[Q], a0_next, k); });
+    multiply(acc[0][1], fa[S], fb[1], [&] { if (LAST == 0 && third) fetch_b(0, Q); }, [&](auto k) { if constexpr (LAST < 2) read_a(fa[Q], a0_next, k); });
     if constexpr (LAST < 2) arrived_a(fa[Q]);
   };
 
@@ -196,6 +200,12 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
   }
   k_step(c0, c1, false);
   k_step(c1, c2, false);
+  if constexpr (PAIR) {
+#pragma unroll
+    for (int i = 0; i < 4 * NT; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i / (2 * NT)][i / NT % 2][0][i % NT][r] += acc[i / (2 * NT)][i / NT % 2][1][i % NT][r];
+  }
 
   // epilogue: out = acc * (alpha * col_scale[n]) + beta * (col_vec[n] + row_vec[m]) + bias[n]
   const float alpha = e.alpha ? *e.alpha : 1.f;
@@ -217,7 +227,7 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
         for (int r = 0; r < 16; ++r) {
           const int dm = 8 * (r >> 2) + (r & 3);
           if (!decltype(inside)::value && mb + dm >= M) continue;
-          const float a = (float)acc[i][j / NT][j % NT][r];
+          const float a = (float)acc[i][j / NT][0][j % NT][r];
           float v;
           if constexpr (decltype(apart)::value) {
             const float t = decltype(with_row)::value ? cv + e.row_vec[mb + dm] : cv;
@@ -248,12 +258,12 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
   else choose(no);
 }
 
-template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE>
+template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE, bool PAIR>
 __global__ __launch_bounds__(512, 1) void gemm_quad_k(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
                                                       TO* __restrict__ C, int ldc, int M, int N, int K, Epilogue e, int tiles_m, int tiles_n) {
   int tm, tn;
   tile_of_block(tiles_m, tiles_n, tm, tn);
-  quad_tile<BM, AT, BT, TO, I8, EDGE>(A, lda, B, ldb, C, ldc, M, N, K, e, tm, tn);
+  quad_tile<BM, AT, BT, TO, I8, EDGE, PAIR>(A, lda, B, ldb, C, ldc, M, N, K, e, tm, tn);
 }
 
 // The weight gradients of a layer in one launch, at most one tile a compute unit.  Products of
@@ -279,7 +289,7 @@ __global__ __launch_bounds__(512, 1) void gemm_quad_wgrads_k(QuadJobs jobs, int 
   tile_of_index(pid - q.first, q.tiles_m, q.tiles_n, tm, tn);
   Epilogue e;
   e.alpha = q.j.alpha;
-  quad_tile<BM, true, true, float, false, EDGE>((const bf16_t*)q.j.dy, q.j.M, (const bf16_t*)q.j.x, q.j.N, q.j.dw, q.j.N, q.j.M, q.j.N, K, e, tm, tn);
+  quad_tile<BM, true, true, float, false, EDGE, false>((const bf16_t*)q.j.dy, q.j.M, (const bf16_t*)q.j.x, q.j.N, q.j.dw, q.j.N, q.j.M, q.j.N, K, e, tm, tn);
 }
 
 // whole stages, an even number of them
@@ -298,13 +308,13 @@ static size_t quad_lds(const void* kernel, std::atomic<int>& configured_dev) {
   return lds;
 }
 
-template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE>
+template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE, bool PAIR = false>
 static void launch_quad(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e, hipStream_t st) {
   constexpr int BN = 256;
   static std::atomic<int> configured_dev{-1};
-  const size_t lds = quad_lds<BM>(reinterpret_cast<const void*>(&gemm_quad_k<BM, AT, BT, TO, I8, EDGE>), configured_dev);
+  const size_t lds = quad_lds<BM>(reinterpret_cast<const void*>(&gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR>), configured_dev);
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  MREM_LAUNCH((gemm_quad_k<BM, AT, BT, TO, I8, EDGE>), dim3(tiles_m * tiles_n), dim3(512), lds, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C,
+  MREM_LAUNCH((gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR>), dim3(tiles_m * tiles_n), dim3(512), lds, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C,
               ldc, M, N, K, e, tiles_m, tiles_n);
 }
 
