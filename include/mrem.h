@@ -208,6 +208,9 @@ mrem_status mrem_module_calibrate(mrem_ctx* ctx, float* params, const float* tea
  *                  the layer outputs f_l and f^_l of Eq. 3; the last slice is the
  *                  module output handed to the next module.  Either may be NULL to
  *                  skip that pass.
+ * The result is that of the full-precision pass followed by the quantized one, also where
+ * one writes what the other reads (x_q may lie in per_layer_fp, and per_layer_q may start
+ * at an input that both read); such passes run one after the other.
  */
 mrem_status mrem_module_forward(mrem_ctx* ctx, const float* params, const float* teacher, const void* teacher_cache,
                                 const void* x_fp, const void* x_q, const int32_t* seqlens, int32_t batch,

@@ -910,6 +910,24 @@ extern "C" mrem_status mrem_module_calibrate(mrem_ctx* ctx, float* params, const
 }
 
 namespace {
+struct Bytes { const void* p; size_t n; };
+bool overlap(const Bytes& a, const Bytes& b) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a.p), y = reinterpret_cast<uintptr_t>(b.p);
+  return a.p && b.p && x < y + b.n && y < x + a.n;
+}
+// Whether either forward pass writes what the other one reads or writes: a quantized pass over the full-precision pass's
+// outputs, or one that leaves its outputs in place of the input that both read.
+bool passes_depend(const mrem_ctx* c, int batch, int seq, const float* params, const float* teacher, const void* teacher_cache, const void* x_fp,
+                   const void* x_q, const int32_t* seqlens, const void* per_layer_fp, const void* per_layer_q) {
+  const size_t io = (size_t)batch * seq * c->H * dt_size(c->dt), vec = (size_t)mrem_param_count(c) * sizeof(float);
+  const Bytes out_fp{per_layer_fp, io * c->L}, out_q{per_layer_q, io * c->L}, lens{seqlens, (size_t)batch * sizeof(int32_t)};
+  for (const Bytes& b : {out_q, Bytes{x_q, io}, Bytes{params, vec}, lens})
+    if (overlap(out_fp, b)) return true;
+  for (const Bytes& b : {Bytes{x_fp, io}, Bytes{teacher, vec}, Bytes{teacher_cache, mrem_teacher_cache_bytes(c)}, lens})
+    if (overlap(out_q, b)) return true;
+  return false;
+}
+
 mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teacher, const void* teacher_cache, const void* x_fp,
                          const void* x_q, const int32_t* seqlens, int32_t batch, int32_t seq, void* per_layer_fp, void* per_layer_q,
                          void* workspace, size_t workspace_bytes, void* hip_stream, bool two_streams, const char* who) {
@@ -929,7 +947,7 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
     REQUIRE_PTR(x_q, who);
     if (!aligned16(per_layer_q)) return fail(ctx, MREM_EINVAL, std::string(who) + ": per_layer_q misaligned");
   }
-  // The passes share nothing but their inputs: the full-precision one runs on a side stream, forked from the caller's and
+  // Where the passes share nothing but their inputs the full-precision one runs on a side stream, forked from the caller's and
   // joined to it (both passes of a 23-token sentence through three layers of 768: 373 us one after the other, 264 now; six
   // layers of 1024 over 4096 tokens: 1840 and 1660).  Not while the caller's stream is being captured: the side stream may
   // serve another thread meanwhile.  Nor for the smallest calls, where forking and joining cost the host 35 us and the device
@@ -939,7 +957,8 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
   // two of 128 over 1024 141 and 148).
   hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
   bool fork = two_streams && per_layer_fp && per_layer_q && !ctx->prof.on &&
-              (ctx->L * ctx->H >= 384 || (int64_t)ctx->L * ctx->H * r.T >= (ctx->L > 1 ? 1 << 18 : 1 << 20));
+              (ctx->L * ctx->H >= 384 || (int64_t)ctx->L * ctx->H * r.T >= (ctx->L > 1 ? 1 << 18 : 1 << 20)) &&
+              !passes_depend(ctx, batch, seq, params, teacher, teacher_cache, x_fp, x_q, seqlens, per_layer_fp, per_layer_q);
   if (fork && (hipStreamIsCapturing(r.st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
     (void)hipGetLastError();
     fork = false;

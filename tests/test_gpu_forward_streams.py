@@ -39,3 +39,33 @@ def test_both_passes_equal_single_passes(layers, hidden, batch, seq):
         assert torch.equal(out_fp, f_fp) and torch.equal(out_q, f_q)
         h_fp, h_q = mod.forward(x, x)
         assert torch.equal(h_fp, f_fp) and torch.equal(h_q, f_q)
+
+
+def _forked_module(torch, B):
+    rng = np.random.default_rng(3)
+    mod = B.MremModule(3, 768, 12, 3072, 16, 64)
+    mod.teacher.copy_(torch.from_numpy(rng.standard_normal(mod.teacher.numel(), dtype=np.float32) * np.float32(0.02)))
+    B.mrem_teacher_prepare(mod.ctx, mod.teacher, mod.teacher_cache)
+    mod.params.copy_(mod.teacher)
+    mod.init_steps()
+    x = torch.from_numpy(rng.standard_normal((16, 64, 768), dtype=np.float32)).cuda().bfloat16()
+    mod.calibrate(x)
+    return mod, x
+
+
+def test_outputs_in_place_of_an_input():
+    """The quantized pass's outputs start at the input that both passes read; and its input lies in the other's outputs."""
+    import torch
+    from paper_2109_15082_amd import binding as B
+    mod, x = _forked_module(torch, B)
+    f_fp, f_q = (f.clone() for f in mod.forward(x, x))
+    out_fp, out_q = mod.new_outputs(16, 64)
+    for _ in range(3):
+        out_q[0].copy_(x)
+        mod.forward(out_q[0], out_q[0], None, out_fp, out_q)
+        assert torch.equal(out_fp, f_fp) and torch.equal(out_q, f_q)
+    g_fp, g_q = (f.clone() for f in mod.forward(x, f_fp[1].clone()))
+    for _ in range(3):
+        out_fp.zero_()
+        mod.forward(x, out_fp[1], None, out_fp, out_q)
+        assert torch.equal(out_fp, g_fp) and torch.equal(out_q, g_q)
