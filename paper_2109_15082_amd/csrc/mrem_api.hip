@@ -8,9 +8,9 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <memory>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 using namespace mrem;
@@ -34,13 +34,6 @@ struct mrem_ctx {
   std::vector<hipEvent_t> ev_ready;  // [4 * l + i]: the output gradient of linear layer i of layer l is written
   std::vector<hipEvent_t> ev_done;   // [4 * l + i]: its weight-gradient product has read it
   int side_device = -1;
-  // The same for the full-precision pass of mrem_module_forward, which has a stream of its own: a step's side stream may be
-  // part of a capture.  Forward passes on one context may come from several threads (each with its own workspace and stream)
-  // and share it: its creation, and each recording of an event with the wait for it, happen under the lock.
-  hipStream_t pass_side = nullptr;
-  hipEvent_t ev_pass_fork = nullptr, ev_pass_join = nullptr;
-  int pass_device = -1;
-  std::shared_ptr<std::mutex> pass_lock = std::make_shared<std::mutex>();
   GemmProfile prof;                // per-launch timing of the matrix products (measurement aid)
   int32_t* nonfinite_flag = nullptr;  // device, caller-owned, optional
 };
@@ -124,32 +117,47 @@ static bool create_side(mrem_ctx* ctx, int dev) {
   return true;
 }
 
-static void release_pass_side(mrem_ctx* ctx) {
-  if (ctx->pass_side) (void)hipStreamSynchronize(ctx->pass_side);
-  for (hipEvent_t* e : {&ctx->ev_pass_fork, &ctx->ev_pass_join}) {
-    if (*e) (void)hipEventDestroy(*e);
-    *e = nullptr;
+// Streams for the full-precision pass of mrem_module_forward: one for each stream that such calls come from, whichever their
+// contexts.  What one caller's stream holds is in order anyway, so nobody waits for another caller's work, and a new context
+// finds the stream of its caller's earlier ones (creating a stream takes 0.1 to 3.5 ms, a call over a sentence 0.25).  They
+// live as long as the process; callers beyond the first kPassStreams get none.  (Not a step's side stream, which may be part
+// of a capture.)
+struct PassStream {
+  hipStream_t caller, st;
+  std::thread::id thread;  // of the caller where its handle means another stream in each thread
+  int dev;
+  hipEvent_t fork, join;
+  std::mutex lock;  // held from the recording of an event to the wait for it: several threads may call on one stream
+};
+constexpr int kPassStreams = 16;
+
+static PassStream* pass_stream(hipStream_t caller) {
+  static std::mutex lock;
+  static PassStream* all[kPassStreams];  // (never destroyed: the runtime may be gone before this library's statics)
+  static int count = 0;
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  const std::thread::id thread = caller == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
+  const std::lock_guard<std::mutex> hold(lock);
+  for (int i = 0; i < count; ++i)
+    if (all[i]->caller == caller && all[i]->dev == dev && all[i]->thread == thread) return all[i];
+  if (count == kPassStreams) return nullptr;
+  hipStream_t st = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
+  if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess || hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&join, hipEventDisableTiming) != hipSuccess) {
+    if (fork) (void)hipEventDestroy(fork);
+    if (st) (void)hipStreamDestroy(st);
+    return nullptr;
   }
-  if (ctx->pass_side) (void)hipStreamDestroy(ctx->pass_side);
-  ctx->pass_side = nullptr;
-  ctx->pass_device = -1;
-}
-static bool create_pass_side(mrem_ctx* ctx, int dev) {
-  if (hipStreamCreateWithFlags(&ctx->pass_side, hipStreamNonBlocking) != hipSuccess ||
-      hipEventCreateWithFlags(&ctx->ev_pass_fork, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&ctx->ev_pass_join, hipEventDisableTiming) != hipSuccess) {
-    release_pass_side(ctx);
-    (void)hipGetLastError();  // the passes run one after the other
-    return false;
-  }
-  ctx->pass_device = dev;
-  return true;
+  PassStream* p = new PassStream;
+  p->caller = caller; p->st = st; p->thread = thread; p->dev = dev; p->fork = fork; p->join = join;
+  return all[count++] = p;
 }
 
 extern "C" void mrem_destroy(mrem_ctx* ctx) {
   if (!ctx) return;
   release_side(ctx);
-  release_pass_side(ctx);
   delete ctx;
 }
 extern "C" int64_t mrem_param_count(const mrem_ctx* ctx) { return ctx ? ctx->layer_stride * ctx->L : -1; }
@@ -949,8 +957,8 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
   }
   // Where the passes share nothing but their inputs the full-precision one runs on a side stream, forked from the caller's and
   // joined to it (both passes of a 23-token sentence through three layers of 768: 373 us one after the other, 264 now; six
-  // layers of 1024 over 4096 tokens: 1840 and 1660).  Not while the caller's stream is being captured: the side stream may
-  // serve another thread meanwhile.  Nor for the smallest calls, where forking and joining cost the host 35 us and the device
+  // layers of 1024 over 4096 tokens: 1840 and 1660).  Not while the caller's stream is being captured: another thread that
+  // calls on that stream would find the side stream in the capture.  Nor for the smallest calls, where forking and joining cost the host 35 us and the device
   // has little to do beside it (us, forked and not: one layer of 64 over 8 tokens 109 and 72, of 256 over 400 107 and 91, of
   // 768 over 23 105 and 118, over 400 133 and 172; two of 128 over 256 150 and 140, of 256 over 400 147 and 178; three of 64
   // over 8 205 and 195, of 128 over 256 200 and 206; many tokens: one of 64 over 4096 93 and 78, of 256 over 2048 95 and 92,
@@ -963,27 +971,25 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
     (void)hipGetLastError();
     fork = false;
   }
-  if (fork) {
-    const std::lock_guard<std::mutex> lock(*ctx->pass_lock);
-    int dev = -1;
-    fork = hipGetDevice(&dev) == hipSuccess && (ctx->pass_side || create_pass_side(ctx, dev)) && dev == ctx->pass_device;
-    if (fork) {
-      (void)hipEventRecord(ctx->ev_pass_fork, r.st);
-      (void)hipStreamWaitEvent(ctx->pass_side, ctx->ev_pass_fork, 0);
-    }
-  }
-  if (fork) {
+  PassStream* const side = fork ? pass_stream(r.st) : nullptr;
+  if (fork && !side) (void)hipGetLastError();  // the passes run one after the other
+  if (side) {
     Run rt = r;
-    rt.st = ctx->pass_side;
+    rt.st = side->st;
+    {
+      const std::lock_guard<std::mutex> lock(side->lock);
+      (void)hipEventRecord(side->fork, r.st);
+      (void)hipStreamWaitEvent(side->st, side->fork, 0);
+    }
     prepare_weights(r, params, false);
     // layer by layer in turn, so that both streams have work from the start
     for (int l = 0; l < ctx->L; ++l) {
       teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, nullptr, l, l + 1);
       student_forward(r, params, x_q, per_layer_q, l, l + 1);
     }
-    const std::lock_guard<std::mutex> lock(*ctx->pass_lock);
-    (void)hipEventRecord(ctx->ev_pass_join, ctx->pass_side);
-    (void)hipStreamWaitEvent(r.st, ctx->ev_pass_join, 0);
+    const std::lock_guard<std::mutex> lock(side->lock);
+    (void)hipEventRecord(side->join, side->st);
+    (void)hipStreamWaitEvent(r.st, side->join, 0);
     return finish(ctx, who);
   }
   if (per_layer_fp) teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp, nullptr);

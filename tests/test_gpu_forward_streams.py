@@ -69,3 +69,49 @@ def test_outputs_in_place_of_an_input():
         out_fp.zero_()
         mod.forward(x, out_fp[1], None, out_fp, out_q)
         assert torch.equal(out_fp, g_fp) and torch.equal(out_q, g_q)
+
+
+@pytest.mark.parametrize("own_streams", [True, False])
+def test_two_callers_on_one_context(own_streams):
+    """Two threads with a workspace and outputs each, on two streams and on one, repeat what one caller gets."""
+    import threading
+    import torch
+    from paper_2109_15082_amd import binding as B
+    mod, x = _forked_module(torch, B)
+    xs = [x, (x.float() * 0.5 + 0.1).bfloat16()]
+    ref = [tuple(f.clone() for f in mod.forward(v, v)) for v in xs]
+    streams = [torch.cuda.Stream() for _ in xs] if own_streams else [torch.cuda.Stream()] * 2
+    spaces = [torch.empty_like(mod.workspace) for _ in xs]
+    torch.cuda.synchronize()
+    got = [[] for _ in xs]
+
+    def call(i):
+        with torch.cuda.stream(streams[i]):
+            for _ in range(8):
+                fp, q = mod.new_outputs(16, 64)
+                B.mrem_module_forward(mod.ctx, mod.params, mod.teacher, mod.teacher_cache, xs[i], xs[i], None, 16, 64, fp, q, spaces[i])
+                got[i].append((fp, q))
+    threads = [threading.Thread(target=call, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert len(got[i]) == 8
+        for fp, q in got[i]:
+            assert torch.equal(fp, ref[i][0]) and torch.equal(q, ref[i][1])
+
+
+def test_more_callers_streams_than_are_served():
+    """Calls from more streams than the library keeps streams for run one pass after the other."""
+    import torch
+    from paper_2109_15082_amd import binding as B
+    mod, x = _forked_module(torch, B)
+    f_fp, f_q = (f.clone() for f in mod.forward(x, x))
+    torch.cuda.synchronize()
+    for _ in range(20):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            g_fp, g_q = mod.forward(x, x)
+        torch.cuda.synchronize()
+        assert torch.equal(g_fp, f_fp) and torch.equal(g_q, f_q)
