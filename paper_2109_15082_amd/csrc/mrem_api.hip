@@ -936,6 +936,25 @@ bool passes_depend(const mrem_ctx* c, int batch, int seq, const float* params, c
   return false;
 }
 
+// Whether two streams are worth the 30 us that forking and joining cost the host.  Small calls are bound by the host and the
+// device has little to do beside them.  Measured over widths 64 to 1024, 1 to 12 layers and 8 to 4096 tokens, both passes
+// (change in percent with two streams, a call by itself / calls behind each other):
+//   from 640 columns in all layers together: 2 of 320 over 8 tokens 0/-3, over 128 -8/-7; 6 of 128 -9/-4 and -15/-16; 3 of 256
+//     -9/-11 and -13/-15; 1 of 768 -1/-11 and 3/-6; 3 of 768 -26/-34 and -29/-33; 6 of 1024 over 4096 -7/-9;
+//   512 to 640: 2 of 256 over 23 -1/-4, over 64 -3/-4, over 1024 -6/-10; 4 of 128 over 23 1/2, over 128 -3/-3;
+//   384 to 512: 3 of 128 over 128 2/3, over 400 -2/-1, over 2048 -7/-6; 6 of 64 over 64 0/5, over 400 -9/-3;
+//   fewer: 4 of 64 over 256 0/3, over 1024 -10/0; 3 of 64 over 1024 4/6, over 2048 -15/-12; 2 of 128 over 1024 7/13, over 2048
+//     6/5, over 4096 -2/-5; 2 of 64 over 4096 6/12;
+//   single layers: 512 over 1024 2/-2, over 2048 -2/-15; 320 over 4096 5/-12; 256 over 128 26/24.
+bool worth_forking(int L, int H, int T) {
+  const int64_t width = (int64_t)L * H;
+  if (width >= 640) return true;
+  if (L == 1) return H >= 512 && T >= 2048;
+  if (width >= 512) return (int64_t)T * H >= 1 << 14;
+  if (L == 2) return width * T >= 1 << 20;
+  return width >= 384 ? T >= 384 : width * T >= 1 << 18;
+}
+
 mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teacher, const void* teacher_cache, const void* x_fp,
                          const void* x_q, const int32_t* seqlens, int32_t batch, int32_t seq, void* per_layer_fp, void* per_layer_q,
                          void* workspace, size_t workspace_bytes, void* hip_stream, bool two_streams, const char* who) {
@@ -958,15 +977,10 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
   // Where the passes share nothing but their inputs the full-precision one runs on a side stream, forked from the caller's and
   // joined to it (both passes of a 23-token sentence through three layers of 768: 373 us one after the other, 264 now; six
   // layers of 1024 over 4096 tokens: 1840 and 1660).  Not while the caller's stream is being captured: another thread that
-  // calls on that stream would find the side stream in the capture.  Nor for the smallest calls, where forking and joining cost the host 35 us and the device
-  // has little to do beside it (us, forked and not: one layer of 64 over 8 tokens 109 and 72, of 256 over 400 107 and 91, of
-  // 768 over 23 105 and 118, over 400 133 and 172; two of 128 over 256 150 and 140, of 256 over 400 147 and 178; three of 64
-  // over 8 205 and 195, of 128 over 256 200 and 206; many tokens: one of 64 over 4096 93 and 78, of 256 over 2048 95 and 92,
-  // two of 128 over 1024 141 and 148).
+  // calls on that stream would find the side stream in the capture.  Nor where worth_forking says so.
   hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
   bool fork = two_streams && per_layer_fp && per_layer_q && !ctx->prof.on &&
-              (ctx->L * ctx->H >= 384 || (int64_t)ctx->L * ctx->H * r.T >= (ctx->L > 1 ? 1 << 18 : 1 << 20)) &&
-              !passes_depend(ctx, batch, seq, params, teacher, teacher_cache, x_fp, x_q, seqlens, per_layer_fp, per_layer_q);
+              worth_forking(ctx->L, ctx->H, r.T) && !passes_depend(ctx, batch, seq, params, teacher, teacher_cache, x_fp, x_q, seqlens, per_layer_fp, per_layer_q);
   if (fork && (hipStreamIsCapturing(r.st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
     (void)hipGetLastError();
     fork = false;

@@ -5,8 +5,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-# around the sizes from which on the full-precision pass gets a stream of its own (layers * width 384; layers * width * tokens
-# 2^20 for one layer, 2^18 for more)
+# small calls, with one stream, and many tokens through one layer and two
 @pytest.mark.parametrize("layers,hidden,batch,seq", [(1, 64, 1, 8), (3, 128, 1, 8), (1, 320, 2, 23), (1, 384, 2, 23), (1, 256, 32, 128), (2, 128, 8, 128)])
 def test_both_passes_equal_single_passes(layers, hidden, batch, seq):
     import torch
@@ -115,3 +114,10 @@ def test_more_callers_streams_than_are_served():
             g_fp, g_q = mod.forward(x, x)
         torch.cuda.synchronize()
         assert torch.equal(g_fp, f_fp) and torch.equal(g_q, f_q)
+
+
+# on both sides of the lines from which on the full-precision pass gets a stream of its own
+@pytest.mark.parametrize("layers,hidden,batch,seq", [(10, 64, 1, 8), (9, 64, 1, 8), (2, 256, 1, 64), (2, 256, 1, 63), (3, 128, 3, 128), (3, 128, 1, 383),
+                                                     (1, 512, 16, 128), (4, 64, 8, 128), (2, 128, 32, 128)])
+def test_both_passes_equal_single_passes_around_the_rule(layers, hidden, batch, seq):
+    test_both_passes_equal_single_passes(layers, hidden, batch, seq)
