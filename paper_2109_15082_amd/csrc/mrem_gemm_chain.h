@@ -51,13 +51,13 @@ template <int MT, int NT, int WM, int WN, int AHEAD>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_chain_k(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
                                                              bf16_t* __restrict__ C, int ldc, int M, int N, int K, Epilogue e, int tiles_m, int tiles_n) {
   constexpr int BM = 16 * MT * WM, BN = 16 * NT * WN, BK = 64, RB = 2 * BK, NW = WM * WN, STAGES = 4, STEPS = BK / 4;
-  constexpr int RING = AHEAD < 2 ? 2 : AHEAD < 4 ? 4 : 8;  // steps whose operands are in registers or on the way
+  constexpr int RING = AHEAD < 2 ? 2 : AHEAD < 3 ? 4 : 8;  // steps whose operands are in registers or on the way
   typedef DlOperand<false, BM, RB, 1> OpA;
   typedef DlOperand<false, BN, RB, 1> OpB;
   constexpr int STAGE_BYTES = OpA::BYTES + OpB::BYTES, LPW = (OpA::LOADS + OpB::LOADS) / NW;
   static_assert((OpA::LOADS + OpB::LOADS) % NW == 0, "the loads of a stage divide evenly over the wavefronts");
   static_assert((STAGES - 1) * STAGE_BYTES + 2048 * (MT > NT ? MT : NT) <= 65536, "an LDS read reaches every stage with its 16-bit offset");
-  static_assert(AHEAD >= 1 && AHEAD < RING && STEPS % RING == 0 && AHEAD * (MT + NT) < 16, "LDS reads in flight fit the 4-bit counter");
+  static_assert(AHEAD >= 1 && 2 * AHEAD <= RING && STEPS % RING == 0 && (2 * AHEAD - 1) * (MT + NT) < 16, "LDS reads in flight fit the 4-bit counter");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE_BYTES];
   int tm, tn;
   tile_of_block(tiles_m, tiles_n, tm, tn);
@@ -124,10 +124,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_chain_k(const bf16_t* __res
     chain_read<off, s>(fa[s % RING], a_addr);
     chain_read<off, s>(fb[s % RING], b_addr);
   };
-  // rows of the accumulator tile are columns of C, so that a lane holds four neighbours of one row
-  auto multiply = [&](auto step) {
+  // rows of the accumulator tile are columns of C, so that a lane holds four neighbours of one row; `later`: the steps that
+  // have been read after this one
+  auto multiply = [&](auto step, auto later) {
     constexpr int s = decltype(step)::value % RING;
-    wait_lgkmcnt<AHEAD * (MT + NT)>();  // the steps read after this one
+    wait_lgkmcnt<decltype(later)::value * (MT + NT)>();
     chain_tie(fa[s]);
     chain_tie(fb[s]);
 #pragma unroll
@@ -136,26 +137,40 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_chain_k(const bf16_t* __res
       for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[s][j], fa[s][i], acc[i][j], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
+  // The first steps of a stage have arrived.
+  auto first_steps_arrived = [&]() {
+    wait_lgkmcnt<0>();
+    static_for<AHEAD>([&](auto s) {
+      chain_tie(fa[s.value]);
+      chain_tie(fb[s.value]);
+    });
+  };
   // Stage kt.  Its operands are read AHEAD steps before they are multiplied, those of the next stage's first steps behind
-  // the barrier that hands it over.  No branch may join while reads are in flight: a register that is copied there is copied
-  // before it has arrived.  So the last stage reads on into the next slot, and what it reads is dropped.
+  // the barrier that hands it over, ahead of this stage's last steps.  A stage is straight code that begins and ends with
+  // nothing in flight: a value that crosses a branch may be copied there, and a copy of what is still on its way into a
+  // register is a copy of what was there before.  So the fetch, which has a branch, stands behind the last wait, which the
+  // last steps' instructions cover (23 x 768 x 3072 in a calibration: 17.4 us with it and with values crossing the loop's
+  // edge, 4000 x 4096 x 1024: 292 and 291).  The last stage reads on into the next slot, and what it reads is dropped.
   auto run_stage = [&](int kt, auto slot) {
+    constexpr std::integral_constant<int, AHEAD> ahead{};
     static_for<STEPS - AHEAD>([&](auto s) {
       read(slot, std::integral_constant<int, s.value + AHEAD>{});
-      multiply(s);
+      multiply(s, ahead);
     });
     wait_vmcnt<LPW*(STAGES - 3)>();  // own loads of the next stage have landed
     __builtin_amdgcn_s_barrier();    // everybody's have, and everybody holds the operands of the stage before this one
-    issue(kt + STAGES - 1, (slot.value + STAGES - 1) % STAGES);
+    static_for<AHEAD>([&](auto s) { read(std::integral_constant<int, (slot.value + 1) % STAGES>{}, s); });
     static_for<AHEAD>([&](auto s) {
-      read(std::integral_constant<int, (slot.value + 1) % STAGES>{}, s);
-      multiply(std::integral_constant<int, STEPS - AHEAD + s.value>{});
+      multiply(std::integral_constant<int, STEPS - AHEAD + s.value>{}, std::integral_constant<int, 2 * AHEAD - 1 - s.value>{});
     });
+    first_steps_arrived();
+    issue(kt + STAGES - 1, (slot.value + STAGES - 1) % STAGES);
   };
   for (int s = 0; s < STAGES - 1; ++s) issue(s, s);
   wait_vmcnt<LPW*(STAGES - 2)>();
   __builtin_amdgcn_s_barrier();  // stage 0 has landed for everybody
   static_for<AHEAD>([&](auto s) { read(std::integral_constant<int, 0>{}, s); });
+  first_steps_arrived();
   for (int kt = 0;;) {
     run_stage(kt, std::integral_constant<int, 0>{});
     if (++kt >= KT) break;
@@ -166,13 +181,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_chain_k(const bf16_t* __res
     run_stage(kt, std::integral_constant<int, 3>{});
     if (++kt >= KT) break;
   }
-  // nothing is on its way into a register or into LDS when the block ends
-  wait_lgkmcnt<0>();
-#pragma unroll
-  for (int s = 0; s < RING; ++s) {
-    chain_tie(fa[s]);
-    chain_tie(fb[s]);
-  }
+  // nothing is on its way into LDS when the block ends
   wait_vmcnt<0>();
   const float alpha = e.alpha ? *e.alpha : 1.f;
   const float beta = (e.beta ? *e.beta : 0.f) + e.beta_alpha * alpha;
