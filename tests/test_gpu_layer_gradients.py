@@ -43,3 +43,83 @@ def test_one_launch_equals_single_products(layers, hidden, heads, ffn, batch, se
             o, n = B.mrem_param_offset(mod.ctx, l, name), B.mrem_param_size(mod.ctx, name)
             a, b = g[o:o + n].double(), g1[o:o + n].double()
             assert float(b.norm()) > 0 and float((a - b).norm() / b.norm()) < 1e-5, (l, name)
+
+
+def _module(shape, seed=0):
+    import torch
+    from paper_2109_15082_amd import binding as B
+    layers, hidden, heads, ffn, batch, seq = shape
+    rng = np.random.default_rng(seed)
+    mod = B.MremModule(layers, hidden, heads, ffn, batch, seq)
+    mod.teacher.copy_(torch.from_numpy(rng.standard_normal(mod.teacher.numel(), dtype=np.float32) * np.float32(0.02)))
+    B.mrem_teacher_prepare(mod.ctx, mod.teacher, mod.teacher_cache)
+    mod.params.copy_(mod.teacher)
+    mod.init_steps()
+    x = torch.from_numpy(rng.standard_normal((batch, seq, hidden), dtype=np.float32)).cuda().bfloat16()
+    mod.calibrate(x)
+    return mod, x
+
+
+def _step(shape, single):
+    import torch
+    from paper_2109_15082_amd import binding as B
+    mod, x = _module(shape)
+    grads = torch.zeros_like(mod.params)
+    if single:
+        B.mrem_profile_gemm_begin(mod.ctx)
+    mod.step(x, x, 1e-4, grads_out=grads)
+    torch.cuda.synchronize()
+    if single:
+        B.mrem_profile_gemm_end(mod.ctx)
+    return mod, grads
+
+
+# Which way a layer's products went shows in their bits: one launch sums a weight gradient in one chain over the tokens, the
+# small tiles and the k-slices of single products in two.  The lowest layer's are single products either way.
+@pytest.mark.parametrize("shape", [(2, 768, 12, 3072, 16, 128), (3, 1024, 16, 4096, 17, 128), (3, 320, 5, 1280, 33, 65)])
+def test_the_one_launch_is_taken(shape):
+    import torch
+    from paper_2109_15082_amd import binding as B
+    (mod, g), (_, g1) = _step(shape, False), _step(shape, True)
+    for l in range(shape[0]):
+        same = []
+        for name in ("w_qkv", "w_o", "w_1", "w_2"):
+            o, n = B.mrem_param_offset(mod.ctx, l, name), B.mrem_param_size(mod.ctx, name)
+            same.append(torch.equal(g[o:o + n], g1[o:o + n]))
+        assert all(same) if l == 0 else not all(same), (l, same)
+
+
+# Few tokens: a layer is handed over as a whole, its products are single ones, so nothing may differ.  Three layers and more
+# use a set of output gradients again; 2^19 activations a layer is the last size of this kind.
+@pytest.mark.parametrize("shape", [(3, 256, 4, 1024, 1, 66), (4, 128, 2, 512, 8, 128), (6, 512, 8, 2048, 1, 100), (3, 1024, 16, 4096, 4, 128)])
+def test_few_tokens_equal_one_stream(shape):
+    import torch
+    (mod, g), (mod1, g1) = _step(shape, False), _step(shape, True)
+    assert torch.equal(g, g1) and torch.equal(mod.loss, mod1.loss)
+    for a, b in ((mod.params, mod1.params), (mod.adam_m, mod1.adam_m), (mod.adam_v, mod1.adam_v)):
+        assert torch.equal(a, b)
+
+
+# both kinds of handover by the layer, the alternating sets of output gradients used again and again, over steps that follow
+# each other without a wait
+@pytest.mark.parametrize("shape", [(5, 768, 12, 3072, 16, 128), (5, 256, 4, 1024, 3, 77)])
+def test_steps_behind_each_other_equal_steps_by_themselves(shape):
+    import torch
+
+    def run(wait, stream):
+        mod, x = _module(shape)
+        xs, losses = [x, (x * 0.5).contiguous(), (x * 1.5).contiguous()], []
+        stream.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(stream):
+            for t in range(5):
+                mod.step(xs[t % 3], xs[t % 3], 1e-3 * (1 - t / 5))
+                losses.append(mod.loss.clone())
+                if wait:
+                    torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        return mod.params.clone(), mod.adam_m.clone(), mod.adam_v.clone(), torch.stack(losses)
+
+    ref = run(True, torch.cuda.current_stream())
+    for stream in (torch.cuda.current_stream(), torch.cuda.Stream()):
+        for a, b in zip(ref, run(False, stream)):
+            assert torch.equal(a, b)
