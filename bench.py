@@ -133,7 +133,8 @@ def main():
     # pass 1 because a timed launch still costs the queue a few microseconds, which with 96 products a
     # step adds up, and because in this pass the library keeps everything on the caller's stream (in
     # pass 1 the full-precision forward pass, the weight-gradient products and the per-layer updates run
-    # on a side stream beside the rest), so that every product is timed alone.
+    # on a side stream beside the rest, those products of the layers above the lowest as one launch a layer),
+    # so that every product is timed alone, by the kernels that serve it alone.
     B.mrem_profile_gemm_begin(mod.ctx)
     t1 = time.perf_counter()
     for _ in range(args.steps):
@@ -166,7 +167,7 @@ def main():
         "config": {"workload": wl.name, "n_layers": wl.n_layers, "hidden": wl.hidden, "n_heads": wl.n_heads, "ffn": wl.ffn,
                    "seq_len": wl.seq, "batch": wl.batch, "w_bits": wl.w_bits, "a_bits": wl.a_bits,
                    "tokens_per_step": wl.tokens, "step_tflop": flops_total / 1e12, "loss_last_step": float(losses[0])},
-        "roofline": {"bound": "mfma", "kernel": "gemm_dl_k and gemm_quad_k on bf16 operands (teacher forward, input and weight gradients)",
+        "roofline": {"bound": "mfma", "kernel": "gemm_dl_k and gemm_quad_k on bf16 operands (teacher forward, input and weight gradients), each product launched by itself",
                      "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": measured_gemm_traffic(wl.name),
                      "traffic_unit": "bytes/launch", "traffic_source": "profiles/module_step_bert_large_6l_hbm_traffic.txt (rocprofv3 --pmc)",
@@ -182,7 +183,9 @@ def main():
                      "all_products": {"achieved": all_flops / (all_ms * 1e-3) / 1e12 if all_ms > 0 else 0.0, "peak": MFMA_BF16_PEAK_TFLOPS,
                                       "unit": "TFLOP/s", "frac": (all_flops / (all_ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS) if all_ms > 0 else 0.0,
                                       "launches_per_step": all_launches / args.steps, "ms_per_step": all_ms / args.steps},
-                     "measured_on": "a second pass of the same K steps, one stream, with a HIP event pair (kernel begin, kernel end) on every product launch",
+                     "measured_on": "a second pass of the same K steps, one stream, with a HIP event pair (kernel begin, kernel end) on every product launch; "
+                                    "in the timed pass the weight gradients of a layer above the lowest are one launch (gemm_quad_wgrads_k), which this "
+                                    "pass does not run",
                      "ms_per_step_with_events": dt_events * 1e3 / args.steps,
                      "flops_per_launch": gemm_flops / max(gemm_launches, 1)},
         "step_tflops": flops_total / 1e12 / (ms_per_step * 1e-3),
