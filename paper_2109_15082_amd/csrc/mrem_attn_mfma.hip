@@ -20,11 +20,13 @@
 // dimension 32) and registers, not LDS, say how many share a compute unit.  Up to 128 keys (one
 // chunk) the scores and probabilities stay in registers between the pass that forms the row
 // statistics and the pass that uses them.  Longer rows are shared out among the wavefronts of a block of 32
-// queries (attn_fwd_row_k, attn_bwd_q_row_k), except in the backward pass of the FAST arithmetic, whose sums
-// over a row keep their order: it forms the tiles again for each pass.  The scores, the exponentials and the
+// queries (attn_fwd_row_k, attn_bwd_q_row_k), with three exceptions: the query-major kernel of the FAST
+// arithmetic forms its tiles again for each pass; the key-major kernels, whose rows are keys, take 128 of
+// them a block and the queries in chunks; and the forward on real-valued operands (REAL) keeps a row of up
+// to 512 keys in one wavefront, since its products are chains.  The scores, the exponentials and the
 // quantizer are vector-ALU work, which is what bounds these kernels, and a whole row in one wavefront's
-// registers leaves one wavefront per SIMD.  Wavefronts per SIMD: forward 3 to 4; backward 2 to 3 (160 to 256
-// registers for head dimension 64).  Chunks beyond the valid keys of a sequence are skipped.
+// registers leaves one wavefront per SIMD.  Wavefronts per SIMD (head dimension 64, not REAL): forward 3 to 4;
+// query-major backward 2 to 3 (160 to 256 registers).  Chunks beyond the valid keys of a sequence are skipped.
 #include "mrem_common.h"
 #include "mrem_kernels.h"
 
@@ -843,8 +845,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
 // attn_fwd_row_k, so that probabilities and their gradients are formed once and stay in registers until the row's sum over
 // them is known, instead of being formed again.  Every sum over keys is one chain with the keys ascending, as in a wavefront
 // that holds the whole row: rowdot, the step gradient's sum and the accumulators of dQ^ go from wavefront to wavefront
-// through LDS.  Inside a step, 8 x 512 tokens, 12 heads: 106 -> 70 us against 128 queries a block and two passes over the keys
-// (64 us with parts summed apart and the row maximum subtracted on its own, which moved a step's results by up to 0.5%).
+// through LDS.  Inside a step, 8 x 512 tokens, 12 heads: 101 -> 72 us against 128 queries a block and two passes over the keys
+// (60 us with parts summed apart and the row maximum subtracted on its own, which moved a step's results by up to 0.5%).
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
                                                            bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S, int B,
