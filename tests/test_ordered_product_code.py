@@ -30,6 +30,7 @@ def in_flight(lines):
         if wait:
             flying = flying[-int(wait[1]):] if int(wait[1]) else []
         elif read:
+            bad += [line] if any(f & registers(line) for f in flying) else []
             flying.append(registers(read[1]))
             reads += 1
         elif flying and (re.match(r"s_c?branch|\.LBB", line) or any(f & registers(line) for f in flying)):
@@ -55,9 +56,10 @@ def test_nothing_touches_a_value_on_its_way(tmp_path):
         assert reads > 0 and not bad, (asm[k], bad[:4])
 
 
-@pytest.mark.parametrize("line", ["v_mov_b32_e32 v9, v3", "s_cbranch_scc1 .LBB0_3", ".LBB0_2:"])
+@pytest.mark.parametrize("line", ["v_mov_b32_e32 v9, v3", "ds_read_u16_d16_hi v5, v3", "s_cbranch_scc1 .LBB0_3", ".LBB0_2:"])
 def test_the_check_sees(line):
     body = ["ds_read_u16_d16_hi v3, v8 offset:16", "ds_read_u16_d16_hi v4, v8", "s_waitcnt lgkmcnt({})", line]
-    assert in_flight([b.format(1) for b in body]) == (2, [] if "v3" in line else [line])
-    assert in_flight([b.format(2) for b in body]) == (2, [line])
-    assert in_flight([b.format(0) for b in body]) == (2, [])
+    reads = 2 + line.startswith("ds_read")
+    assert in_flight([b.format(1) for b in body]) == (reads, [] if "v3" in line else [line])
+    assert in_flight([b.format(2) for b in body]) == (reads, [line])
+    assert in_flight([b.format(0) for b in body]) == (reads, [])
