@@ -22,10 +22,11 @@
  *    priority, created on the first call that uses it), forked from the caller's
  *    stream by events and joined to it before the loss and before the call's last
  *    kernels; mrem_module_forward does the same with the full-precision pass and a
- *    stream that the library keeps for each caller's stream (for the first 16 that
- *    such calls come from, until the process ends), except in the smallest calls and
- *    while the caller's stream is being captured.  To the caller a call behaves like
- *    work on its own stream.  Calls return without synchronising.
+ *    stream that the library keeps for each caller's stream (up to 16; all but one
+ *    are given back with the last context), except in the smallest calls, while the
+ *    caller's stream is being captured and while all 16 are busy for others.  To the
+ *    caller a call behaves like work on its own stream.  Calls return without
+ *    synchronising.
  *  - Arguments are validated on the host before anything is enqueued; a call that
  *    returns an error has had no effect on device memory.
  *  - Return value: MREM_OK or a negative mrem_status.  mrem_last_error() gives a

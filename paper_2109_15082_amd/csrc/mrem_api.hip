@@ -48,6 +48,8 @@ static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 extern "C" const char* mrem_last_error(const mrem_ctx* ctx) { return ctx ? ctx->err.c_str() : g_err.c_str(); }
 
+static void count_contexts(int more);
+
 extern "C" mrem_status mrem_create(const mrem_config* cfg, mrem_ctx** out) {
   if (!cfg || !out) return fail(nullptr, MREM_EINVAL, "mrem_create: null argument");
   const mrem_config& c = *cfg;
@@ -76,6 +78,7 @@ extern "C" mrem_status mrem_create(const mrem_config* cfg, mrem_ctx** out) {
   int64_t t = 0;
   for (int i = 0; i < 4; ++i) { x->tc_off[i] = t; t += (int64_t)x->wN[i] * x->wK[i]; }
   x->tc_layer_stride = t;
+  count_contexts(1);
   *out = x;
   return MREM_OK;
 }
@@ -119,46 +122,103 @@ static bool create_side(mrem_ctx* ctx, int dev) {
 
 // Streams for the full-precision pass of mrem_module_forward: one for each stream that such calls come from, whichever their
 // contexts.  What one caller's stream holds is in order anyway, so nobody waits for another caller's work, and a new context
-// finds the stream of its caller's earlier ones (creating a stream takes 0.1 to 3.5 ms, a call over a sentence 0.25).  They
-// live as long as the process; callers beyond the first kPassStreams get none.  (Not a step's side stream, which may be part
-// of a capture.)
+// finds the stream of its caller's earlier ones (creating a stream takes 0.1 to 3.5 ms, a call over a sentence 0.25).  There
+// are up to kPassStreams; a further caller takes over one that has nothing left to do, or gets none.  With the last context
+// they are given back but for the one used last, which the next context's first call finds.  (Not a step's side stream, which
+// may be part of a capture.)
 struct PassStream {
   hipStream_t caller, st;
   std::thread::id thread;  // of the caller where its handle means another stream in each thread
   int dev;
   hipEvent_t fork, join;
   std::mutex lock;  // held from the recording of an event to the wait for it: several threads may call on one stream
+  int calls = 0;    // that are using it now
+  uint64_t used = 0;
 };
 constexpr int kPassStreams = 16;
+struct PassPool {
+  std::mutex lock;
+  std::vector<PassStream*> all;
+  int contexts = 0;
+  uint64_t used = 0;
+};
+static PassPool& pass_pool() {
+  static PassPool* const pool = new PassPool;  // never destroyed: the runtime may be gone before this library's statics
+  return *pool;
+}
 
-static PassStream* pass_stream(hipStream_t caller) {
-  static std::mutex lock;
-  static PassStream* all[kPassStreams];  // (never destroyed: the runtime may be gone before this library's statics)
-  static int count = 0;
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
-  const std::thread::id thread = caller == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
-  const std::lock_guard<std::mutex> hold(lock);
-  for (int i = 0; i < count; ++i)
-    if (all[i]->caller == caller && all[i]->dev == dev && all[i]->thread == thread) return all[i];
-  if (count == kPassStreams) return nullptr;
+static bool pass_idle(const PassStream* p) {
+  if (p->calls) return false;
+  const bool idle = hipStreamQuery(p->st) == hipSuccess;
+  (void)hipGetLastError();
+  return idle;
+}
+static PassStream* new_pass_stream(int dev) {
   hipStream_t st = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
   if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess || hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&join, hipEventDisableTiming) != hipSuccess) {
     if (fork) (void)hipEventDestroy(fork);
     if (st) (void)hipStreamDestroy(st);
+    (void)hipGetLastError();
     return nullptr;
   }
   PassStream* p = new PassStream;
-  p->caller = caller; p->st = st; p->thread = thread; p->dev = dev; p->fork = fork; p->join = join;
-  return all[count++] = p;
+  p->st = st; p->dev = dev; p->fork = fork; p->join = join;
+  return p;
+}
+// null: the passes run one after the other
+static PassStream* take_pass_stream(hipStream_t caller) {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  const std::thread::id thread = caller == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
+  PassPool& pool = pass_pool();
+  const std::lock_guard<std::mutex> hold(pool.lock);
+  PassStream* found = nullptr;
+  for (PassStream* p : pool.all)
+    if (p->caller == caller && p->dev == dev && p->thread == thread) found = p;
+  if (!found) {
+    if (pool.all.size() < kPassStreams) {
+      if ((found = new_pass_stream(dev))) pool.all.push_back(found);
+    } else {
+      for (PassStream* p : pool.all)
+        if (p->dev == dev && (!found || p->used < found->used) && pass_idle(p)) found = p;
+    }
+    if (!found) return nullptr;
+    found->caller = caller;
+    found->thread = thread;
+  }
+  ++found->calls;
+  found->used = ++pool.used;
+  return found;
+}
+static void leave_pass_stream(PassStream* p) {
+  const std::lock_guard<std::mutex> hold(pass_pool().lock);
+  --p->calls;
+}
+static void count_contexts(int more) {
+  PassPool& pool = pass_pool();
+  const std::lock_guard<std::mutex> hold(pool.lock);
+  if ((pool.contexts += more) > 0) return;
+  std::vector<PassStream*> kept;
+  for (PassStream* p : pool.all) {
+    if (p->used == pool.used || !pass_idle(p)) {
+      kept.push_back(p);
+      continue;
+    }
+    (void)hipEventDestroy(p->fork);
+    (void)hipEventDestroy(p->join);
+    (void)hipStreamDestroy(p->st);
+    delete p;
+  }
+  pool.all.swap(kept);
 }
 
 extern "C" void mrem_destroy(mrem_ctx* ctx) {
   if (!ctx) return;
   release_side(ctx);
   delete ctx;
+  count_contexts(-1);
 }
 extern "C" int64_t mrem_param_count(const mrem_ctx* ctx) { return ctx ? ctx->layer_stride * ctx->L : -1; }
 extern "C" int64_t mrem_teacher_count(const mrem_ctx* ctx) { return mrem_param_count(ctx); }
@@ -985,8 +1045,7 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
     (void)hipGetLastError();
     fork = false;
   }
-  PassStream* const side = fork ? pass_stream(r.st) : nullptr;
-  if (fork && !side) (void)hipGetLastError();  // the passes run one after the other
+  PassStream* const side = fork ? take_pass_stream(r.st) : nullptr;
   if (side) {
     Run rt = r;
     rt.st = side->st;
@@ -1001,9 +1060,12 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
       teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, nullptr, l, l + 1);
       student_forward(r, params, x_q, per_layer_q, l, l + 1);
     }
-    const std::lock_guard<std::mutex> lock(side->lock);
-    (void)hipEventRecord(side->join, side->st);
-    (void)hipStreamWaitEvent(r.st, side->join, 0);
+    {
+      const std::lock_guard<std::mutex> lock(side->lock);
+      (void)hipEventRecord(side->join, side->st);
+      (void)hipStreamWaitEvent(r.st, side->join, 0);
+    }
+    leave_pass_stream(side);
     return finish(ctx, who);
   }
   if (per_layer_fp) teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp, nullptr);

@@ -103,7 +103,7 @@ def test_two_callers_on_one_context(own_streams):
 
 
 def test_more_callers_streams_than_are_served():
-    """Calls from more streams than the library keeps streams for run one pass after the other."""
+    """Calls from more streams than the library keeps streams for take over those that are idle."""
     import torch
     from paper_2109_15082_amd import binding as B
     mod, x = _forked_module(torch, B)
@@ -114,6 +114,29 @@ def test_more_callers_streams_than_are_served():
             g_fp, g_q = mod.forward(x, x)
         torch.cuda.synchronize()
         assert torch.equal(g_fp, f_fp) and torch.equal(g_q, f_q)
+
+
+def test_streams_stay_sound_when_busy_and_when_given_back():
+    """More callers' streams than the library keeps, all with work queued; then contexts that end, the last one among them."""
+    import gc
+    import torch
+    from paper_2109_15082_amd import binding as B
+    gc.collect()
+    for _ in range(3):
+        mod, x = _forked_module(torch, B)
+        f_fp, f_q = (f.clone() for f in mod.forward(x, x))
+        streams = [torch.cuda.Stream() for _ in range(20)]
+        spaces = [torch.empty_like(mod.workspace) for _ in streams]
+        outs = [mod.new_outputs(16, 64) for _ in streams]
+        torch.cuda.synchronize()
+        for _ in range(2):
+            for st, ws, (fp, q) in zip(streams, spaces, outs):
+                with torch.cuda.stream(st):
+                    B.mrem_module_forward(mod.ctx, mod.params, mod.teacher, mod.teacher_cache, x, x, None, 16, 64, fp, q, ws)
+        mod.close()  # work may still be queued
+        torch.cuda.synchronize()
+        for fp, q in outs:
+            assert torch.equal(fp, f_fp) and torch.equal(q, f_q)
 
 
 # on both sides of the lines from which on the full-precision pass gets a stream of its own
