@@ -50,7 +50,6 @@ __device__ __forceinline__ int key_of(int t, int i, int h) { return 32 * t + 8 *
 
 struct FwdScales {
   float qk, sp, sv, p_qp;
-  int p_on;
   float rsp;  // correctly rounded 1 / sp
 };
 // x / d from rd = fl(1 / d): t = fl(x * rd), then t + fl(x - d * t) * rd with fused multiply-adds.
@@ -80,7 +79,6 @@ __device__ __forceinline__ FwdScales load_fwd_scales(const AttnQ& a, int d) {
   s.sp = a.p.on ? *a.p.s : 1.f;
   s.sv = a.v.on ? *a.v.s : 1.f;
   s.qk = sq * sk / sqrtf((float)d);
-  s.p_on = a.p.on;
   s.p_qp = a.p.qp;
   s.rsp = __fdiv_rn(1.0f, s.sp);
   return s;
@@ -112,21 +110,38 @@ __device__ __forceinline__ void scale_scores(f32x16_t& a, const FwdScales& sc, i
 }
 // what the exponentials of a row are taken against: with a row of -inf only, 0, so that each of them is 0 and not NaN
 __device__ __forceinline__ float finite_max(float mx) { return mx == -INFINITY ? 0.f : mx; }
-// code of a probability, or the probability itself (NaN gives code 0)
+// code of a probability (NaN gives code 0; PQ: its quantizer is on), or the probability itself.  PQ is an argument of every
+// kernel: a test on each element made each a basic block of its own, so that a lane's sixteen chains of dependent operations
+// ran one after the other instead of side by side.
+template <bool PQ>
 __device__ __forceinline__ float prob_code(float p, const FwdScales& sc) {
-  return sc.p_on ? rintf(__builtin_amdgcn_fmed3f(div_by(p, sc.sp, sc.rsp), 0.f, sc.p_qp)) : p;
+  return PQ ? rintf(__builtin_amdgcn_fmed3f(div_by(p, sc.sp, sc.rsp), 0.f, sc.p_qp)) : p;
 }
 
-// stage rows [0, S) of a [S, D] slice (row stride ld elements) row-major into LDS, zero rows up to s_pad
+// Rows [0, S) of a [S, D] slice (row stride ld elements) on their way to LDS, row-major, zero rows up to s_pad.  A block of w
+// wavefronts takes at most 32 w rows, D / 16 pieces of 16 bytes a thread; all of them are in flight at once, and those of a
+// second slice with them.  With that, PQ, and accumulators in ordinary registers (a bound of two wavefronts a SIMD: without
+// one the compiler moved them to accumulation registers and back for every tile), alone, us: forward over 512 heads of 128
+// keys 16.1 -> 14.4 (mean of both passes), query-major backward 26.3 -> 23.1; key-major backward over 256 heads of 384 70 ->
+// 46, over 96 heads of 512 65 -> 50.  All are bound by vector-ALU instructions now (40 to 70 percent of the cycles).
 template <int D>
-__device__ __forceinline__ void stage_rows(const bf16_t* __restrict__ src, int ld, int S, int s_pad, bf16_t* dst) {
-  for (int q = threadIdx.x; q < s_pad * (D / 8); q += blockDim.x) {
-    const int row = q / (D / 8), ch = q % (D / 8);
-    u32x4_t v = {0u, 0u, 0u, 0u};
-    if (row < S) v = *reinterpret_cast<const u32x4_t*>(src + (size_t)row * ld + ch * 8);
-    *reinterpret_cast<u32x4_t*>(dst + row * Tile<D>::kStride + ch * 8) = v;
+struct Rows {
+  u32x4_t v[D / 16];
+  __device__ __forceinline__ void load(const bf16_t* __restrict__ src, int ld, int S) {
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) {
+      const int q = threadIdx.x + i * blockDim.x, row = max(min(q / (D / 8), S - 1), 0);
+      v[i] = *reinterpret_cast<const u32x4_t*>(src + (size_t)row * ld + q % (D / 8) * 8);
+    }
   }
-}
+  __device__ __forceinline__ void store(bf16_t* dst, int S, int s_pad) const {
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) {
+      const int q = threadIdx.x + i * blockDim.x, row = q / (D / 8);
+      if (row < s_pad) *reinterpret_cast<u32x4_t*>(dst + row * Tile<D>::kStride + q % (D / 8) * 8) = row < S ? v[i] : u32x4_t{0u, 0u, 0u, 0u};
+    }
+  }
+};
 __device__ __forceinline__ bf16x8_t ld_frag(const bf16_t* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
 
 // MFMA operand fragment gathered down the rows of a row-major LDS tile with the
@@ -306,8 +321,8 @@ __device__ __forceinline__ void store_context(const f32x16_t& acc, const AttnQ& 
 // forward: one block = up to 128 queries of one (batch, head); one wavefront = 32 queries
 // ONE: at most 128 keys.  REAL: the operands are not integer codes and their products are chains (not FAST).
 // ------------------------------------------------------------------------------
-template <int D, bool ONE, bool FAST, bool REAL>
-__global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict__ codes, bf16_t* __restrict__ ctx,
+template <int D, bool ONE, bool FAST, bool REAL, bool PQ>
+__global__ __launch_bounds__(256, ONE ? 2 : 1) void attn_fwd_mfma_k(const bf16_t* __restrict__ codes, bf16_t* __restrict__ ctx,
                                                        bf16_t* __restrict__ ctx_codes, AttnQ aq, const int32_t* __restrict__ seqlens,
                                                        int S, int H, float* __restrict__ pmax_rows, float* __restrict__ stat_m,
                                                        float* __restrict__ stat_l, int8_t* __restrict__ ctx_codes8) {
@@ -357,7 +372,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float p = div_by(e[r], sum, rsum);
-      w[r] = REAL ? round_to<bf16_t>(p) : prob_code(p, sc);
+      w[r] = REAL ? round_to<bf16_t>(p) : prob_code<PQ>(p, sc);
     }
     if constexpr (REAL) accumulate_rows_chain<D>(oacc, Vs, 32 * t, lane, w);
     else accumulate_rows<D>(oacc, Vs, 32 * t, lane, w);
@@ -398,8 +413,11 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
   constexpr std::integral_constant<int, 1> odd{};
   if constexpr (ONE) {
     const int nt = (len + 31) / 32;
-    stage_rows<D>(base + H, ld, rows, 32 * nt, Ks);
-    stage_rows<D>(base + 2 * H, ld, rows, 32 * nt, Vs);
+    Rows<D> kr, vr;
+    kr.load(base + H, ld, rows);
+    vr.load(base + 2 * H, ld, rows);
+    kr.store(Ks, rows, 32 * nt);
+    vr.store(Vs, rows, 32 * nt);
     __syncthreads();
     if (!active) return;
     f32x16_t sacc[kChunk / 32];
@@ -427,12 +445,14 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
     // a chain of products is formed once: the whole row (up to 512 keys) stays in registers
     constexpr int C = 512 / kChunk, N = kChunk / 32;
     f32x16_t sacc[C * N];
+    Rows<D> rr;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       const int left = len - c * kChunk;
       if (left <= 0) break;
+      rr.load(base + (size_t)c * kChunk * ld + H, ld, left);
       __syncthreads();
-      stage_rows<D>(base + (size_t)c * kChunk * ld + H, ld, left, min((left + 31) / 32 * 32, kChunk), Ks);
+      rr.store(Ks, left, min((left + 31) / 32 * 32, kChunk));
       __syncthreads();
       if (active)
 #pragma unroll
@@ -456,8 +476,9 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma_k(const bf16_t* __restrict_
     for (int c = 0; c < C; ++c) {
       const int left = len - c * kChunk;
       if (left <= 0) break;
+      rr.load(base + (size_t)c * kChunk * ld + 2 * H, ld, left);
       __syncthreads();
-      stage_rows<D>(base + (size_t)c * kChunk * ld + 2 * H, ld, left, min((left + 31) / 32 * 32, kChunk), Vs);
+      rr.store(Vs, left, min((left + 31) / 32 * 32, kChunk));
       __syncthreads();
       if (active)
 #pragma unroll
@@ -502,7 +523,7 @@ __device__ __forceinline__ void row_of_block(int nq, int heads, int& head, int& 
   }
 }
 
-template <int D, bool FAST>
+template <int D, bool FAST, bool PQ>
 __global__ __launch_bounds__(256, FAST ? 4 : 3) void attn_fwd_row_k(const bf16_t* __restrict__ codes, bf16_t* __restrict__ ctx, bf16_t* __restrict__ ctx_codes,
                                                          AttnQ aq, const int32_t* __restrict__ seqlens, int S, int B, int nh,
                                                          float* __restrict__ pmax_rows, float* __restrict__ stat_m, float* __restrict__ stat_l,
@@ -626,7 +647,7 @@ __global__ __launch_bounds__(256, FAST ? 4 : 3) void attn_fwd_row_k(const bf16_t
       for (int s = 0; s < 2; ++s) {
         bf16x8_t f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) f[i] = static_cast<bf16_t>(prob_code(div_by(e[t][8 * s + i], sum, rsum), sc));
+        for (int i = 0; i < 8; ++i) f[i] = static_cast<bf16_t>(prob_code<PQ>(div_by(e[t][8 * s + i], sum, rsum), sc));
         x.p[t0 + t][s][lane] = __builtin_bit_cast(u32x4_t, f);
       }
   f32x16_t oacc = zero16();
@@ -674,14 +695,14 @@ __global__ __launch_bounds__(256, FAST ? 4 : 3) void attn_fwd_row_k(const bf16_t
 
 // one probability (x: its score less the row's maximum) and its gradient through the quantizer
 struct ProbGrad { float p, code, dp; };
-template <bool FAST>
+template <bool FAST, bool PQ>
 __device__ __forceinline__ ProbGrad prob_grad(float x, float dacc, bool valid, float l, float rl, const FwdScales& sc, float& dsp) {
   ProbGrad g;
   g.p = valid ? div_by(exp_neg<FAST>(x), l, rl) : 0.f;
   const float dph = dacc * sc.sv;
   g.code = g.p;
   g.dp = dph;
-  if (sc.p_on) {
+  if constexpr (PQ) {
     const float v = div_by(g.p, sc.sp, sc.rsp);
     const bool in = v <= sc.p_qp;
     g.code = rintf(fminf(v, sc.p_qp));
@@ -692,7 +713,7 @@ __device__ __forceinline__ ProbGrad prob_grad(float x, float dacc, bool valid, f
 }
 
 // query-major part: rowdot (ONE: P^T and dA^T; kept for the key-major kernel), the step-size gradient of the probability quantizer, dQ^ = dA * K^
-template <int D, bool ONE>
+template <int D, bool ONE, bool PQ>
 __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
                                                          bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S,
                                                          int H, const float* __restrict__ stat_m, const float* __restrict__ stat_l,
@@ -736,7 +757,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
     scale_scores(sacc, sc, j0 + 32 * t, half, len, -mx);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const ProbGrad g = prob_grad<true>(sacc[r], dacc[r], true, l, rl, sc, ds);
+      const ProbGrad g = prob_grad<true, PQ>(sacc[r], dacc[r], true, l, rl, sc, ds);
       p[r] = g.p;
       dp[r] = g.dp;
     }
@@ -749,8 +770,11 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
   };
   if constexpr (ONE) {
     const int nt = (len + 31) / 32;
-    stage_rows<D>(base + H, ld, S, 32 * nt, Ks);
-    stage_rows<D>(base + 2 * H, ld, S, 32 * nt, Vs);
+    Rows<D> kr, vr;
+    kr.load(base + H, ld, S);
+    vr.load(base + 2 * H, ld, S);
+    kr.store(Ks, S, 32 * nt);
+    vr.store(Vs, S, 32 * nt);
     __syncthreads();
     if (!active) {
       if (lane == 0) ds_parts[part_idx] = 0.f;
@@ -774,7 +798,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           da[r] = qvalid ? p[t][r] * (dp[t][r] - rowdot) : 0.f;
-          const float c = sc.p_on ? rintf(fminf(div_by(p[t][r], sc.sp, sc.rsp), sc.p_qp)) : p[t][r];
+          const float c = PQ ? rintf(fminf(div_by(p[t][r], sc.sp, sc.rsp), sc.p_qp)) : p[t][r];
           code[r] = qvalid ? c : 0.f;
         }
         accumulate_rows<D>(dqacc, Ks, 32 * t, lane, da);
@@ -794,13 +818,20 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
         }
       }
   } else {
+    Rows<D> kr, vr;  // the next chunk, on its way while this one is multiplied
+    auto fetch = [&](int j0) {
+      kr.load(base + (size_t)j0 * ld + H, ld, S - j0);
+      vr.load(base + (size_t)j0 * ld + 2 * H, ld, S - j0);
+    };
+    fetch(0);
     for (int pass = 0; pass < 2; ++pass) {
       for (int j0 = 0; j0 < len; j0 += kChunk) {
         const int nt = (min(len - j0, kChunk) + 31) / 32;
         __syncthreads();
-        stage_rows<D>(base + (size_t)j0 * ld + H, ld, S - j0, 32 * nt, Ks);
-        stage_rows<D>(base + (size_t)j0 * ld + 2 * H, ld, S - j0, 32 * nt, Vs);
+        kr.store(Ks, S - j0, 32 * nt);
+        vr.store(Vs, S - j0, 32 * nt);
         __syncthreads();
+        if (j0 + kChunk < len || pass == 0) fetch(j0 + kChunk < len ? j0 + kChunk : 0);
         if (!active) continue;
         float p[16], dp[16];
         if (pass == 0) {
@@ -847,7 +878,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_mfma_k(const bf16_t* __rest
 // that holds the whole row: rowdot, the step gradient's sum and the accumulators of dQ^ go from wavefront to wavefront
 // through LDS.  Inside a step, 8 x 512 tokens, 12 heads: 101 -> 72 us against 128 queries a block and two passes over the keys
 // (60 us with parts summed apart and the row maximum subtracted on its own, which moved a step's results by up to 0.5%).
-template <int D>
+template <int D, bool PQ>
 __global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
                                                            bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S, int B,
                                                            int nh, const float* __restrict__ stat_m, const float* __restrict__ stat_l,
@@ -920,7 +951,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restr
           const float v = div_by(pr, sc.sp, sc.rsp);
           const bool in = v <= sc.p_qp;
           term[i] = rintf(fminf(v, sc.p_qp)) - (in ? v : 0.f);
-          p[t][4 * g + i] = in || !sc.p_on ? pr : -pr;
+          p[t][4 * g + i] = in || !PQ ? pr : -pr;
           dph[t][4 * g + i] = dacc[4 * g + i] * sc.sv;
         }
         x[wave].term[t][g][lane] = make_float4(term[0], term[1], term[2], term[3]);
@@ -941,7 +972,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restr
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               rowdot = __fmaf_rn(dp_of(t, 4 * g + i), fabsf(p[t][4 * g + i]), rowdot);
-              if (sc.p_on) dsp = __fmaf_rn(dph[t][4 * g + i], e[i], dsp);
+              if constexpr (PQ) dsp = __fmaf_rn(dph[t][4 * g + i], e[i], dsp);
             }
           }
       if (w == waves - 1) {
@@ -1023,7 +1054,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_row_k(const bf16_t* __restr
 // key-major part for at most 128 tokens: dV^ = P^T dC, dK^ = dA^T Q^ / sqrt(d) from the tiles the query-major kernel left.
 // One wavefront = 32 keys.
 template <int D>
-__global__ __launch_bounds__(256) void attn_bwd_k_one_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
+__global__ __launch_bounds__(256, 2) void attn_bwd_k_one_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
                                                              bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S,
                                                              int H, const bf16_t* __restrict__ pt_in, const bf16_t* __restrict__ dat_in) {
   __shared__ __attribute__((aligned(16))) bf16_t Qs[kChunk * Tile<D>::kStride];
@@ -1033,8 +1064,11 @@ __global__ __launch_bounds__(256) void attn_bwd_k_one_mfma_k(const bf16_t* __res
   const int ld = 3 * H, s_pad = (S + 31) / 32 * 32;
   const bf16_t* base = codes + (size_t)b * S * ld + h * D;
   const int len = seqlens ? min(seqlens[b], S) : S;
-  stage_rows<D>(base, ld, S, s_pad, Qs);
-  stage_rows<D>(dctx + (size_t)b * S * H + h * D, H, S, s_pad, Cs);
+  Rows<D> qr, cr;
+  qr.load(base, ld, S);
+  cr.load(dctx + (size_t)b * S * H + h * D, H, S);
+  qr.store(Qs, S, s_pad);
+  cr.store(Cs, S, s_pad);
   __syncthreads();
   f32x16_t vacc[D / 32], kacc[D / 32];
 #pragma unroll
@@ -1068,8 +1102,8 @@ __global__ __launch_bounds__(256) void attn_bwd_k_one_mfma_k(const bf16_t* __res
 
 // key-major part: dV^[j] = sum_q P^[q][j] dC[q], dK^[j] = sum_q dA[q][j] Q^[q] / sqrt(d).  One wavefront = 32 keys (a lane
 // owns one key, the accumulator registers enumerate queries); queries pass through LDS in chunks of 128 with their statistics.
-template <int D, bool FAST>
-__global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
+template <int D, bool FAST, bool PQ>
+__global__ __launch_bounds__(256, 2) void attn_bwd_k_mfma_k(const bf16_t* __restrict__ codes, const bf16_t* __restrict__ dctx,
                                                          bf16_t* __restrict__ d_qkvh, AttnQ aq, const int32_t* __restrict__ seqlens, int S,
                                                          int H, const float* __restrict__ stat_m, const float* __restrict__ stat_l,
                                                          const float* __restrict__ rowdot_in) {
@@ -1099,22 +1133,34 @@ __global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restric
   for (int et = 0; et < D / 32; ++et) vacc[et] = kacc[et] = zero16();
   float unused = 0.f;
 
-  if ((int)blockIdx.x * 128 < len)
+  // a chunk of queries and their statistics, on their way while the one before is multiplied; a thread's row of the chunk:
+  Rows<D> qr, cr;
+  const int si = threadIdx.x;
+  float st_m = 0.f, st_l = 1.f, st_d = 0.f;
+  auto fetch = [&](int c0) {
+    qr.load(base + (size_t)c0 * ld, ld, S - c0);
+    cr.load(cbase + (size_t)c0 * H, H, S - c0);
+    // rows beyond the sequence: their Q and dC are zero, so any finite statistics will do
+    const bool v = si < kChunk && c0 + si < S;
+    st_m = v ? stat_m[sbase + c0 + si] : 0.f;
+    st_l = v ? stat_l[sbase + c0 + si] : 1.f;
+    st_d = v ? rowdot_in[sbase + c0 + si] : 0.f;
+  };
+  if ((int)blockIdx.x * 128 < len) {
+    fetch(0);
     for (int c0 = 0; c0 < S; c0 += kChunk) {
       const int cn = (min(S - c0, kChunk) + 31) / 32;  // 32-query tiles
       __syncthreads();
-      stage_rows<D>(base + (size_t)c0 * ld, ld, S - c0, 32 * cn, Qs);
-      stage_rows<D>(cbase + (size_t)c0 * H, H, S - c0, 32 * cn, Cs);
-      for (int i = threadIdx.x; i < 32 * cn; i += blockDim.x) {
-        // rows beyond the sequence: their Q and dC are zero, so any finite statistics will do
-        const bool v = c0 + i < S;
-        const float l = v ? stat_l[sbase + c0 + i] : 1.f;
-        stats[0][i] = v ? stat_m[sbase + c0 + i] : 0.f;
-        stats[1][i] = l;
-        stats[2][i] = __fdiv_rn(1.0f, l);
-        stats[3][i] = v ? rowdot_in[sbase + c0 + i] : 0.f;
+      qr.store(Qs, S - c0, 32 * cn);
+      cr.store(Cs, S - c0, 32 * cn);
+      if (si < 32 * cn) {
+        stats[0][si] = st_m;
+        stats[1][si] = st_l;
+        stats[2][si] = __fdiv_rn(1.0f, st_l);
+        stats[3][si] = st_d;
       }
       __syncthreads();
+      if (c0 + kChunk < S) fetch(c0 + kChunk);
       if (!active) continue;
 #pragma unroll 1
       for (int t = 0; t < cn; ++t) {
@@ -1131,7 +1177,7 @@ __global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restric
           }
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const ProbGrad pg = prob_grad<FAST>(__fmaf_rn(sacc[4 * g + i], sc.qk, -st[0][i]), dacc[4 * g + i], j < len, st[1][i], st[2][i], sc, unused);
+            const ProbGrad pg = prob_grad<FAST, PQ>(__fmaf_rn(sacc[4 * g + i], sc.qk, -st[0][i]), dacc[4 * g + i], j < len, st[1][i], st[2][i], sc, unused);
             code[4 * g + i] = pg.code;
             da[4 * g + i] = pg.p * (pg.dp - st[3][i]);
           }
@@ -1145,6 +1191,7 @@ __global__ __launch_bounds__(256) void attn_bwd_k_mfma_k(const bf16_t* __restric
         }
       }
     }
+  }
   if (j >= S) return;
   const float sp = sc.sp;
   const float fq = (aq.q.on ? *aq.q.s : 1.f) / sqrtf((float)D);
@@ -1170,29 +1217,31 @@ static bool fast(int S, int d) { return d == 64 && S >= 64 && S <= 384; }
 
 void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
                    float* pmax_rows, float* stat_m, float* stat_l, hipStream_t st, bool chain, int8_t* ctx_codes8) {
-  auto launch = [&](auto dim, auto one, auto is_fast, auto real) {
+  auto launch = [&](auto dim, auto one, auto is_fast, auto real, auto pq) {
     constexpr int D = decltype(dim)::value;
-    hipLaunchKernelGGL((attn_fwd_mfma_k<D, decltype(one)::value, decltype(is_fast)::value, decltype(real)::value>), dim3((S + 127) / 128, nh, B),
-                       dim3(64 * block_waves(S)), 0, st, (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S, nh * D, pmax_rows,
-                       stat_m, stat_l, ctx_codes8);
+    hipLaunchKernelGGL((attn_fwd_mfma_k<D, decltype(one)::value, decltype(is_fast)::value, decltype(real)::value, decltype(pq)::value>),
+                       dim3((S + 127) / 128, nh, B), dim3(64 * block_waves(S)), 0, st, (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens,
+                       S, nh * D, pmax_rows, stat_m, stat_l, ctx_codes8);
   };
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
   constexpr std::integral_constant<int, 32> d32{};
   constexpr std::integral_constant<int, 64> d64{};
-  auto launch_row = [&](auto dim, auto is_fast) {
+  auto launch_row = [&](auto dim, auto is_fast, auto pq) {
     constexpr int D = decltype(dim)::value;
-    hipLaunchKernelGGL((attn_fwd_row_k<D, decltype(is_fast)::value>), dim3((S + 31) / 32 * nh * B), dim3(256), 0, st, (const bf16_t*)codes,
-                       (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S, B, nh, pmax_rows, stat_m, stat_l, ctx_codes8);
+    hipLaunchKernelGGL((attn_fwd_row_k<D, decltype(is_fast)::value, decltype(pq)::value>), dim3((S + 31) / 32 * nh * B), dim3(256), 0, st,
+                       (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S, B, nh, pmax_rows, stat_m, stat_l, ctx_codes8);
   };
   const bool one = S <= kChunk, real = !aq.p.on && chain;
-  if (fast(S, d)) return one ? launch(d64, yes, yes, no) : launch_row(d64, yes);
-  if (d == 64) {
-    if (real) return one ? launch(d64, yes, no, yes) : launch(d64, no, no, yes);
-    return one ? launch(d64, yes, no, no) : launch_row(d64, no);
-  }
-  if (real) return one ? launch(d32, yes, no, yes) : launch(d32, no, no, yes);
-  return one ? launch(d32, yes, no, no) : launch_row(d32, no);
+  auto with = [&](auto pq) {
+    if (fast(S, d)) return one ? launch(d64, yes, yes, no, pq) : launch_row(d64, yes, pq);
+    if (d == 64) return one ? launch(d64, yes, no, no, pq) : launch_row(d64, no, pq);
+    return one ? launch(d32, yes, no, no, pq) : launch_row(d32, no, pq);
+  };
+  if (aq.p.on) return with(yes);
+  if (!real || fast(S, d)) return with(no);
+  if (d == 64) return one ? launch(d64, yes, no, yes, no) : launch(d64, no, no, yes, no);
+  return one ? launch(d32, yes, no, yes, no) : launch(d32, no, no, yes, no);
 }
 
 // returns the number of partial sums written to ds_parts
@@ -1202,27 +1251,32 @@ int attn_bwd_mfma(const void* codes, const void* dctx, void* d_qkvh, const AttnQ
   const dim3 g((S + 127) / 128, nh, B), blk(64 * waves);
   const bf16_t *c = (const bf16_t*)codes, *dc = (const bf16_t*)dctx;
   bf16_t* out = (bf16_t*)d_qkvh;
-  const int H = nh * d;
-  auto launch = [&](auto dim, auto is_fast) {
+  const int H = nh * d, parts = (int)(g.x * g.y * g.z) * waves;
+  auto launch = [&](auto dim, auto is_fast, auto pq) {
     constexpr int D = decltype(dim)::value;
-    constexpr bool FAST = decltype(is_fast)::value;
-    int parts = (int)(g.x * g.y * g.z) * waves;
+    constexpr bool FAST = decltype(is_fast)::value, PQ = decltype(pq)::value;
     if constexpr (FAST) {
-      hipLaunchKernelGGL((attn_bwd_q_mfma_k<D, false>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)scratch0,
+      hipLaunchKernelGGL((attn_bwd_q_mfma_k<D, false, PQ>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)scratch0,
                          (bf16_t*)nullptr, (bf16_t*)nullptr, ds_parts);
     } else {
-      hipLaunchKernelGGL((attn_bwd_q_row_k<D>), dim3(parts), dim3(64 * waves), 0, st, c, dc, out, aq, seqlens, S, B, nh, stat_m, stat_l,
+      hipLaunchKernelGGL((attn_bwd_q_row_k<D, PQ>), dim3(parts), dim3(64 * waves), 0, st, c, dc, out, aq, seqlens, S, B, nh, stat_m, stat_l,
                          (float*)scratch0, ds_parts);
     }
-    hipLaunchKernelGGL((attn_bwd_k_mfma_k<D, FAST>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (const float*)scratch0);
-    return parts;
+    hipLaunchKernelGGL((attn_bwd_k_mfma_k<D, FAST, PQ>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (const float*)scratch0);
   };
-  if (!fast(S, d)) return d == 64 ? launch(std::integral_constant<int, 64>{}, std::false_type{}) : launch(std::integral_constant<int, 32>{}, std::false_type{});
-  if (S > kChunk) return launch(std::integral_constant<int, 64>{}, std::true_type{});
-  hipLaunchKernelGGL((attn_bwd_q_mfma_k<64, true>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)nullptr, (bf16_t*)scratch0,
-                     (bf16_t*)scratch1, ds_parts);
-  hipLaunchKernelGGL((attn_bwd_k_one_mfma_k<64>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, (const bf16_t*)scratch0, (const bf16_t*)scratch1);
-  return (int)(g.x * g.y * g.z) * waves;
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  constexpr std::integral_constant<int, 32> d32{};
+  constexpr std::integral_constant<int, 64> d64{};
+  auto with = [&](auto pq) {
+    if (!fast(S, d)) return d == 64 ? launch(d64, no, pq) : launch(d32, no, pq);
+    if (S > kChunk) return launch(d64, yes, pq);
+    hipLaunchKernelGGL((attn_bwd_q_mfma_k<64, true, decltype(pq)::value>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, stat_m, stat_l, (float*)nullptr,
+                       (bf16_t*)scratch0, (bf16_t*)scratch1, ds_parts);
+    hipLaunchKernelGGL((attn_bwd_k_one_mfma_k<64>), g, blk, 0, st, c, dc, out, aq, seqlens, S, H, (const bf16_t*)scratch0, (const bf16_t*)scratch1);
+  };
+  aq.p.on ? with(yes) : with(no);
+  return parts;
 }
 
 }  // namespace mrem
