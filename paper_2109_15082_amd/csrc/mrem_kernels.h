@@ -156,7 +156,7 @@ int quant_bwd_reduce(int dt, const void* d_q, const void* a, int64_t n, QArg q, 
 // y = LN(x + r) * gamma + beta ; optional codes of y ; mean/rstd saved
 void ln_fwd(int dt, const void* x, const void* r, const float* gamma, const float* beta, void* y, void* ycodes, QArg q,
             float* mu, float* rstd, int T, int H, float eps, hipStream_t st, int8_t* ycodes8 = nullptr);
-// dy = d_a + d_q * inside(a_q) + 2 * loss_scale * (a_q - loss_ref)   (each of d_a, d_q, loss_ref may be null; the
+// dy = d_a + d_q * inside(a_q) + 2 * loss_scale * (a_q - loss_ref)   (d_a and d_q, or loss_ref, may be null; the
 // last term is the gradient of the squared-error term of Eq. 3, and the sum of (a_q - loss_ref)^2 is returned in
 // the partials).
 // dr = LN backward of dy through LN(x + r); partials[nparts][3H+2]: dgamma, dbeta, colsum(dr), ds, squared error
