@@ -499,24 +499,38 @@ void student_forward(const Run& r, const float* params, const void* x_q, void* p
 // ordered products take 3 to 5 times as long (both passes of six layers of 1024 over 4000 tokens: 7264 against 2611 us).
 constexpr int kChainTokens = 512;
 
-// Full-precision module.  With calib_params != null the ranges of the inputs of the eight activation quantizers of
-// every layer are taken on the way, into `parts`; calib_jobs collects what turns them into steps and offsets.
-// Layers [l0, l1) (l1 < 0: to the last layer).
-void teacher_forward(const Run& r, const float* teacher, const void* cache, const void* x_fp, void* per_layer_fp, float* calib_params,
-                     int l0 = 0, int l1 = -1, float* parts = nullptr, std::vector<CalibJob>* calib_jobs = nullptr) {
+// Where a calibration's partial ranges go and what turns them into steps and offsets; `first`, `last`: of the module's layers.
+struct Calibration {
+  float* params;  // of the layer that the pass runs
+  float* parts;
+  std::vector<CalibJob>* jobs;
+  bool first, last;
+};
+
+// Full-precision module, layers [l0, l1) (l1 < 0: to the last layer).  With `cal` (one layer) the ranges of the inputs of the
+// activation quantizers are taken on the way, by the kernels that write them where these can: a pass of its own for each
+// (5 to 7 us, 18 with the GELU) was a fifth of a calibration of six layers of 1024 over 4096 tokens (1198 -> 990 us).
+void teacher_forward(const Run& r, const float* teacher, const void* cache, const void* x_fp, void* per_layer_fp, int l0 = 0, int l1 = -1,
+                     Calibration* cal = nullptr) {
   const mrem_ctx* c = r.c;
   const size_t es = dt_size(c->dt);
   const int H = c->H, F = c->F, T = r.T;
   const size_t slice = (size_t)T * H * es;
   const float qp_s = (float)((1 << (c->cfg.a_bits > 0 ? c->cfg.a_bits - 1 : 1)) - 1);
   const float qp_u = (float)((1 << (c->cfg.a_bits > 0 ? c->cfg.a_bits : 1)) - 1);
-  auto job = [&](int l, int idx, int nparts, int mode) {
-    float* base = calib_params + c->layer_stride * l;
-    calib_jobs->push_back(CalibJob{parts, base + c->foff[MREM_F_S_A] + idx, base + c->foff[MREM_F_Z_A] + idx, nparts, mode, mode == 0 ? qp_s : qp_u});
-    parts += 3 * nparts;
+  // quantizer idx of the layer, or of the one above it
+  auto job = [&](int idx, int nparts, int mode, bool above = false) {
+    float* base = cal->params + (above ? c->layer_stride : 0);
+    cal->jobs->push_back(CalibJob{cal->parts, base + c->foff[MREM_F_S_A] + idx, base + c->foff[MREM_F_Z_A] + idx, nparts, mode, mode == 0 ? qp_s : qp_u});
+    cal->parts += 3 * nparts;
   };
-  auto calib = [&](int l, int idx, const void* a, int dt, int rows, int cols, int mode) { job(l, idx, absminmax(dt, a, rows, cols, 1, cols, parts, r.st), mode); };
-  const bool chain = calib_params || T < kChainTokens;
+  auto calib = [&](int idx, const void* a, int dt, int rows, int cols, int mode) { job(idx, absminmax(dt, a, rows, cols, 1, cols, cal->parts, r.st), mode); };
+  // ranges from the products' epilogues: the partials of the smallest tiles (32 x 32) fit the area, with those of the other kernels
+  auto tiles = [&](int n) { return (size_t)((T + 31) / 32) * ((n + 31) / 32); };
+  const bool attn_mfma = attn_mfma_ok(c->dt, c->d);
+  const bool ranges = cal && c->dt == DT_BF16 && H % 32 == 0 &&
+                      3 * (3 * tiles(3 * H) + tiles(F) + 2 * (size_t)T + 2 * (size_t)attn_fwd_mfma_parts(r.B, r.S, c->nh, c->d) + 2 * kCalibParts) <= r.p.partials_per_layer;
+  const bool chain = cal || T < kChainTokens;
   if (l1 < 0) l1 = c->L;
   for (int l = l0; l < l1; ++l) {
     const float* base = teacher + c->layer_stride * l;
@@ -526,48 +540,59 @@ void teacher_forward(const Run& r, const float* teacher, const void* cache, cons
     void* f = (char*)per_layer_fp + slice * l;
     Epilogue e;
     e.chain = chain;
-    if (calib_params) calib(l, 0, x, c->dt, T, H, 0);
+    int nparts = 0;
+    auto with_range = [&](const Epilogue& plain, int cols) {
+      Epilogue er = plain;
+      if (ranges) { er.range = cal->parts; er.range_cols = cols; er.range_parts = &nparts; }
+      return er;
+    };
+    if (cal && (cal->first || !ranges)) calib(0, x, c->dt, T, H, 0);
     e.bias = base + c->foff[MREM_F_B_QKV];
-    gemm_nt(c->dt, x, H, W(0), H, r.at(r.p.t_qkv), 3 * H, T, 3 * H, H, e, r.st, r.prof);
-    if (calib_params) {
-      const int n = absminmax(c->dt, r.at(r.p.t_qkv), T, H, 3, 3 * H, parts, r.st);
-      job(l, 1, n, 0);
-      job(l, 2, n, 0);
-      job(l, 4, n, 0);
+    gemm_nt(c->dt, x, H, W(0), H, r.at(r.p.t_qkv), 3 * H, T, 3 * H, H, with_range(e, H), r.st, r.prof);
+    if (cal) {
+      if (!ranges) nparts = absminmax(c->dt, r.at(r.p.t_qkv), T, H, 3, 3 * H, cal->parts, r.st);
+      job(1, nparts, 0);
+      job(2, nparts, 0);
+      job(4, nparts, 0);
     }
-    if (attn_mfma_ok(c->dt, c->d))
-      attn_fwd_mfma(r.at(r.p.t_qkv), r.at(r.p.t_ctx), nullptr, AttnQ(), r.seqlens, r.B, r.S, c->nh, c->d,
-                    calib_params ? r.at<float>(r.p.pmax) : nullptr, nullptr, nullptr, r.st, chain);
+    const bool attn_ranges = cal && attn_mfma;  // (24 floats a head and query in the area, against 12.4 that these take at most)
+    if (attn_mfma)
+      nparts = attn_fwd_mfma(r.at(r.p.t_qkv), r.at(r.p.t_ctx), nullptr, AttnQ(), r.seqlens, r.B, r.S, c->nh, c->d, attn_ranges ? cal->parts : nullptr, nullptr,
+                             nullptr, r.st, chain);
     else
       attn_fwd(c->dt, r.at(r.p.t_qkv), r.at(r.p.t_ctx), nullptr, AttnQ(), r.seqlens, r.B, r.S, c->nh, c->d,
-               calib_params ? r.at<float>(r.p.pmax) : nullptr, r.st);
-    if (calib_params) {
-      calib(l, 3, r.at(r.p.pmax), DT_F32, 1, r.B * c->nh * r.S, 1);
-      calib(l, 5, r.at(r.p.t_ctx), c->dt, T, H, 0);
+               cal ? r.at<float>(r.p.pmax) : nullptr, r.st);
+    if (attn_ranges) {
+      job(3, nparts, 1);
+      job(5, nparts, 0);
+    } else if (cal) {
+      calib(3, r.at(r.p.pmax), DT_F32, 1, r.B * c->nh * r.S, 1);
+      calib(5, r.at(r.p.t_ctx), c->dt, T, H, 0);
     }
     e.bias = base + c->foff[MREM_F_B_O];
     gemm_nt(c->dt, r.at(r.p.t_ctx), H, W(1), H, r.at(r.p.t_o), H, T, H, H, e, r.st, r.prof);
     timed(r, "ln_fwd_k", (double)T * H * 3 * es, [&] {
       ln_fwd(c->dt, x, r.at(r.p.t_o), base + c->foff[MREM_F_LN1_G], base + c->foff[MREM_F_LN1_B], r.at(r.p.t_x1), nullptr, QArg(),
-             r.at<float>(r.p.t_mu), r.at<float>(r.p.t_rstd), T, H, c->cfg.ln_eps, r.st);
+             r.at<float>(r.p.t_mu), r.at<float>(r.p.t_rstd), T, H, c->cfg.ln_eps, r.st, nullptr, ranges ? cal->parts : nullptr);
     });
-    if (calib_params) calib(l, 6, r.at(r.p.t_x1), c->dt, T, H, 0);
+    if (ranges) job(6, T, 0);
+    else if (cal) calib(6, r.at(r.p.t_x1), c->dt, T, H, 0);
     e.bias = base + c->foff[MREM_F_B_1];
-    if (calib_params) {
-      // pre-activation first, so that the range of gelu(u) can be measured on unrounded values
-      gemm_nt(c->dt, r.at(r.p.t_x1), H, W(2), H, r.at(r.p.t_g), F, T, F, H, e, r.st, r.prof);
-      job(l, 7, gelu_minmax(c->dt, r.at(r.p.t_g), (int64_t)T * F, parts, r.st), 2);
-    } else {
-      e.gelu = 1;
-      gemm_nt(c->dt, r.at(r.p.t_x1), H, W(2), H, r.at(r.p.t_g), F, T, F, H, e, r.st, r.prof);
-      e.gelu = 0;
-    }
+    e.gelu = !cal || ranges;
+    gemm_nt(c->dt, r.at(r.p.t_x1), H, W(2), H, r.at(r.p.t_g), F, T, F, H, with_range(e, 0), r.st, r.prof);
+    e.gelu = 0;
+    // (the range of gelu(u) is that of its unrounded values)
+    if (ranges) job(7, nparts, 2);
+    else if (cal) job(7, gelu_minmax(c->dt, r.at(r.p.t_g), (int64_t)T * F, cal->parts, r.st), 2);
     e.bias = base + c->foff[MREM_F_B_2];
     gemm_nt(c->dt, r.at(r.p.t_g), F, W(3), F, r.at(r.p.t_y), H, T, H, F, e, r.st, r.prof);
+    // the layer's output is the next one's input
+    const bool above = ranges && !cal->last;
     timed(r, "ln_fwd_k", (double)T * H * 3 * es, [&] {
       ln_fwd(c->dt, r.at(r.p.t_x1), r.at(r.p.t_y), base + c->foff[MREM_F_LN2_G], base + c->foff[MREM_F_LN2_B], f, nullptr, QArg(),
-             r.at<float>(r.p.t_mu), r.at<float>(r.p.t_rstd), T, H, c->cfg.ln_eps, r.st);
+             r.at<float>(r.p.t_mu), r.at<float>(r.p.t_rstd), T, H, c->cfg.ln_eps, r.st, nullptr, above ? cal->parts : nullptr);
     });
+    if (above) job(0, T, 0, true);
   }
 }
 
@@ -968,8 +993,8 @@ extern "C" mrem_status mrem_module_calibrate(mrem_ctx* ctx, float* params, const
     for (int l = 0; l < ctx->L; ++l) {
       Run rl = r;
       rl.c = &one;
-      teacher_forward(rl, teacher + ctx->layer_stride * l, (const char*)teacher_cache + (size_t)ctx->tc_layer_stride * l * es, x,
-                      bufs[l & 1], params + ctx->layer_stride * l, 0, -1, r.at<float>(r.p.partials) + r.p.partials_per_layer * l, &jobs);
+      Calibration cal{params + ctx->layer_stride * l, r.at<float>(r.p.partials) + r.p.partials_per_layer * l, &jobs, l == 0, l + 1 == ctx->L};
+      teacher_forward(rl, teacher + ctx->layer_stride * l, (const char*)teacher_cache + (size_t)ctx->tc_layer_stride * l * es, x, bufs[l & 1], 0, -1, &cal);
       x = bufs[l & 1];
     }
     calib_finalize(jobs.data(), (int)jobs.size(), r.st);
@@ -1057,7 +1082,7 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
     prepare_weights(r, params, false);
     // layer by layer in turn, so that both streams have work from the start
     for (int l = 0; l < ctx->L; ++l) {
-      teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, nullptr, l, l + 1);
+      teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, l, l + 1);
       student_forward(r, params, x_q, per_layer_q, l, l + 1);
     }
     {
@@ -1068,7 +1093,7 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
     leave_pass_stream(side);
     return finish(ctx, who);
   }
-  if (per_layer_fp) teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp, nullptr);
+  if (per_layer_fp) teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp);
   if (per_layer_q) {
     prepare_weights(r, params, false);
     student_forward(r, params, x_q, per_layer_q);
@@ -1193,13 +1218,13 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
     // the two passes are enqueued layer by layer in turn, so that both streams have work from the
     // start also when the caller's queue was empty
     for (int l = 0; l < ctx->L; ++l) {
-      teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, nullptr, l, l + 1);
+      teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, l, l + 1);
       if (l == 1 && !few) (void)hipStreamWaitEvent(r.st, ctx->ev_codes, 0);
       student_forward(r, params, x_in, per_layer_q, l, l + 1, mix_fp, x_q, lambda);
     }
     (void)hipEventRecord(ctx->ev_join, ctx->side);
   } else {
-    teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp, nullptr);
+    teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp);
     zero_gradient_slots(r, grads, false);
     prepare_weights(r, params, true);
     student_forward(r, params, x_in, per_layer_q, 0, -1, mix_fp, x_q, lambda);

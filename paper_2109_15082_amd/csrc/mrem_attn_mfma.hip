@@ -284,10 +284,18 @@ __device__ __forceinline__ float sum_of_parts(const float (&part)[16]) {
   }
   return (x[0] + x[1]) + (x[2] + x[3]);
 }
+// a wavefront's partial ranges: of its rows' largest probabilities, and behind all of those of its part of the context
+__device__ __forceinline__ void store_ranges(float* __restrict__ ranges, int part, int nparts, const MinMax& pmax, const MinMax& ctx, int lane) {
+  const MinMax p = pmax.wave(), c = ctx.wave();
+  if (lane == 0) {
+    p.store(ranges + (size_t)part * 3);
+    c.rounded<bf16_t>().store(ranges + ((size_t)nparts + part) * 3);
+  }
+}
 // 32 columns of the context of a lane's query (16 of them here, from element `o` on) and their codes
 template <bool FAST>
 __device__ __forceinline__ void store_context(const f32x16_t& acc, const AttnQ& aq, const FwdScales& sc, int len, size_t o, bf16_t* __restrict__ ctx,
-                                              bf16_t* __restrict__ ctx_codes, int8_t* __restrict__ ctx_codes8) {
+                                              bf16_t* __restrict__ ctx_codes, int8_t* __restrict__ ctx_codes8, MinMax& range) {
   const float os = sc.sp * sc.sv;
   QuantParam qc5 = {aq.c.on ? *aq.c.s : 1.f, 0.f, aq.c.qn, aq.c.qp, aq.c.on, 0.f};
   qc5.rs = quant_reciprocal(qc5.s);
@@ -301,6 +309,8 @@ __device__ __forceinline__ void store_context(const f32x16_t& acc, const AttnQ& 
       v[i] = len <= 0 ? NAN : FAST ? __fmul_rn(a, os) : __fmul_rn(__fmul_rn(a, sc.sp), sc.sv);
     }
     store4(ctx + o + 8 * g, v[0], v[1], v[2], v[3]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) range.add(v[i]);  // (dead where nobody asks)
     if (ctx_codes) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -324,7 +334,7 @@ __device__ __forceinline__ void store_context(const f32x16_t& acc, const AttnQ& 
 template <int D, bool ONE, bool FAST, bool REAL, bool PQ>
 __global__ __launch_bounds__(256, ONE ? 2 : 1) void attn_fwd_mfma_k(const bf16_t* __restrict__ codes, bf16_t* __restrict__ ctx,
                                                        bf16_t* __restrict__ ctx_codes, AttnQ aq, const int32_t* __restrict__ seqlens,
-                                                       int S, int H, float* __restrict__ pmax_rows, float* __restrict__ stat_m,
+                                                       int S, int H, float* __restrict__ ranges, float* __restrict__ stat_m,
                                                        float* __restrict__ stat_l, int8_t* __restrict__ ctx_codes8) {
   __shared__ __attribute__((aligned(16))) bf16_t Ks[kChunk * Tile<D>::kStride];
   __shared__ __attribute__((aligned(16))) bf16_t Vs[kChunk * Tile<D>::kStride];
@@ -337,6 +347,7 @@ __global__ __launch_bounds__(256, ONE ? 2 : 1) void attn_fwd_mfma_k(const bf16_t
   const FwdScales sc = load_fwd_scales(aq, D);
 
   const int q0 = blockIdx.x * 128 + wave * 32;
+  const int waves = blockDim.x >> 6, nparts = gridDim.x * nh * gridDim.z * waves, part_idx = ((b * nh + h) * gridDim.x + blockIdx.x) * waves + wave;
   const bool active = q0 < S;
   const int q = q0 + (lane & 31);
   const int qc = q < S ? q : S - 1;
@@ -419,7 +430,10 @@ __global__ __launch_bounds__(256, ONE ? 2 : 1) void attn_fwd_mfma_k(const bf16_t
     kr.store(Ks, rows, 32 * nt);
     vr.store(Vs, rows, 32 * nt);
     __syncthreads();
-    if (!active) return;
+    if (!active) {
+      if (ranges) store_ranges(ranges, part_idx, nparts, MinMax(), MinMax(), lane);
+      return;
+    }
     f32x16_t sacc[kChunk / 32];
 #pragma unroll
     for (int t = 0; t < kChunk / 32; ++t)
@@ -485,18 +499,23 @@ __global__ __launch_bounds__(256, ONE ? 2 : 1) void attn_fwd_mfma_k(const bf16_t
         for (int t = 0; t < N; ++t)
           if (32 * t < left) weigh(sacc[N * c + t], t, rsum);
     }
-    if (!active) return;
+    if (!active) {
+      if (ranges) store_ranges(ranges, part_idx, nparts, MinMax(), MinMax(), lane);
+      return;
+    }
   }
   const size_t stat_idx = ((size_t)b * nh + h) * S + q;
+  MinMax pmax, range;
   if (half == 0 && q < S) {
     if (stat_m) { stat_m[stat_idx] = mx; stat_l[stat_idx] = sum; }
-    if (pmax_rows) pmax_rows[stat_idx] = 1.0f / sum;  // the largest exponential of a row is exp(0) = 1
+    pmax.add(1.0f / sum);  // the largest exponential of a row is exp(0) = 1
   }
   if (q < S) {
     const size_t orow = ((size_t)b * S + q) * H + h * D;
 #pragma unroll
-    for (int et = 0; et < D / 32; ++et) store_context<FAST>(oacc[et], aq, sc, len, orow + 32 * et + 4 * half, ctx, ctx_codes, ctx_codes8);
+    for (int et = 0; et < D / 32; ++et) store_context<FAST>(oacc[et], aq, sc, len, orow + 32 * et + 4 * half, ctx, ctx_codes, ctx_codes8, range);
   }
+  if (ranges) store_ranges(ranges, part_idx, nparts, pmax, range, lane);
 }
 
 // ------------------------------------------------------------------------------
@@ -526,7 +545,7 @@ __device__ __forceinline__ void row_of_block(int nq, int heads, int& head, int& 
 template <int D, bool FAST, bool PQ>
 __global__ __launch_bounds__(256, FAST ? 4 : 3) void attn_fwd_row_k(const bf16_t* __restrict__ codes, bf16_t* __restrict__ ctx, bf16_t* __restrict__ ctx_codes,
                                                          AttnQ aq, const int32_t* __restrict__ seqlens, int S, int B, int nh,
-                                                         float* __restrict__ pmax_rows, float* __restrict__ stat_m, float* __restrict__ stat_l,
+                                                         float* __restrict__ ranges, float* __restrict__ stat_m, float* __restrict__ stat_l,
                                                          int8_t* __restrict__ ctx_codes8) {
   // tiles of a wavefront (up to 384 or 512 keys); rows of V in LDS at a time (FAST: four blocks a compute unit); 16-byte pieces of those per thread
   constexpr int TW = FAST ? 3 : 4, RC = 32 * TW, CH = RC * (D / 8) / 256;
@@ -670,14 +689,15 @@ __global__ __launch_bounds__(256, FAST ? 4 : 3) void attn_fwd_row_k(const bf16_t
       store_v();
     }
   }
-  if (q >= S) return;
+  if (wave >= D / 32) return;
   const size_t stat_idx = (size_t)head * S + q;
-  if (wave == 0 && half == 0) {
-    if (stat_m) { stat_m[stat_idx] = mx; stat_l[stat_idx] = sum; }
-    if (pmax_rows) pmax_rows[stat_idx] = 1.0f / sum;  // the largest exponential of a row is exp(0) = 1
+  MinMax pmax, range;
+  if (q < S) {
+    if (wave == 0 && half == 0 && stat_m) { stat_m[stat_idx] = mx; stat_l[stat_idx] = sum; }
+    pmax.add(1.0f / sum);  // the largest exponential of a row is exp(0) = 1
+    store_context<FAST>(oacc, aq, sc, len, ((size_t)b * S + q) * H + h * D + 32 * wave + 4 * half, ctx, ctx_codes, ctx_codes8, range);
   }
-  if (wave < D / 32)
-    store_context<FAST>(oacc, aq, sc, len, ((size_t)b * S + q) * H + h * D + 32 * wave + 4 * half, ctx, ctx_codes, ctx_codes8);
+  if (ranges) store_ranges(ranges, (int)blockIdx.x * (D / 32) + wave, (int)gridDim.x * (D / 32), pmax, range, lane);
 }
 
 // ------------------------------------------------------------------------------
@@ -1215,13 +1235,17 @@ static int block_waves(int S) { return S >= 128 ? 4 : (S + 31) / 32; }
 
 static bool fast(int S, int d) { return d == 64 && S >= 64 && S <= 384; }
 
-void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
-                   float* pmax_rows, float* stat_m, float* stat_l, hipStream_t st, bool chain, int8_t* ctx_codes8) {
+// partial ranges that the forward leaves (at most: rows of more than 128 keys may have fewer)
+int attn_fwd_mfma_parts(int B, int S, int nh, int d) { return max((S + 127) / 128 * block_waves(S), (S + 31) / 32 * (d / 32)) * nh * B; }
+
+int attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
+                  float* ranges, float* stat_m, float* stat_l, hipStream_t st, bool chain, int8_t* ctx_codes8) {
   auto launch = [&](auto dim, auto one, auto is_fast, auto real, auto pq) {
     constexpr int D = decltype(dim)::value;
     hipLaunchKernelGGL((attn_fwd_mfma_k<D, decltype(one)::value, decltype(is_fast)::value, decltype(real)::value, decltype(pq)::value>),
                        dim3((S + 127) / 128, nh, B), dim3(64 * block_waves(S)), 0, st, (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens,
-                       S, nh * D, pmax_rows, stat_m, stat_l, ctx_codes8);
+                       S, nh * D, ranges, stat_m, stat_l, ctx_codes8);
+    return (S + 127) / 128 * nh * B * block_waves(S);
   };
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
@@ -1230,10 +1254,11 @@ void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& a
   auto launch_row = [&](auto dim, auto is_fast, auto pq) {
     constexpr int D = decltype(dim)::value;
     hipLaunchKernelGGL((attn_fwd_row_k<D, decltype(is_fast)::value, decltype(pq)::value>), dim3((S + 31) / 32 * nh * B), dim3(256), 0, st,
-                       (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S, B, nh, pmax_rows, stat_m, stat_l, ctx_codes8);
+                       (const bf16_t*)codes, (bf16_t*)ctx, (bf16_t*)ctx_codes, aq, seqlens, S, B, nh, ranges, stat_m, stat_l, ctx_codes8);
+    return (S + 31) / 32 * nh * B * (D / 32);
   };
   const bool one = S <= kChunk, real = !aq.p.on && chain;
-  auto with = [&](auto pq) {
+  auto with = [&](auto pq) -> int {
     if (fast(S, d)) return one ? launch(d64, yes, yes, no, pq) : launch_row(d64, yes, pq);
     if (d == 64) return one ? launch(d64, yes, no, no, pq) : launch_row(d64, no, pq);
     return one ? launch(d32, yes, no, no, pq) : launch_row(d32, no, pq);

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <stdint.h>
 
 #include "mrem_quant_math.h"
@@ -76,6 +77,42 @@ __device__ __forceinline__ float wave_min(float v) {
   for (int o = kWave / 2; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, kWave));
   return v;
 }
+
+// The range of some values, for a calibration (a NaN counts for nothing).
+struct MinMax {
+  float mn = FLT_MAX, mx = -FLT_MAX;
+  __device__ __forceinline__ void add(float v) {
+    mn = fminf(mn, v);
+    mx = fmaxf(mx, v);
+  }
+  __device__ __forceinline__ void add(const MinMax& o) {
+    mn = fminf(mn, o.mn);
+    mx = fmaxf(mx, o.mx);
+  }
+  // over the wavefront
+  __device__ __forceinline__ MinMax wave() const {
+    MinMax r;
+    r.mn = wave_min(mn);
+    r.mx = wave_max(mx);
+    return r;
+  }
+  // of the values as they are stored: rounding keeps their order
+  template <class T>
+  __device__ __forceinline__ MinMax rounded() const {
+    MinMax r = *this;
+    if (mn <= mx) {
+      r.mn = round_to<T>(mn);
+      r.mx = round_to<T>(mx);
+    }
+    return r;
+  }
+  // one partial range: max|a|, min(a), max(a)
+  __device__ __forceinline__ void store(float* out) const {
+    out[0] = mn <= mx ? fmaxf(fabsf(mn), fabsf(mx)) : 0.f;
+    out[1] = mn;
+    out[2] = mx;
+  }
+};
 
 // Sum over a block of up to 1024 threads (blockDim.x multiple of 64). Result valid
 // in every thread.  `scratch` is 17 floats of LDS.  Fixed order: deterministic.

@@ -5,8 +5,6 @@
 #include "mrem_common.h"
 #include "mrem_kernels.h"
 
-#include <float.h>
-
 namespace mrem {
 
 // ------------------------------------------------------------------------------
@@ -446,8 +444,9 @@ template <class T, int NCH, LnQuant Q>
 __global__ __launch_bounds__(256) void ln_fwd_k(const T* __restrict__ x, const T* __restrict__ r, const float* __restrict__ gamma,
                          const float* __restrict__ beta, T* __restrict__ y, T* __restrict__ ycodes, QArg qa,
                          float* __restrict__ mu_out, float* __restrict__ rstd_out, int T_, int H, float eps,
-                         int8_t* __restrict__ ycodes8) {
+                         int8_t* __restrict__ ycodes8, float* __restrict__ ranges) {
   const QuantParam q = load_q(qa);
+  MinMax range;
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
   if (row >= T_) return;
@@ -499,6 +498,12 @@ __global__ __launch_bounds__(256) void ln_fwd_k(const T* __restrict__ x, const T
 #pragma unroll
       for (int j = 0; j < 8; ++j) o[j] = (v[i][j] - mean) * rstd * rg[i].get(j) + rbeta[i].get(j);
       store8(y + (size_t)row * H + c * 8, o);
+      if constexpr (Q == LN_NONE) {
+        if (ranges) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) range.add(o[j]);
+        }
+      }
       if constexpr (Q != LN_NONE) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) o[j] = code_of<T, Q == LN_ON>(round_to<T>(o[j]), q);
@@ -507,12 +512,18 @@ __global__ __launch_bounds__(256) void ln_fwd_k(const T* __restrict__ x, const T
       }
     }
   }
+  if constexpr (Q == LN_NONE) {
+    if (ranges) {
+      range = range.wave();
+      if (lane == 0) range.rounded<T>().store(ranges + (size_t)row * 3);
+    }
+  }
 }
 void ln_fwd(int dt, const void* x, const void* r, const float* gamma, const float* beta, void* y, void* ycodes, QArg q,
-            float* mu, float* rstd, int T_, int H, float eps, hipStream_t st, int8_t* ycodes8) {
+            float* mu, float* rstd, int T_, int H, float eps, hipStream_t st, int8_t* ycodes8, float* ranges) {
 #define MREM_LN_FWD_Q(NCH, Q)                                                                                                    \
   MREM_DISPATCH(dt, MREM_LAUNCH((ln_fwd_k<T, NCH, Q>), dim3((T_ + 3) / 4), dim3(256), 0, st, (const T*)x, (const T*)r, gamma, beta, \
-                                (T*)y, (T*)ycodes, q, mu, rstd, T_, H, eps, ycodes8))
+                                (T*)y, (T*)ycodes, q, mu, rstd, T_, H, eps, ycodes8, ranges))
 #define MREM_LN_FWD(NCH)                                  \
   do {                                                    \
     const LnQuant lq = ln_quant(ycodes, q);               \
@@ -1167,7 +1178,7 @@ struct Range {
 // blockIdx.y: one of several column sections of `cols` values (a multiple of 8) with their own partials; rows = 1 takes any
 // number of columns.  Bound by memory traffic: 8 values a load and one division for them (with a load and a 64-bit division
 // per value, a launch a section and a finishing launch a quantizer, 96 launches in all, the ranges of six layers of 1024
-// over 4096 tokens took 830 of 1774 us; the whole call takes 1177 us now).
+// over 4096 tokens took 830 of 1774 us; most are taken by the kernels that write the tensors now, and the call takes 990 us).
 template <class T>
 __global__ __launch_bounds__(256) void absminmax_k(const T* __restrict__ a, int rows, int cols, int ld, float* __restrict__ partials) {
   __shared__ float red[17];

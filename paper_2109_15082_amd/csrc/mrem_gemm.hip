@@ -69,6 +69,26 @@ __device__ __forceinline__ float epilogue_apart(float acc, float cs, bool has_be
   if (has_bias) v = v + bias;
   return v;
 }
+// The ranges of a block's groups of columns (`groups` slots of lds, filled before; a slot holds them and its section) go out
+// as one partial a section.
+struct RangeSlot { MinMax r; int sec; };
+__device__ __forceinline__ void store_ranges(const RangeSlot* lds, int groups, const Epilogue& e, int N) {
+  __syncthreads();
+  const int sections = e.range_cols ? N / e.range_cols : 1;
+  for (int s = threadIdx.x; s < sections; s += blockDim.x) {
+    MinMax r;
+    for (int i = 0; i < groups; ++i)
+      if (lds[i].sec == s) r.add(lds[i].r);
+    r.store(e.range + ((size_t)s * gridDim.x + blockIdx.x) * 3);
+  }
+}
+__device__ __forceinline__ void put_range(RangeSlot* lds, int slot, const MinMax& r, int n, const Epilogue& e, int lane) {
+  const MinMax w = r.wave();
+  if (lane == 0) {
+    lds[slot].r = e.gelu ? w : w.rounded<bf16_t>();
+    lds[slot].sec = e.range_cols ? n / e.range_cols : 0;
+  }
+}
 template <class TO>
 __device__ __forceinline__ void epilogue_store(TO* C, int ldc, int m, int n, float acc, const Epilogue& e, const EpiVals& ev) {
   float v = acc * (ev.alpha * (e.col_scale ? e.col_scale[n] : 1.f));

@@ -185,6 +185,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_chain_k(const bf16_t* __res
   wait_vmcnt<0>();
   const float alpha = e.alpha ? *e.alpha : 1.f;
   const float beta = (e.beta ? *e.beta : 0.f) + e.beta_alpha * alpha;
+  MinMax range[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int n = n0 + wn + 16 * j + 4 * quarter;
@@ -207,10 +208,18 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_chain_k(const bf16_t* __res
         const float t = e.beta && e.row_vec ? cv[r] + e.row_vec[m] : cv[r];
         float v = epilogue_apart(acc[i][j][r], cs[r], e.beta != nullptr, beta, t, e.bias != nullptr, cb[r]);
         if (e.gelu) v = gelu_t<bf16_t>(round_to<bf16_t>(v));
+        if (e.range) range[j].add(v);
         out[r] = static_cast<bf16_t>(v);
       }
       *reinterpret_cast<bf16x4_t*>(C + (size_t)m * ldc + n) = out;
     }
+  }
+  if (e.range) {
+    RangeSlot* const slots = reinterpret_cast<RangeSlot*>(smem);
+    __syncthreads();  // nobody reads operands any more
+#pragma unroll
+    for (int j = 0; j < NT; ++j) put_range(slots, wave * NT + j, range[j], n0 + wn + 16 * j, e, lane);
+    store_ranges(slots, NW * NT, e, N);
   }
 }
 
@@ -219,6 +228,7 @@ static void launch_chain_tile(const void* A, int lda, const void* B, int ldb, vo
                               hipStream_t st) {
   constexpr int BM = 16 * MT * WM, BN = 16 * NT * WN;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  if (e.range) *e.range_parts = tiles_m * tiles_n;
   MREM_LAUNCH((gemm_chain_k<MT, NT, WM, WN, AHEAD>), dim3(tiles_m * tiles_n), dim3(64 * WM * WN), 0, st, (const bf16_t*)A, lda, (const bf16_t*)B,
               ldb, (bf16_t*)C, ldc, M, N, K, e, tiles_m, tiles_n);
 }

@@ -421,11 +421,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
   const float alpha = e.alpha ? *e.alpha : 1.f;
   const float beta = (e.beta ? *e.beta : 0.f) + e.beta_alpha * alpha;
   const bool split = !EDGE && gridDim.y > 1, lead = EDGE || blockIdx.y == 0;
-  auto write_out = [&](auto with_row, auto with_gelu, auto with_split, auto apart) {
+  auto write_out = [&](auto with_row, auto with_gelu, auto with_split, auto apart, auto with_range) {
+    constexpr bool RANGE = decltype(with_range)::value;
+    if constexpr (RANGE) __syncthreads();  // nobody reads operands or partial sums any more
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-      const int n = n0 + wn * WN + j * 32 + (lane & 31);
-      if (EDGE && n >= N) continue;
+      int n = n0 + wn * WN + j * 32 + (lane & 31);
+      const bool column = !EDGE || n < N;
+      if (!RANGE && !column) continue;
+      if (!column) n = N - 1;
+      MinMax range;
       const float cs = alpha * (e.col_scale ? e.col_scale[n] : 1.f);
       float cb = (e.bias && lead) ? e.bias[n] : 0.f;
       const float cv = (e.beta && e.col_vec && lead) ? e.col_vec[n] : 0.f;
@@ -439,7 +444,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
         for (int r = 0; r < 16; ++r) {
           if (KG > 1 && !BY_ROWS && (r >> 3) != kg) continue;
           const int dm = 8 * (r >> 2) + (r & 3);
-          if (EDGE && mb + dm >= M) continue;
+          if (EDGE && (mb + dm >= M || (RANGE && !column))) continue;
           float v;
           if constexpr (decltype(apart)::value) {
             const float t = decltype(with_row)::value ? cv + e.row_vec[mb + dm] : cv;
@@ -452,24 +457,34 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
             atomicAdd(reinterpret_cast<float*>(out) + (size_t)dm * ldc, v);
           } else {
             if constexpr (decltype(with_gelu)::value) v = gelu_t<TO>(round_to<TO>(v));
+            if constexpr (RANGE) range.add(v);
             stf(out, (size_t)dm * ldc, v);
           }
         }
       }
+      if constexpr (RANGE) {
+        // each group's range leaves the registers before the next group
+        put_range(reinterpret_cast<RangeSlot*>(smem_dl), wave * NT + j, range, n0 + wn * WN + j * 32, e, lane);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
+    if constexpr (RANGE) store_ranges(reinterpret_cast<RangeSlot*>(smem_dl), NW * NT, e, N);
   };
   const bool row_term = e.beta && e.row_vec && lead;
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
   if constexpr (EDGE && !AT && !BT && !I8) {
-    if (e.apart && e.gelu) return row_term ? write_out(yes, yes, no, yes) : write_out(no, yes, no, yes);
-    if (e.apart) return row_term ? write_out(yes, no, no, yes) : write_out(no, no, no, yes);
+    if (e.apart && e.gelu) return row_term ? write_out(yes, yes, no, yes, no) : write_out(no, yes, no, yes, no);
+    if (e.apart) return row_term ? write_out(yes, no, no, yes, no) : write_out(no, no, no, yes, no);
+  }
+  if constexpr (!AT && !BT && !I8) {
+    if (e.range) return e.gelu ? write_out(no, yes, no, no, yes) : write_out(no, no, no, no, yes);
   }
   if constexpr (sizeof(TO) == 4 && !EDGE) {
-    if (split) return row_term ? write_out(yes, no, yes, no) : write_out(no, no, yes, no);
+    if (split) return row_term ? write_out(yes, no, yes, no, no) : write_out(no, no, yes, no, no);
   }
-  if (e.gelu) return row_term ? write_out(yes, yes, no, no) : write_out(no, yes, no, no);
-  return row_term ? write_out(yes, no, no, no) : write_out(no, no, no, no);
+  if (e.gelu) return row_term ? write_out(yes, yes, no, no, no) : write_out(no, yes, no, no, no);
+  return row_term ? write_out(yes, no, no, no, no) : write_out(no, no, no, no, no);
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool AT, bool BT, int STAGES, int RB, class TO, bool I8 = false, int MINB = 1, int KG = 1, bool EDGE = false>
@@ -487,6 +502,7 @@ static void launch_dl(const void* A, int lda, const void* B, int ldb, void* C, i
     configured_dev.store(dev);
   }
   const int tiles_m = EDGE ? (M + BM - 1) / BM : M / BM, tiles_n = EDGE ? (N + BN - 1) / BN : N / BN;
+  if (e.range) *e.range_parts = tiles_m * tiles_n;
   if (tl_launch_events.e0) {
     hipExtLaunchKernelGGL((gemm_dl_k<BM, BN, WAVES_M, WAVES_N, AT, BT, STAGES, RB, TO, I8, MINB, KG, EDGE>), dim3(tiles_m * tiles_n, k_splits),
                           dim3(NTHREADS), lds, st, tl_launch_events.e0, tl_launch_events.e1, 0, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C, ldc, M, N,

@@ -210,11 +210,9 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
   // epilogue: out = acc * (alpha * col_scale[n]) + beta * (col_vec[n] + row_vec[m]) + bias[n]
   const float alpha = e.alpha ? *e.alpha : 1.f;
   const float beta = (e.beta ? *e.beta : 0.f) + e.beta_alpha * alpha;
-  auto write_out = [&](auto inside, auto with_row, auto with_gelu, auto apart) {
-#pragma unroll
-    for (int j = 0; j < 2 * NT; ++j) {
-      const int n = n0 + j / NT * HN + wn * WN + j % NT * 32 + (lane & 31);
-      if (!decltype(inside)::value && n >= N) continue;
+  auto write_out = [&](auto inside, auto with_row, auto with_gelu, auto apart, auto with_range) {
+    auto write_group = [&](auto j_, int n, MinMax& range) {
+      constexpr int j = decltype(j_)::value;
       const float cs = alpha * (e.col_scale ? e.col_scale[n] : 1.f);
       float cb = e.bias ? e.bias[n] : 0.f;
       const float cv = (e.beta && e.col_vec) ? e.col_vec[n] : 0.f;
@@ -237,21 +235,37 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
             if constexpr (decltype(with_row)::value) v += beta * e.row_vec[mb + dm];
           }
           if constexpr (decltype(with_gelu)::value) v = gelu_t<TO>(round_to<TO>(v));
+          if constexpr (decltype(with_range)::value) range.add(v);
           stf(out, (size_t)dm * ldc, v);
         }
       }
-    }
+    };
+    if constexpr (decltype(with_range)::value) __syncthreads();  // nobody reads operands any more
+    static_for<2 * NT>([&](auto j) {
+      const int n = n0 + j.value / NT * HN + wn * WN + j.value % NT * 32;
+      MinMax range;
+      if (decltype(inside)::value || n + (lane & 31) < N) write_group(j, n + (lane & 31), range);
+      if constexpr (decltype(with_range)::value) {
+        // each group's range leaves the registers before the next group (93 registers spilled without the barrier)
+        put_range(reinterpret_cast<RangeSlot*>(smem_quad), wave * 2 * NT + j.value, range, n, e, lane);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+    if constexpr (decltype(with_range)::value) store_ranges(reinterpret_cast<RangeSlot*>(smem_quad), 16 * NT, e, N);
   };
   const bool row_term = e.beta && e.row_vec;
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
   auto choose = [&](auto inside) {
     if constexpr (EDGE && !AT && !BT && !I8) {
-      if (e.apart && e.gelu) return row_term ? write_out(inside, yes, yes, yes) : write_out(inside, no, yes, yes);
-      if (e.apart) return row_term ? write_out(inside, yes, no, yes) : write_out(inside, no, no, yes);
+      if (e.apart && e.gelu) return row_term ? write_out(inside, yes, yes, yes, no) : write_out(inside, no, yes, yes, no);
+      if (e.apart) return row_term ? write_out(inside, yes, no, yes, no) : write_out(inside, no, no, yes, no);
     }
-    if (e.gelu) return row_term ? write_out(inside, yes, yes, no) : write_out(inside, no, yes, no);
-    return row_term ? write_out(inside, yes, no, no) : write_out(inside, no, no, no);
+    if constexpr (!AT && !BT && !I8 && !PAIR) {
+      if (e.range) return e.gelu ? write_out(inside, no, yes, no, yes) : write_out(inside, no, no, no, yes);
+    }
+    if (e.gelu) return row_term ? write_out(inside, yes, yes, no, no) : write_out(inside, no, yes, no, no);
+    return row_term ? write_out(inside, yes, no, no, no) : write_out(inside, no, no, no, no);
   };
   // (a test per stored value costs a tenth of 4096 x 4096 x 1024)
   if (!EDGE || (m0 + BM <= M && n0 + BN <= N)) choose(yes);
@@ -314,6 +328,7 @@ static void launch_quad(const void* A, int lda, const void* B, int ldb, void* C,
   static std::atomic<int> configured_dev{-1};
   const size_t lds = quad_lds<BM>(reinterpret_cast<const void*>(&gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR>), configured_dev);
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  if (e.range) *e.range_parts = tiles_m * tiles_n;
   MREM_LAUNCH((gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR>), dim3(tiles_m * tiles_n), dim3(512), lds, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C,
               ldc, M, N, K, e, tiles_m, tiles_n);
 }

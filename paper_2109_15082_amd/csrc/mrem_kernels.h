@@ -45,6 +45,12 @@ struct Epilogue {
   float beta_alpha = 0.f;
   int chain = 0;
   int apart = 0;
+  // range (not with transposes, int8 codes or fp32): the products' blocks also leave the range of what they store (with gelu:
+  // of its values before they are rounded) as partials, as absminmax does; range_cols: section width, a multiple of 32 (0: one
+  // section); *range_parts: how many blocks
+  float* range = nullptr;
+  int range_cols = 0;
+  int* range_parts = nullptr;
 };
 
 // Timing of product launches with the pair of HIP events that a launch itself carries (measurement aid).
@@ -153,9 +159,10 @@ int quant_bwd(int dt, const void* d_q, const void* a, void* d_out, int64_t n, QA
 // partial sums of d_q * (code - v*inside) only (layer-0 input quantizer)
 int quant_bwd_reduce(int dt, const void* d_q, const void* a, int64_t n, QArg q, float* partials, hipStream_t st);
 
-// y = LN(x + r) * gamma + beta ; optional codes of y ; mean/rstd saved
+// y = LN(x + r) * gamma + beta ; optional codes of y ; mean/rstd saved ; ranges (without codes, may be null): the range of y,
+// T partials as absminmax leaves them
 void ln_fwd(int dt, const void* x, const void* r, const float* gamma, const float* beta, void* y, void* ycodes, QArg q,
-            float* mu, float* rstd, int T, int H, float eps, hipStream_t st, int8_t* ycodes8 = nullptr);
+            float* mu, float* rstd, int T, int H, float eps, hipStream_t st, int8_t* ycodes8 = nullptr, float* ranges = nullptr);
 // dy = d_a + d_q * inside(a_q) + 2 * loss_scale * (a_q - loss_ref)   (d_a and d_q, or loss_ref, may be null; the
 // last term is the gradient of the squared-error term of Eq. 3, and the sum of (a_q - loss_ref)^2 is returned in
 // the partials).
@@ -217,8 +224,11 @@ void attn_bwd(int dt, const void* codes, const void* dctx, void* d_qkvh, const A
 // fp32 values)
 // and returns the number of partial sums written to ds_parts (at most B*nh*S).  chain: as in Epilogue.
 bool attn_mfma_ok(int dt, int d);
-void attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
-                   float* pmax_rows, float* stat_m, float* stat_l, hipStream_t st, bool chain, int8_t* ctx_codes8 = nullptr);
+// ranges (may be null): partial ranges, as absminmax leaves them, of the rows' largest probabilities and behind them of the
+// context; the return value is how many of either.
+int attn_fwd_mfma(const void* codes, void* ctx, void* ctx_codes, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
+                  float* ranges, float* stat_m, float* stat_l, hipStream_t st, bool chain, int8_t* ctx_codes8 = nullptr);
+int attn_fwd_mfma_parts(int B, int S, int nh, int d);
 int attn_bwd_mfma(const void* codes, const void* dctx, void* d_qkvh, const AttnQ& aq, const int32_t* seqlens, int B, int S, int nh, int d,
                   const float* stat_m, const float* stat_l, void* scratch0, void* scratch1, float* ds_parts, hipStream_t st);
 
