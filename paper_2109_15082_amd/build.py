@@ -11,6 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libmrem.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["mrem_api.hip", "mrem_elem.hip", "mrem_gemm.hip", "mrem_attn.hip", "mrem_attn_mfma.hip"]
+# the products' kernels take longest to compile: one unit for each operand form of mrem_gemm.hip, and the rest of it
+PARTS = {"mrem_gemm.hip": [0, 1, 2, 3, 4]}
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
@@ -26,9 +28,10 @@ def build(verbose: bool = True) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     cc = hipcc()
 
-    def compile_one(src: str) -> str:
-        obj = os.path.join(OBJ_DIR, src.replace(".hip", ".o"))
-        cmd = [cc, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    def compile_one(unit) -> str:
+        src, part = unit
+        obj = os.path.join(OBJ_DIR, src.replace(".hip", f"{'' if part is None else part}.o"))
+        cmd = [cc, *FLAGS, *([] if part is None else [f"-DMREM_GEMM_PART={part}"]), "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
@@ -39,8 +42,9 @@ def build(verbose: bool = True) -> str:
                 print("\n".join(lines), file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(5, len(SOURCES))) as ex:
-        objs = list(ex.map(compile_one, SOURCES))
+    units = sorted(((s, p) for s in SOURCES for p in PARTS.get(s, [None])), key=lambda u: u[0] not in PARTS)  # the longest first
+    with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
+        objs = list(ex.map(compile_one, units))
     cmd = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", OUT]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -14,12 +14,22 @@
 
 #include <vector>
 
+// Compiled as a whole, or in five parts: 1 to 4 hold the tiles of one operand form each, 0 the rest.
+#if !defined(MREM_GEMM_PART)
+#define MREM_GEMM_REST 1
+#elif MREM_GEMM_PART == 0
+#define MREM_GEMM_REST 1
+#else
+#define MREM_GEMM_REST 0
+#endif
+
 namespace mrem {
 
 // ---- optional timing of every product launch with HIP events (measurement aid) ----
 // The records live in a GemmProfile that the caller (a context) owns.  Return codes of event calls are
 // not looked at here: the runtime keeps the last error, and every entry point of the library ends by
 // reading it (hipGetLastError).
+#if MREM_GEMM_REST
 thread_local LaunchEvents tl_launch_events;
 
 void gemm_profile_begin(GemmProfile* p) {
@@ -55,6 +65,8 @@ int gemm_profile_end(GemmProfile* p, double ms[2], double flops[2], int64_t laun
   p->recs.clear();
   return rc;
 }
+
+#endif
 
 struct EpiVals {
   float alpha, beta;
@@ -208,6 +220,7 @@ namespace mrem {
 // no tile of 128 x 128 and no stage of the contraction is partly filled
 static bool whole_tiles(int M, int N, int K) { return M % 128 == 0 && N % 128 == 0 && K % kBK == 0; }
 
+#if MREM_GEMM_REST
 static void gemm_launch(int dt, int a_t, int b_t, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K,
                         const Epilogue& e, hipStream_t st);
 
@@ -232,6 +245,7 @@ bool gemm_i8_ok(const void* A, int lda, const void* B, int ldb, int M, int N, in
   return M % 128 == 0 && N % 128 == 0 && K % 128 == 0 && lda % 16 == 0 && ldb % 16 == 0 &&
          (reinterpret_cast<uintptr_t>(A) & 15) == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0;
 }
+#endif
 // int8 mode: two int8 codes travel as one 16-bit element, so leading dimensions and the contraction
 // length are halved.
 // Which tile serves a product, by how many compute units (256) the output's tiles can occupy.  Times of single
@@ -263,7 +277,7 @@ bool gemm_i8_ok(const void* A, int lda, const void* B, int ldb, int M, int N, in
 //     the second block fills the barrier and epilogue gaps of the first (6144 x 768 x 3072: 51.6 against 57.3 for
 //     128 x 64).  Sizes with partly filled tiles take 128 x 64 here (2310 x 3072 x 768: 22.2 against 23.1).
 template <bool AT, bool BT, class TO, bool I8>
-static void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
+void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                             hipStream_t st, int splits) {
   auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const bool whole = whole_tiles(M, N, K);
@@ -302,6 +316,26 @@ static void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void
   }
   return launch_dl<128, 128, 2, 2, AT, BT, 4, 64, TO, I8, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
 }
+#if defined(MREM_GEMM_PART)
+#define MREM_TILES(AT, BT, TO, I8)                                                                                                              \
+  template void launch_dl_tiles<AT, BT, TO, I8>(const void*, int, const void*, int, void*, int, int, int, int, const Epilogue&, hipStream_t, int)
+#if MREM_GEMM_PART == 0
+extern MREM_TILES(false, false, bf16_t, false);
+extern MREM_TILES(false, false, bf16_t, true);
+extern MREM_TILES(false, true, bf16_t, false);
+extern MREM_TILES(true, true, float, false);
+#elif MREM_GEMM_PART == 1
+MREM_TILES(false, false, bf16_t, false);
+#elif MREM_GEMM_PART == 2
+MREM_TILES(false, false, bf16_t, true);
+#elif MREM_GEMM_PART == 3
+MREM_TILES(false, true, bf16_t, false);
+#elif MREM_GEMM_PART == 4
+MREM_TILES(true, true, float, false);
+#endif
+#endif
+
+#if MREM_GEMM_REST
 static void gemm_i8_launch(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                            hipStream_t st) {
   launch_dl_tiles<false, false, bf16_t, true>(A, lda / 2, B, ldb / 2, C, ldc, M, N, K / 2, e, st, 1);
@@ -392,5 +426,7 @@ static void gemm_launch(int dt, int a_t, int b_t, const void* A, int lda, const 
     launch_dl_tiles<false, false, bf16_t, false>(A, lda, B, ldb, C, ldc, M, N, K, ee, st, 1);
   }
 }
+
+#endif
 
 }  // namespace mrem
