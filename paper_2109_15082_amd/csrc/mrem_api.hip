@@ -543,7 +543,7 @@ void teacher_forward(const Run& r, const float* teacher, const void* cache, cons
     int nparts = 0;
     auto with_range = [&](const Epilogue& plain, int cols) {
       Epilogue er = plain;
-      if (ranges) { er.range = cal->parts; er.range_cols = cols; er.range_parts = &nparts; }
+      if (ranges) { er.range = cal->parts; er.range_cols = cols; er.blocks = &nparts; }
       return er;
     };
     if (cal && (cal->first || !ranges)) calib(0, x, c->dt, T, H, 0);
@@ -1291,34 +1291,50 @@ extern "C" mrem_status mrem_rem_step(mrem_ctx* ctx, int64_t T, int64_t N, int64_
   GemmProfile* prof = &ctx->prof;
   // one launch for both weight sets: the frozen ones rounded to the storage type; codes and the dequantized copy of the trained ones
   WeightJob wj[2];
-  wj[0].w = w; wj[0].sw = sw; wj[0].codes = ws + p.wcodes; wj[0].what = ws + p.what; wj[0].zcorr = nullptr; wj[0].codes8 = nullptr;
+  // Whole tiles multiply int8 codes (4096 x 4096 x 1024: 20 us, 31 on bf16 ones); those of the weights take the place of their
+  // bf16 codes, those of the input that of its gradient, which is written behind the product.
+  int8_t* const wcodes8 = reinterpret_cast<int8_t*>(ws + p.wcodes);
+  int8_t* const xcodes8 = reinterpret_cast<int8_t*>(ws + p.dxh);
+  const bool i8 = dt == DT_BF16 && gemm_i8_ok(xcodes8, (int)K, wcodes8, (int)K, (int)T, (int)N, (int)K);
+  wj[0].w = w; wj[0].sw = sw; wj[0].codes = i8 ? nullptr : ws + p.wcodes; wj[0].what = ws + p.what; wj[0].zcorr = nullptr;
+  wj[0].codes8 = i8 ? wcodes8 : nullptr;
   wj[0].N = (int)N; wj[0].K = (int)K;
   wj[1] = wj[0];
-  wj[1].w = w_fp; wj[1].sw = nullptr; wj[1].codes = ws + p.wt; wj[1].what = nullptr;
+  wj[1].w = w_fp; wj[1].sw = nullptr; wj[1].codes = ws + p.wt; wj[1].codes8 = nullptr; wj[1].what = nullptr;
   weight_prepare(dt, wj, 2, ctx->cfg.w_bits, st);
   // full-precision product  y = a W^T  on the original weights
   gemm_nt(dt, a_fp, (int)K, ws + p.wt, (int)K, y_fp, (int)N, (int)T, (int)N, (int)K, Epilogue(), st, prof);
   // quantized product  y^ = Q(a) Q(w)^T: codes of both operands, the two steps in the epilogue
   QArg qa;
   qa.on = 1; qa.s = sa; qa.qp = (float)((1 << (ctx->cfg.a_bits - 1)) - 1); qa.qn = -qa.qp;
-  act_quantize(dt, a_q, ws + p.xcodes, T * K, qa, st);
+  act_quantize(dt, a_q, ws + p.xcodes, T * K, qa, st, i8 ? xcodes8 : nullptr);
+  // Eq. 2 and its gradient with respect to y^, by the product's kernel where it can (4096 x 4096 x 1024: 33 us for what took 31 on bf16 codes and 16 in a pass over three tensors)
+  const float scale = ctx->cfg.loss_mean ? 1.0f / (float)((double)T * (double)N) : 1.0f;
+  int nl = 0, ns = 0;
   Epilogue e;
   e.alpha = sa; e.col_scale = sw;
-  gemm_nt(dt, ws + p.xcodes, (int)K, ws + p.wcodes, (int)K, y_q, (int)N, (int)T, (int)N, (int)K, e, st, prof);
-  // Eq. 2 and its gradient with respect to y^
-  const float scale = ctx->cfg.loss_mean ? 1.0f / (float)((double)T * (double)N) : 1.0f;
-  const int nl = mse_grad(dt, y_q, y_fp, ws + p.dy, T * N, scale, parts, st);
+  const bool fused_loss = dt == DT_BF16 && post_ok((int)T, (int)N, (int)(i8 ? K / 2 : K));
+  if (fused_loss) {
+    e.post = POST_MSE; e.post_in = y_fp; e.post_out = ws + p.dy; e.post_parts = parts; e.post_scale = scale; e.blocks = &nl;
+  }
+  if (i8) gemm_i8(xcodes8, (int)K, wcodes8, (int)K, y_q, (int)N, (int)T, (int)N, (int)K, e, st, prof);
+  else gemm_nt(dt, ws + p.xcodes, (int)K, ws + p.wcodes, (int)K, y_q, (int)N, (int)T, (int)N, (int)K, e, st, prof);
+  if (!fused_loss) nl = mse_grad(dt, y_q, y_fp, ws + p.dy, T * N, scale, parts, st);
   // straight-through backward: d w^ = dy^T a^ (the update kernel applies the mask and forms ds_w), d a^ = dy W^ for ds_a
   Epilogue ew;
   ew.alpha = sa; ew.out_f32 = 1;
   gemm(dt, 1, 1, ws + p.dy, (int)N, ws + p.xcodes, (int)K, grads, (int)K, (int)N, (int)K, (int)T, ew, st, prof);
-  gemm(dt, 0, 1, ws + p.dy, (int)N, ws + p.what, (int)K, ws + p.dxh, (int)K, (int)T, (int)K, (int)N, Epilogue(), st, prof);
-  const int ns = quant_bwd_reduce(dt, ws + p.dxh, a_q, T * K, qa, parts + 2048, st);
+  Epilogue ex;
+  const bool fused_step = dt == DT_BF16 && post_ok((int)T, (int)K, (int)N);
+  if (fused_step) {
+    ex.post = POST_STEP; ex.post_in = a_q; ex.post_parts = parts + 2048; ex.post_q = qa; ex.blocks = &ns;
+  }
+  gemm(dt, 0, 1, ws + p.dy, (int)N, ws + p.what, (int)K, ws + p.dxh, (int)K, (int)T, (int)K, (int)N, ex, st, prof);
+  if (!fused_step) ns = quant_bwd_reduce(dt, ws + p.dxh, a_q, T * K, qa, parts + 2048, st);
   ReduceJob jobs[2];
   jobs[0].partials = parts; jobs[0].nparts = nl; jobs[0].width = 1; jobs[0].begin = 0; jobs[0].len = 1; jobs[0].out = loss_out; jobs[0].scale = scale;
   jobs[1].partials = parts + 2048; jobs[1].nparts = ns; jobs[1].width = 1; jobs[1].begin = 0; jobs[1].len = 1; jobs[1].out = grads + N * K + N;
-  reduce_jobs(jobs, 2, st);
-  // AdamW on w (decay) and s_w, then on s_a (no decay, floor)
+  // AdamW on w (decay) and s_w, and on s_a (no decay, floor) behind its gradient
   const AdamArg a = adam_arg(ctx, step_index, lr);
   AdamJob aj;
   aj.w = w; aj.sw = sw; aj.g_w = grads; aj.g_sw = grads + N * K; aj.m_w = adam_m; aj.v_w = adam_v; aj.m_sw = adam_m + N * K; aj.v_sw = adam_v + N * K;
@@ -1326,8 +1342,7 @@ extern "C" mrem_status mrem_rem_step(mrem_ctx* ctx, int64_t T, int64_t N, int64_
   adam_matrix(&aj, 1, ctx->cfg.w_bits, a, grads_out != nullptr, ctx->cfg.per_channel ? 0 : 1, st);
   AdamArg nodecay = a;
   nodecay.wd = 0.f;
-  const VecJob vj{N * K + N, 1, 1};
-  adam_vector(vec, grads, adam_m, adam_v, &vj, 1, nodecay, st);
+  reduce_and_step(jobs[0], jobs[1], sa, adam_m + N * K + N, adam_v + N * K + N, nodecay, st);
   return finish(ctx, who);
 }
 

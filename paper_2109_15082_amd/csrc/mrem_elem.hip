@@ -751,6 +751,11 @@ struct ReduceJobTable {
   int unit_start[kMaxReduceJobs + 1];  // prefix sums of work units (16 columns each; 1 for a scalar)
   int n;
 };
+__device__ __forceinline__ float reduce_scalar(const ReduceJob& jb, float* scratch) {
+  float v = 0.f;
+  for (int p = threadIdx.x; p < jb.nparts; p += blockDim.x) v += jb.partials[(size_t)p * jb.width + jb.begin];
+  return block_sum(v, scratch) * jb.scale;
+}
 __global__ __launch_bounds__(256) void reduce_jobs_k(ReduceJobTable t) {
   // 256 threads = 16 columns x 16 groups of partial rows; the group sums are added in group
   // order, so the result does not depend on scheduling.
@@ -761,10 +766,8 @@ __global__ __launch_bounds__(256) void reduce_jobs_k(ReduceJobTable t) {
   const ReduceJob jb = t.j[ji];
   const int unit = blockIdx.x - t.unit_start[ji];
   if (jb.len == 1) {
-    float v = 0.f;
-    for (int p = threadIdx.x; p < jb.nparts; p += blockDim.x) v += jb.partials[(size_t)p * jb.width + jb.begin];
-    v = block_sum(v, sred);
-    if (threadIdx.x == 0) jb.out[0] = v * jb.scale;
+    const float v = reduce_scalar(jb, sred);
+    if (threadIdx.x == 0) jb.out[0] = v;
     return;
   }
   const int col = threadIdx.x & 15, grp = threadIdx.x >> 4;
@@ -1373,6 +1376,23 @@ void adam_matrix(const AdamJob* jobs, int njobs, int bits, AdamArg a, int write_
     MREM_LAUNCH(adam_matrix_k, dim3(rows), dim3(256), 0, st, tab, qp, on, a, write_grads, (on && tied) ? 1 : 0);
     if (on && tied) MREM_LAUNCH(adam_tied_steps_k, dim3(tab.njobs), dim3(256), 0, st, tab, a);
   }
+}
+
+// a scalar's gradient and its update, and another reduction, in one launch
+__global__ __launch_bounds__(256) void reduce_and_step_k(ReduceJob other, ReduceJob grad, float* p, float* m, float* v, AdamArg a) {
+  __shared__ float red[17];
+  const ReduceJob& jb = blockIdx.x ? grad : other;
+  const float g = reduce_scalar(jb, red);
+  if (threadIdx.x) return;
+  jb.out[0] = g;
+  if (blockIdx.x == 0) return;
+  float mm = *m, vv = *v;
+  *p = fmaxf(adam_one(*p, g, mm, vv, a), a.floor);
+  *m = mm;
+  *v = vv;
+}
+void reduce_and_step(const ReduceJob& other, const ReduceJob& grad, float* p, float* m, float* v, AdamArg a, hipStream_t st) {
+  MREM_LAUNCH(reduce_and_step_k, dim3(2), dim3(256), 0, st, other, grad, p, m, v, a);
 }
 
 struct VecJobTable {

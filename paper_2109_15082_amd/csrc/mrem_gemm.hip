@@ -7,6 +7,7 @@
 
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <atomic>
 #include <string>
 #include <cstdlib>
@@ -68,6 +69,9 @@ int gemm_profile_end(GemmProfile* p, double ms[2], double flops[2], int64_t laun
 
 #endif
 
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+
 struct EpiVals {
   float alpha, beta;
 };
@@ -81,6 +85,56 @@ __device__ __forceinline__ float epilogue_apart(float acc, float cs, bool has_be
   if (has_bias) v = v + bias;
   return v;
 }
+// Epilogue::post: the block's output tile, as it is stored, lies in LDS (rows of post_stride values), and goes out in whole
+// 16-byte pieces beside those of post_in.  The accumulators are dead by then: with the other tensors' values and addresses beside
+// them the kernel of 256 x 256 tiles spilled 99 registers.
+template <int BN>
+constexpr int post_stride = BN + 8;
+template <int POST, int BM, int BN, int THREADS>
+__device__ __forceinline__ void post_tile(unsigned char* lds, const Epilogue& e, bf16_t* __restrict__ C, int ldc, int m0, int n0) {
+  constexpr int ROWS = THREADS / (BN / 8), R = 4;  // rows a pass, passes in flight
+  static_assert(BM % (ROWS * R) == 0, "whole passes");
+  const bf16_t* tile = reinterpret_cast<const bf16_t*>(lds);
+  const int row0 = threadIdx.x / (BN / 8), col = threadIdx.x % (BN / 8) * 8;
+  const size_t at0 = (size_t)(m0 + row0) * ldc + n0 + col;
+  QuantParam q{};
+  if constexpr (POST == POST_STEP) {
+    q = QuantParam{*e.post_q.s, e.post_q.z ? *e.post_q.z : 0.f, e.post_q.qn, e.post_q.qp, 1, 0.f};
+    q.rs = quant_reciprocal(q.s);
+  }
+  auto get = [](const u32x4_t& w, int j) { return __uint_as_float((j & 1) ? w[j >> 1] & 0xffff0000u : w[j >> 1] << 16); };
+  float sum = 0.f;
+  for (int p = 0; p < BM; p += ROWS * R) {
+    u32x4_t in[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) in[i] = *reinterpret_cast<const u32x4_t*>(static_cast<const bf16_t*>(e.post_in) + at0 + (size_t)(p + i * ROWS) * ldc);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const size_t at = at0 + (size_t)(p + i * ROWS) * ldc;
+      const u32x4_t o = *reinterpret_cast<const u32x4_t*>(tile + (row0 + p + i * ROWS) * post_stride<BN> + col);
+      if constexpr (POST == POST_MSE) {
+        bf16x8_t dy;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float d = get(o, j) - get(in[i], j);
+          sum += d * d;
+          dy[j] = static_cast<bf16_t>(2.0f * d * e.post_scale);
+        }
+        *reinterpret_cast<u32x4_t*>(C + at) = o;
+        *reinterpret_cast<bf16x8_t*>(static_cast<bf16_t*>(e.post_out) + at) = dy;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float v = q_ratio_fma(get(in[i], j), q);
+          sum += get(o, j) * (q_code(v, q) - (q_inside(v, q) ? v : 0.f));
+        }
+      }
+    }
+  }
+  sum = block_sum(sum, reinterpret_cast<float*>(lds));
+  if (threadIdx.x == 0) e.post_parts[blockIdx.x] = sum;
+}
+
 // The ranges of a block's groups of columns (`groups` slots of lds, filled before; a slot holds them and its section) go out
 // as one partial a section.
 struct RangeSlot { MinMax r; int sec; };
@@ -202,9 +256,7 @@ static void launch_f32(int a_t, int b_t, const void* A, int lda, const void* B, 
 // that a product on bf16 codes rounds like any fp32 sum); the int8 mode is exact for every supported K.
 // Which sizes it takes: see gemm_launch (bf16) and gemm_i8_ok.
 // ------------------------------------------------------------------------------
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x16_t __attribute__((ext_vector_type(16)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
@@ -281,6 +333,13 @@ void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void* C, in
                             hipStream_t st, int splits) {
   auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const bool whole = whole_tiles(M, N, K);
+  if constexpr (!AT) {
+    if (e.post) {
+      constexpr int POST = BT ? POST_STEP : POST_MSE;
+      if (tiles(128, 128) <= 256) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, false, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+      return launch_quad<256, AT, BT, TO, I8, false, false, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+    }
+  }
   if constexpr (AT && BT) {
     if (splits > 1) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st, splits);
   }
@@ -336,6 +395,13 @@ MREM_TILES(true, true, float, false);
 #endif
 
 #if MREM_GEMM_REST
+// Which sizes have kernels with Epilogue::post: those of one 128 x 128 tile a compute unit, or of whole 256 x 256 ones in an
+// even number of stages.
+bool post_ok(int M, int N, int K) {
+  auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  if (!whole_tiles(M, N, K) || tiles(128, 64) <= 256) return false;
+  return tiles(128, 128) <= 256 || (tiles(128, 256) > 256 && tiles(256, 256) <= 2048 && quad_ok(K) && M % 256 == 0 && N % 256 == 0);
+}
 static void gemm_i8_launch(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                            hipStream_t st) {
   launch_dl_tiles<false, false, bf16_t, true>(A, lda / 2, B, ldb / 2, C, ldc, M, N, K / 2, e, st, 1);

@@ -228,7 +228,7 @@ static void launch_chain_tile(const void* A, int lda, const void* B, int ldb, vo
                               hipStream_t st) {
   constexpr int BM = 16 * MT * WM, BN = 16 * NT * WN;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  if (e.range) *e.range_parts = tiles_m * tiles_n;
+  if (e.blocks) *e.blocks = tiles_m * tiles_n;
   MREM_LAUNCH((gemm_chain_k<MT, NT, WM, WN, AHEAD>), dim3(tiles_m * tiles_n), dim3(64 * WM * WN), 0, st, (const bf16_t*)A, lda, (const bf16_t*)B,
               ldb, (bf16_t*)C, ldc, M, N, K, e, tiles_m, tiles_n);
 }

@@ -204,7 +204,7 @@ __device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm,
   tile_of_index(pid, tiles_m, tiles_n, tm, tn);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool AT, bool BT, int STAGES, int RB, class TO, bool I8, int MINB, int KG, bool EDGE>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool AT, bool BT, int STAGES, int RB, class TO, bool I8, int MINB, int KG, bool EDGE, int POST>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B,
                                                                          int ldb, TO* __restrict__ C, int ldc, int M, int N, int K, Epilogue e,
                                                                          int tiles_m, int tiles_n) {
@@ -458,7 +458,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
           } else {
             if constexpr (decltype(with_gelu)::value) v = gelu_t<TO>(round_to<TO>(v));
             if constexpr (RANGE) range.add(v);
-            stf(out, (size_t)dm * ldc, v);
+            if constexpr (POST != POST_NONE) stf(reinterpret_cast<bf16_t*>(smem_dl), (mb - m0 + dm) * post_stride<BN> + n - n0, v);
+            else stf(out, (size_t)dm * ldc, v);
           }
         }
       }
@@ -473,6 +474,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
   const bool row_term = e.beta && e.row_vec && lead;
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
+  if constexpr (POST != POST_NONE) {
+    static_assert(!EDGE && !AT && (KG == 1 || BY_ROWS), "whole tiles");
+    static_assert(BM * post_stride<BN> * 2 <= STAGES * STAGE_BYTES, "the tile fits the stages");
+    __syncthreads();  // nobody reads operands or partial sums any more
+    write_out(no, no, no, no, no);
+    __syncthreads();
+    post_tile<POST, BM, BN, 64 * NW>(smem_dl, e, C, ldc, m0, n0);
+    return;
+  }
   if constexpr (EDGE && !AT && !BT && !I8) {
     if (e.apart && e.gelu) return row_term ? write_out(yes, yes, no, yes, no) : write_out(no, yes, no, yes, no);
     if (e.apart) return row_term ? write_out(yes, no, no, yes, no) : write_out(no, no, no, yes, no);
@@ -487,7 +497,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
   return row_term ? write_out(yes, no, no, no, no) : write_out(no, no, no, no, no);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool AT, bool BT, int STAGES, int RB, class TO, bool I8 = false, int MINB = 1, int KG = 1, bool EDGE = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool AT, bool BT, int STAGES, int RB, class TO, bool I8 = false, int MINB = 1, int KG = 1, bool EDGE = false,
+          int POST = POST_NONE>
 static void launch_dl(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                       hipStream_t st, int k_splits = 1) {
   constexpr int NTHREADS = 64 * WAVES_M * WAVES_N * KG;
@@ -497,19 +508,19 @@ static void launch_dl(const void* A, int lda, const void* B, int ldb, void* C, i
   int dev = -1;
   (void)hipGetDevice(&dev);
   if (dev != configured_dev.load()) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dl_k<BM, BN, WAVES_M, WAVES_N, AT, BT, STAGES, RB, TO, I8, MINB, KG, EDGE>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dl_k<BM, BN, WAVES_M, WAVES_N, AT, BT, STAGES, RB, TO, I8, MINB, KG, EDGE, POST>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     configured_dev.store(dev);
   }
   const int tiles_m = EDGE ? (M + BM - 1) / BM : M / BM, tiles_n = EDGE ? (N + BN - 1) / BN : N / BN;
-  if (e.range) *e.range_parts = tiles_m * tiles_n;
+  if (e.blocks) *e.blocks = tiles_m * tiles_n;
   if (tl_launch_events.e0) {
-    hipExtLaunchKernelGGL((gemm_dl_k<BM, BN, WAVES_M, WAVES_N, AT, BT, STAGES, RB, TO, I8, MINB, KG, EDGE>), dim3(tiles_m * tiles_n, k_splits),
+    hipExtLaunchKernelGGL((gemm_dl_k<BM, BN, WAVES_M, WAVES_N, AT, BT, STAGES, RB, TO, I8, MINB, KG, EDGE, POST>), dim3(tiles_m * tiles_n, k_splits),
                           dim3(NTHREADS), lds, st, tl_launch_events.e0, tl_launch_events.e1, 0, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C, ldc, M, N,
                           K, e, tiles_m, tiles_n);
     return;
   }
-  hipLaunchKernelGGL((gemm_dl_k<BM, BN, WAVES_M, WAVES_N, AT, BT, STAGES, RB, TO, I8, MINB, KG, EDGE>), dim3(tiles_m * tiles_n, k_splits), dim3(NTHREADS),
+  hipLaunchKernelGGL((gemm_dl_k<BM, BN, WAVES_M, WAVES_N, AT, BT, STAGES, RB, TO, I8, MINB, KG, EDGE, POST>), dim3(tiles_m * tiles_n, k_splits), dim3(NTHREADS),
                      lds, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C, ldc, M, N, K, e, tiles_m, tiles_n);
 }
 

@@ -34,7 +34,7 @@ __device__ __forceinline__ void buffer_to_lds(const unsigned char* p, const unsi
 }
 
 // tile (tm, tn) of a product
-template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE, bool PAIR>
+template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE, bool PAIR, int POST = POST_NONE>
 __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb, TO* __restrict__ C, int ldc, int M,
                                           int N, int K, const Epilogue& e, int tm, int tn) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_quad[];
@@ -236,7 +236,8 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
           }
           if constexpr (decltype(with_gelu)::value) v = gelu_t<TO>(round_to<TO>(v));
           if constexpr (decltype(with_range)::value) range.add(v);
-          stf(out, (size_t)dm * ldc, v);
+          if constexpr (POST != POST_NONE) stf(reinterpret_cast<bf16_t*>(smem_quad), (mb - m0 + dm) * post_stride<BN> + n - n0, v);
+          else stf(out, (size_t)dm * ldc, v);
         }
       }
     };
@@ -256,6 +257,14 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
   const bool row_term = e.beta && e.row_vec;
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
+  if constexpr (POST != POST_NONE) {
+    static_assert(!EDGE && !PAIR && !AT, "whole tiles");
+    __syncthreads();  // nobody reads operands any more
+    write_out(yes, no, no, no, no);
+    __syncthreads();
+    post_tile<POST, BM, BN, 512>(smem_quad, e, C, ldc, m0, n0);
+    return;
+  }
   auto choose = [&](auto inside) {
     if constexpr (EDGE && !AT && !BT && !I8) {
       if (e.apart && e.gelu) return row_term ? write_out(inside, yes, yes, yes, no) : write_out(inside, no, yes, yes, no);
@@ -272,12 +281,12 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
   else choose(no);
 }
 
-template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE, bool PAIR>
+template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE, bool PAIR, int POST>
 __global__ __launch_bounds__(512, 1) void gemm_quad_k(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
                                                       TO* __restrict__ C, int ldc, int M, int N, int K, Epilogue e, int tiles_m, int tiles_n) {
   int tm, tn;
   tile_of_block(tiles_m, tiles_n, tm, tn);
-  quad_tile<BM, AT, BT, TO, I8, EDGE, PAIR>(A, lda, B, ldb, C, ldc, M, N, K, e, tm, tn);
+  quad_tile<BM, AT, BT, TO, I8, EDGE, PAIR, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, tm, tn);
 }
 
 // The weight gradients of a layer in one launch, at most one tile a compute unit.  Products of
@@ -311,8 +320,8 @@ static bool quad_ok(int K) { return K % (2 * kBK) == 0; }
 
 // LDS of a kernel of BM x 256 tiles, beyond what is allowed without asking
 template <int BM>
-static size_t quad_lds(const void* kernel, std::atomic<int>& configured_dev) {
-  constexpr size_t lds = 2 * (BM + 256) * 128;
+static size_t quad_lds(const void* kernel, std::atomic<int>& configured_dev, bool post = false) {
+  const size_t stages = 2 * (BM + 256) * 128, lds = post ? std::max(stages, BM * post_stride<256> * sizeof(bf16_t)) : stages;
   int dev = -1;
   (void)hipGetDevice(&dev);
   if (dev != configured_dev.load()) {
@@ -322,14 +331,14 @@ static size_t quad_lds(const void* kernel, std::atomic<int>& configured_dev) {
   return lds;
 }
 
-template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE, bool PAIR = false>
+template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE, bool PAIR = false, int POST = POST_NONE>
 static void launch_quad(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e, hipStream_t st) {
   constexpr int BN = 256;
   static std::atomic<int> configured_dev{-1};
-  const size_t lds = quad_lds<BM>(reinterpret_cast<const void*>(&gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR>), configured_dev);
+  const size_t lds = quad_lds<BM>(reinterpret_cast<const void*>(&gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR, POST>), configured_dev, POST != POST_NONE);
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  if (e.range) *e.range_parts = tiles_m * tiles_n;
-  MREM_LAUNCH((gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR>), dim3(tiles_m * tiles_n), dim3(512), lds, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C,
+  if (e.blocks) *e.blocks = tiles_m * tiles_n;
+  MREM_LAUNCH((gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR, POST>), dim3(tiles_m * tiles_n), dim3(512), lds, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C,
               ldc, M, N, K, e, tiles_m, tiles_n);
 }
 

@@ -47,11 +47,24 @@ struct Epilogue {
   int apart = 0;
   // range (not with transposes, int8 codes or fp32): the products' blocks also leave the range of what they store (with gelu:
   // of its values before they are rounded) as partials, as absminmax does; range_cols: section width, a multiple of 32 (0: one
-  // section); *range_parts: how many blocks
+  // section); *blocks: how many blocks
   float* range = nullptr;
   int range_cols = 0;
-  int* range_parts = nullptr;
+  int* blocks = nullptr;
+  // post (bf16 output, POST_MSE without transposes, POST_STEP with B transposed; post_ok says for which sizes): what else becomes
+  // of an output value o beside that of `post_in` at its place, t (both as stored); the blocks leave a partial sum each in
+  // post_parts (*blocks of them).
+  //   POST_MSE: post_out = 2 post_scale (o - t), sums of (o - t)^2, as mse_grad
+  //   POST_STEP: o is not stored; sums of o (code - v inside) of t under post_q, as quant_bwd_reduce
+  int post = 0;
+  const void* post_in = nullptr;
+  void* post_out = nullptr;
+  float* post_parts = nullptr;
+  float post_scale = 0.f;
+  QArg post_q;
 };
+enum { POST_NONE = 0, POST_MSE, POST_STEP };
+bool post_ok(int M, int N, int K);  // (K: in 2-byte elements)
 
 // Timing of product launches with the pair of HIP events that a launch itself carries (measurement aid).
 // A context owns one; products launched with a profile whose `on` is set are recorded in it.
@@ -280,5 +293,7 @@ struct VecJob {
   int clamp;
 };
 void adam_vector(float* p, const float* g, float* m, float* v, const VecJob* jobs, int njobs, AdamArg a, hipStream_t st);
+// both jobs have len = 1; behind `grad` AdamW without decay on the scalar p, which keeps the lower bound
+void reduce_and_step(const ReduceJob& other, const ReduceJob& grad, float* p, float* m, float* v, AdamArg a, hipStream_t st);
 
 }  // namespace mrem

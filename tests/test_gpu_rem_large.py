@@ -1,0 +1,50 @@
+"""Reconstruction of one product in sizes whose products also form the loss, its gradient and the step gradient's sum: 128 x 128
+tiles, one a compute unit, and whole 256 x 256 ones; int8 codes and (a contraction that is no whole int8 stage) bf16 ones.  The
+reference follows Eq. 2 in fp64 from the device's own outputs, so roundings do not multiply."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+# tokens, outputs, inputs, weight bits
+@pytest.mark.parametrize("T,N,K,bits", [(2048, 2048, 128, 4), (2048, 2048, 2048, 8), (1920, 2176, 192, 4), (4096, 2304, 256, 8), (2304, 256, 4096, 4), (2304, 4096, 4352, 4)])
+def test_rem_step(T, N, K, bits):
+    import torch
+    from paper_2109_15082_amd import binding as B
+    g = torch.Generator("cuda").manual_seed(T + N + K)
+    randn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    ctx = B.mrem_create(n_layers=1, hidden=64, n_heads=1, ffn=64, max_batch=1, max_seq=8, w_bits=bits, a_bits=8, act_dtype=B.MREM_BF16, per_channel=1)
+    w_fp = randn(N, K) * 0.02
+    a_fp = randn(T, K).bfloat16()
+    a_q = (a_fp.float() + 0.05 * randn(T, K)).bfloat16()
+    qp = 2 ** (bits - 1) - 1
+    vec = torch.zeros(B.mrem_rem_vector_count(N, K), device="cuda")
+    w = w_fp + 5e-4 * randn(N, K)
+    s_w = w.abs().amax(1) / qp * 0.9
+    s_a = a_q.float().abs().max() / 127 * 0.9
+    vec[:N * K], vec[N * K:N * K + N], vec[N * K + N] = w.reshape(-1), s_w, s_a
+    m, v, grads = torch.zeros_like(vec), torch.zeros_like(vec), torch.zeros_like(vec)
+    loss = torch.zeros(1, device="cuda")
+    y_fp, y_q = (torch.empty(T, N, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    ws = torch.empty(B.mrem_rem_workspace_bytes(ctx, T, N, K), dtype=torch.uint8, device="cuda")
+    B.mrem_rem_step(ctx, T, N, K, vec, m, v, 1, 1e-3, w_fp, a_fp, a_q, loss, y_fp, y_q, grads, ws)
+
+    ratio_a, ratio_w = a_q.float() / s_a, w / s_w[:, None]
+    codes_a, codes_w = ratio_a.clamp(-127, 127).round().double(), ratio_w.clamp(-qp, qp).round().double()
+    close = lambda got, ref, rel: (got.double() - ref).norm() <= rel * ref.norm()
+    assert close(y_fp, a_fp.double() @ w_fp.bfloat16().double().T, 2.0 ** -8)
+    assert close(y_q, (codes_a @ codes_w.T) * s_a.double() * s_w.double(), 2.0 ** -8)
+    d = y_q.float() - y_fp.float()
+    assert abs(loss.item() / d.double().square().mean().item() - 1) <= 1e-5
+    dy = (2.0 * d * torch.tensor(1.0 / (T * N), device="cuda")).bfloat16().double()
+    inside_w = (ratio_w >= -qp) & (ratio_w <= qp)
+    dw = dy.T @ codes_a * s_a.double()
+    assert close(grads[:N * K].reshape(N, K), dw * inside_w, 1e-5)
+    terms = dw * (codes_w - torch.where(inside_w, ratio_w.double(), 0.0))
+    # fp32 products and sums: 2^-20 of the terms' magnitude
+    assert torch.all((grads[N * K:N * K + N].double() - terms.sum(1)).abs() <= 2.0 ** -20 * terms.abs().sum(1) + 1e-5 * terms.norm(dim=1))
+    dxh = (dy @ (s_w[:, None] * codes_w.float()).bfloat16().double()).float().bfloat16().double()
+    t = dxh * (codes_a - torch.where((ratio_a >= -127) & (ratio_a <= 127), ratio_a.double(), 0.0))
+    # dxh is rounded to bf16 from fp32 sums: an element may round the other way
+    assert (grads[N * K + N].double() - t.sum()).abs() <= 2.0 ** -8 * t.norm() + 1e-5 * t.abs().sum()
+    B.mrem_destroy(ctx)
