@@ -128,6 +128,7 @@ __device__ __forceinline__ void post_tile(unsigned char* lds, const Epilogue& e,
           const float v = q_ratio_fma(get(in[i], j), q);
           sum += get(o, j) * (q_code(v, q) - (q_inside(v, q) ? v : 0.f));
         }
+        if (e.post_out) *reinterpret_cast<u32x4_t*>(C + at) = o;
       }
     }
   }
@@ -348,12 +349,10 @@ void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void* C, in
   if (tiles(128, 64) <= 256)
     return launch_dl<128, 64, 2, 2, AT, BT, 3, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   if (tiles(128, 128) <= 256) {
-    if constexpr (!I8) {  // (int8 products have whole tiles of 128, see gemm_i8_ok)
-      if (!whole) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-    }
+    if (!whole) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
     return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   }
-  const bool pair = !whole && tiles(256, 256) < 144;
+  const bool pair = !I8 && !whole && tiles(256, 256) < 144;  // (sums of codes are exact in any order)
   if (quad_ok(K) && (tiles(128, 256) <= 256 || !pair)) {
     if (tiles(128, 256) <= 256) {
       if constexpr (!I8) {
@@ -370,9 +369,7 @@ void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void* C, in
       return launch_dl<256, 256, 4, 2, AT, BT, 2, 128, TO, I8, 1>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
     return launch_dl<256, 256, 4, 2, AT, BT, 2, 128, TO, I8, 1, 1, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   }
-  if constexpr (!I8) {
-    if (!whole) return launch_dl<128, 64, 2, 2, AT, BT, 3, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-  }
+  if (!whole) return launch_dl<128, 64, 2, 2, AT, BT, 3, 128, TO, I8, 2, 2, true>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
   return launch_dl<128, 128, 2, 2, AT, BT, 4, 64, TO, I8, 2>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
 }
 #if defined(MREM_GEMM_PART)
@@ -404,7 +401,9 @@ bool post_ok(int M, int N, int K) {
 }
 static void gemm_i8_launch(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                            hipStream_t st) {
-  launch_dl_tiles<false, false, bf16_t, true>(A, lda / 2, B, ldb / 2, C, ldc, M, N, K / 2, e, st, 1);
+  Epilogue ee = e;
+  ee.apart = !whole_tiles(M, N, K / 2);
+  launch_dl_tiles<false, false, bf16_t, true>(A, lda / 2, B, ldb / 2, C, ldc, M, N, K / 2, ee, st, 1);
 }
 void gemm_i8(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e, hipStream_t st,
              GemmProfile* prof) {

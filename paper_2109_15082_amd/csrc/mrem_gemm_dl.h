@@ -435,6 +435,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
       float cb = (e.bias && lead) ? e.bias[n] : 0.f;
       const float cv = (e.beta && e.col_vec && lead) ? e.col_vec[n] : 0.f;
       if (!decltype(apart)::value && e.beta && e.col_vec && lead) cb += beta * cv;
+      int shift = 0;
+      if constexpr (I8 && decltype(apart)::value) shift = e.row_codes ? e.code_shift * e.row_codes[n] : 0;
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         if (KG > 1 && BY_ROWS && i % KG != kg) continue;  // a partner wavefront writes this tile row
@@ -448,7 +450,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
           float v;
           if constexpr (decltype(apart)::value) {
             const float t = decltype(with_row)::value ? cv + e.row_vec[mb + dm] : cv;
-            v = epilogue_apart((float)acc[i][j][r], cs, e.beta != nullptr, beta, t, e.bias != nullptr, cb);
+            auto sum = acc[i][j][r];
+            if constexpr (I8) sum += shift;
+            v = epilogue_apart((float)sum, cs, e.beta != nullptr, beta, t, e.bias != nullptr, cb);
           } else {
             v = (float)acc[i][j][r] * cs + cb;
             if constexpr (decltype(with_row)::value) v += beta * e.row_vec[mb + dm];
@@ -482,6 +486,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
     __syncthreads();
     post_tile<POST, BM, BN, 64 * NW>(smem_dl, e, C, ldc, m0, n0);
     return;
+  }
+  if constexpr (EDGE && I8) {
+    if (e.apart) return write_out(no, no, no, yes, no);
   }
   if constexpr (EDGE && !AT && !BT && !I8) {
     if (e.apart && e.gelu) return row_term ? write_out(yes, yes, no, yes, no) : write_out(no, yes, no, yes, no);

@@ -217,6 +217,8 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
       float cb = e.bias ? e.bias[n] : 0.f;
       const float cv = (e.beta && e.col_vec) ? e.col_vec[n] : 0.f;
       if (!decltype(apart)::value && e.beta && e.col_vec) cb += beta * cv;
+      int shift = 0;
+      if constexpr (I8 && decltype(apart)::value) shift = e.row_codes ? e.code_shift * e.row_codes[n] : 0;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int mb = m0 + i * HA + wm * 32 + 4 * (lane >> 5);
@@ -225,7 +227,9 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
         for (int r = 0; r < 16; ++r) {
           const int dm = 8 * (r >> 2) + (r & 3);
           if (!decltype(inside)::value && mb + dm >= M) continue;
-          const float a = (float)acc[i][j / NT][0][j % NT][r];
+          auto sum = acc[i][j / NT][0][j % NT][r];
+          if constexpr (I8 && decltype(apart)::value) sum += shift;
+          const float a = (float)sum;
           float v;
           if constexpr (decltype(apart)::value) {
             const float t = decltype(with_row)::value ? cv + e.row_vec[mb + dm] : cv;
@@ -266,6 +270,9 @@ __device__ __forceinline__ void quad_tile(const bf16_t* __restrict__ A, int lda,
     return;
   }
   auto choose = [&](auto inside) {
+    if constexpr (EDGE && I8) {
+      if (e.apart) return write_out(inside, no, no, yes, no);
+    }
     if constexpr (EDGE && !AT && !BT && !I8) {
       if (e.apart && e.gelu) return row_term ? write_out(inside, yes, yes, yes, no) : write_out(inside, no, yes, yes, no);
       if (e.apart) return row_term ? write_out(inside, yes, no, yes, no) : write_out(inside, no, no, yes, no);

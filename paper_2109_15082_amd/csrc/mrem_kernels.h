@@ -45,6 +45,10 @@ struct Epilogue {
   float beta_alpha = 0.f;
   int chain = 0;
   int apart = 0;
+  // int8 codes in sizes that are not whole tiles: acc + code_shift * row_codes[n] is the sum over the codes of A before a constant
+  // was subtracted from them (row_codes: sums of B's rows), which the formula above then takes as it is (beta_alpha = 0)
+  const int* row_codes = nullptr;
+  int code_shift = 0;
   // range (not with transposes, int8 codes or fp32): the products' blocks also leave the range of what they store (with gelu:
   // of its values before they are rounded) as partials, as absminmax does; range_cols: section width, a multiple of 32 (0: one
   // section); *blocks: how many blocks
@@ -55,7 +59,7 @@ struct Epilogue {
   // of an output value o beside that of `post_in` at its place, t (both as stored); the blocks leave a partial sum each in
   // post_parts (*blocks of them).
   //   POST_MSE: post_out = 2 post_scale (o - t), sums of (o - t)^2, as mse_grad
-  //   POST_STEP: o is not stored; sums of o (code - v inside) of t under post_q, as quant_bwd_reduce
+  //   POST_STEP: sums of o (code - v inside) of t under post_q, as quant_bwd_reduce; o is stored only if post_out is not null
   int post = 0;
   const void* post_in = nullptr;
   void* post_out = nullptr;
@@ -106,7 +110,8 @@ int gemm_profile_end(GemmProfile* p, double ms[2], double flops[2], int64_t laun
 void gemm(int dt, int a_t, int b_t, const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K,
           const Epilogue& e, hipStream_t st, GemmProfile* prof = nullptr);
 // C[M,N] (bf16) = A[M,K] * B[N,K]^T on int8 codes with exact int32 accumulation; needs
-// gemm_i8_ok(...).  Same epilogue.
+// gemm_i8_ok(...), or that for M = 128: sizes with any M round as products of bf16 codes do, whose sums are exact too where they
+// stay below 2^24.  Same epilogue.
 bool gemm_i8_ok(const void* A, int lda, const void* B, int ldb, int M, int N, int K);
 void gemm_i8(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e, hipStream_t st,
              GemmProfile* prof = nullptr);
@@ -143,6 +148,7 @@ struct WeightJob {
   void* what;
   float* zcorr;    // may be null
   int8_t* codes8;  // may be null
+  int* row_codes = nullptr;  // sums of the codes of a row; may be null
   int N, K;
 };
 void weight_prepare(int dt, const WeightJob* jobs, int njobs, int bits, hipStream_t st);
