@@ -385,11 +385,12 @@ const int kBField[4] = {MREM_F_B_QKV, MREM_F_B_O, MREM_F_B_1, MREM_F_B_2};
 const int kSField[4] = {MREM_F_SW_QKV, MREM_F_SW_O, MREM_F_SW_1, MREM_F_SW_2};
 const int kInQuant[4] = {0, 5, 6, 7};  // activation quantizer feeding each linear layer
 
-// quantized linear layer i of layer l: out = codes_in * wcodes^T with the steps in the epilogue
-void student_linear(const Run& r, const float* params, int l, int i, const void* in_codes, const int8_t* in_codes8, void* out) {
+// quantized linear layer i of layer l: out = codes_in * wcodes^T with the steps in the epilogue; `post`: what else its kernel does
+void student_linear(const Run& r, const float* params, int l, int i, const void* in_codes, const int8_t* in_codes8, void* out,
+                    const Epilogue& post = Epilogue()) {
   const mrem_ctx* c = r.c;
   const float* base = params + c->layer_stride * l;
-  Epilogue e;
+  Epilogue e = post;
   const QArg q = make_q(c, params, l, kInQuant[i]);
   if (q.on) e.alpha = q.s;
   if (c->cfg.w_bits > 0) e.col_scale = base + c->foff[kSField[i]];
@@ -434,16 +435,21 @@ void prepare_weights(const Run& r, const float* params, bool backward, int l0 = 
         [&] { weight_prepare(c->dt, jobs.data(), (int)jobs.size(), c->cfg.w_bits, r.st); });
 }
 
-// Layers [l0, l1) of the quantized module (l1 < 0: to the last layer).
+// Layers [l0, l1) of the quantized module (l1 < 0: to the last layer).  backward: with what only a backward pass reads, the codes
+// in the storage type (where the products read int8 ones) and the first feed-forward projection's output (where its kernel forms
+// the codes of its GELU).  Without it both passes of six layers of 1024 over 4096 tokens take 1575 us, 1740 with it.
 // mix_fp != null (with 0 < lambda <= 1): the module input is lambda * mix_fp + (1 - lambda) * x_in (Eq. 4), formed and
 // stored in x_q (a workspace buffer) by the kernel that quantizes the first layer's input.
-void student_forward(const Run& r, const float* params, const void* x_q, void* per_layer_q, int l0 = 0, int l1 = -1,
+void student_forward(const Run& r, const float* params, const void* x_q, void* per_layer_q, bool backward, int l0 = 0, int l1 = -1,
                      const void* mix_fp = nullptr, const void* mix_in = nullptr, float lambda = 0.f) {
   const mrem_ctx* c = r.c;
   const size_t es = dt_size(c->dt);
   const int H = c->H, F = c->F, T = r.T;
   const size_t slice = (size_t)T * H * es;
   if (l1 < 0) l1 = c->L;
+  const bool only8 = !backward && r.i8();
+  auto codes = [&](size_t off) { return only8 ? nullptr : r.at(off); };
+  const double es_codes = only8 ? 1 : es + (r.i8() ? 1 : 0);
   for (int l = l0; l < l1; ++l) {
     const LayerWs& w = r.p.lw[l];
     const float* base = params + c->layer_stride * l;
@@ -455,36 +461,40 @@ void student_forward(const Run& r, const float* params, const void* x_q, void* p
       mix_quantize(c->dt, mix_fp, mix_in, lambda, 1.f - lambda, const_cast<void*>(x), r.at(w.xcodes), (int64_t)T * H, make_q(c, params, l, 0), r.st,
                    r.at8(w.xcodes8));
     else if (l == 0)
-      timed(r, "act_quantize_k", (double)T * H * (2 * es + (r.i8() ? 1 : 0)),
-            [&] { act_quantize(c->dt, x, r.at(w.xcodes), (int64_t)T * H, make_q(c, params, l, 0), r.st, r.at8(w.xcodes8)); });
+      timed(r, "act_quantize_k", (double)T * H * (es + es_codes),
+            [&] { act_quantize(c->dt, x, codes(w.xcodes), (int64_t)T * H, make_q(c, params, l, 0), r.st, r.at8(w.xcodes8)); });
     student_linear(r, params, l, 0, r.at(w.xcodes), r.at8(w.xcodes8), r.at(w.qkv));
     const AttnQ aq = make_attn_q(c, params, l, true);
     timed(r, "qkv_quantize_k", (double)T * 3 * H * 2 * es, [&] { qkv_quantize(c->dt, r.at(w.qkv), r.at(w.qkvcodes), T, H, aq.q, aq.k, aq.v, r.st); });
     if (attn_mfma_ok(c->dt, c->d)) {
-      attn_fwd_mfma(r.at(w.qkvcodes), r.at(w.ctx), r.at(w.ctxcodes), aq, r.seqlens, r.B, r.S, c->nh, c->d, nullptr, r.at<float>(w.stat_m),
+      attn_fwd_mfma(r.at(w.qkvcodes), r.at(w.ctx), codes(w.ctxcodes), aq, r.seqlens, r.B, r.S, c->nh, c->d, nullptr, r.at<float>(w.stat_m),
                     r.at<float>(w.stat_l), r.st, true, r.at8(w.ctxcodes8));
     } else {
       attn_fwd(c->dt, r.at(w.qkvcodes), r.at(w.ctx), r.at(w.ctxcodes), aq, r.seqlens, r.B, r.S, c->nh, c->d, nullptr, r.st);
       if (r.i8()) codes_to_i8(c->dt, r.at(w.ctxcodes), r.at8(w.ctxcodes8), (int64_t)T * H, 0.f, r.st);
     }
     student_linear(r, params, l, 1, r.at(w.ctxcodes), r.at8(w.ctxcodes8), r.at(w.o));
-    const double ln_q_bytes = (double)T * H * (4 * es + (r.i8() ? 1 : 0));  // x, r in; y and its codes (and int8 codes) out
+    const double ln_q_bytes = (double)T * H * (3 * es + es_codes);  // x, r in; y and its codes out
     timed(r, "ln_fwd_k", ln_q_bytes, [&] {
-      ln_fwd(c->dt, x, r.at(w.o), base + c->foff[MREM_F_LN1_G], base + c->foff[MREM_F_LN1_B], r.at(w.x1), r.at(w.x1codes),
+      ln_fwd(c->dt, x, r.at(w.o), base + c->foff[MREM_F_LN1_G], base + c->foff[MREM_F_LN1_B], r.at(w.x1), codes(w.x1codes),
              make_q(c, params, l, 6), r.at<float>(w.mu1), r.at<float>(w.rstd1), T, H, c->cfg.ln_eps, r.st, r.at8(w.x1codes8));
     });
-    student_linear(r, params, l, 2, r.at(w.x1codes), r.at8(w.x1codes8), r.at(w.u));
-    {
-      const QArg qg = make_q(c, params, l, 7);
-      timed(r, "gelu_quantize_k", (double)T * F * (2 * es + (r.i8() ? 1 : 0)),
-            [&] { gelu_quantize(c->dt, r.at(w.u), r.at(w.gcodes), (int64_t)T * F, qg, r.st, r.at8(w.gcodes8), 0.5f * (qg.qp + 1.f)); });
+    const QArg qg = make_q(c, params, l, 7);
+    if (r.i8() && post_ok(T, F, H / 2)) {
+      Epilogue post;
+      post.post = POST_GELU; post.post_q = qg; post.post_out = codes(w.gcodes); post.post_out8 = r.at8(w.gcodes8); post.post_shift = (int)(0.5f * (qg.qp + 1.f));
+      student_linear(r, params, l, 2, r.at(w.x1codes), r.at8(w.x1codes8), backward ? r.at(w.u) : nullptr, post);
+    } else {
+      student_linear(r, params, l, 2, r.at(w.x1codes), r.at8(w.x1codes8), r.at(w.u));
+      timed(r, "gelu_quantize_k", (double)T * F * (es + es_codes),
+            [&] { gelu_quantize(c->dt, r.at(w.u), codes(w.gcodes), (int64_t)T * F, qg, r.st, r.at8(w.gcodes8), 0.5f * (qg.qp + 1.f)); });
     }
     student_linear(r, params, l, 3, r.at(w.gcodes), r.at8(w.gcodes8), r.at(w.y));
     if (l + 1 < c->L) {
       // the layer output and, in the same pass, its codes under the next layer's input quantizer
       const LayerWs& wn = r.p.lw[l + 1];
       timed(r, "ln_fwd_k", ln_q_bytes, [&] {
-        ln_fwd(c->dt, r.at(w.x1), r.at(w.y), base + c->foff[MREM_F_LN2_G], base + c->foff[MREM_F_LN2_B], f, r.at(wn.xcodes),
+        ln_fwd(c->dt, r.at(w.x1), r.at(w.y), base + c->foff[MREM_F_LN2_G], base + c->foff[MREM_F_LN2_B], f, codes(wn.xcodes),
                make_q(c, params, l + 1, 0), r.at<float>(w.mu2), r.at<float>(w.rstd2), T, H, c->cfg.ln_eps, r.st, r.at8(wn.xcodes8));
       });
     } else {
@@ -1087,7 +1097,7 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
     // layer by layer in turn, so that both streams have work from the start
     for (int l = 0; l < ctx->L; ++l) {
       teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, l, l + 1);
-      student_forward(r, params, x_q, per_layer_q, l, l + 1);
+      student_forward(r, params, x_q, per_layer_q, false, l, l + 1);
     }
     {
       const std::lock_guard<std::mutex> lock(side->lock);
@@ -1100,7 +1110,7 @@ mrem_status forward_impl(mrem_ctx* ctx, const float* params, const float* teache
   if (per_layer_fp) teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp);
   if (per_layer_q) {
     prepare_weights(r, params, false);
-    student_forward(r, params, x_q, per_layer_q);
+    student_forward(r, params, x_q, per_layer_q, false);
   }
   return finish(ctx, who);
 }
@@ -1224,14 +1234,14 @@ extern "C" mrem_status mrem_module_step(mrem_ctx* ctx, float* params, float* ada
     for (int l = 0; l < ctx->L; ++l) {
       teacher_forward(rt, teacher, teacher_cache, x_fp, per_layer_fp, l, l + 1);
       if (l == 1 && !few) (void)hipStreamWaitEvent(r.st, ctx->ev_codes, 0);
-      student_forward(r, params, x_in, per_layer_q, l, l + 1, mix_fp, x_q, lambda);
+      student_forward(r, params, x_in, per_layer_q, true, l, l + 1, mix_fp, x_q, lambda);
     }
     (void)hipEventRecord(ctx->ev_join, ctx->side);
   } else {
     teacher_forward(r, teacher, teacher_cache, x_fp, per_layer_fp);
     zero_gradient_slots(r, grads, false);
     prepare_weights(r, params, true);
-    student_forward(r, params, x_in, per_layer_q, 0, -1, mix_fp, x_q, lambda);
+    student_forward(r, params, x_in, per_layer_q, true, 0, -1, mix_fp, x_q, lambda);
   }
   if (fork) (void)hipStreamWaitEvent(r.st, ctx->ev_join, 0);
   const Update up{params, adam_m, adam_v, adam_arg(ctx, step_index, lr), grads_out != nullptr, fork ? ctx->side : nullptr,

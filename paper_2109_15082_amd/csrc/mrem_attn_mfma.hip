@@ -311,13 +311,13 @@ __device__ __forceinline__ void store_context(const f32x16_t& acc, const AttnQ& 
     store4(ctx + o + 8 * g, v[0], v[1], v[2], v[3]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) range.add(v[i]);  // (dead where nobody asks)
-    if (ctx_codes) {
+    if (ctx_codes || ctx_codes8) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float r = round_to<bf16_t>(v[i]);
         v[i] = qc5.on ? q_code(q_ratio_fma(r, qc5), qc5) : r;
       }
-      store4(ctx_codes + o + 8 * g, v[0], v[1], v[2], v[3]);
+      if (ctx_codes) store4(ctx_codes + o + 8 * g, v[0], v[1], v[2], v[3]);
       if (ctx_codes8) {
         const unsigned pk = ((unsigned)(int)v[0] & 0xffu) | (((unsigned)(int)v[1] & 0xffu) << 8) | (((unsigned)(int)v[2] & 0xffu) << 16) |
                             (((unsigned)(int)v[3] & 0xffu) << 24);

@@ -163,7 +163,7 @@ __global__ void act_quantize_k(const T* __restrict__ a, T* __restrict__ codes, i
   walk_chunks(a, nchunks, [&](int64_t c, float (&v)[8]) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = code_of<T, ON>(v[j], q);
-    store8(codes + c * 8, v);
+    if (codes) store8(codes + c * 8, v);
     if (codes8) store8_i8(codes8 + c * 8, v, 0.f);
   });
 }
@@ -373,7 +373,7 @@ __global__ void gelu_quantize_k(const T* __restrict__ u, T* __restrict__ codes, 
   walk_chunks(u, nchunks, [&](int64_t c, float (&v)[8]) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = code_of<T, ON>(gelu_t<T>(v[j]), q);
-    store8(codes + c * 8, v);
+    if (codes) store8(codes + c * 8, v);
     if (codes8) store8_i8(codes8 + c * 8, v, shift8);
   });
 }
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(256) void ln_fwd_k(const T* __restrict__ x, const T
       if constexpr (Q != LN_NONE) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) o[j] = code_of<T, Q == LN_ON>(round_to<T>(o[j]), q);
-        store8(ycodes + (size_t)row * H + c * 8, o);
+        if (ycodes) store8(ycodes + (size_t)row * H + c * 8, o);
         if (ycodes8) store8_i8(ycodes8 + (size_t)row * H + c * 8, o, 0.f);
       }
     }
@@ -526,7 +526,7 @@ void ln_fwd(int dt, const void* x, const void* r, const float* gamma, const floa
                                 (T*)y, (T*)ycodes, q, mu, rstd, T_, H, eps, ycodes8, ranges))
 #define MREM_LN_FWD(NCH)                                  \
   do {                                                    \
-    const LnQuant lq = ln_quant(ycodes, q);               \
+    const LnQuant lq = ln_quant(ycodes ? ycodes : ycodes8, q); \
     if (lq == LN_ON) MREM_LN_FWD_Q(NCH, LN_ON);           \
     else if (lq == LN_OFF) MREM_LN_FWD_Q(NCH, LN_OFF);    \
     else MREM_LN_FWD_Q(NCH, LN_NONE);                     \

@@ -90,10 +90,75 @@ __device__ __forceinline__ float epilogue_apart(float acc, float cs, bool has_be
 // them the kernel of 256 x 256 tiles spilled 99 registers.
 template <int BN>
 constexpr int post_stride = BN + 8;
+// GELU and its quantizer for stored values: bf16 values between 2^-14 and 8 of either sign are 4352, whose codes a block forms once
+// and then looks up (8 vector instructions a value, 29 when each is formed by itself, which are 13 us for 4096 x 4096 values).
+struct GeluCodes {
+  static constexpr unsigned LOW = 113u << 7, N = 17u * 128u;  // bits of 2^-14; values of one sign
+  unsigned char code[2 * N];
+  static __device__ __forceinline__ unsigned form(unsigned bits, const QuantParam& q) {
+    return (unsigned)q_code(q_ratio_fma(gelu_t<bf16_t>(__uint_as_float(bits << 16)), q), q);
+  }
+  __device__ __forceinline__ void fill(const QuantParam& q) {
+    for (unsigned i = threadIdx.x; i < 2 * N; i += blockDim.x) code[i] = (unsigned char)form((i < N ? LOW : 0x8000u + LOW - N) + i, q);
+  }
+};
+template <int BM, int BN, int THREADS>
+__device__ __forceinline__ void gelu_tile(unsigned char* lds, const Epilogue& e, bf16_t* __restrict__ C, int ldc, int m0, int n0) {
+  constexpr int ROWS = THREADS / (BN / 8);
+  const bf16_t* tile = reinterpret_cast<const bf16_t*>(lds);
+  GeluCodes* table = reinterpret_cast<GeluCodes*>(lds + BM * post_stride<BN> * sizeof(bf16_t));
+  QuantParam q = {*e.post_q.s, e.post_q.z ? *e.post_q.z : 0.f, e.post_q.qn, e.post_q.qp, 1, 0.f};
+  q.rs = quant_reciprocal(q.s);
+  table->fill(q);
+  __syncthreads();
+  const int row0 = threadIdx.x / (BN / 8), col = threadIdx.x % (BN / 8) * 8;
+  const size_t at0 = (size_t)(m0 + row0) * ldc + n0 + col;
+  const unsigned shift = 0x01010101u * (unsigned)e.post_shift;
+#pragma unroll 4
+  for (int p = 0; p < BM; p += ROWS) {
+    const u32x4_t o = *reinterpret_cast<const u32x4_t*>(tile + (row0 + p) * post_stride<BN> + col);
+    unsigned code[8], low = ~0u, high = 0u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const unsigned bits = (j & 1) ? o[j >> 1] >> 16 : o[j >> 1] & 0xffffu, i = (bits & 0x7fffu) - GeluCodes::LOW;
+      low = min(low, bits & 0x7fffu);
+      high = max(high, bits & 0x7fffu);
+      code[j] = table->code[min(i, GeluCodes::N - 1) + (bits >> 15) * GeluCodes::N];
+    }
+    if (low < GeluCodes::LOW || high >= GeluCodes::LOW + GeluCodes::N) {
+#pragma unroll 1
+      for (int j = 0; j < 8; ++j) {
+        const unsigned bits = (unsigned)(o[j >> 1] >> (16 * (j & 1))) & 0xffffu, c = GeluCodes::form(bits, q);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (k == j) code[k] = c;
+      }
+    }
+    const size_t at = at0 + (size_t)p * ldc;
+    if (C) *reinterpret_cast<u32x4_t*>(C + at) = o;
+    if (e.post_out) {
+      bf16x8_t c;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) c[j] = static_cast<bf16_t>((float)code[j]);
+      *reinterpret_cast<bf16x8_t*>(static_cast<bf16_t*>(e.post_out) + at) = c;
+    }
+    if (e.post_out8) {
+      unsigned w[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        w[h] = code[4 * h] | code[4 * h + 1] << 8 | code[4 * h + 2] << 16 | code[4 * h + 3] << 24;
+        // less the shift, byte by byte: bit 7 keeps a borrow inside (and is the shift itself with 8-bit codes)
+        w[h] = e.post_shift == 128 ? w[h] ^ 0x80808080u : ((w[h] | 0x80808080u) - shift) ^ 0x80808080u;
+      }
+      *reinterpret_cast<uint2*>(e.post_out8 + at) = make_uint2(w[0], w[1]);
+    }
+  }
+}
 template <int POST, int BM, int BN, int THREADS>
 __device__ __forceinline__ void post_tile(unsigned char* lds, const Epilogue& e, bf16_t* __restrict__ C, int ldc, int m0, int n0) {
   constexpr int ROWS = THREADS / (BN / 8), R = 4;  // rows a pass, passes in flight
   static_assert(BM % (ROWS * R) == 0, "whole passes");
+  if constexpr (POST == POST_GELU) return gelu_tile<BM, BN, THREADS>(lds, e, C, ldc, m0, n0);
   const bf16_t* tile = reinterpret_cast<const bf16_t*>(lds);
   const int row0 = threadIdx.x / (BN / 8), col = threadIdx.x % (BN / 8) * 8;
   const size_t at0 = (size_t)(m0 + row0) * ldc + n0 + col;
@@ -336,9 +401,16 @@ void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void* C, in
   const bool whole = whole_tiles(M, N, K);
   if constexpr (!AT) {
     if (e.post) {
-      constexpr int POST = BT ? POST_STEP : POST_MSE;
-      if (tiles(128, 128) <= 256) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, false, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
-      return launch_quad<256, AT, BT, TO, I8, false, false, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+      auto go = [&](auto post) {
+        constexpr int POST = decltype(post)::value;
+        if (tiles(128, 128) <= 256) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, false, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+        if (tiles(128, 256) <= 256) return launch_quad<128, AT, BT, TO, I8, false, false, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+        return launch_quad<256, AT, BT, TO, I8, false, false, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+      };
+      if constexpr (I8) {
+        if (e.post == POST_GELU) return go(std::integral_constant<int, POST_GELU>{});
+      }
+      return go(std::integral_constant<int, BT ? POST_STEP : POST_MSE>{});
     }
   }
   if constexpr (AT && BT) {
@@ -392,12 +464,12 @@ MREM_TILES(true, true, float, false);
 #endif
 
 #if MREM_GEMM_REST
-// Which sizes have kernels with Epilogue::post: those of one 128 x 128 tile a compute unit, or of whole 256 x 256 ones in an
-// even number of stages.
+// Which sizes have kernels with Epilogue::post: whole tiles from 128 x 128 on.
 bool post_ok(int M, int N, int K) {
   auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   if (!whole_tiles(M, N, K) || tiles(128, 64) <= 256) return false;
-  return tiles(128, 128) <= 256 || (tiles(128, 256) > 256 && tiles(256, 256) <= 2048 && quad_ok(K) && M % 256 == 0 && N % 256 == 0);
+  if (tiles(128, 128) <= 256) return true;
+  return quad_ok(K) && N % 256 == 0 && (tiles(128, 256) <= 256 || (tiles(256, 256) <= 2048 && M % 256 == 0));
 }
 static void gemm_i8_launch(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                            hipStream_t st) {

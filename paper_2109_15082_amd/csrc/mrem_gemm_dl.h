@@ -480,7 +480,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
   constexpr std::false_type no{};
   if constexpr (POST != POST_NONE) {
     static_assert(!EDGE && !AT && (KG == 1 || BY_ROWS), "whole tiles");
-    static_assert(BM * post_stride<BN> * 2 <= STAGES * STAGE_BYTES, "the tile fits the stages");
+    static_assert(BM * post_stride<BN> * 2 + sizeof(GeluCodes) <= STAGES * STAGE_BYTES, "the tile fits the stages");
     __syncthreads();  // nobody reads operands or partial sums any more
     write_out(no, no, no, no, no);
     __syncthreads();

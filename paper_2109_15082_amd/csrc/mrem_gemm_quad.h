@@ -328,7 +328,7 @@ static bool quad_ok(int K) { return K % (2 * kBK) == 0; }
 // LDS of a kernel of BM x 256 tiles, beyond what is allowed without asking
 template <int BM>
 static size_t quad_lds(const void* kernel, std::atomic<int>& configured_dev, bool post = false) {
-  const size_t stages = 2 * (BM + 256) * 128, lds = post ? std::max(stages, BM * post_stride<256> * sizeof(bf16_t)) : stages;
+  const size_t stages = 2 * (BM + 256) * 128, lds = post ? std::max(stages, BM * post_stride<256> * sizeof(bf16_t) + sizeof(GeluCodes)) : stages;
   int dev = -1;
   (void)hipGetDevice(&dev);
   if (dev != configured_dev.load()) {

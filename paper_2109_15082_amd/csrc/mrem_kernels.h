@@ -59,15 +59,19 @@ struct Epilogue {
   // of an output value o beside that of `post_in` at its place, t (both as stored); the blocks leave a partial sum each in
   // post_parts (*blocks of them).
   //   POST_MSE: post_out = 2 post_scale (o - t), sums of (o - t)^2, as mse_grad
+  //   POST_GELU (int8 codes): the code c of gelu(o) under post_q, post_out = c, post_out8 = c - post_shift, as gelu_quantize; each
+  //     of them and o itself (C) may be null; without post_in and post_parts
   //   POST_STEP: sums of o (code - v inside) of t under post_q, as quant_bwd_reduce; o is stored only if post_out is not null
   int post = 0;
   const void* post_in = nullptr;
   void* post_out = nullptr;
+  int8_t* post_out8 = nullptr;
+  int post_shift = 0;
   float* post_parts = nullptr;
   float post_scale = 0.f;
   QArg post_q;
 };
-enum { POST_NONE = 0, POST_MSE, POST_STEP };
+enum { POST_NONE = 0, POST_MSE, POST_STEP, POST_GELU };
 bool post_ok(int M, int N, int K);  // (K: in 2-byte elements)
 
 // Timing of product launches with the pair of HIP events that a launch itself carries (measurement aid).
@@ -155,12 +159,12 @@ void weight_prepare(int dt, const WeightJob* jobs, int njobs, int bits, hipStrea
 void convert_f32(int dt, const float* src, void* dst, int64_t n, hipStream_t st);
 
 // ---- elementwise / normalisation ------------------------------------------------
-// codes8 (may be null): the same codes as int8, for the int8 products of the forward pass
+// codes8: the same codes as int8, for the int8 products of the forward pass; either of the two may be null
 void act_quantize(int dt, const void* a, void* codes, int64_t n, QArg q, hipStream_t st, int8_t* codes8 = nullptr);
 // Eq. 4 in the same pass: mixed = round(wa * a + wb * b) is stored and quantized
 void mix_quantize(int dt, const void* a, const void* b, float wa, float wb, void* mixed, void* codes, int64_t n, QArg q, hipStream_t st,
                   int8_t* codes8 = nullptr);
-// codes8 (may be null): codes - shift8 as int8 (the unsigned grid of the GELU output, recentred)
+// codes8: codes - shift8 as int8 (the unsigned grid of the GELU output, recentred); either of the two may be null
 void gelu_quantize(int dt, const void* u, void* codes, int64_t n, QArg q, hipStream_t st, int8_t* codes8 = nullptr, float shift8 = 0.f);
 // bf16/fp32 integer codes -> int8 (codes - shift); for producers without an int8 output of their own
 void codes_to_i8(int dt, const void* codes, int8_t* codes8, int64_t n, float shift, hipStream_t st);
@@ -178,7 +182,7 @@ int quant_bwd(int dt, const void* d_q, const void* a, void* d_out, int64_t n, QA
 // partial sums of d_q * (code - v*inside) only (layer-0 input quantizer)
 int quant_bwd_reduce(int dt, const void* d_q, const void* a, int64_t n, QArg q, float* partials, hipStream_t st);
 
-// y = LN(x + r) * gamma + beta ; optional codes of y ; mean/rstd saved ; ranges (without codes, may be null): the range of y,
+// y = LN(x + r) * gamma + beta ; optional codes of y (in the storage type, as int8, or both) ; mean/rstd saved ; ranges (without codes, may be null): the range of y,
 // T partials as absminmax leaves them
 void ln_fwd(int dt, const void* x, const void* r, const float* gamma, const float* beta, void* y, void* ycodes, QArg q,
             float* mu, float* rstd, int T, int H, float eps, hipStream_t st, int8_t* ycodes8 = nullptr, float* ranges = nullptr);
