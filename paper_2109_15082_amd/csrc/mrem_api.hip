@@ -463,9 +463,15 @@ void student_forward(const Run& r, const float* params, const void* x_q, void* p
     else if (l == 0)
       timed(r, "act_quantize_k", (double)T * H * (es + es_codes),
             [&] { act_quantize(c->dt, x, codes(w.xcodes), (int64_t)T * H, make_q(c, params, l, 0), r.st, r.at8(w.xcodes8)); });
-    student_linear(r, params, l, 0, r.at(w.xcodes), r.at8(w.xcodes8), r.at(w.qkv));
     const AttnQ aq = make_attn_q(c, params, l, true);
-    timed(r, "qkv_quantize_k", (double)T * 3 * H * 2 * es, [&] { qkv_quantize(c->dt, r.at(w.qkv), r.at(w.qkvcodes), T, H, aq.q, aq.k, aq.v, r.st); });
+    if (r.i8() && post_codes_ok(T, 3 * H, H)) {
+      Epilogue post;
+      post.post = POST_QKV; post.post_q = aq.q; post.post_q1 = aq.k; post.post_q2 = aq.v; post.post_cols = H; post.post_out = r.at(w.qkvcodes);
+      student_linear(r, params, l, 0, r.at(w.xcodes), r.at8(w.xcodes8), r.at(w.qkv), post);
+    } else {
+      student_linear(r, params, l, 0, r.at(w.xcodes), r.at8(w.xcodes8), r.at(w.qkv));
+      timed(r, "qkv_quantize_k", (double)T * 3 * H * 2 * es, [&] { qkv_quantize(c->dt, r.at(w.qkv), r.at(w.qkvcodes), T, H, aq.q, aq.k, aq.v, r.st); });
+    }
     if (attn_mfma_ok(c->dt, c->d)) {
       attn_fwd_mfma(r.at(w.qkvcodes), r.at(w.ctx), codes(w.ctxcodes), aq, r.seqlens, r.B, r.S, c->nh, c->d, nullptr, r.at<float>(w.stat_m),
                     r.at<float>(w.stat_l), r.st, true, r.at8(w.ctxcodes8));
@@ -480,7 +486,7 @@ void student_forward(const Run& r, const float* params, const void* x_q, void* p
              make_q(c, params, l, 6), r.at<float>(w.mu1), r.at<float>(w.rstd1), T, H, c->cfg.ln_eps, r.st, r.at8(w.x1codes8));
     });
     const QArg qg = make_q(c, params, l, 7);
-    if (r.i8() && post_ok(T, F, H / 2)) {
+    if (r.i8() && post_codes_ok(T, F, H)) {
       Epilogue post;
       post.post = POST_GELU; post.post_q = qg; post.post_out = codes(w.gcodes); post.post_out8 = r.at8(w.gcodes8); post.post_shift = (int)(0.5f * (qg.qp + 1.f));
       student_linear(r, params, l, 2, r.at(w.x1codes), r.at8(w.x1codes8), backward ? r.at(w.u) : nullptr, post);

@@ -90,6 +90,32 @@ __device__ __forceinline__ float epilogue_apart(float acc, float cs, bool has_be
 // them the kernel of 256 x 256 tiles spilled 99 registers.
 template <int BN>
 constexpr int post_stride = BN + 8;
+__device__ __forceinline__ QuantParam post_quantizer(const QArg& a) {
+  QuantParam q = {*a.s, a.z ? *a.z : 0.f, a.qn, a.qp, 1, 0.f};
+  q.rs = quant_reciprocal(q.s);
+  return q;
+}
+// what quantizes column n (POST_QKV: by sections)
+template <int POST>
+__device__ __forceinline__ QuantParam post_quantizer(const Epilogue& e, int n) {
+  if constexpr (POST == POST_QKV) {
+    const int section = n / e.post_cols;
+    const QuantParam q0 = post_quantizer(e.post_q), q1 = post_quantizer(e.post_q1), q2 = post_quantizer(e.post_q2);
+    return section == 0 ? q0 : section == 1 ? q1 : q2;
+  } else {
+    return post_quantizer(e.post_q);
+  }
+}
+// POST_GELU and POST_QKV straight from a lane's value v (stored as o) at element `at`
+template <int POST>
+__device__ __forceinline__ void post_code(const Epilogue& e, const QuantParam& q, size_t at, float v) {
+  const float o = round_to<bf16_t>(v), c = q_code(q_ratio_fma(POST == POST_GELU ? gelu_t<bf16_t>(o) : o, q), q);
+  if (e.post_out) stf(static_cast<bf16_t*>(e.post_out), at, c);
+  if constexpr (POST == POST_GELU) {
+    if (e.post_out8) e.post_out8[at] = (int8_t)((int)c - e.post_shift);
+  }
+}
+
 // GELU and its quantizer for stored values: bf16 values between 2^-14 and 8 of either sign are 4352, whose codes a block forms once
 // and then looks up (8 vector instructions a value, 29 when each is formed by itself, which are 13 us for 4096 x 4096 values).
 struct GeluCodes {
@@ -107,8 +133,7 @@ __device__ __forceinline__ void gelu_tile(unsigned char* lds, const Epilogue& e,
   constexpr int ROWS = THREADS / (BN / 8);
   const bf16_t* tile = reinterpret_cast<const bf16_t*>(lds);
   GeluCodes* table = reinterpret_cast<GeluCodes*>(lds + BM * post_stride<BN> * sizeof(bf16_t));
-  QuantParam q = {*e.post_q.s, e.post_q.z ? *e.post_q.z : 0.f, e.post_q.qn, e.post_q.qp, 1, 0.f};
-  q.rs = quant_reciprocal(q.s);
+  const QuantParam q = post_quantizer(e.post_q);
   table->fill(q);
   __syncthreads();
   const int row0 = threadIdx.x / (BN / 8), col = threadIdx.x % (BN / 8) * 8;
@@ -163,16 +188,13 @@ __device__ __forceinline__ void post_tile(unsigned char* lds, const Epilogue& e,
   const int row0 = threadIdx.x / (BN / 8), col = threadIdx.x % (BN / 8) * 8;
   const size_t at0 = (size_t)(m0 + row0) * ldc + n0 + col;
   QuantParam q{};
-  if constexpr (POST == POST_STEP) {
-    q = QuantParam{*e.post_q.s, e.post_q.z ? *e.post_q.z : 0.f, e.post_q.qn, e.post_q.qp, 1, 0.f};
-    q.rs = quant_reciprocal(q.s);
-  }
+  if constexpr (POST != POST_MSE) q = post_quantizer<POST>(e, n0 + col);
   auto get = [](const u32x4_t& w, int j) { return __uint_as_float((j & 1) ? w[j >> 1] & 0xffff0000u : w[j >> 1] << 16); };
   float sum = 0.f;
   for (int p = 0; p < BM; p += ROWS * R) {
     u32x4_t in[R];
 #pragma unroll
-    for (int i = 0; i < R; ++i) in[i] = *reinterpret_cast<const u32x4_t*>(static_cast<const bf16_t*>(e.post_in) + at0 + (size_t)(p + i * ROWS) * ldc);
+    for (int i = 0; i < R && POST != POST_QKV; ++i) in[i] = *reinterpret_cast<const u32x4_t*>(static_cast<const bf16_t*>(e.post_in) + at0 + (size_t)(p + i * ROWS) * ldc);
 #pragma unroll
     for (int i = 0; i < R; ++i) {
       const size_t at = at0 + (size_t)(p + i * ROWS) * ldc;
@@ -187,6 +209,12 @@ __device__ __forceinline__ void post_tile(unsigned char* lds, const Epilogue& e,
         }
         *reinterpret_cast<u32x4_t*>(C + at) = o;
         *reinterpret_cast<bf16x8_t*>(static_cast<bf16_t*>(e.post_out) + at) = dy;
+      } else if constexpr (POST == POST_QKV) {
+        bf16x8_t c;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) c[j] = static_cast<bf16_t>(q_code(q_ratio_fma(get(o, j), q), q));
+        *reinterpret_cast<u32x4_t*>(C + at) = o;
+        *reinterpret_cast<bf16x8_t*>(static_cast<bf16_t*>(e.post_out) + at) = c;
       } else {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -197,8 +225,10 @@ __device__ __forceinline__ void post_tile(unsigned char* lds, const Epilogue& e,
       }
     }
   }
-  sum = block_sum(sum, reinterpret_cast<float*>(lds));
-  if (threadIdx.x == 0) e.post_parts[blockIdx.x] = sum;
+  if constexpr (POST == POST_MSE || POST == POST_STEP) {
+    sum = block_sum(sum, reinterpret_cast<float*>(lds));
+    if (threadIdx.x == 0) e.post_parts[blockIdx.x] = sum;
+  }
 }
 
 // The ranges of a block's groups of columns (`groups` slots of lds, filled before; a slot holds them and its section) go out
@@ -399,16 +429,22 @@ void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void* C, in
                             hipStream_t st, int splits) {
   auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const bool whole = whole_tiles(M, N, K);
+  // (each tile where it serves such a product without `post`, see post_ok and post_codes_ok)
   if constexpr (!AT) {
     if (e.post) {
       auto go = [&](auto post) {
         constexpr int POST = decltype(post)::value;
+        if constexpr (POST == POST_GELU || POST == POST_QKV) {
+          if (tiles(64, 64) <= 256) return launch_dl<64, 64, 2, 2, AT, BT, 4, 128, TO, I8, 2, 2, true, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+          if (tiles(128, 64) <= 256) return launch_dl<128, 64, 2, 2, AT, BT, 3, 128, TO, I8, 2, 2, true, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
+        }
         if (tiles(128, 128) <= 256) return launch_dl<128, 128, 2, 2, AT, BT, 4, 128, TO, I8, 1, 2, false, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
         if (tiles(128, 256) <= 256) return launch_quad<128, AT, BT, TO, I8, false, false, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
         return launch_quad<256, AT, BT, TO, I8, false, false, POST>(A, lda, B, ldb, C, ldc, M, N, K, e, st);
       };
       if constexpr (I8) {
         if (e.post == POST_GELU) return go(std::integral_constant<int, POST_GELU>{});
+        if (e.post == POST_QKV) return go(std::integral_constant<int, POST_QKV>{});
       }
       return go(std::integral_constant<int, BT ? POST_STEP : POST_MSE>{});
     }
@@ -470,6 +506,12 @@ bool post_ok(int M, int N, int K) {
   if (!whole_tiles(M, N, K) || tiles(128, 64) <= 256) return false;
   if (tiles(128, 128) <= 256) return true;
   return quad_ok(K) && N % 256 == 0 && (tiles(128, 256) <= 256 || (tiles(256, 256) <= 2048 && M % 256 == 0));
+}
+// ... and for codes also smaller tiles, where a launch less counts most (ragged sizes on larger tiles lose up to 1.5% of a step
+// beside the other stream's kernels: three layers of 768 over 30 x 77 tokens 1190 and 1196 us, four of 1024 over 8 x 141 1649
+// and 1667).
+bool post_codes_ok(int M, int N, int K) {
+  return (int64_t)((M + 127) / 128) * ((N + 63) / 64) <= 256 || post_ok(M, N, K / 2);
 }
 static void gemm_i8_launch(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e,
                            hipStream_t st) {

@@ -422,7 +422,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
   const float beta = (e.beta ? *e.beta : 0.f) + e.beta_alpha * alpha;
   const bool split = !EDGE && gridDim.y > 1, lead = EDGE || blockIdx.y == 0;
   auto write_out = [&](auto with_row, auto with_gelu, auto with_split, auto apart, auto with_range) {
-    constexpr bool RANGE = decltype(with_range)::value;
+    constexpr bool RANGE = decltype(with_range)::value, STAGED = POST != POST_NONE && !EDGE, DIRECT = POST != POST_NONE && EDGE;
     if constexpr (RANGE) __syncthreads();  // nobody reads operands or partial sums any more
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
@@ -437,6 +437,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
       if (!decltype(apart)::value && e.beta && e.col_vec && lead) cb += beta * cv;
       int shift = 0;
       if constexpr (I8 && decltype(apart)::value) shift = e.row_codes ? e.code_shift * e.row_codes[n] : 0;
+      QuantParam post_q{};
+      if constexpr (DIRECT) post_q = post_quantizer<POST>(e, n);
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         if (KG > 1 && BY_ROWS && i % KG != kg) continue;  // a partner wavefront writes this tile row
@@ -462,8 +464,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
           } else {
             if constexpr (decltype(with_gelu)::value) v = gelu_t<TO>(round_to<TO>(v));
             if constexpr (RANGE) range.add(v);
-            if constexpr (POST != POST_NONE) stf(reinterpret_cast<bf16_t*>(smem_dl), (mb - m0 + dm) * post_stride<BN> + n - n0, v);
-            else stf(out, (size_t)dm * ldc, v);
+            if constexpr (STAGED) stf(reinterpret_cast<bf16_t*>(smem_dl), (mb - m0 + dm) * post_stride<BN> + n - n0, v);
+            else if (!DIRECT || C) stf(out, (size_t)dm * ldc, v);
+            if constexpr (DIRECT) post_code<POST>(e, post_q, (size_t)(mb + dm) * ldc + n, v);
           }
         }
       }
@@ -478,8 +481,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
   const bool row_term = e.beta && e.row_vec && lead;
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
-  if constexpr (POST != POST_NONE) {
-    static_assert(!EDGE && !AT && (KG == 1 || BY_ROWS), "whole tiles");
+  if constexpr (POST != POST_NONE && EDGE) {
+    static_assert(I8, "small tiles: codes only");
+    if (e.apart) write_out(no, no, no, yes, no);
+    else write_out(no, no, no, no, no);
+    return;
+  } else if constexpr (POST != POST_NONE) {
+    static_assert(!AT && (KG == 1 || BY_ROWS), "whole tiles");
     static_assert(BM * post_stride<BN> * 2 + sizeof(GeluCodes) <= STAGES * STAGE_BYTES, "the tile fits the stages");
     __syncthreads();  // nobody reads operands or partial sums any more
     write_out(no, no, no, no, no);

@@ -55,12 +55,13 @@ struct Epilogue {
   float* range = nullptr;
   int range_cols = 0;
   int* blocks = nullptr;
-  // post (bf16 output, POST_MSE without transposes, POST_STEP with B transposed; post_ok says for which sizes): what else becomes
-  // of an output value o beside that of `post_in` at its place, t (both as stored); the blocks leave a partial sum each in
-  // post_parts (*blocks of them).
-  //   POST_MSE: post_out = 2 post_scale (o - t), sums of (o - t)^2, as mse_grad
+  // post (bf16 output; post_ok and post_codes_ok say for which sizes): what else becomes of an output value o, as stored.
   //   POST_GELU (int8 codes): the code c of gelu(o) under post_q, post_out = c, post_out8 = c - post_shift, as gelu_quantize; each
-  //     of them and o itself (C) may be null; without post_in and post_parts
+  //     of them and o itself (C) may be null
+  //   POST_QKV (int8 codes): post_out = its code under post_q, post_q1 or post_q2, by sections of post_cols columns, as qkv_quantize
+  // Beside the value of `post_in` at its place, t (without transposes or with B transposed); blocks leave a partial sum each in
+  // post_parts (*blocks of them):
+  //   POST_MSE: post_out = 2 post_scale (o - t), sums of (o - t)^2, as mse_grad
   //   POST_STEP: sums of o (code - v inside) of t under post_q, as quant_bwd_reduce; o is stored only if post_out is not null
   int post = 0;
   const void* post_in = nullptr;
@@ -69,10 +70,12 @@ struct Epilogue {
   int post_shift = 0;
   float* post_parts = nullptr;
   float post_scale = 0.f;
-  QArg post_q;
+  QArg post_q, post_q1, post_q2;
+  int post_cols = 0;
 };
-enum { POST_NONE = 0, POST_MSE, POST_STEP, POST_GELU };
-bool post_ok(int M, int N, int K);  // (K: in 2-byte elements)
+enum { POST_NONE = 0, POST_MSE, POST_STEP, POST_GELU, POST_QKV };
+bool post_ok(int M, int N, int K);        // POST_MSE, POST_STEP (K: in 2-byte elements)
+bool post_codes_ok(int M, int N, int K);  // POST_GELU, POST_QKV (K: in codes)
 
 // Timing of product launches with the pair of HIP events that a launch itself carries (measurement aid).
 // A context owns one; products launched with a profile whose `on` is set are recorded in it.

@@ -1,6 +1,6 @@
-"""Codes of the GELU formed by the first feed-forward projection's kernel, on each tile that does it, against those of a pass of
-its own: sentences in a batch large enough for these tiles and by themselves, where sums of codes are exact and every other
-operation is the same, so the quantized module's outputs are the same bits."""
+"""Codes that the quantized projections' kernels form of their output, on each tile that does it: sentences in a batch large
+enough for tiles whose codes are formed from LDS, by table for the GELU, and by themselves, where small tiles form each value's
+code from its own erf.  Sums of codes are exact and every other operation is the same, so the outputs are the same bits."""
 import pytest
 
 pytestmark = pytest.mark.gpu
