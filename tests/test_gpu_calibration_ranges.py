@@ -20,14 +20,14 @@ def test_ranges(name):
     H, nh, ffn, batch, seq = SHAPES[name]
     g = torch.Generator("cuda").manual_seed(3)
     mod = B.MremModule(1, H, nh, ffn, batch, seq)
-    t = torch.randn(mod.teacher.numel(), generator=g, device="cuda") * 0.05
+    t = torch.randn(mod.teacher.numel(), generator=g, device="cuda", dtype=torch.float32) * 0.05
     field = lambda f: t[B.mrem_param_offset(mod.ctx, 0, f):][:B.mrem_param_size(mod.ctx, f)]
     for f in ("ln1_g", "ln2_g"):
         field(f).add_(1.0)
     mod.teacher.copy_(t)
     B.mrem_teacher_prepare(mod.ctx, mod.teacher, mod.teacher_cache)
     mod.params.copy_(mod.teacher)
-    x = torch.randn(batch, seq, H, generator=g, device="cuda")
+    x = torch.randn(batch, seq, H, generator=g, device="cuda", dtype=torch.float32)
     x[-1] *= 2.0
     x = x.bfloat16()
     mod.calibrate(x)
@@ -45,7 +45,7 @@ def test_ranges(name):
     got = mod.params[B.mrem_param_offset(mod.ctx, 0, "s_a"):][:8]
     z = mod.params[B.mrem_param_offset(mod.ctx, 0, "z_a") + 7]
     # a stored value is off by 2^-9 of itself; up to four roundings in a row, and a probability by the score's, at most 10 here
-    tol = torch.tensor([2.0 ** -7] * 8, device="cuda")
+    tol = torch.tensor([2.0 ** -7] * 8, device="cuda", dtype=torch.float32)
     tol[3] = 10 * 2.0 ** -8
     assert torch.all((got - ref).abs() <= tol * ref), (got / ref).tolist()
     assert (z - gelu.min()).abs() <= 2.0 ** -7 * 0.17 + 2.0 ** -9

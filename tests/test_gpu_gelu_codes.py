@@ -14,7 +14,7 @@ def test_same_bits(hidden, heads, ffn, batch, a_bits):
     from paper_2109_15082_amd import binding as B
     g = torch.Generator("cuda").manual_seed(hidden + a_bits)
     mod = B.MremModule(1, hidden, heads, ffn, batch, 128, w_bits=8, a_bits=a_bits)
-    t = torch.randn(mod.teacher.numel(), generator=g, device="cuda") * 0.03
+    t = torch.randn(mod.teacher.numel(), generator=g, device="cuda", dtype=torch.float32) * 0.03
     field = lambda f: t[B.mrem_param_offset(mod.ctx, 0, f):][:B.mrem_param_size(mod.ctx, f)]
     for f in ("ln1_g", "ln2_g"):
         field(f).add_(1.0)
@@ -29,7 +29,7 @@ def test_same_bits(hidden, heads, ffn, batch, a_bits):
     B.mrem_teacher_prepare(mod.ctx, mod.teacher, mod.teacher_cache)
     mod.params.copy_(mod.teacher)
     mod.init_steps()
-    x = torch.randn(batch, 128, hidden, generator=g, device="cuda").bfloat16()
+    x = torch.randn(batch, 128, hidden, generator=g, device="cuda", dtype=torch.float32).bfloat16()
     mod.calibrate(x[:1].contiguous())
     _, among = mod.forward(x, x)
     among = among.clone()

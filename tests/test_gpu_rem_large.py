@@ -12,19 +12,19 @@ def test_rem_step(T, N, K, bits):
     import torch
     from paper_2109_15082_amd import binding as B
     g = torch.Generator("cuda").manual_seed(T + N + K)
-    randn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    randn = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.float32)
     ctx = B.mrem_create(n_layers=1, hidden=64, n_heads=1, ffn=64, max_batch=1, max_seq=8, w_bits=bits, a_bits=8, act_dtype=B.MREM_BF16, per_channel=1)
     w_fp = randn(N, K) * 0.02
     a_fp = randn(T, K).bfloat16()
     a_q = (a_fp.float() + 0.05 * randn(T, K)).bfloat16()
     qp = 2 ** (bits - 1) - 1
-    vec = torch.zeros(B.mrem_rem_vector_count(N, K), device="cuda")
+    vec = torch.zeros(B.mrem_rem_vector_count(N, K), device="cuda", dtype=torch.float32)
     w = w_fp + 5e-4 * randn(N, K)
     s_w = w.abs().amax(1) / qp * 0.9
     s_a = a_q.float().abs().max() / 127 * 0.9
     vec[:N * K], vec[N * K:N * K + N], vec[N * K + N] = w.reshape(-1), s_w, s_a
     m, v, grads = torch.zeros_like(vec), torch.zeros_like(vec), torch.zeros_like(vec)
-    loss = torch.zeros(1, device="cuda")
+    loss = torch.zeros(1, device="cuda", dtype=torch.float32)
     y_fp, y_q = (torch.empty(T, N, dtype=torch.bfloat16, device="cuda") for _ in range(2))
     ws = torch.empty(B.mrem_rem_workspace_bytes(ctx, T, N, K), dtype=torch.uint8, device="cuda")
     B.mrem_rem_step(ctx, T, N, K, vec, m, v, 1, 1e-3, w_fp, a_fp, a_q, loss, y_fp, y_q, grads, ws)
@@ -36,7 +36,7 @@ def test_rem_step(T, N, K, bits):
     assert close(y_q, (codes_a @ codes_w.T) * s_a.double() * s_w.double(), 2.0 ** -8)
     d = y_q.float() - y_fp.float()
     assert abs(loss.item() / d.double().square().mean().item() - 1) <= 1e-5
-    dy = (2.0 * d * torch.tensor(1.0 / (T * N), device="cuda")).bfloat16().double()
+    dy = (2.0 * d * torch.tensor(1.0 / (T * N), device="cuda", dtype=torch.float32)).bfloat16().double()
     inside_w = (ratio_w >= -qp) & (ratio_w <= qp)
     dw = dy.T @ codes_a * s_a.double()
     assert close(grads[:N * K].reshape(N, K), dw * inside_w, 1e-5)
