@@ -307,6 +307,7 @@ Plan make_plan(const mrem_ctx* c, int B, int S) {
   // first-stage partial sums of one layer's backward pass (all of them stay until the single
   // second-stage launch at the end of the backward pass): two LayerNorms, two bias column sums,
   // the elementwise kernels (at most 2048 blocks, up to 3 values each) and the attention rows
+  // (in the forward pass, the sums of the weight codes' rows)
   size_t np = 2 * (size_t)ln_bwd_parts((int)T) * (3 * H + 2) + (size_t)kColMaxParts * (F + 3 * H) + 8 * 2048 + (size_t)B * c->nh * S;
   static_assert(8 * 3 * kCalibParts <= 8 * 2048, "the partial ranges of a layer's eight quantizers fit too");
   np = (np + 63) & ~size_t(63);
@@ -385,6 +386,12 @@ const int kBField[4] = {MREM_F_B_QKV, MREM_F_B_O, MREM_F_B_1, MREM_F_B_2};
 const int kSField[4] = {MREM_F_SW_QKV, MREM_F_SW_O, MREM_F_SW_1, MREM_F_SW_2};
 const int kInQuant[4] = {0, 5, 6, 7};  // activation quantizer feeding each linear layer
 
+// sums of the weight codes of linear layer i's rows; they wait in the layer's partial sums, which only the backward pass forms
+int* row_codes(const Run& r, int l, int i) {
+  int* at = r.at<int>(r.p.partials) + r.p.partials_per_layer * l;
+  for (int k = 0; k < i; ++k) at += r.c->wN[k];
+  return at;
+}
 // quantized linear layer i of layer l: out = codes_in * wcodes^T with the steps in the epilogue; `post`: what else its kernel does
 void student_linear(const Run& r, const float* params, int l, int i, const void* in_codes, const int8_t* in_codes8, void* out,
                     const Epilogue& post = Epilogue()) {
@@ -401,7 +408,7 @@ void student_linear(const Run& r, const float* params, int l, int i, const void*
     // unsigned codes (GELU output) are stored recentred by half their range; the epilogue adds that back, in whole tiles to the
     // result, in others to the sum of codes, which then is that of a product of bf16 codes
     if (q.z && r.T % 128 == 0) e.beta_alpha = 0.5f * (q.qp + 1.f);
-    else if (q.z) { e.row_codes = r.at<int>(r.p.lw[l].wcodes[i]); e.code_shift = (int)(0.5f * (q.qp + 1.f)); }
+    else if (q.z) { e.row_codes = row_codes(r, l, i); e.code_shift = (int)(0.5f * (q.qp + 1.f)); }
     gemm_i8(in_codes8, c->wK[i], r.at8(r.p.lw[l].wcodes8[i]), c->wK[i], out, c->wN[i], r.T, c->wN[i], c->wK[i], e, r.st, r.prof);
     return;
   }
@@ -421,8 +428,9 @@ void prepare_weights(const Run& r, const float* params, bool backward, int l0 = 
       WeightJob j;
       j.w = base + c->foff[kWField[i]]; j.sw = base + c->foff[kSField[i]];
       j.codes8 = r.at8(r.p.lw[l].wcodes8[i]);
-      j.codes = j.codes8 ? nullptr : r.at(r.p.lw[l].wcodes[i]);  // the forward reads one or the other
-      j.row_codes = j.codes8 ? r.at<int>(r.p.lw[l].wcodes[i]) : nullptr;
+      // (the forward reads one or the other; beside int8 ones of a call that has no whole tiles they are left for inspection)
+      j.codes = j.codes8 && r.T % 128 == 0 ? nullptr : r.at(r.p.lw[l].wcodes[i]);
+      j.row_codes = j.codes8 ? row_codes(r, l, i) : nullptr;
       j.what = backward ? r.at(r.p.lw[l].what[i]) : nullptr; j.zcorr = r.at<float>(r.p.lw[l].zcorr[i]);
       j.N = c->wN[i]; j.K = c->wK[i];
       jobs.push_back(j);
@@ -431,7 +439,7 @@ void prepare_weights(const Run& r, const float* params, bool backward, int l0 = 
   double nw = 0;
   for (const WeightJob& j : jobs) nw += (double)j.N * j.K;
   // fp32 master in; codes (int8, or the storage type) and the dequantized copy out
-  timed(r, "weight_codes_k", nw * (4 + (r.i8() ? 1 : dt_size(c->dt)) + (backward ? dt_size(c->dt) : 0)),
+  timed(r, "weight_codes_k", nw * (4 + (r.i8() ? 1 : 0) + (r.i8() && r.T % 128 == 0 ? 0 : dt_size(c->dt)) + (backward ? dt_size(c->dt) : 0)),
         [&] { weight_prepare(c->dt, jobs.data(), (int)jobs.size(), c->cfg.w_bits, r.st); });
 }
 
@@ -939,7 +947,7 @@ extern "C" int64_t mrem_workspace_offset(const mrem_ctx* ctx, int32_t batch, int
   if (!ctx || batch < 1 || seq < 1 || layer < 0 || layer >= ctx->L) return -1;
   const Plan p = make_plan(ctx, batch, seq);
   const LayerWs& w = p.lw[layer];
-  const bool i8 = i8_config(ctx);
+  const bool i8 = i8_config(ctx) && (batch * seq) % 128 == 0;
   if (item >= MREM_WS_WCODES8 && item < MREM_WS_WCODES8 + 4) return i8 ? (int64_t)w.wcodes8[item - MREM_WS_WCODES8] : -1;
   if (item >= MREM_WS_WCODES && item < MREM_WS_WCODES + 4) return i8 ? -1 : (int64_t)w.wcodes[item - MREM_WS_WCODES];
   if (item == MREM_WS_QKV) return (int64_t)w.qkv;
