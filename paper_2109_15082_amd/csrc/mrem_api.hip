@@ -649,9 +649,8 @@ std::vector<WgradJob> wgrad_jobs(const Run& r, const float* params, float* grads
   return jobs;
 }
 // input-gradient product: d(in^) = dY * W^ with the dequantized weights [N_out, K_in]
-void dgrad(const Run& r, int l, int i, const void* dy, void* out) {
+void dgrad(const Run& r, int l, int i, const void* dy, void* out, const Epilogue& e = Epilogue()) {
   const mrem_ctx* c = r.c;
-  Epilogue e;
   gemm(c->dt, 0, 1, dy, c->wN[i], r.at(r.p.lw[l].what[i]), c->wK[i], out, c->wK[i], r.T, c->wK[i], c->wN[i], e, r.st, r.prof);
 }
 
@@ -774,18 +773,28 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
     }
     // second feed-forward projection
     issue_wgrad(3, r.at(dr2), r.at(w.gcodes));
-    dgrad(r, l, 3, r.at(dr2), r.at(r.p.dgh));
     // GELU and its output quantizer
     {
       // the kernel also leaves the column sums of du per row slab: the bias gradient of the first projection
       float* parts = red.take(2048);
       float* cols = red.take((size_t)kColMaxParts * F);
+      const QArg qg = make_q(c, params, l, 7);
       before_overwrite(2);
-      ColGrid cg{};
-      timed(r, "gelu_quant_bwd_k", (double)T * F * 3 * es,
-            [&] { cg = gelu_quant_bwd(c->dt, r.at(r.p.dgh), r.at(w.u), r.at(du), T, F, make_q(c, params, l, 7), parts, cols, r.st); });
-      red.add(parts, cg.gx * cg.gy, 1, 0, 1, g + c->foff[MREM_F_S_A] + 7);
-      red.add(cols, cg.gy, F, 0, F, g + c->foff[MREM_F_B_1]);
+      int n = 0, slabs = 0;
+      if (c->dt == DT_BF16 && qg.on && post_ok(T, F, H) && T / 128 <= kColMaxParts) {
+        Epilogue post;
+        post.post = POST_DGELU; post.post_in = r.at(w.u); post.post_q = qg; post.post_parts = parts; post.post_col_parts = cols; post.blocks = &n; post.row_tiles = &slabs;
+        dgrad(r, l, 3, r.at(dr2), r.at(du), post);
+      } else {
+        dgrad(r, l, 3, r.at(dr2), r.at(r.p.dgh));
+        timed(r, "gelu_quant_bwd_k", (double)T * F * 3 * es, [&] {
+          const ColGrid cg = gelu_quant_bwd(c->dt, r.at(r.p.dgh), r.at(w.u), r.at(du), T, F, qg, parts, cols, r.st);
+          n = cg.gx * cg.gy;
+          slabs = cg.gy;
+        });
+      }
+      red.add(parts, n, 1, 0, 1, g + c->foff[MREM_F_S_A] + 7);
+      red.add(cols, slabs, F, 0, F, g + c->foff[MREM_F_B_1]);
     }
     // first feed-forward projection
     issue_wgrad(2, r.at(du), r.at(w.x1codes));
@@ -807,12 +816,18 @@ void student_backward(const Run& r, const float* params, const void* x_q, const 
     }
     // attention output projection
     issue_wgrad(1, r.at(dr1), r.at(w.ctxcodes));
-    dgrad(r, l, 1, r.at(dr1), r.at(r.p.dch));
     {
       float* parts = red.take(2048);
+      const QArg qc = make_q(c, params, l, 5);
       int n = 0;
-      timed(r, "quant_bwd_k", (double)numel * 3 * es,
-            [&] { n = quant_bwd(c->dt, r.at(r.p.dch), r.at(w.ctx), r.at(r.p.dc), numel, make_q(c, params, l, 5), parts, r.st); });
+      if (c->dt == DT_BF16 && qc.on && post_ok(T, H, H)) {
+        Epilogue post;
+        post.post = POST_MASK; post.post_in = r.at(w.ctx); post.post_q = qc; post.post_parts = parts; post.blocks = &n;
+        dgrad(r, l, 1, r.at(dr1), r.at(r.p.dc), post);
+      } else {
+        dgrad(r, l, 1, r.at(dr1), r.at(r.p.dch));
+        timed(r, "quant_bwd_k", (double)numel * 3 * es, [&] { n = quant_bwd(c->dt, r.at(r.p.dch), r.at(w.ctx), r.at(r.p.dc), numel, qc, parts, r.st); });
+      }
       red.add(parts, n, 1, 0, 1, g + c->foff[MREM_F_S_A] + 5);
     }
     // attention

@@ -179,11 +179,101 @@ __device__ __forceinline__ void gelu_tile(unsigned char* lds, const Epilogue& e,
     }
   }
 }
+// What the backward pass needs of a stored value u in front of the GELU and its quantizer is a function of its 16 bits too: the
+// derivative, zero outside the quantizer's range, and the term of the step's gradient.  Values between 2^-11 and 8 are looked up
+// (34 vector instructions when formed); 6 values in 10000 of N(0, 0.64) lie outside and are formed one by one.  A pass of its own
+// read both tensors again and was bound by those instructions: 26 us for 4096 x 4096 values.  With it and the context's
+// (POST_MASK, 8 us) in the products a step of six layers of 1024 over 4096 tokens takes 3975 us instead of 4112, over 16 x 384
+// 5588 instead of 5802, three of 768 over 32 x 128 1541 instead of 1603.
+struct GeluSlopes {
+  static constexpr unsigned LOW = 116u << 7, N = 14u * 128u;  // bits of 2^-11; values of one sign
+  float2 of[2 * N];
+  static __device__ __forceinline__ float2 form(unsigned bits, const QuantParam& q) {
+    const float u = __uint_as_float(bits << 16), v = q_ratio_fma(gelu_t<bf16_t>(u), q);
+    const bool in = q_inside(v, q);
+    return make_float2((in ? 1.f : 0.f) * gelu_grad_t<bf16_t>(u), q_code(v, q) - (in ? v : 0.f));
+  }
+  __device__ __forceinline__ void fill(const QuantParam& q) {
+    for (unsigned i = threadIdx.x; i < 2 * N; i += blockDim.x) of[i] = form((i < N ? LOW : 0x8000u + LOW - N) + i, q);
+  }
+};
+template <int POST>
+constexpr size_t post_table = POST == POST_DGELU ? sizeof(GeluSlopes) : POST == POST_GELU ? sizeof(GeluCodes) : 0;
+template <int BM, int BN, int THREADS>
+__device__ __forceinline__ void dgelu_tile(unsigned char* lds, const Epilogue& e, bf16_t* __restrict__ C, int ldc, int m0, int n0) {
+  constexpr int CHUNKS = BN / 8, ROWS = THREADS / CHUNKS, R = 4;
+  static_assert(BM % (ROWS * R) == 0 && ROWS * BN * 4 <= BM * post_stride<BN> * 2, "whole passes, column sums fit the tile");
+  const bf16_t* tile = reinterpret_cast<const bf16_t*>(lds);
+  GeluSlopes* table = reinterpret_cast<GeluSlopes*>(lds + BM * post_stride<BN> * sizeof(bf16_t));
+  const QuantParam q = post_quantizer(e.post_q);
+  const int row0 = threadIdx.x / CHUNKS, col = threadIdx.x % CHUNKS * 8;
+  const size_t at0 = (size_t)(m0 + row0) * ldc + n0 + col;
+  const bf16_t* const u = static_cast<const bf16_t*>(e.post_in) + at0;
+  u32x4_t in[R];
+  auto fetch = [&](int p) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) in[i] = *reinterpret_cast<const u32x4_t*>(u + (size_t)(p + i * ROWS) * ldc);
+  };
+  fetch(0);
+  table->fill(q);
+  __syncthreads();
+  float sum = 0.f, cols[8] = {};
+  for (int p = 0; p < BM; p += ROWS * R) {
+    if (p) fetch(p);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const u32x4_t o = *reinterpret_cast<const u32x4_t*>(tile + (row0 + p + i * ROWS) * post_stride<BN> + col);
+      float2 t[8];
+      unsigned outside = 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const unsigned bits = (j & 1) ? in[i][j >> 1] >> 16 : in[i][j >> 1] & 0xffffu, k = (bits & 0x7fffu) - GeluSlopes::LOW;
+        t[j] = table->of[min(k, GeluSlopes::N - 1) + (bits >> 15) * GeluSlopes::N];
+        outside |= k < GeluSlopes::N ? 0u : 1u << j;
+      }
+      while (outside) {
+        const int j = __ffs((int)outside) - 1;
+        outside &= outside - 1;
+        unsigned word = in[i][0];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) word = j >> 1 == k ? in[i][k] : word;
+        const float2 f = GeluSlopes::form((j & 1) ? word >> 16 : word & 0xffffu, q);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (k == j) t[k] = f;
+      }
+      bf16x8_t d;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float g = __uint_as_float((j & 1) ? o[j >> 1] & 0xffff0000u : o[j >> 1] << 16);
+        sum += g * t[j].y;
+        d[j] = static_cast<bf16_t>(t[j].x != 0.f ? g * t[j].x : 0.f);  // (zero outside whatever g is)
+        cols[j] += static_cast<float>(d[j]);
+      }
+      *reinterpret_cast<bf16x8_t*>(C + at0 + (size_t)(p + i * ROWS) * ldc) = d;
+    }
+  }
+  __syncthreads();  // nobody reads the tile any more
+  float* const part = reinterpret_cast<float*>(lds);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) part[row0 * BN + col + j] = cols[j];
+  __syncthreads();
+  for (int n = threadIdx.x; n < BN; n += THREADS) {
+    float c = 0.f;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) c += part[r * BN + n];
+    e.post_col_parts[(size_t)(m0 / BM) * ldc + n0 + n] = c;
+  }
+  __syncthreads();
+  sum = block_sum(sum, part);
+  if (threadIdx.x == 0) e.post_parts[blockIdx.x] = sum;
+}
 template <int POST, int BM, int BN, int THREADS>
 __device__ __forceinline__ void post_tile(unsigned char* lds, const Epilogue& e, bf16_t* __restrict__ C, int ldc, int m0, int n0) {
   constexpr int ROWS = THREADS / (BN / 8), R = 4;  // rows a pass, passes in flight
   static_assert(BM % (ROWS * R) == 0, "whole passes");
   if constexpr (POST == POST_GELU) return gelu_tile<BM, BN, THREADS>(lds, e, C, ldc, m0, n0);
+  if constexpr (POST == POST_DGELU) return dgelu_tile<BM, BN, THREADS>(lds, e, C, ldc, m0, n0);
   const bf16_t* tile = reinterpret_cast<const bf16_t*>(lds);
   const int row0 = threadIdx.x / (BN / 8), col = threadIdx.x % (BN / 8) * 8;
   const size_t at0 = (size_t)(m0 + row0) * ldc + n0 + col;
@@ -216,16 +306,20 @@ __device__ __forceinline__ void post_tile(unsigned char* lds, const Epilogue& e,
         *reinterpret_cast<u32x4_t*>(C + at) = o;
         *reinterpret_cast<bf16x8_t*>(static_cast<bf16_t*>(e.post_out) + at) = c;
       } else {
+        bf16x8_t d;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           const float v = q_ratio_fma(get(in[i], j), q);
-          sum += get(o, j) * (q_code(v, q) - (q_inside(v, q) ? v : 0.f));
+          const bool inside = q_inside(v, q);
+          sum += get(o, j) * (q_code(v, q) - (inside ? v : 0.f));
+          if constexpr (POST == POST_MASK) d[j] = static_cast<bf16_t>(inside ? get(o, j) : 0.f);
         }
-        if (e.post_out) *reinterpret_cast<u32x4_t*>(C + at) = o;
+        if constexpr (POST == POST_MASK) *reinterpret_cast<bf16x8_t*>(C + at) = d;
+        else if (e.post_out) *reinterpret_cast<u32x4_t*>(C + at) = o;
       }
     }
   }
-  if constexpr (POST == POST_MSE || POST == POST_STEP) {
+  if constexpr (POST != POST_QKV) {
     sum = block_sum(sum, reinterpret_cast<float*>(lds));
     if (threadIdx.x == 0) e.post_parts[blockIdx.x] = sum;
   }
@@ -445,6 +539,10 @@ void launch_dl_tiles(const void* A, int lda, const void* B, int ldb, void* C, in
       if constexpr (I8) {
         if (e.post == POST_GELU) return go(std::integral_constant<int, POST_GELU>{});
         if (e.post == POST_QKV) return go(std::integral_constant<int, POST_QKV>{});
+      }
+      if constexpr (BT) {
+        if (e.post == POST_DGELU) return go(std::integral_constant<int, POST_DGELU>{});
+        if (e.post == POST_MASK) return go(std::integral_constant<int, POST_MASK>{});
       }
       return go(std::integral_constant<int, BT ? POST_STEP : POST_MSE>{});
     }

@@ -488,7 +488,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG, MINB) void gemm_dl_k(c
     return;
   } else if constexpr (POST != POST_NONE) {
     static_assert(!AT && (KG == 1 || BY_ROWS), "whole tiles");
-    static_assert(BM * post_stride<BN> * 2 + sizeof(GeluCodes) <= STAGES * STAGE_BYTES, "the tile fits the stages");
+    static_assert(BM * post_stride<BN> * 2 + post_table<POST> <= STAGES * STAGE_BYTES, "the tile fits the stages");
     __syncthreads();  // nobody reads operands or partial sums any more
     write_out(no, no, no, no, no);
     __syncthreads();
@@ -529,6 +529,7 @@ static void launch_dl(const void* A, int lda, const void* B, int ldb, void* C, i
   }
   const int tiles_m = EDGE ? (M + BM - 1) / BM : M / BM, tiles_n = EDGE ? (N + BN - 1) / BN : N / BN;
   if (e.blocks) *e.blocks = tiles_m * tiles_n;
+  if (e.row_tiles) *e.row_tiles = tiles_m;
   if (tl_launch_events.e0) {
     hipExtLaunchKernelGGL((gemm_dl_k<BM, BN, WAVES_M, WAVES_N, AT, BT, STAGES, RB, TO, I8, MINB, KG, EDGE, POST>), dim3(tiles_m * tiles_n, k_splits),
                           dim3(NTHREADS), lds, st, tl_launch_events.e0, tl_launch_events.e1, 0, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C, ldc, M, N,

@@ -326,9 +326,10 @@ __global__ __launch_bounds__(512, 1) void gemm_quad_wgrads_k(QuadJobs jobs, int 
 static bool quad_ok(int K) { return K % (2 * kBK) == 0; }
 
 // LDS of a kernel of BM x 256 tiles, beyond what is allowed without asking
-template <int BM>
-static size_t quad_lds(const void* kernel, std::atomic<int>& configured_dev, bool post = false) {
-  const size_t stages = 2 * (BM + 256) * 128, lds = post ? std::max(stages, BM * post_stride<256> * sizeof(bf16_t) + sizeof(GeluCodes)) : stages;
+template <int BM, int POST = POST_NONE>
+static size_t quad_lds(const void* kernel, std::atomic<int>& configured_dev) {
+  constexpr size_t stages = 2 * (BM + 256) * 128, lds = POST != POST_NONE ? std::max(stages, BM * post_stride<256> * sizeof(bf16_t) + post_table<POST>) : stages;
+  static_assert(lds <= 160 * 1024, "LDS of a compute unit");
   int dev = -1;
   (void)hipGetDevice(&dev);
   if (dev != configured_dev.load()) {
@@ -342,9 +343,10 @@ template <int BM, bool AT, bool BT, class TO, bool I8, bool EDGE, bool PAIR = fa
 static void launch_quad(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e, hipStream_t st) {
   constexpr int BN = 256;
   static std::atomic<int> configured_dev{-1};
-  const size_t lds = quad_lds<BM>(reinterpret_cast<const void*>(&gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR, POST>), configured_dev, POST != POST_NONE);
+  const size_t lds = quad_lds<BM, POST>(reinterpret_cast<const void*>(&gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR, POST>), configured_dev);
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   if (e.blocks) *e.blocks = tiles_m * tiles_n;
+  if (e.row_tiles) *e.row_tiles = tiles_m;
   MREM_LAUNCH((gemm_quad_k<BM, AT, BT, TO, I8, EDGE, PAIR, POST>), dim3(tiles_m * tiles_n), dim3(512), lds, st, (const bf16_t*)A, lda, (const bf16_t*)B, ldb, (TO*)C,
               ldc, M, N, K, e, tiles_m, tiles_n);
 }

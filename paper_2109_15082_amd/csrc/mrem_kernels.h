@@ -51,10 +51,11 @@ struct Epilogue {
   int code_shift = 0;
   // range (not with transposes, int8 codes or fp32): the products' blocks also leave the range of what they store (with gelu:
   // of its values before they are rounded) as partials, as absminmax does; range_cols: section width, a multiple of 32 (0: one
-  // section); *blocks: how many blocks
+  // section); *blocks: how many blocks, *row_tiles: how many rows of tiles
   float* range = nullptr;
   int range_cols = 0;
   int* blocks = nullptr;
+  int* row_tiles = nullptr;
   // post (bf16 output; post_ok and post_codes_ok say for which sizes): what else becomes of an output value o, as stored.
   //   POST_GELU (int8 codes): the code c of gelu(o) under post_q, post_out = c, post_out8 = c - post_shift, as gelu_quantize; each
   //     of them and o itself (C) may be null
@@ -63,18 +64,23 @@ struct Epilogue {
   // post_parts (*blocks of them):
   //   POST_MSE: post_out = 2 post_scale (o - t), sums of (o - t)^2, as mse_grad
   //   POST_STEP: sums of o (code - v inside) of t under post_q, as quant_bwd_reduce; o is stored only if post_out is not null
+  //   POST_MASK (B transposed): the same sums; what is stored is o where t is inside post_q, as quant_bwd
+  //   POST_DGELU (B transposed): t is what the GELU and its quantizer post_q were applied to; what is stored is o times their
+  //     derivative, with sums of o (code - v inside) and, in post_col_parts, one row of column sums of what is stored for every
+  //     row of tiles, as gelu_quant_bwd
   int post = 0;
   const void* post_in = nullptr;
   void* post_out = nullptr;
   int8_t* post_out8 = nullptr;
   int post_shift = 0;
   float* post_parts = nullptr;
+  float* post_col_parts = nullptr;
   float post_scale = 0.f;
   QArg post_q, post_q1, post_q2;
   int post_cols = 0;
 };
-enum { POST_NONE = 0, POST_MSE, POST_STEP, POST_GELU, POST_QKV };
-bool post_ok(int M, int N, int K);        // POST_MSE, POST_STEP (K: in 2-byte elements)
+enum { POST_NONE = 0, POST_MSE, POST_STEP, POST_GELU, POST_QKV, POST_DGELU, POST_MASK };
+bool post_ok(int M, int N, int K);        // POST_MSE, POST_STEP, POST_MASK, POST_DGELU (K: in 2-byte elements)
 bool post_codes_ok(int M, int N, int K);  // POST_GELU, POST_QKV (K: in codes)
 
 // Timing of product launches with the pair of HIP events that a launch itself carries (measurement aid).
