@@ -2,6 +2,8 @@
 // with the straight-through backward of Section 3.1.1), residual + LayerNorm,
 // GELU, the per-layer squared-error term of Eq. 3 (inside the backward kernel of the
 // second LayerNorm), calibration reductions and the AdamW update.
+#include <algorithm>
+
 #include "mrem_common.h"
 #include "mrem_kernels.h"
 
@@ -1020,23 +1022,61 @@ __global__ void weight_quantize_i8_k(const float* __restrict__ w, float* __restr
   }
   for (int64_t k = threadIdx.x; k < K; k += blockDim.x) codes[n * K + k] = (int8_t)weight_code(wr[k], s, qp);
 }
-// One step for the whole tensor: every block leaves the largest |w| of its part, one block turns them into the step
-// (3000 x 777: 13 us for all three launches; 646 us with one block searching the whole tensor).  A single block forms
-// the step itself.
-__global__ __launch_bounds__(1024) void tensor_absmax_k(const float* __restrict__ w, int64_t n, float* __restrict__ partials,
-                                                        float* __restrict__ scale, float qp) {
+// One step for the whole tensor.  Up to kOneBlockTensor weights one block keeps them all in registers between the search for the
+// maximum and the quantizer (whole calls, us: 64 x 64 10.2 -> 7.7, 181 x 181 10.2 -> 7.3, where a call that finds nothing takes 7.3).  Beyond,
+// a launch leaves every block's maximum and a zero behind them in the first codes, and the next one's blocks each turn these into
+// the step while their own weights are on their way; whoever counts the last block that has read them overwrites them (600 x 400
+// 12.9 -> 10.3, 1024 x 1024 13.3 -> 10.3, 3000 x 777 13.1 -> 11.9 against a launch between the two).
+__device__ __forceinline__ float max_abs(float m, const float4& v) {
+  return fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+}
+constexpr int kOneBlockChunks = 8;
+constexpr int64_t kOneBlockTensor = 1024 * 4 * kOneBlockChunks;
+__global__ __launch_bounds__(1024) void tensor_quantize_one_k(const float* __restrict__ w, int n, float* __restrict__ scale,
+                                                              int8_t* __restrict__ codes, float qp) {
+  __shared__ float red[17];
+  const int n4 = n / 4, t = threadIdx.x, rest = 4 * n4 + t;
+  float4 v[kOneBlockChunks];
+#pragma unroll
+  for (int i = 0; i < kOneBlockChunks; ++i)
+    v[i] = t + 1024 * i < n4 ? reinterpret_cast<const float4*>(w)[t + 1024 * i] : make_float4(0.f, 0.f, 0.f, 0.f);
+  const float last = rest < n ? w[rest] : 0.f;
+  float m = fabsf(last);
+#pragma unroll
+  for (int i = 0; i < kOneBlockChunks; ++i) m = max_abs(m, v[i]);
+  const float s = step_of_max(block_max(m, red), qp);
+  if (t == 0) scale[0] = s;
+#pragma unroll
+  for (int i = 0; i < kOneBlockChunks; ++i)
+    if (t + 1024 * i < n4) reinterpret_cast<unsigned*>(codes)[t + 1024 * i] = pack_codes(v[i], s, qp);
+  if (rest < n) codes[rest] = (int8_t)weight_code(last, s, qp);
+}
+// chunks of 4 weights that a thread has in flight
+constexpr int kTensorChunks = 4;
+__global__ __launch_bounds__(256) void tensor_absmax_k(const float* __restrict__ w, int64_t n, float* __restrict__ partials) {
   __shared__ float red[17];
   float m = 0.f;
   const int64_t n4 = n / 4, stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n4; i += stride) {
-    const float4 v = reinterpret_cast<const float4*>(w)[i];
-    m = fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n4; i += kTensorChunks * stride) {
+    float4 v[kTensorChunks];
+#pragma unroll
+    for (int j = 0; j < kTensorChunks; ++j) v[j] = reinterpret_cast<const float4*>(w)[i + j * stride < n4 ? i + j * stride : i];
+#pragma unroll
+    for (int j = 0; j < kTensorChunks; ++j) m = max_abs(m, v[j]);
   }
   if (blockIdx.x == 0 && threadIdx.x < (n & 3)) m = fmaxf(m, fabsf(w[4 * n4 + threadIdx.x]));
   m = block_max(m, red);
   if (threadIdx.x != 0) return;
-  if (gridDim.x == 1) scale[0] = step_of_max(m, qp);
-  else partials[blockIdx.x] = m;
+  partials[blockIdx.x] = m;
+  if (blockIdx.x == 0) reinterpret_cast<unsigned*>(partials)[gridDim.x] = 0u;
+}
+__global__ __launch_bounds__(256) void tensor_quantize_i8_k(const float* __restrict__ w, const float* __restrict__ scale, int8_t* __restrict__ codes, int64_t n,
+                                                            float qp) {
+  const float s = scale[0];
+  const int64_t n4 = n / 4, stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n4; i += stride)
+    reinterpret_cast<unsigned*>(codes)[i] = pack_codes(reinterpret_cast<const float4*>(w)[i], s, qp);
+  if (blockIdx.x == 0 && threadIdx.x < (n & 3)) codes[4 * n4 + threadIdx.x] = (int8_t)weight_code(w[4 * n4 + threadIdx.x], s, qp);
 }
 __global__ __launch_bounds__(256) void tensor_step_k(const float* __restrict__ partials, int nparts, float* __restrict__ scale, float qp) {
   __shared__ float red[17];
@@ -1045,13 +1085,43 @@ __global__ __launch_bounds__(256) void tensor_step_k(const float* __restrict__ p
   m = block_max(m, red);
   if (threadIdx.x == 0) scale[0] = step_of_max(m, qp);
 }
-__global__ __launch_bounds__(256) void tensor_quantize_i8_k(const float* __restrict__ w, const float* __restrict__ scale,
-                                                            int8_t* __restrict__ codes, int64_t n, float qp) {
-  const float s = scale[0];
+// The step comes of nparts maxima, which lie in the codes' first chunks with a counter behind them.  Few blocks, since an address
+// takes one addition in about 10 ns (3000 x 777: 11.9 us, with 570 blocks 15.9), so beyond this size a launch for the step is the
+// lesser evil (4096 x 4096: 28 us, in two launches with 512 blocks 31).
+constexpr int64_t kCountedTensor = 4 << 20;
+__global__ __launch_bounds__(512) void tensor_step_quantize_k(const float* __restrict__ w, float* __restrict__ scale, int8_t* codes, int64_t n, float qp,
+                                                              int nparts) {
+  __shared__ float red[17];
+  __shared__ unsigned before;
+  unsigned* const out = reinterpret_cast<unsigned*>(codes);
+  const float4* const in = reinterpret_cast<const float4*>(w);
   const int64_t n4 = n / 4, stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n4; i += stride)
-    reinterpret_cast<unsigned*>(codes)[i] = pack_codes(reinterpret_cast<const float4*>(w)[i], s, qp);
+  const int first = nparts / 32 * 32 + 32;  // (whole lines of 128 bytes)
+  int64_t i = first + blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  float4 v[kTensorChunks];
+  auto load = [&] {
+#pragma unroll
+    for (int j = 0; j < kTensorChunks; ++j) v[j] = i + j * stride < n4 ? in[i + j * stride] : make_float4(0.f, 0.f, 0.f, 0.f);
+  };
+  load();
+  float m = 0.f;
+  for (int p = threadIdx.x; p < nparts; p += blockDim.x) m = fmaxf(m, __uint_as_float(out[p]));
+  const float s = step_of_max(block_max(m, red), qp);  // (every thread's reads are over behind its barriers)
+  if (threadIdx.x == 0) {
+    if (blockIdx.x == 0) scale[0] = s;
+    before = atomicAdd(out + nparts, 1u);
+  }
+  while (i < n4) {
+#pragma unroll
+    for (int j = 0; j < kTensorChunks; ++j)
+      if (i + j * stride < n4) out[i + j * stride] = pack_codes(v[j], s, qp);
+    i += kTensorChunks * stride;
+    load();
+  }
   if (blockIdx.x == 0 && threadIdx.x < (n & 3)) codes[4 * n4 + threadIdx.x] = (int8_t)weight_code(w[4 * n4 + threadIdx.x], s, qp);
+  __syncthreads();
+  if (before + 1 != gridDim.x) return;
+  for (int p = threadIdx.x; p < first; p += blockDim.x) out[p] = pack_codes(in[p], s, qp);
 }
 template <bool VEC>
 static void quantize_rows(const float* w, float* scale, int8_t* codes, int64_t N, int64_t K, float qp, int init_scale, hipStream_t st) {
@@ -1060,9 +1130,6 @@ static void quantize_rows(const float* w, float* scale, int8_t* codes, int64_t N
   else
     MREM_LAUNCH((weight_quantize_rows_k<4, VEC>), dim3((unsigned)N), dim3(256), 0, st, w, scale, codes, N, (int)K, qp, init_scale);
 }
-// Up to here one block finds the maximum of a tensor: its 128 weights a thread take no longer than a launch more (whole
-// calls, us, against several blocks: 64 x 64 10.2 and 12.9, 1024 x 128 10.6 and 13.2, 2048 x 128 12.2 and 12.9).
-constexpr int64_t kOneBlockTensor = 131072;
 void weight_quantize_i8(const float* w, float* scale, int8_t* codes, int64_t N, int64_t K, int bits, int per_channel, int init_scale,
                         hipStream_t st) {
   const float qp = (float)((1 << (bits - 1)) - 1);
@@ -1075,16 +1142,17 @@ void weight_quantize_i8(const float* w, float* scale, int8_t* codes, int64_t N, 
   const int64_t n = N * K;
   if (init_scale) {
     if (n <= kOneBlockTensor) {
-      MREM_LAUNCH(tensor_absmax_k, dim3(1), dim3(1024), 0, st, w, n, (float*)nullptr, scale, qp);
-    } else {
-      // about 4096 weights a block; the partial maxima (4 bytes a block) wait in the codes until the quantizer
-      // overwrites them
-      int64_t g = (n + 4095) / 4096;
-      if (g > 512) g = 512;
-      float* partials = reinterpret_cast<float*>(codes);
-      MREM_LAUNCH(tensor_absmax_k, dim3((unsigned)g), dim3(256), 0, st, w, n, partials, scale, qp);
-      MREM_LAUNCH(tensor_step_k, dim3(1), dim3(256), 0, st, (const float*)partials, (int)g, scale, qp);
+      MREM_LAUNCH(tensor_quantize_one_k, dim3(1), dim3(1024), 0, st, w, (int)n, scale, codes, qp);
+      return;
     }
+    const int64_t parts = std::min<int64_t>((n + 4095) / 4096, 512);  // (they and the counter lie far below the last code)
+    MREM_LAUNCH(tensor_absmax_k, dim3((unsigned)parts), dim3(256), 0, st, w, n, reinterpret_cast<float*>(codes));
+    if (n <= kCountedTensor) {
+      const int64_t g = std::min<int64_t>((n / 4 + 512 * kTensorChunks - 1) / (512 * kTensorChunks), 256);
+      MREM_LAUNCH(tensor_step_quantize_k, dim3((unsigned)g), dim3(512), 0, st, w, scale, codes, n, qp, (int)parts);
+      return;
+    }
+    MREM_LAUNCH(tensor_step_k, dim3(1), dim3(256), 0, st, (const float*)codes, (int)parts, scale, qp);
   }
   int64_t g = (n / 4 + 255) / 256;
   if (g > 8192) g = 8192;
