@@ -133,12 +133,14 @@ size_t mrem_teacher_cache_bytes(const mrem_ctx* ctx);
  * are those of the last mrem_module_forward / mrem_module_step on that workspace.
  *   MREM_WS_WCODES8 + i  int8 [N,K] codes of linear weight i (0 query/key/value, 1 attention output,
  *                        2 first, 3 second feed-forward projection): Eq. 1 applied to the current
- *                        parameters; present when the forward products run on int8 codes
- *                        (bf16 storage, both bit widths on, hidden and ffn multiples of 128, batch*seq
- *                        a multiple of 128)
+ *                        parameters; present with bf16 storage, both bit widths on, hidden and ffn
+ *                        multiples of 128, batch*seq a multiple of 128 and
+ *                        2^(a_bits-1) * (2^(w_bits-1) - 1) * ffn < 2^31 (8 bits: ffn <= 132096)
  *   MREM_WS_WCODES + i   the same codes as integer values of the activation type; present otherwise
+ *                        (beside int8 codes, which are not given here, where the products of a batch*seq
+ *                        that is no multiple of 128 run on those)
  *   MREM_WS_QKV          act_dtype [batch*seq, 3*hidden]: output of the query/key/value projection
- *   MREM_WS_XCODES8      int8 [batch*seq, hidden]: codes of the layer input (when int8 products are in use)
+ *   MREM_WS_XCODES8      int8 [batch*seq, hidden]: codes of the layer input; present with MREM_WS_WCODES8
  */
 typedef enum {
   MREM_WS_WCODES8 = 0, /* .. 3 */

@@ -271,6 +271,13 @@ bool i8_config(const mrem_ctx* c) {
   return c->dt == DT_BF16 && c->cfg.a_bits >= 1 && c->cfg.a_bits <= 8 && c->cfg.w_bits >= 1 && c->cfg.w_bits <= 8 && c->H % 128 == 0 &&
          c->F % 128 == 0;
 }
+// ... and no sum can leave int32: the largest codes are the GELU's, recentred in whole tiles (8 bits: ffn <= 132104), added up
+// before that in others (ffn <= 66311), where the sums of the weight codes' rows, formed in fp32, have to be exact too.
+bool i8_products(const mrem_ctx* c, int64_t T) {
+  if (!i8_config(c)) return false;
+  const int a = 1 << (c->cfg.a_bits - 1), w = (1 << (c->cfg.w_bits - 1)) - 1;
+  return T % 128 == 0 ? i8_sums_fit(c->F, a, w) : i8_sums_fit(c->F, 2 * a - 1, w) && (int64_t)c->F * w <= 1 << 24;
+}
 
 Plan make_plan(const mrem_ctx* c, int B, int S) {
   Plan p;
@@ -328,7 +335,7 @@ struct Run {
   const int32_t* seqlens;
   GemmProfile* prof = nullptr;
   template <class X = void> X* at(size_t off) const { return reinterpret_cast<X*>(ws + off); }
-  bool i8() const { return i8_config(c); }
+  bool i8() const { return i8_products(c, T); }
   int8_t* at8(size_t off) const { return i8() ? reinterpret_cast<int8_t*>(ws + off) : nullptr; }
 };
 
@@ -962,7 +969,8 @@ extern "C" int64_t mrem_workspace_offset(const mrem_ctx* ctx, int32_t batch, int
   if (!ctx || batch < 1 || seq < 1 || layer < 0 || layer >= ctx->L) return -1;
   const Plan p = make_plan(ctx, batch, seq);
   const LayerWs& w = p.lw[layer];
-  const bool i8 = i8_config(ctx) && (batch * seq) % 128 == 0;
+  const int64_t T = (int64_t)batch * seq;
+  const bool i8 = T % 128 == 0 && i8_products(ctx, T);
   if (item >= MREM_WS_WCODES8 && item < MREM_WS_WCODES8 + 4) return i8 ? (int64_t)w.wcodes8[item - MREM_WS_WCODES8] : -1;
   if (item >= MREM_WS_WCODES && item < MREM_WS_WCODES + 4) return i8 ? -1 : (int64_t)w.wcodes[item - MREM_WS_WCODES];
   if (item == MREM_WS_QKV) return (int64_t)w.qkv;
@@ -1335,10 +1343,11 @@ extern "C" mrem_status mrem_rem_step(mrem_ctx* ctx, int64_t T, int64_t N, int64_
   // one launch for both weight sets: the frozen ones rounded to the storage type; codes and the dequantized copy of the trained ones
   WeightJob wj[2];
   // Whole tiles multiply int8 codes (4096 x 4096 x 1024: 20 us, 31 on bf16 ones); those of the weights take the place of their
-  // bf16 codes, those of the input that of its gradient, which is written behind the product.
+  // bf16 codes, those of the input that of its gradient, which is written behind the product.  Not where a sum could leave int32.
   int8_t* const wcodes8 = reinterpret_cast<int8_t*>(ws + p.wcodes);
   int8_t* const xcodes8 = reinterpret_cast<int8_t*>(ws + p.dxh);
-  const bool i8 = dt == DT_BF16 && gemm_i8_ok(xcodes8, (int)K, wcodes8, (int)K, (int)T, (int)N, (int)K);
+  const bool i8 = dt == DT_BF16 && gemm_i8_ok(xcodes8, (int)K, wcodes8, (int)K, (int)T, (int)N, (int)K) &&
+                  i8_sums_fit(K, (1 << (ctx->cfg.a_bits - 1)) - 1, (1 << (ctx->cfg.w_bits - 1)) - 1);
   wj[0].w = w; wj[0].sw = sw; wj[0].codes = i8 ? nullptr : ws + p.wcodes; wj[0].what = ws + p.what; wj[0].zcorr = nullptr;
   wj[0].codes8 = i8 ? wcodes8 : nullptr;
   wj[0].N = (int)N; wj[0].K = (int)K;

@@ -1209,7 +1209,7 @@ __global__ __launch_bounds__(128) void weight_codes_k(WeightJobTable tab, float 
     if (what) store8(what + row + k, x);
   }
   if (!jb.zcorr) return;
-  acc = block_sum(acc, red);  // (a sum of codes is exact: at most 2^17 of them below 2^7)
+  acc = block_sum(acc, red);  // (the sum of a row's codes is exact up to 2^24; row_codes is read only where K times the largest is no more)
   if (threadIdx.x == 0 && jb.row_codes) jb.row_codes[n] = (int)acc;
   // s * sum_k code (s = 1 with the weight quantizers off): what the offset z of an asymmetric input
   // quantizer multiplies in the product's epilogue, x^ = s_a q + z (Section 3.1)

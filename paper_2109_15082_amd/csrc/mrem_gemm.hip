@@ -443,8 +443,8 @@ static void launch_f32(int a_t, int b_t, const void* A, int lda, const void* B, 
 // int32 accumulation): kernel gemm_dl_k in mrem_gemm_dl.h.  Integer codes (|q| <= 255) are exact in
 // bf16 and their products and partial sums are exact in fp32 while they stay below 2^24 (always for
 // 4-bit weights: K * 255 * 7 < 2^24 up to K = 9398; with 8-bit weights only up to K = 518, beyond
-// that a product on bf16 codes rounds like any fp32 sum); the int8 mode is exact for every supported K.
-// Which sizes it takes: see gemm_launch (bf16) and gemm_i8_ok.
+// that a product on bf16 codes rounds like any fp32 sum); the int8 mode is exact while sums stay in int32 (i8_sums_fit, which
+// its callers ask).  Which sizes it takes: see gemm_launch (bf16) and gemm_i8_ok.
 // ------------------------------------------------------------------------------
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));

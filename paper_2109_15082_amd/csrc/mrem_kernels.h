@@ -126,6 +126,8 @@ void gemm(int dt, int a_t, int b_t, const void* A, int lda, const void* B, int l
 // gemm_i8_ok(...), or that for M = 128: sizes with any M round as products of bf16 codes do, whose sums are exact too where they
 // stay below 2^24.  Same epilogue.
 bool gemm_i8_ok(const void* A, int lda, const void* B, int ldb, int M, int N, int K);
+// ... and that the sums of K products of codes up to a and w fit into int32 (8-bit codes of either sign: K <= 133144)
+inline bool i8_sums_fit(int64_t K, int64_t a, int64_t w) { return K * a * w <= 0x7fffffff; }
 void gemm_i8(const void* A, int lda, const void* B, int ldb, void* C, int ldc, int M, int N, int K, const Epilogue& e, hipStream_t st,
              GemmProfile* prof = nullptr);
 // Weight gradients of one layer in one launch: dw[M,N] (fp32) = alpha * dy[K,M]^T * x[K,N], bf16 operands, K tokens.
