@@ -180,18 +180,21 @@ __device__ __forceinline__ void gelu_tile(unsigned char* lds, const Epilogue& e,
   }
 }
 // What the backward pass needs of a stored value u in front of the GELU and its quantizer is a function of its 16 bits too: the
-// derivative, zero outside the quantizer's range, and the term of the step's gradient.  Values between 2^-11 and 8 are looked up
+// derivative (outside the quantizer's range OUTSIDE, which gives zero whatever flows back, or NaN where that is no number), and the
+// term of the step's gradient.  Values between 2^-11 and 8 are looked up
 // (34 vector instructions when formed); 6 values in 10000 of N(0, 0.64) lie outside and are formed one by one.  A pass of its own
 // read both tensors again and was bound by those instructions: 26 us for 4096 x 4096 values.  With it and the context's
 // (POST_MASK, 8 us) in the products a step of six layers of 1024 over 4096 tokens takes 3975 us instead of 4112, over 16 x 384
 // 5588 instead of 5802, three of 768 over 32 x 128 1541 instead of 1603.
 struct GeluSlopes {
   static constexpr unsigned LOW = 116u << 7, N = 14u * 128u;  // bits of 2^-11; values of one sign
+  static constexpr unsigned OUTSIDE = 0x80000000u;            // bits of -0, which no derivative inside has
   float2 of[2 * N];
   static __device__ __forceinline__ float2 form(unsigned bits, const QuantParam& q) {
     const float u = __uint_as_float(bits << 16), v = q_ratio_fma(gelu_t<bf16_t>(u), q);
     const bool in = q_inside(v, q);
-    return make_float2((in ? 1.f : 0.f) * gelu_grad_t<bf16_t>(u), q_code(v, q) - (in ? v : 0.f));
+    const float d = gelu_grad_t<bf16_t>(u);
+    return make_float2(in ? d + 0.f : -fabsf(0.f * d), q_code(v, q) - (in ? v : 0.f));
   }
   __device__ __forceinline__ void fill(const QuantParam& q) {
     for (unsigned i = threadIdx.x; i < 2 * N; i += blockDim.x) of[i] = form((i < N ? LOW : 0x8000u + LOW - N) + i, q);
@@ -247,7 +250,7 @@ __device__ __forceinline__ void dgelu_tile(unsigned char* lds, const Epilogue& e
       for (int j = 0; j < 8; ++j) {
         const float g = __uint_as_float((j & 1) ? o[j >> 1] & 0xffff0000u : o[j >> 1] << 16);
         sum += g * t[j].y;
-        d[j] = static_cast<bf16_t>(t[j].x != 0.f ? g * t[j].x : 0.f);  // (zero outside whatever g is)
+        d[j] = static_cast<bf16_t>(__float_as_uint(t[j].x) != GeluSlopes::OUTSIDE ? g * t[j].x : 0.f);
         cols[j] += static_cast<float>(d[j]);
       }
       *reinterpret_cast<bf16x8_t*>(C + at0 + (size_t)(p + i * ROWS) * ldc) = d;

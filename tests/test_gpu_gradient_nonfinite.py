@@ -1,0 +1,70 @@
+"""Gradients of values that are not finite, through the GELU's and the context's quantizers: the input-gradient products that form
+them (32 sentences) leave a NaN where the kernels of their own (2 sentences) do, and nowhere else."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+H, HEADS, FFN, SEQ = 256, 4, 1024, 128
+
+
+def module(batch):
+    import torch
+    from paper_2109_15082_amd import binding as B
+    g = torch.Generator("cuda").manual_seed(7)
+    mod = B.MremModule(1, H, HEADS, FFN, batch, SEQ)
+    t = torch.randn(mod.teacher.numel(), generator=g, device="cuda", dtype=torch.float32) * 0.03
+    field = lambda v, f: v[B.mrem_param_offset(mod.ctx, 0, f):][:B.mrem_param_size(mod.ctx, f)]
+    for f in ("ln1_g", "ln2_g"):
+        field(t, f).add_(1.0)
+    mod.teacher.copy_(t)
+    B.mrem_teacher_prepare(mod.ctx, mod.teacher, mod.teacher_cache)
+    mod.params.copy_(mod.teacher)
+    mod.init_steps()
+    x = torch.randn(2, SEQ, H, generator=g, device="cuda", dtype=torch.float32).bfloat16()
+    mod.calibrate(x)
+    return mod, x, lambda f: field(mod.params, f)
+
+
+def nan_fields(batch, change, fp_change):
+    import torch
+    from paper_2109_15082_amd import binding as B
+    mod, x, field = module(batch)
+    change(field)
+    x = torch.cat([x, x[1:].expand(batch - 2, SEQ, H)]).contiguous()
+    x_fp = x.clone()
+    fp_change(x_fp)
+    grads = torch.zeros_like(mod.params)
+    mod.step(x_fp, x, 0.0, grads_out=grads)
+    out = {f: grads[B.mrem_param_offset(mod.ctx, 0, f):][:B.mrem_param_size(mod.ctx, f)].isnan().cpu() for f in B.FIELDS}
+    mod.close()
+    return out
+
+
+# columns of the first feed-forward projection: GELU in range with slope zero, beyond the range, infinite, NaN
+VALUES = {3: -40.0, 10: 40.0, 17: float("inf"), 24: float("-inf"), 31: float("nan")}
+
+
+@pytest.mark.parametrize("columns", [(), (3, 10), (17,), (24,), (31,)])
+@pytest.mark.parametrize("loss", ["finite", "nan"])
+def test_same_nans(columns, loss):
+    import torch
+
+    def change(field):
+        for c in columns:
+            field("w_1").reshape(FFN, H)[c] = 0.0
+            field("b_1")[c] = VALUES[c]
+
+    def fp_change(x_fp):
+        if loss == "nan":
+            x_fp[0, 5, 0] = float("inf")
+
+    whole, few = nan_fields(32, change, fp_change), nan_fields(2, change, fp_change)
+    for f in few:
+        assert int((whole[f] != few[f]).sum()) == 0, f
+    b_1 = few["b_1"]
+    if loss == "nan" and 3 in columns:
+        assert b_1[3] and not b_1[10]
+    elif columns and columns[0] > 10:
+        assert b_1[columns[0]]
+    elif loss == "finite":
+        assert not any(bool(v.any()) for v in few.values())
