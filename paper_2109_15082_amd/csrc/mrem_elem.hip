@@ -1023,10 +1023,17 @@ __global__ void weight_quantize_i8_k(const float* __restrict__ w, float* __restr
   for (int64_t k = threadIdx.x; k < K; k += blockDim.x) codes[n * K + k] = (int8_t)weight_code(wr[k], s, qp);
 }
 // One step for the whole tensor.  Up to kOneBlockTensor weights one block keeps them all in registers between the search for the
-// maximum and the quantizer (whole calls, us: 64 x 64 10.2 -> 7.7, 181 x 181 10.2 -> 7.3, where a call that finds nothing takes 7.3).  Beyond,
-// a launch leaves every block's maximum and a zero behind them in the first codes, and the next one's blocks each turn these into
-// the step while their own weights are on their way; whoever counts the last block that has read them overwrites them (600 x 400
-// 12.9 -> 10.3, 1024 x 1024 13.3 -> 10.3, 3000 x 777 13.1 -> 11.9 against a launch between the two).
+// maximum and the quantizer.  Up to kTwoLaunchTensor a launch searches a part a block and leaves every part's maximum at the head of
+// each part's codes; the next one's blocks turn these into the step while their own weights are on their way, and write their codes
+// over them, so that no block waits for another.  Block j has the same part in both, so that it finds the weights in its XCD's L2
+// (parts shifted against each other: 24.4 us instead of 21.4 for 2048 x 2048).  Beyond, one block forms the step in a launch of
+// its own.  Whole calls, us, of a tensor that was just read | of one in no cache, three launches (to 131072 weights two, one block
+// searching) first, in brackets two launches with the maxima in one place, whose readers were counted before it was overwritten:
+//   64 x 64 10.2 and 7.7;  181 x 181 9.5, 7.1 | 15.5, 15.3;  300 x 300 10.1, 9.9 | 22.6, 14.0
+//   1024 x 1024 12.9, 10.0 (10.3) | 16.5, 14.9 (16.2);  1500 x 1400 12.9, 10.2 (10.5) | 17.6, 17.1 (19.6)
+//   3000 x 777 12.9, 10.1 (10.5) | 18.1, 17.6 (20.0);  2048 x 2048 12.9, 10.3 (12.4) | 21.6, 21.4 (23.5)
+// and where three launches serve it, against these two: 2500 x 2500 11.6 and 11.9 | 25.2 and 26.6;  3500 x 3500 19.1 and 22.1 |
+// 36.8 and 40.1
 __device__ __forceinline__ float max_abs(float m, const float4& v) {
   return fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
 }
@@ -1051,7 +1058,65 @@ __global__ __launch_bounds__(1024) void tensor_quantize_one_k(const float* __res
     if (t + 1024 * i < n4) reinterpret_cast<unsigned*>(codes)[t + 1024 * i] = pack_codes(v[i], s, qp);
   if (rest < n) codes[rest] = (int8_t)weight_code(last, s, qp);
 }
-// chunks of 4 weights that a thread has in flight
+// The parts of a tensor, in chunks of 4 weights: whole lines of 128 bytes of codes but for the end.  A thread has up to U of a
+// part's chunks, all in flight.  One part a compute unit (with 259 of them 2048 x 2048 in no cache took 23.8 us instead of 21.4), fewer where
+// that would leave less than a chunk a thread.
+constexpr int kPartThreads = 1024, kPartChunks = 4, kMaxParts = 256;
+constexpr int64_t kTwoLaunchTensor = 4 * (int64_t)kPartThreads * kPartChunks * kMaxParts;
+struct TensorParts {
+  int64_t n4;
+  int parts;
+  explicit TensorParts(int64_t n) : n4(n / 4), parts((int)std::min<int64_t>((n4 + kPartThreads - 1) / kPartThreads, kMaxParts)) {}
+  // of the largest part at most: both ends are rounded up to a line, so it is no longer than its length rounded up
+  int chunks() const { return (int)((n4 + parts - 1) / parts + 31) / 32 * 32; }
+  __device__ __forceinline__ int64_t start(int j) const { return j < parts ? (n4 * j / parts + 31) & ~int64_t(31) : n4; }
+};
+template <int U>
+__device__ __forceinline__ void load_part(float4 (&v)[U], const float* __restrict__ w, int64_t begin, int64_t end) {
+#pragma unroll
+  for (int j = 0; j < U; ++j) {
+    const int64_t i = begin + threadIdx.x + j * kPartThreads;
+    v[j] = reinterpret_cast<const float4*>(w)[i < end ? i : begin];
+  }
+}
+template <int U>
+__global__ __launch_bounds__(kPartThreads) void tensor_part_max_k(const float* __restrict__ w, int64_t n, unsigned* __restrict__ codes, TensorParts p) {
+  __shared__ float red[17];
+  float4 v[U];
+  load_part(v, w, p.start(blockIdx.x), p.start(blockIdx.x + 1));
+  float m = 0.f;
+#pragma unroll
+  for (int j = 0; j < U; ++j) m = max_abs(m, v[j]);
+  if (blockIdx.x == 0 && threadIdx.x < (n & 3)) m = fmaxf(m, fabsf(w[4 * p.n4 + threadIdx.x]));
+  m = block_max(m, red);
+  // the maxima of an XCD's blocks lie together, so that its L2 writes few lines
+  const int xcd = blockIdx.x % 8, slot = xcd * (p.parts / 8) + min(xcd, p.parts % 8) + blockIdx.x / 8;
+  for (int j = threadIdx.x; j < p.parts; j += kPartThreads) codes[p.start(j) + slot] = __float_as_uint(m);
+}
+template <int U>
+__global__ __launch_bounds__(kPartThreads) void tensor_part_quantize_k(const float* __restrict__ w, float* __restrict__ scale, int8_t* codes, int64_t n,
+                                                                       float qp, TensorParts p) {
+  __shared__ float red[17];
+  unsigned* const out = reinterpret_cast<unsigned*>(codes);
+  const int64_t begin = p.start(blockIdx.x), end = p.start(blockIdx.x + 1);
+  float m = threadIdx.x < p.parts ? __uint_as_float(out[begin + threadIdx.x]) : 0.f;
+  float4 v[U];
+  load_part(v, w, begin, end);
+  const float s = step_of_max(block_max(m, red), qp);  // (every thread's maximum is read behind its barriers)
+  if (blockIdx.x == 0 && threadIdx.x == 0) scale[0] = s;
+#pragma unroll
+  for (int j = 0; j < U; ++j) {
+    const int64_t i = begin + threadIdx.x + j * kPartThreads;
+    if (i < end) out[i] = pack_codes(v[j], s, qp);
+  }
+  if (blockIdx.x == 0 && threadIdx.x < (n & 3)) codes[4 * p.n4 + threadIdx.x] = (int8_t)weight_code(w[4 * p.n4 + threadIdx.x], s, qp);
+}
+template <int U>
+static void quantize_parts(const float* w, float* scale, int8_t* codes, int64_t n, float qp, const TensorParts& p, hipStream_t st) {
+  MREM_LAUNCH((tensor_part_max_k<U>), dim3(p.parts), dim3(kPartThreads), 0, st, w, n, reinterpret_cast<unsigned*>(codes), p);
+  MREM_LAUNCH((tensor_part_quantize_k<U>), dim3(p.parts), dim3(kPartThreads), 0, st, w, scale, codes, n, qp, p);
+}
+// chunks that a thread of the search over a larger tensor has in flight
 constexpr int kTensorChunks = 4;
 __global__ __launch_bounds__(256) void tensor_absmax_k(const float* __restrict__ w, int64_t n, float* __restrict__ partials) {
   __shared__ float red[17];
@@ -1066,9 +1131,7 @@ __global__ __launch_bounds__(256) void tensor_absmax_k(const float* __restrict__
   }
   if (blockIdx.x == 0 && threadIdx.x < (n & 3)) m = fmaxf(m, fabsf(w[4 * n4 + threadIdx.x]));
   m = block_max(m, red);
-  if (threadIdx.x != 0) return;
-  partials[blockIdx.x] = m;
-  if (blockIdx.x == 0) reinterpret_cast<unsigned*>(partials)[gridDim.x] = 0u;
+  if (threadIdx.x == 0) partials[blockIdx.x] = m;
 }
 __global__ __launch_bounds__(256) void tensor_quantize_i8_k(const float* __restrict__ w, const float* __restrict__ scale, int8_t* __restrict__ codes, int64_t n,
                                                             float qp) {
@@ -1084,44 +1147,6 @@ __global__ __launch_bounds__(256) void tensor_step_k(const float* __restrict__ p
   for (int i = threadIdx.x; i < nparts; i += blockDim.x) m = fmaxf(m, partials[i]);
   m = block_max(m, red);
   if (threadIdx.x == 0) scale[0] = step_of_max(m, qp);
-}
-// The step comes of nparts maxima, which lie in the codes' first chunks with a counter behind them.  Few blocks, since an address
-// takes one addition in about 10 ns (3000 x 777: 11.9 us, with 570 blocks 15.9), so beyond this size a launch for the step is the
-// lesser evil (4096 x 4096: 28 us, in two launches with 512 blocks 31).
-constexpr int64_t kCountedTensor = 4 << 20;
-__global__ __launch_bounds__(512) void tensor_step_quantize_k(const float* __restrict__ w, float* __restrict__ scale, int8_t* codes, int64_t n, float qp,
-                                                              int nparts) {
-  __shared__ float red[17];
-  __shared__ unsigned before;
-  unsigned* const out = reinterpret_cast<unsigned*>(codes);
-  const float4* const in = reinterpret_cast<const float4*>(w);
-  const int64_t n4 = n / 4, stride = (int64_t)gridDim.x * blockDim.x;
-  const int first = nparts / 32 * 32 + 32;  // (whole lines of 128 bytes)
-  int64_t i = first + blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  float4 v[kTensorChunks];
-  auto load = [&] {
-#pragma unroll
-    for (int j = 0; j < kTensorChunks; ++j) v[j] = i + j * stride < n4 ? in[i + j * stride] : make_float4(0.f, 0.f, 0.f, 0.f);
-  };
-  load();
-  float m = 0.f;
-  for (int p = threadIdx.x; p < nparts; p += blockDim.x) m = fmaxf(m, __uint_as_float(out[p]));
-  const float s = step_of_max(block_max(m, red), qp);  // (every thread's reads are over behind its barriers)
-  if (threadIdx.x == 0) {
-    if (blockIdx.x == 0) scale[0] = s;
-    before = atomicAdd(out + nparts, 1u);
-  }
-  while (i < n4) {
-#pragma unroll
-    for (int j = 0; j < kTensorChunks; ++j)
-      if (i + j * stride < n4) out[i + j * stride] = pack_codes(v[j], s, qp);
-    i += kTensorChunks * stride;
-    load();
-  }
-  if (blockIdx.x == 0 && threadIdx.x < (n & 3)) codes[4 * n4 + threadIdx.x] = (int8_t)weight_code(w[4 * n4 + threadIdx.x], s, qp);
-  __syncthreads();
-  if (before + 1 != gridDim.x) return;
-  for (int p = threadIdx.x; p < first; p += blockDim.x) out[p] = pack_codes(in[p], s, qp);
 }
 template <bool VEC>
 static void quantize_rows(const float* w, float* scale, int8_t* codes, int64_t N, int64_t K, float qp, int init_scale, hipStream_t st) {
@@ -1145,14 +1170,17 @@ void weight_quantize_i8(const float* w, float* scale, int8_t* codes, int64_t N, 
       MREM_LAUNCH(tensor_quantize_one_k, dim3(1), dim3(1024), 0, st, w, (int)n, scale, codes, qp);
       return;
     }
-    const int64_t parts = std::min<int64_t>((n + 4095) / 4096, 512);  // (they and the counter lie far below the last code)
-    MREM_LAUNCH(tensor_absmax_k, dim3((unsigned)parts), dim3(256), 0, st, w, n, reinterpret_cast<float*>(codes));
-    if (n <= kCountedTensor) {
-      const int64_t g = std::min<int64_t>((n / 4 + 512 * kTensorChunks - 1) / (512 * kTensorChunks), 256);
-      MREM_LAUNCH(tensor_step_quantize_k, dim3((unsigned)g), dim3(512), 0, st, w, scale, codes, n, qp, (int)parts);
+    if (n <= kTwoLaunchTensor) {
+      const TensorParts p(n);
+      if (p.chunks() <= kPartThreads) quantize_parts<1>(w, scale, codes, n, qp, p, st);
+      else if (p.chunks() <= 2 * kPartThreads) quantize_parts<2>(w, scale, codes, n, qp, p, st);
+      else quantize_parts<kPartChunks>(w, scale, codes, n, qp, p, st);
       return;
     }
-    MREM_LAUNCH(tensor_step_k, dim3(1), dim3(256), 0, st, (const float*)codes, (int)parts, scale, qp);
+    // the maxima of 512 blocks wait in the first codes
+    constexpr int parts = 512;
+    MREM_LAUNCH(tensor_absmax_k, dim3(parts), dim3(256), 0, st, w, n, reinterpret_cast<float*>(codes));
+    MREM_LAUNCH(tensor_step_k, dim3(1), dim3(256), 0, st, (const float*)codes, parts, scale, qp);
   }
   int64_t g = (n / 4 + 255) / 256;
   if (g > 8192) g = 8192;

@@ -1,12 +1,13 @@
-"""One step for a whole tensor, around the sizes where one block holds all weights (32768), where the second launch's blocks take a
-second round (256 or 512 blocks of 8192 weights) and where the first codes, which carry the partial maxima, are quantized by themselves.
-The reference is Eq. 1 in fp32, whose operations are the kernels' own."""
+"""One step for a whole tensor, around the sizes where one block holds all weights (32768), where a thread has a second and a third
+chunk of its part (1048576, 2097152) and where one block forms the step in a launch of its own (4194304).  The codes carry the parts'
+maxima in between.  The reference is Eq. 1 in fp32, whose operations are the kernels' own."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N,K", [(1, 32764), (1, 32767), (2, 16384), (1, 32769), (4, 8193), (5, 6555), (31, 4001), (512, 4099), (2048, 4096), (3001, 2999)])
+@pytest.mark.parametrize("N,K", [(1, 32764), (1, 32767), (2, 16384), (1, 32769), (4, 8193), (5, 6555), (31, 4001), (512, 4099), (2048, 4096), (3001, 2999),
+                                 (1, 1048579), (1, 1048580), (1, 2097155), (1, 2097156), (1, 4194303), (1, 4194305)])
 @pytest.mark.parametrize("at", [0, 70, -1])  # the largest weight among the first codes or the last one
 def test_tensor(N, K, at):
     import torch
