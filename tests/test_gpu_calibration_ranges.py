@@ -1,6 +1,7 @@
 """Clip ranges that the kernels of a calibration take of what they write: products on each of their tiles (ordered ones, 128 and
 256 rows, the last tile partly filled), sections of the query/key/value projection that are no whole tiles, short and long rows
-of attention, LayerNorm.  The reference is the layer in fp32; the largest values lie in the last sentence, so in the last tiles."""
+of attention, LayerNorm; with and without padded keys.  The reference is the layer in fp32; the largest values lie in the last
+sentence, so in the last tiles."""
 import math
 
 import pytest
@@ -12,8 +13,9 @@ SHAPES = {"one_token": (64, 2, 256, 1, 1), "sections_320": (320, 5, 1280, 3, 50)
           "long_rows": (256, 4, 1024, 2, 300), "d32_long_rows": (128, 4, 512, 3, 140)}
 
 
+@pytest.mark.parametrize("padded", [False, True])
 @pytest.mark.parametrize("name", SHAPES)
-def test_ranges(name):
+def test_ranges(name, padded):
     import torch
     import torch.nn.functional as F
     from paper_2109_15082_amd import binding as B
@@ -30,13 +32,18 @@ def test_ranges(name):
     x = torch.randn(batch, seq, H, generator=g, device="cuda", dtype=torch.float32)
     x[-1] *= 2.0
     x = x.bfloat16()
-    mod.calibrate(x)
+    # down to one valid key; the last sentence keeps its largest values
+    lengths = torch.tensor([1 + (37 * b + seq // 2) % seq for b in range(batch)], device="cuda", dtype=torch.int32) if padded else None
+    mod.calibrate(x, lengths)
 
     w = lambda f, n: field(f).reshape(n, -1).bfloat16().float()
     xf = x.float().reshape(-1, H)
     qkv = F.linear(xf, w("w_qkv", 3 * H), field("b_qkv"))
     q, k, v = (a.reshape(batch, seq, nh, H // nh).transpose(1, 2) for a in qkv.split(H, 1))
-    p = torch.softmax(q @ k.transpose(-1, -2) / math.sqrt(H // nh), -1)
+    scores = q @ k.transpose(-1, -2) / math.sqrt(H // nh)
+    if padded:
+        scores = scores.masked_fill(torch.arange(seq, device="cuda")[None, None, None] >= lengths[:, None, None, None], -math.inf)
+    p = torch.softmax(scores, -1)
     ctx = (p @ v).transpose(1, 2).reshape(-1, H)
     x1 = F.layer_norm(xf + F.linear(ctx, w("w_o", H), field("b_o")), (H,), field("ln1_g"), field("ln1_b"), 1e-12)
     gelu = F.gelu(F.linear(x1, w("w_1", ffn), field("b_1")))
