@@ -601,7 +601,8 @@ MREM_TILES(true, true, float, false);
 #endif
 
 #if MREM_GEMM_REST
-// Which sizes have kernels with Epilogue::post: whole tiles from 128 x 128 on.
+// Which sizes have kernels with Epilogue::post: whole tiles from 128 x 128 on.  (Backward passes in partly filled ones are neither
+// built nor measured; in smaller tiles they would take the step gradients' sums in another order, which small steps pin.)
 bool post_ok(int M, int N, int K) {
   auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   if (!whole_tiles(M, N, K) || tiles(128, 64) <= 256) return false;
